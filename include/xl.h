@@ -17,9 +17,9 @@
  * LD.G, CONV1, ST.S, barrier, LD.S, CONV2, ST.G) or, for comparison, one
  * kernel per layer with every intermediate written to and re-read from HBM
  * (Fig. 3a).  Both paths use the same tiled implicit-GEMM convolution
- * (section 3.2) on the fp32 matrix cores, or, when xl_options.precision asks
- * for it, on the bf16 matrix cores with every operand split into two bf16
- * numbers.
+ * (section 3.2) in fp32 arithmetic -- on the fp32 matrix cores, or on the bf16
+ * ones with every operand as the exact sum of three bf16 numbers -- or, when
+ * xl_options.precision asks for it, with every operand rounded to two bf16 numbers.
  *
  * Data.  All tensors are dense fp32 NCHW in DEVICE memory owned by the caller
  * (e.g. allocated by PyTorch).  Filters are [Cout, Cin, K, K] fp32 (section 4.1
@@ -118,7 +118,10 @@ typedef struct xl_options {
     int paper_tuner_only;   /* 1: restrict candidates to the paper's square common-factor
                                (tile, grid) pairs (section 3.2)                               */
     int force_threads;      /* >0: fix the workgroup size (256 or 512) of every block         */
-    int precision;          /* XL_PRECISION_FP32 (0, default): fp32 matrix operations.
+    int precision;          /* XL_PRECISION_FP32 (0, default): fp32 matrix operations, or operands taken apart
+                               exactly into three bf16 numbers and multiplied by six bf16 matrix operations
+                               per product, accumulated in fp32: no less exact (the sums meet fewer
+                               roundings), same results for infinities, NaN and values near FLT_MAX.
                                XL_PRECISION_BF16X3: every operand of a convolution is split into
                                two bf16 numbers, hi = bf16(x) and lo = bf16(x - hi), and a product
                                is hi*hi + hi*lo + lo*hi on the bf16 matrix cores, accumulated in
@@ -256,8 +259,9 @@ xl_status xl_tune(xl_plan *plan, const void *const *tensors, int ntensors,
  * static device array inside the library, XL_STATIC_SCRATCH_BYTES long, which every GPU the library
  * runs on holds from the first call on that GPU until the process ends.  The call allocates no
  * device memory and frees none; it enqueues kernels on `stream` and returns without synchronising.
- *   - XL_E_SCRATCH when xl_plan_workspace_bytes(plan) exceeds XL_STATIC_SCRATCH_BYTES (configs 1-4 at
- *     their full sizes fit; config 5 up to batch 4).
+ *   - XL_E_SCRATCH when the plan's workspace, with filters re-laid out for the fp32 matrix operations alone (the array
+ *     has room of its own for the other forms), exceeds XL_STATIC_SCRATCH_BYTES (configs 1-4 at their full sizes
+ *     fit; config 5 up to batch 4).
  *   - relayout != 0: the filters are re-laid out into the array first (as xl_prepare does), from
  *     `weights` / `nweights`; needed on the first call and whenever filter values change.
  *     relayout == 0: the filters are re-laid out only if the array's last user on this GPU was another

@@ -15,10 +15,14 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libxl.so")
-# (source, object name, extra defines): kernels.hip is compiled twice, the split-bf16 variants on their own
-SOURCES = [("kernels.hip", "kernels", []), ("kernels.hip", "kernels_b3", ["-DXL_TU_B3"]),
+# (source, object name, extra defines): kernels.hip is compiled once for the fp32 variants and once for each part of the
+# split-bf16 ones
+SOURCES = [("kernels.hip", "kernels", []),
+           *[("kernels.hip", f"kernels_split_{part}{pr}", [f"-DXL_TU_SPLIT={part}", f"-DXL_TU_PR={pr}"])
+             for part in "ABC" for pr in (1, 2)],
            ("plan.cpp", "plan", []), ("api.cpp", "api", []), ("static_run.hip", "static_run", [])]
 HEADERS = [os.path.join(CSRC, "xl_internal.h"), os.path.join(CSRC, "plan.h"), os.path.join(CSRC, "thin_conv.h"),
+           os.path.join(CSRC, "split_conv.h"),
            os.path.join(ROOT, "include", "xl.h")]
 
 # packed-fp32 instructions are switched off for all device code

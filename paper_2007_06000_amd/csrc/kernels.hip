@@ -33,38 +33,11 @@ namespace xl {
 // ----------------------------------------------------------------------------
 // matrix-core wrappers
 // ----------------------------------------------------------------------------
-// PR = 0: fp32 operands.  PR = 1: every operand is held as two bf16 numbers, hi = bf16(x) and
-// lo = bf16(x - hi) (round to nearest), and a product is the sum of three bf16 matrix operations
-// hi*hi + hi*lo + lo*hi accumulated in fp32; what is left out is at most 3 * 2^-16 of |a||b|.  One K step
-// then covers 16 (MF = 32) or 32 (MF = 16) channels, 8 per lane.  The accumulator layout is the
-// same in both modes.
-template <int MF, int PR = 0>
+template <int MF>
 struct MM;
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
 template <>
-struct MM<32, 1> {
-    typedef f32x16 Acc;
-    static constexpr int KC = 16, GPS = 4, NQ = 4;
-    static __device__ __forceinline__ Acc mma(f32x4 a, f32x4 b, Acc c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    }
-};
-
-template <>
-struct MM<16, 1> {
-    typedef f32x4 Acc;
-    static constexpr int KC = 32, GPS = 8, NQ = 1;
-    static __device__ __forceinline__ Acc mma(f32x4 a, f32x4 b, Acc c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    }
-};
-
-template <>
-struct MM<32, 0> {
+struct MM<32> {
     typedef f32x16 Acc;
     static constexpr int KC = 8, GPS = 2, NQ = 4;
     static __device__ __forceinline__ Acc mma(float a, float b, Acc c)
@@ -76,7 +49,7 @@ struct MM<32, 0> {
 };
 
 template <>
-struct MM<16, 0> {
+struct MM<16> {
     typedef f32x4 Acc;
     static constexpr int KC = 16, GPS = 4, NQ = 1;
     static __device__ __forceinline__ Acc mma(float a, float b, Acc c)
@@ -223,106 +196,6 @@ __device__ __forceinline__ void conv_accum(typename MM<MF>::Acc (&acc)[NRT][NPT]
     }
 }
 
-// The same K loop for split-bf16 operands (PR = 1).  Every operand row exists twice in LDS, a hi and
-// a lo one: the filter chunk is [K step][tap][row tile][hi, lo][lane] 16 bytes, the pixels are 16-byte
-// planes [8-channel group][hi, lo][row][col][8 bf16], `gstride` floats apart (the plane of the
-// lane's 8-channel group is part of `off`).  Three matrix operations per tile pair and K step.
-template <int MF, int KS, int NRT, int NPT>
-__device__ __forceinline__ void conv_accum_b3(typename MM<MF, 1>::Acc (&acc)[NRT][NPT],
-                                              const float *bsrc, const int (&off)[NPT], int src_w, int gstride,
-                                              const float *wsrc, const int (&rloc)[NRT], int wg_rt, int nkg)
-{
-    typedef MM<MF, 1> M;
-    constexpr int T = KS * KS;
-    const int lane = threadIdx.x & 63;
-    f32x4 ah[2][NRT], al[2][NRT], bh[2][NPT], bl[2][NPT];
-    auto fetch = [&](int set, int kg, int t) {
-        const int u = t / KS, v = t % KS;
-        const float *w = wsrc + ((kg * T + t) * wg_rt * 128 + lane) * 4;
-#pragma unroll
-        for (int r = 0; r < NRT; ++r) {
-            ah[set][r] = *(const f32x4 *)(w + rloc[r] * 512);
-            al[set][r] = *(const f32x4 *)(w + rloc[r] * 512 + 256);
-        }
-        const float *s = bsrc + kg * (M::GPS * gstride) + (u * src_w + v) * 4;
-#pragma unroll
-        for (int p = 0; p < NPT; ++p) {
-            bh[set][p] = *(const f32x4 *)(s + off[p]);
-            bl[set][p] = *(const f32x4 *)(s + off[p] + gstride);
-        }
-    };
-    static_assert(T % 2 == 1, "filter taps are odd");
-    auto step = [&](int cur, int kg, int t) {
-        if (t + 1 < T || kg + 1 < nkg) fetch(cur ^ 1, kg + (t + 1) / T, (t + 1) % T);
-        __builtin_amdgcn_sched_barrier(0);
-        // small terms first; the three products of one tile pair are spread over the other pairs
-#pragma unroll
-        for (int r = 0; r < NRT; ++r)
-#pragma unroll
-            for (int p = 0; p < NPT; ++p) acc[r][p] = M::mma(al[cur][r], bh[cur][p], acc[r][p]);
-#pragma unroll
-        for (int r = 0; r < NRT; ++r)
-#pragma unroll
-            for (int p = 0; p < NPT; ++p) acc[r][p] = M::mma(ah[cur][r], bl[cur][p], acc[r][p]);
-#pragma unroll
-        for (int r = 0; r < NRT; ++r)
-#pragma unroll
-            for (int p = 0; p < NPT; ++p) acc[r][p] = M::mma(ah[cur][r], bh[cur][p], acc[r][p]);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    // Four or more tile pairs per wave: one operand set only (two would not fit 256 registers); the
-    // reads of a step are covered by the other wave of the SIMD and by the step's own 12+ operations.
-    if constexpr (NRT * NPT >= 4) {
-        for (int kg = 0; kg < nkg; ++kg) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                fetch(0, kg, t);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int r = 0; r < NRT; ++r)
-#pragma unroll
-                    for (int p = 0; p < NPT; ++p) acc[r][p] = M::mma(al[0][r], bh[0][p], acc[r][p]);
-#pragma unroll
-                for (int r = 0; r < NRT; ++r)
-#pragma unroll
-                    for (int p = 0; p < NPT; ++p) acc[r][p] = M::mma(ah[0][r], bl[0][p], acc[r][p]);
-#pragma unroll
-                for (int r = 0; r < NRT; ++r)
-#pragma unroll
-                    for (int p = 0; p < NPT; ++p) acc[r][p] = M::mma(ah[0][r], bh[0][p], acc[r][p]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        return;
-    }
-    fetch(0, 0, 0);
-    if constexpr (T == 1) {
-        for (int kg = 0; kg < nkg; kg += 2) {
-            step(0, kg, 0);
-            if (kg + 1 < nkg) step(1, kg + 1, 0);
-        }
-    } else {
-        for (int kg = 0; kg < nkg; ++kg) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) step(t & 1, kg, t);
-#pragma unroll
-            for (int r = 0; r < NRT; ++r) { ah[0][r] = ah[1][r]; al[0][r] = al[1][r]; }
-#pragma unroll
-            for (int p = 0; p < NPT; ++p) { bh[0][p] = bh[1][p]; bl[0][p] = bl[1][p]; }
-        }
-    }
-}
-
-// hi / lo bf16 halves of two floats, packed (first float in the low half of each word)
-__device__ __forceinline__ void split_bf16(float a, float b, unsigned &hi, unsigned &lo)
-{
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    hi = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
-    const float ha = __builtin_bit_cast(float, hi << 16), hb = __builtin_bit_cast(float, hi & 0xffff0000u);
-    lo = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a - ha, b - hb}, bf16x2));
-}
-
 // ----------------------------------------------------------------------------
 // One pass of a convolution over the tiles this workgroup holds in registers.
 // The filter (and, for STAGE_X, the halo-extended input tile) is streamed
@@ -342,15 +215,13 @@ struct PassGeom {
     bool active;        // this wave owns at least one real tile
 };
 
-template <int MF, int KS, int NRT, int NPT, bool STAGE_X, int PX = 0, int PR = 0>
+template <int MF, int KS, int NRT, int NPT, bool STAGE_X, int PX = 0>
 __device__ __forceinline__ void conv_pass(typename MM<MF>::Acc (&acc)[NRT][NPT], const BlockParams &P, const ConvW &c,
                                           const PassGeom &g, const float *bsrc, const int (&off)[NPT], float *buf,
                                           const float *__restrict__ ximg, unsigned long long x_bytes, int iy0, int ix0)
 {
     // ximg: first element of this image of the block input, x_bytes: bytes from there to the end of the tensor
-    typedef MM<MF, PR> M;
-    static_assert(PR == 0 || PX == 0, "split-bf16 operands are staged through registers");
-    constexpr int RW = PR ? 2 : 1;      // 1 KB rows per (K step, tap, row tile) of the filter: hi and lo for PR = 1
+    typedef MM<MF> M;
     constexpr int T = KS * KS;
     const int tid = threadIdx.x, nthreads = blockDim.x;
     int rloc[NRT];
@@ -367,7 +238,7 @@ __device__ __forceinline__ void conv_pass(typename MM<MF>::Acc (&acc)[NRT][NPT],
     // compiler then keeps counting outstanding LDS reads exactly instead of waiting for all of them.)
     const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves_wg = nthreads >> 6, lane_id = tid & 63;
     const int nkt = c.nkg * T;
-    const int f_nrt = c.nrt * RW, f_wg_rt = g.wg_rt * RW, f_base = g.rt_base * RW;     // in 1 KB rows
+    const int f_nrt = c.nrt, f_wg_rt = g.wg_rt, f_base = g.rt_base;     // in 1 KB rows
     const __amdgpu_buffer_rsrc_t wrsrc = make_rsrc(c.wp, (unsigned long long)nkt * f_nrt * 1024ull);
     const int w_lane = (tid & 63) * 16;
     const int w_dkt = div_upto8(nwaves_wg, f_wg_rt), w_drl = nwaves_wg - w_dkt * f_wg_rt;       // row step = nwaves rows
@@ -493,9 +364,7 @@ __device__ __forceinline__ void conv_pass(typename MM<MF>::Acc (&acc)[NRT][NPT],
             }
             xmask[i] = m;
             xgrp[i] = gr * 4;
-            // PR = 1: the hi halves of 4-channel group gr go to plane gr & ~1 (the lo halves to the next
-            // one), 8 bytes per pixel, after those of group gr - 1 when gr is odd
-            xdst[i] = PR ? ((gr & ~1) * plane + r * P.iws + cc) * 4 + (gr & 1) * 2 : (gr * plane + r * P.iws + cc) * 4;
+            xdst[i] = (gr * plane + r * P.iws + cc) * 4;
             // lanes without a unit aim past the end of the buffer: the load returns zeros and moves no data
             xoff[i] = u < x_units ? (unsigned)(((gr * 4 * P.H + min(max(gy, 0), P.H - 1)) * P.W + gx) * 4) : 0xfffffff0u;
         }
@@ -529,12 +398,7 @@ __device__ __forceinline__ void conv_pass(typename MM<MF>::Acc (&acc)[NRT][NPT],
                 if (i * nthreads < x_units && (xmask[i] & 0x10u)) {
                     if (xs > 0 && (xmask[i] & 0x100u)) {
                         for (int e = 1; e <= xs; ++e) {
-                            if constexpr (PR) {
-                                *(uint2 *)(dst + xdst[i] - 4 * e) = uint2{0u, 0u};
-                                *(uint2 *)(dst + xdst[i] - 4 * e + plane * 4) = uint2{0u, 0u};
-                            } else {
-                                *(f32x4 *)(dst + xdst[i] - 4 * e) = f32x4{0.f, 0.f, 0.f, 0.f};
-                            }
+                            *(f32x4 *)(dst + xdst[i] - 4 * e) = f32x4{0.f, 0.f, 0.f, 0.f};
                         }
                     }
                     const int live = whole ? 4 : nch - xgrp[i];        // channels of this unit that exist
@@ -544,15 +408,7 @@ __device__ __forceinline__ void conv_pass(typename MM<MF>::Acc (&acc)[NRT][NPT],
                         f32x4 v;
 #pragma unroll
                         for (int j = 0; j < 4; ++j) v[j] = (in && j < live) ? xst[i][j][k] : 0.f;
-                        if constexpr (PR) {
-                            uint2 hi, lo;
-                            split_bf16(v[0], v[1], hi.x, lo.x);
-                            split_bf16(v[2], v[3], hi.y, lo.y);
-                            *(uint2 *)(dst + xdst[i] + 4 * k) = hi;
-                            *(uint2 *)(dst + xdst[i] + 4 * k + plane * 4) = lo;
-                        } else {
-                            *(f32x4 *)(dst + xdst[i] + 4 * k) = v;
-                        }
+                        *(f32x4 *)(dst + xdst[i] + 4 * k) = v;
                     }
                 }
             }
@@ -584,15 +440,16 @@ __device__ __forceinline__ void conv_pass(typename MM<MF>::Acc (&acc)[NRT][NPT],
         const int nkg = min(g.chunk_kg, c.nkg - kg0);
         if (g.active) {
             const float *bs = STAGE_X ? cur : bsrc + kg0 * (M::GPS * g.gstride);
-            if constexpr (PR)
-                conv_accum_b3<MF, KS, NRT, NPT>(acc, bs, off, g.src_w, g.gstride, cur + g.w_off, rloc, g.wg_rt, nkg);
-            else
-                conv_accum<MF, KS, NRT, NPT>(acc, bs, off, g.src_w, g.gstride, cur + g.w_off, rloc, g.wg_rt, nkg);
+            conv_accum<MF, KS, NRT, NPT>(acc, bs, off, g.src_w, g.gstride, cur + g.w_off, rloc, g.wg_rt, nkg);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     }
 }
+
+}  // namespace xl
+#include "split_conv.h"
+namespace xl {
 
 // The per-channel scale and shift (folded BN, bias) cost the epilogues nothing: xl_prepare multiplies
 // the scale into the re-laid-out filter (scale * sum(w x) = sum((scale w) x)), and the accumulators start
@@ -757,11 +614,12 @@ __device__ __forceinline__ void store_gap(const typename MM<MF>::Acc (&acc)[NRT]
 // must see outside the image: 0 for a convolution, -FLT_MAX for max pooling.
 // With `add` the result is added to what the tile already holds (the first of two producer layers
 // of a merge block, written by this same lane) and `relu_sum` is applied to the sum.
-// PR = 1: the tile is written as split-bf16 planes (see conv_accum_b3); `add` reads hi + lo back (exact in fp32).
+// PR > 0: the tile is written as planes of bf16 parts (split_conv.h), `flag` raised where a value does not come apart;
+// `add` reads the sum of the parts back.
 template <int MF, int NRT, int NPT, int PR = 0>
 __device__ __forceinline__ void store_mid(const typename MM<MF>::Acc (&acc)[NRT][NPT], const BlockParams &P,
                                           const ConvW &c, float *mid, int my0, int mx0, int rt0, int rt_end, int pt0,
-                                          int npx, float fill, bool add = false, bool relu_sum = false)
+                                          int npx, float fill, int *flag, bool add = false, bool relu_sum = false)
 {
     typedef MM<MF> M;
     const int lane = threadIdx.x & 63;
@@ -784,17 +642,19 @@ __device__ __forceinline__ void store_mid(const typename MM<MF>::Acc (&acc)[NRT]
                 const int cb = (rt0 + r) * MF + M::quad_row(q, sub);
                 f32x4 v;
                 const int gr = cb >> 2;
-                float *dst = PR ? mid + (gr & ~1) * P.mid_gstride + pidx * 4 + (gr & 1) * 2
+                float *dst = PR ? mid + (gr >> 1) * (PR + 1) * P.mid_gstride + pidx * 4 + (gr & 1) * 2
                                 : mid + gr * P.mid_gstride + pidx * 4;
                 f32x4 old = {0.f, 0.f, 0.f, 0.f};
                 if (add && pidx < npx) {
                     if constexpr (PR) {
-                        const uint2 oh = *(const uint2 *)dst, ol = *(const uint2 *)(dst + P.mid_gstride);
-                        auto up = [](unsigned bits) { return __builtin_bit_cast(float, bits); };
-                        old[0] = up(oh.x << 16) + up(ol.x << 16);
-                        old[1] = up(oh.x & 0xffff0000u) + up(ol.x & 0xffff0000u);
-                        old[2] = up(oh.y << 16) + up(ol.y << 16);
-                        old[3] = up(oh.y & 0xffff0000u) + up(ol.y & 0xffff0000u);
+#pragma unroll
+                        for (int i = PR; i >= 0; --i) {
+                            const uint2 w = *(const uint2 *)(dst + i * P.mid_gstride);
+                            old[0] += bf16_low(w.x);
+                            old[1] += bf16_high(w.x);
+                            old[2] += bf16_low(w.y);
+                            old[3] += bf16_high(w.y);
+                        }
                     } else {
                         old = *(const f32x4 *)dst;
                     }
@@ -808,12 +668,15 @@ __device__ __forceinline__ void store_mid(const typename MM<MF>::Acc (&acc)[NRT]
                     v[i] = z;
                 }
                 if constexpr (PR) {
-                    uint2 hi, lo;
-                    split_bf16(v[0], v[1], hi.x, lo.x);
-                    split_bf16(v[2], v[3], hi.y, lo.y);
                     if (pidx < npx) {
-                        *(uint2 *)dst = hi;
-                        *(uint2 *)(dst + P.mid_gstride) = lo;
+                        bool odd = false;
+                        store_parts<PR>(v, dst, P.mid_gstride, odd);
+                        if constexpr (PR == 2) {
+                            if (__builtin_expect(odd, 0)) {
+                                store_value_parts(v, dst, P.mid_gstride);
+                                *flag = 1;
+                            }
+                        }
                     }
                 } else {
                     if (pidx < npx) *(f32x4 *)dst = v;
@@ -870,7 +733,7 @@ __device__ __forceinline__ void store_tile(const typename MM<MF>::Acc (&acc)[NRT
 // Filter: [channel group][tap] float4, scale / shift: [channel group][2] float4 (re-laid out once).
 // ----------------------------------------------------------------------------
 template <int PR>
-__device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mid, float *xs, const float *ximg,
+__device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mid, float *xs, int *flag, const float *ximg,
                                                  unsigned long long x_bytes, int my0, int mx0, int iy0, int ix0)
 {
     const ConvW &c = P.c1;
@@ -924,13 +787,16 @@ __device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mi
                 o[j] = (inside && g * 4 + j < P.Cin) ? t : 0.f;
             }
         }
-        if constexpr (PR) {     // split-bf16 planes for the pointwise stage (see conv_accum_b3)
-            uint2 hi, lo;
-            split_bf16(o[0], o[1], hi.x, lo.x);
-            split_bf16(o[2], o[3], hi.y, lo.y);
-            float *dst = mid + (g & ~1) * P.mid_gstride + pidx * 4 + (g & 1) * 2;
-            *(uint2 *)dst = hi;
-            *(uint2 *)(dst + P.mid_gstride) = lo;
+        if constexpr (PR) {     // planes of bf16 parts for the pointwise stage
+            float *dst = mid + (g >> 1) * (PR + 1) * P.mid_gstride + pidx * 4 + (g & 1) * 2;
+            bool odd = false;
+            store_parts<PR>(o, dst, P.mid_gstride, odd);
+            if constexpr (PR == 2) {
+                if (__builtin_expect(odd, 0)) {
+                    store_value_parts(o, dst, P.mid_gstride);
+                    *flag = 1;
+                }
+            }
         } else {
             *(f32x4 *)(mid + g * P.mid_gstride + pidx * 4) = o;
         }
@@ -940,10 +806,12 @@ __device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mi
 // ----------------------------------------------------------------------------
 // The block kernel
 // ----------------------------------------------------------------------------
-template <int KIND, int MF1, int K1, int NRT1, int NPT1, int MF2, int NRT2, int NPT2, int K2A, int K2B, bool SC, int PX1, int PR = 0>
+// PR: bf16 parts of the operands of stage 2 (0: fp32 operands), PR1: of stage 1 (split_conv.h).
+template <int KIND, int MF1, int K1, int NRT1, int NPT1, int MF2, int NRT2, int NPT2, int K2A, int K2B, bool SC, int PX1, int PR = 0, int PR1 = 0>
 __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_WAVES)) block_kernel(const BlockParams P)
 {
-    static_assert(PR == 0 || PX1 == 0, "split-bf16 operands are staged through registers");
+    static_assert(PR1 == 0 || (PX1 == 0 && MF1 == 32), "split operands are staged through registers");
+    static_assert(PR == 0 || MF2 == 32, "split operands use 32-wide matrix-core tiles");
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int L = logical_block();
     if (L >= P.nblocks) return;
@@ -959,8 +827,7 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-    typedef MM<MF1, PR> M1;
-    constexpr int SUBP = PR ? 2 : 1;    // 16-byte planes per lane group of a K step (hi and lo for PR = 1)
+    typedef MM<MF1> M1;
 
     // tile origins: output -> intermediate (stage-2 window) -> input (stage-1 window)
     const int my0 = (KIND == KIND_SINGLE) ? oy0 : oy0 * P.s2 - P.P2;
@@ -971,10 +838,15 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
     float *mid = lds;
     float *buf = lds + P.lds_buf_off;
     const float *ximg = P.x + (size_t)n * P.Cin * P.H * P.W;
+    int *flag = (int *)(lds + P.flag_off);          // some pixel in LDS does not come apart (three parts only)
+    if constexpr (PR == 2) {
+        if (threadIdx.x == 0) *flag = 0;
+        if constexpr (PR1 == 2) lds_barrier();      // (stage 1 on fp32 operands has barriers before it could be raised)
+    }
 
     if constexpr (KIND == KIND_DW) {
         // ---- S1/S2 for a depthwise first layer: vector ALU from a staged input tile into the LDS tile
-        depthwise_stage1<PR>(P, mid, buf, ximg, (unsigned long long)(P.N - n) * P.Cin * P.H * P.W * 4ull, my0, mx0, iy0, ix0);
+        depthwise_stage1<PR>(P, mid, buf, flag, ximg, (unsigned long long)(P.N - n) * P.Cin * P.H * P.W * 4ull, my0, mx0, iy0, ix0);
     } else {
     // ---- S1: layer 1 over the (halo-extended) tile
     const int npx1 = P.mh * P.mw;
@@ -1001,12 +873,21 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
             pidx = pidx < npx1 ? pidx : 0;
             const int my = fdiv(pidx, P.rcp_mw), mx = pidx - my * P.mw;
             off1[p] = PX1 > 0 ? my * P.iws + max(mx - max(0, -ix0), 0) + sub * (4 * PX1 * 64)
-                              : ((my * P.c1.stride) * P.iws + mx * P.c1.stride) * 4 + sub * SUBP * P.in_gstride;
+                              : ((my * P.c1.stride) * P.iws + mx * P.c1.stride) * 4 + sub * (PR1 + 1) * P.in_gstride;
         }
     }
-    init_acc<MF1, NRT1, NPT1>(acc, P.c1, rt0);
-    conv_pass<MF1, K1, NRT1, NPT1, true, PX1, PR>(acc, P, P.c1, g1, nullptr, off1, buf, ximg,
-                                                  (unsigned long long)(P.N - n) * P.Cin * P.H * P.W * 4ull, iy0, ix0);
+    auto stage1 = [&](const ConvW &c) {
+        const unsigned long long x_bytes = (unsigned long long)(P.N - n) * P.Cin * P.H * P.W * 4ull;
+        auto init = [&](typename M1::Acc (&a)[NRT1][NPT1]) { init_acc<MF1, NRT1, NPT1>(a, c, rt0); };
+        init(acc);
+        if constexpr (PR1)
+            conv_pass_split<K1, NRT1, NPT1, PR1>(acc, P, c, rt0, pt0,
+                                                 g1.active ? __builtin_amdgcn_readfirstlane((npx1 - pt0 * MF1 + MF1 - 1) / MF1) : 0,
+                                                 off1, buf, flag, ximg, iy0, ix0, init);
+        else
+            conv_pass<MF1, K1, NRT1, NPT1, true, PX1>(acc, P, c, g1, nullptr, off1, buf, ximg, x_bytes, iy0, ix0);
+    };
+    stage1(P.c1);
 
     if constexpr (KIND == KIND_SINGLE) {
         if (P.gap) {
@@ -1021,15 +902,13 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
     } else {
         // ---- S2: epilogue of layer 1 into the LDS tile
         store_mid<MF1, NRT1, NPT1, (KIND == KIND_POOL ? 0 : PR)>(acc, P, P.c1, mid, my0, mx0, rt0, rt_end1, pt0, npx1,
-                                                                 KIND == KIND_POOL ? -FLT_MAX : 0.f);
+                                                                 KIND == KIND_POOL ? -FLT_MAX : 0.f, flag);
         if constexpr (KIND == KIND_FUSED2 && K1 == 1 && K2A == 1 && K2B == 0 && !SC) {
             if (P.n1 == 2) {
                 // second producer of a merge block (paper Fig. 4c): same input, same geometry, its own
                 // filter; its result is added to the first one's in the LDS tile
-                init_acc<MF1, NRT1, NPT1>(acc, P.c1b, rt0);
-                conv_pass<MF1, K1, NRT1, NPT1, true, PX1, PR>(acc, P, P.c1b, g1, nullptr, off1, buf, ximg,
-                                                         (unsigned long long)(P.N - n) * P.Cin * P.H * P.W * 4ull, iy0, ix0);
-                store_mid<MF1, NRT1, NPT1, PR>(acc, P, P.c1b, mid, my0, mx0, rt0, rt_end1, pt0, npx1, 0.f, true,
+                stage1(P.c1b);
+                store_mid<MF1, NRT1, NPT1, PR>(acc, P, P.c1b, mid, my0, mx0, rt0, rt_end1, pt0, npx1, 0.f, flag, true,
                                                P.relu_mid != 0);
             }
         }
@@ -1084,8 +963,11 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
             const int lg_r2 = __builtin_ctz(P.waves_r2);
             const int wr2 = wave & (P.waves_r2 - 1), wp2 = wave >> lg_r2;
             const int wg_pt2 = (nwaves >> lg_r2) * NPT2;
+            float *tile2 = PR ? lds + P.tile2_off : buf;        // KIND_FUSED2P: what is pooled
+            const bool whole_px = PR == 2 && __builtin_amdgcn_readfirstlane(*flag) != 0;
             auto run_conv = [&](auto ks_tag, const ConvW &c, int coff, int chunk_kg2) {
                 constexpr int KS2 = decltype(ks_tag)::value;
+                const bool whole = PR == 2 && (whole_px || weights_flag(c));
                 const int per = udiv(c.nrt + P.csplit - 1, P.csplit, P.rcp_csplit);     // row tiles of this workgroup
                 const int rtb = cs * per, rte = min(c.nrt, rtb + per);
                 PassGeom g2;
@@ -1110,14 +992,35 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
                             const int pidx = (p0 + p) * MF2 + col;
                             const int oyu = fdiv(pidx, P.rcp_vw2);
                             const int oy = min(oyu, P.th - 1), ox = min(pidx - oyu * P.vw2, P.tw - 1);
-                            off2[p] = ((oy * P.s2 + d) * P.mw + ox * P.s2 + d) * 4 + sub * SUBP * P.mid_gstride;
+                            off2[p] = ((oy * P.s2 + d) * P.mw + ox * P.s2 + d) * 4 + sub * (PR + 1) * P.mid_gstride;
                         }
-                        conv_pass<MF2, KS2, NRT2, NPT2, false, 0, PR>(acc2, P, c, g2, mid, off2, buf, nullptr, 0ull, 0, 0);
+                        if constexpr (PR) {
+                            // the filter comes from memory: a wave needs nothing of the others, and a pass whose
+                            // result stays in registers has no barrier
+                            if (g2.active && !whole) {
+                                f32x16 small[NRT2][NPT2];
+#pragma unroll
+                                for (int r = 0; r < NRT2; ++r)
+#pragma unroll
+                                    for (int p = 0; p < NPT2; ++p) zero_acc(small[r][p]);
+                                conv_direct<KS2, NRT2, NPT2, PR>(acc2, small, mid, off2, P.mw, P.mid_gstride, c, r0, 0,
+                                                                 c.nkg, __builtin_amdgcn_readfirstlane(npt2 - p0), [] {});
+                                if constexpr (PR == 2) add_small<NRT2, NPT2>(acc2, small);
+                            } else if (g2.active) {
+                                conv_whole<KS2, NRT2, NPT2>(acc2, c, r0, [&](int p, int kg, int t, int e) {
+                                    const int at = kg * 6 * P.mid_gstride + off2[p] + (t / KS2 * P.mw + t % KS2) * 4;
+                                    const unsigned short *v = (const unsigned short *)(mid + at) + e;
+                                    return bf16_low(v[0]) + (bf16_low(v[2 * P.mid_gstride]) + bf16_low(v[4 * P.mid_gstride]));
+                                });
+                            }
+                        } else {
+                            conv_pass<MF2, KS2, NRT2, NPT2, false>(acc2, P, c, g2, mid, off2, buf, nullptr, 0ull, 0, 0);
+                        }
                         if constexpr (KIND == KIND_FUSED2P) {
                             // the pass covers every pixel of the tile (planner): its result goes to an LDS tile
                             // over the staging buffers, which no wave reads any more, and is pooled from there
                             if (g2.active)
-                                store_tile<MF2, NRT2, NPT2>(acc2, P, c, buf, oy0, ox0, wr2 * NRT2, r0, rte, p0);
+                                store_tile<MF2, NRT2, NPT2>(acc2, P, c, tile2, oy0, ox0, wr2 * NRT2, r0, rte, p0);
                             __syncthreads();
                             const int ngr = (min(rte - rp, g2.wg_rt) * MF2) >> 2;
                             const int npo = P.pth * P.ptw, npx2 = P.th * P.tw;
@@ -1127,7 +1030,7 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
                                 const int py = fdiv(pidx, P.rcp_pw), px = pidx - py * P.ptw;
                                 const int gy = ty * P.pth + py, gx = tx * P.ptw + px;
                                 if (gy >= P.Ho || gx >= P.Wo) continue;
-                                const float *sp = buf + (gq * npx2 + (py * P.ps2) * P.tw + px * P.ps2) * 4;
+                                const float *sp = tile2 + (gq * npx2 + (py * P.ps2) * P.tw + px * P.ps2) * 4;
                                 f32x4 m = {-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX};
                                 if (P.pool_k == 3) {        // the usual window, unrolled: nine reads in flight together
                                     f32x4 t[9];
@@ -1419,7 +1322,7 @@ __global__ void __launch_bounds__(MAX_THREADS, 4) pool_stream_kernel(const Block
 }
 
 }  // namespace xl
-#ifndef XL_TU_B3
+#ifndef XL_TU_SPLIT
 #include "thin_conv.h"
 #endif
 namespace xl {
@@ -1439,20 +1342,24 @@ static hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, size_
     return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, argv, lds, s);
 }
 
-// This file is compiled twice: once for the fp32 variants and everything else, and once with
-// XL_TU_B3 defined for the split-bf16 variants alone (the two halves build in parallel).
+// This file is compiled several times, in parallel: once for the fp32 variants and everything else, and once for each
+// part of the split-bf16 variants (XL_TU_SPLIT = the list, XL_TU_PR = parts - 1).
 typedef void (*BlockKernel)(const BlockParams);
-BlockKernel kernel_of_b3(int variant);
+BlockKernel split_kernel_A1(int), split_kernel_B1(int), split_kernel_C1(int);
+BlockKernel split_kernel_A2(int), split_kernel_B2(int), split_kernel_C2(int);
 
-#ifdef XL_TU_B3
-BlockKernel kernel_of_b3(int variant)
+#ifdef XL_TU_SPLIT
+#define XL_CAT_(a, b, c) a##b##c
+#define XL_CAT(a, b, c) XL_CAT_(a, b, c)
+BlockKernel XL_CAT(split_kernel_, XL_TU_SPLIT, XL_TU_PR)(int variant)
 {
-    switch (variant) {
-#define X(ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1)                                 \
-    case ID:                                                                                                 \
-        return block_kernel<KIND, MF1, K1, NRT1, NPT1, (MF2 == 0 ? 32 : MF2), (NRT2 == 0 ? 1 : NRT2),        \
-                            (NPT2 == 0 ? 1 : NPT2), (K2A == 0 ? 1 : K2A), K2B, (SC != 0), PX1, 1>;
-        XL_VARIANT_LIST_B3(X)
+    switch (variant - SPLIT_ID0[XL_TU_PR]) {
+#define X(ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, S1)                                     \
+    case ID:                                                                                                         \
+        return block_kernel<KIND, MF1, K1, NRT1, NPT1, (MF2 == 0 ? 32 : MF2), (NRT2 == 0 ? 1 : NRT2),                \
+                            (NPT2 == 0 ? 1 : NPT2), (K2A == 0 ? 1 : K2A), K2B, (SC != 0), PX1, XL_TU_PR,             \
+                            (S1 ? XL_TU_PR : 0)>;
+        XL_CAT(XL_SPLIT_LIST, _, XL_TU_SPLIT)(X)
 #undef X
     }
     return nullptr;
@@ -1481,7 +1388,11 @@ static BlockKernel kernel_of(int variant)
         XL_VARIANT_LIST(X)
 #undef X
     }
-    return kernel_of_b3(variant);
+    if (variant >= SPLIT_ID0[1]) {
+        for (auto part : {split_kernel_A1, split_kernel_B1, split_kernel_C1, split_kernel_A2, split_kernel_B2, split_kernel_C2})
+            if (BlockKernel k = part(variant)) return k;
+    }
+    return nullptr;
 }
 
 hipError_t configure_kernels(int max_lds_bytes)
@@ -1536,50 +1447,63 @@ __global__ void pack_filter_kernel(const float *__restrict__ w, const float *__r
     wp[idx] = v;
 }
 
-// split-bf16 form: [K step][tap][row tile][hi, lo][lane] of 8 bf16;
-//   lane l holds cout = rt*mf + l%mf, cin = kg*kc + (l/mf)*8 + e, kc = 16 (mf = 32) or 32 (mf = 16);
-//   hi = bf16(w), lo = bf16(w - hi), round to nearest.
-__global__ void pack_filter_b3_kernel(const float *__restrict__ w, const float *__restrict__ scale, uint4 *__restrict__ wp,
-                                      int cout, int cin, int k, int mf, int nkg, int nrt)
+// Split-bf16 form (32-wide tiles): [K step][tap][row tile][part][lane] of 8 bf16;
+//   lane l holds cout = rt*32 + l%32, cin = kg*16 + (l/32)*8 + e.  `flag` (three parts) is raised by a value that does
+// not come apart (split_conv.h); launch_pack_affine has cleared it.
+template <int PR>
+__global__ void pack_filter_split_kernel(const float *__restrict__ w, const float *__restrict__ scale,
+                                         uint4 *__restrict__ wp, int *flag, int cout, int cin, int k, int nkg, int nrt)
 {
     const int taps = k * k;
-    const long long total = (long long)nkg * taps * nrt * 128;
+    const long long total = (long long)nkg * taps * nrt * 64;
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= total) return;
     const int lane = (int)(idx & 63);
-    const int part = (int)((idx >> 6) & 1);
-    long long r = idx >> 7;
+    long long r = idx >> 6;
     const int rt = (int)(r % nrt);
     r /= nrt;
     const int t = (int)(r % taps);
     const int kg = (int)(r / taps);
-    const int o = rt * mf + lane % mf;
-    const int sub = lane / mf;
-    const int kc = mf == 32 ? 16 : 32;
-    unsigned out[4];
+    const int o = rt * 32 + lane % 32;
+    const int sub = lane / 32;
+    unsigned out[PR + 1][4];
+    bool odd = false;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         float v[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int ci = kg * kc + sub * 8 + 2 * e + h;
+            const int ci = kg * 16 + sub * 8 + 2 * e + h;
             v[h] = (o < cout && ci < cin) ? w[((size_t)o * cin + ci) * taps + t] * (scale ? scale[o] : 1.f) : 0.f;
         }
-        unsigned hi, lo;
-        split_bf16(v[0], v[1], hi, lo);
-        out[e] = part ? lo : hi;
+        unsigned p[PR + 1];
+        bool here = false;
+        split_pair<PR>(v[0], v[1], p, here);
+        if constexpr (PR == 2) {
+            if (here) value_parts(v[0], v[1], p);
+        }
+        odd |= here;
+#pragma unroll
+        for (int i = 0; i <= PR; ++i) out[i][e] = p[i];
     }
-    wp[idx] = uint4{out[0], out[1], out[2], out[3]};
+    if (PR == 2 && odd) atomicOr(flag, 1);
+    uint4 *dst = wp + (idx >> 6) * (64 * (PR + 1)) + lane;
+#pragma unroll
+    for (int i = 0; i <= PR; ++i) dst[i * 64] = uint4{out[i][0], out[i][1], out[i][2], out[i][3]};
 }
 
 hipError_t launch_pack_filter(const float *w, const float *scale, f32x4 *wp, int cout, int cin, int k, int mf, int nkg,
                               int nrt, hipStream_t s, int pairs, int pr)
 {
-    const long long total = (long long)nkg * k * k * nrt * (pr ? 128 : 64);
+    const long long total = (long long)nkg * k * k * nrt * 64;
     const int threads = 256;
     const int grid = (int)((total + threads - 1) / threads);
-    if (pr)
-        return launch(pack_filter_b3_kernel, dim3(grid), dim3(threads), 0, s, w, scale, (uint4 *)wp, cout, cin, k, mf, nkg, nrt);
+    if (pr) {
+        const size_t bytes = packed_filter_bytes(nkg, k * k, nrt, pr);
+        int *flag = reinterpret_cast<int *>(reinterpret_cast<char *>(wp) + packed_affine_offset(bytes) + packed_affine_bytes(nrt, mf) - 16);
+        return launch(pr == 2 ? pack_filter_split_kernel<2> : pack_filter_split_kernel<1>, dim3(grid), dim3(threads), 0, s,
+                      w, scale, (uint4 *)wp, flag, cout, cin, k, nkg, nrt);
+    }
     return launch(pack_filter_kernel, dim3(grid), dim3(threads), 0, s, w, scale, wp, cout, cin, k, mf, nkg, nrt, pairs);
 }
 
@@ -1595,6 +1519,7 @@ __global__ void pack_affine_kernel(const float *__restrict__ shift, f32x4 *__res
 {
     const int nq = mf == 32 ? 4 : 1;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;     // over nrt * nq * 64
+    if (mf == 32 && idx == 0) *reinterpret_cast<int *>(out + nrt * nq * 64) = 0;     // see packed_affine_bytes
     if (idx >= nrt * nq * 64) return;
     const int lane = idx & 63, q = (idx >> 6) % nq, rt = (idx >> 6) / nq;
     const int sub = lane / mf;
@@ -1913,7 +1838,7 @@ hipError_t launch_depthwise(const float *x, float *y, const f32x4 *wp, const f32
                        pad, relu, Cy, coff, total);
 }
 
-#endif  // XL_TU_B3
+#endif  // XL_TU_SPLIT
 
 }  // namespace xl
 

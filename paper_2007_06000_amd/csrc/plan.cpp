@@ -18,12 +18,15 @@ const std::vector<Variant> &variants()
 {
     static const std::vector<Variant> v = {
 #define X(ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1) \
-    Variant{ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, 0},
+    Variant{ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, 0, 0},
         XL_VARIANT_LIST(X)
 #undef X
-#define X(ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1) \
-    Variant{ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, 1},
-        XL_VARIANT_LIST_B3(X)
+#define X(ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, S1) \
+    Variant{SPLIT_ID0[1] + ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, 1, S1 ? 1 : 0}, \
+    Variant{SPLIT_ID0[2] + ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, 2, S1 ? 2 : 0},
+        XL_SPLIT_LIST_A(X)
+        XL_SPLIT_LIST_B(X)
+        XL_SPLIT_LIST_C(X)
 #undef X
     };
     return v;
@@ -101,6 +104,8 @@ struct Choice {
     int tiles_y = 0, tiles_x = 0;
     int chunk_kg = 0, chunk_kg2[2] = {1, 1};
     int mid_floats = 0, buf_floats = 0, w_off1 = 0;
+    int tile2_floats = 0, tile2_off = 0, flag_off = 0;      // KIND_FUSED2P on split operands: the tile that is pooled; the flag
+    bool mid_over_staging = false;
     int lds_bytes = 0, occ = 1;
     long long flops_exec = 0;
     bool lds_rejected = false;
@@ -114,15 +119,17 @@ static std::vector<int> tile_candidates(int extent)
 }
 
 // matrix-pipe cycles of one K step of one (row tile, pixel tile) pair and tap: four fp32 operations of
-// 64 / 32 cycles, or three bf16 ones of 32 / 16 cycles over twice the channels
-static double kstep_clk(int mf, int pr) { return pr ? 3 * (mf == 32 ? 32.0 : 16.0) : 4 * (mf == 32 ? 64.0 : 32.0); }
+// 64 / 32 cycles, or three or six bf16 ones over 16 channels.  Those take 32 cycles, but a chip full of them runs at its
+// power limit (1.65 to 1.75 GHz with real operands, 2.2 with zeros): 44 cycles of the nominal 2.4 GHz.
+static double kstep_clk(int mf, int pr) { return pr ? products_of(pr) * 44.0 : 4 * (mf == 32 ? 64.0 : 32.0); }
 
 // Largest number of K steps per chunk the stagers can hold, shortened so that one chunk keeps
 // the matrix cores busy for about `want_clk` cycles (amortises the per-chunk barrier) and no more.
-static int pick_chunk(int nkg, int x_units_per_kg, int w_items_per_kg, int threads, double clk_per_kg, double want_clk)
+// max_units: input units the workgroup stages per chunk.
+static int pick_chunk(int nkg, int x_units_per_kg, int w_items_per_kg, int max_units, double clk_per_kg, double want_clk)
 {
     int cap = nkg;
-    if (x_units_per_kg > 0) cap = std::min(cap, STAGE_UNITS * threads / x_units_per_kg);
+    if (x_units_per_kg > 0) cap = std::min(cap, max_units / x_units_per_kg);
     cap = std::min(cap, MAX_W_CHUNK_BYTES / (16 * std::max(w_items_per_kg, 1)));
     if (cap < 1) return 0;
     int want = (int)std::ceil(want_clk / std::max(clk_per_kg, 1.0));
@@ -137,11 +144,11 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     const Variant &v = c.v;
     const int nw = c.threads / 64;
     const int mf1 = v.mf1;
-    const int nrt1 = ceil_div(b.c1.cout, mf1), nkg1 = ceil_div(b.c1.cin, kc_of(mf1, v.pr));
+    const int nrt1 = ceil_div(b.c1.cout, mf1), nkg1 = ceil_div(b.c1.cin, kc_of(mf1, v.pr1));
     const int taps1 = b.c1.k * b.c1.k;
     const int npx1 = c.mh * c.mw;
     const int wg_rt = c.waves_r1 * v.nrt1;
-    const double wave1 = (double)v.nrt1 * v.npt1 * nkg1 * taps1 * kstep_clk(mf1, v.pr);
+    const double wave1 = (double)v.nrt1 * v.npt1 * nkg1 * taps1 * kstep_clk(mf1, v.pr1);
     double simd[4] = {0, 0, 0, 0};
     for (int w = 0; w < nw; ++w) {
         const int wr = w % c.waves_r1, wp = w / c.waves_r1;
@@ -152,6 +159,8 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     double t1 = *std::max_element(simd, simd + 4) * b.n1;
     if (v.px1 < 0) t1 *= -v.px1 / 4.0;      // only -px1 of the 4 channel slots carry matrix operations
     if (v.px1 > 0) t1 *= 0.9;       // planar input chunks: no register staging, no vector-ALU work in the K loop
+    // taking the input apart: about 110 vector instructions per 64 pixels x 8 channels
+    if (v.pr1) t1 += b.n1 * ceil_div(b.c1.cin, 8) * ceil_div(c.ih * c.iw, 64) / 4.0 * 500.0;
     int barriers = ceil_div(nkg1, c.chunk_kg) * b.n1;
     if (b.kind == KIND_DW) {
         // vector ALU: staging one float4 per (channel group, input pixel), then per (channel group,
@@ -162,6 +171,7 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
         barriers = 1;
     }
     double t2 = 0;
+    int passes = 0;
     long long flops2 = 0;
     if (b.kind == KIND_FUSED2 || b.kind == KIND_DW || b.kind == KIND_FUSED2P) {
         const int mf2 = v.mf2, NRT2 = v.nrt2, NPT2 = v.npt2;
@@ -180,10 +190,11 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
                         if (r0 < per && p0 < npt2) s2[w % 4] += wave2;
                     }
                     t2 += *std::max_element(s2, s2 + 4) + 2500.0;       // + epilogue / prologue of the pass
+                    ++passes;
                     if (b.kind == KIND_FUSED2P)     // pooling of the pass from LDS: two barriers, one float4 window per item
                         t2 += 700.0 + (double)std::min(wg_rt2, per - rp) * mf2 / 4 * c.pth * c.ptw * b.pool_k * b.pool_k * 8.0 /
                                           c.threads * 4;
-                    barriers += ceil_div(nkg, c.chunk_kg2[ci]);
+                    if (!v.pr) barriers += ceil_div(nkg, c.chunk_kg2[ci]);      // (split operands: no filter chunks)
                     flops2 += 2LL * std::min(wg_rt2, per - rp) * mf2 * std::min(wg_pt2, npt2 - pp) * mf2 * nkg *
                               kc_of(mf2, v.pr) * s.k * s.k;
                 }
@@ -195,7 +206,17 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     const double wg_clk = t1 + t2 + ovh;
     const long long nwg = (long long)c.tiles_x * c.tiles_y * c.csplit * b.N;
     const double rounds = std::ceil((double)nwg / pl.num_cus);
-    const double t_mfma = rounds * wg_clk * (c.occ >= 2 ? 1.0 : 1.08) / 2.4e9;
+    double t_mfma = rounds * wg_clk * (c.occ >= 2 ? 1.0 : 1.08) / 2.4e9;
+    if (v.pr) {
+        // `occ` workgroups of a compute unit share the matrix cores while each waits for its own loads, barriers and
+        // stores: they finish after the matrix work of all or the whole life of one, whichever is longer.  (The three
+        // latencies are fitted to 36 blocks of 600 timed candidates each: the first choice is 5.5 % behind the best one on
+        // average, 14 % with the formula above; the best of the 64 kept ones 0.6 %.)
+        const double lat = 5000.0 + 700.0 * barriers + 2000.0 * passes, mat = t1 + t2 - 2500.0 * passes;
+        const int per_cu = (int)rounds, full = per_cu / c.occ, rest = per_cu % c.occ;
+        const double life = mat + lat;
+        t_mfma = (full * std::max(c.occ * mat, life) + (rest ? std::max(rest * mat, life) : 0.0)) / 2.4e9;
+    }
 
     // memory side: algorithmic bytes at HBM speed plus per-workgroup cache-line traffic at L2 speed
     auto lines = [](int w) { return (double)((w * 4 + 64 + 127) / 128) * 128.0; };
@@ -210,7 +231,7 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     // with pixels and channels rounded up to whole matrix-core tiles
     const long long tiles = (long long)c.tiles_x * c.tiles_y * b.N;
     const long long s1 = b.kind == KIND_DW ? 2LL * b.Cin * npx1 * taps1
-                                           : 2LL * nrt1 * mf1 * ceil_div(npx1, mf1) * mf1 * nkg1 * kc_of(mf1, v.pr) * taps1;
+                                           : 2LL * nrt1 * mf1 * ceil_div(npx1, mf1) * mf1 * nkg1 * kc_of(mf1, v.pr1) * taps1;
     c.flops_exec = tiles * (b.kind == KIND_SINGLE ? 1 : c.csplit) * s1 * b.n1 + tiles * c.csplit * flops2;
 }
 
@@ -339,8 +360,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
         const int px = v.px1 > 0 ? v.px1 : 0;
         if (px > 0 && !(b.c1.k == 1 && b.c1.stride == 1 && b.c1.pad == 0 && b.c1.cin % kc_of(v.mf1) == 0)) continue;
         const int mf1 = v.mf1;
-        const int nrt1 = ceil_div(b.c1.cout, mf1), nkg1 = ceil_div(b.c1.cin, kc_of(mf1, v.pr));
-        const int frows = v.pr ? 2 : 1;         // 1 KB filter rows per (K step, tap, row tile): hi and lo when split
+        const int nrt1 = ceil_div(b.c1.cout, mf1), nkg1 = ceil_div(b.c1.cin, kc_of(mf1, v.pr1));
         const int taps1 = b.c1.k * b.c1.k;
         for (int threads : {256, 512}) {
             if (pl.opts.force_threads > 0 && pl.opts.force_threads != threads) continue;
@@ -387,11 +407,15 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     c.tiles_y = ceil_div(b.Ho, th);
                     c.tiles_x = ceil_div(b.Wo, tw);
                     // stage-1 chunk: input tile chunk + filter chunk per buffer
-                    const int x_per_kg = gps_of(mf1, v.pr) * c.ih * ((c.iw + 3) / 4 * 4);       // LDS rows hold whole 4-pixel units
-                    const int w_per_kg = taps1 * wg_rt * 64 * frows;
-                    const double clk1 = (double)(nw / 4.0) * v.nrt1 * v.npt1 * taps1 * kstep_clk(mf1, v.pr);
-                    const int x_units_per_kg = gps_of(mf1, v.pr) * c.ih * ceil_div(c.iw, 4);     // 4-pixel row pieces
-                    c.chunk_kg = dw ? 1 : pick_chunk(nkg1, px > 0 ? 0 : x_units_per_kg, w_per_kg, threads, clk1, want_clk);
+                    // (16-byte LDS items per K step: 4-channel groups whose rows hold whole 4-pixel units, or the part
+                    // planes of 8-channel groups; split operands take the filter from memory)
+                    const int x_per_kg = v.pr1 ? 2 * parts_of(v.pr1) * c.ih * c.iw : gps_of(mf1) * c.ih * ((c.iw + 3) / 4 * 4);
+                    const int w_per_kg = v.pr1 ? 0 : taps1 * wg_rt * 64;
+                    const int max_units = v.pr1 ? SPLIT_STAGE_UNITS * nw : STAGE_UNITS * threads;
+                    const double clk1 = (double)(nw / 4.0) * v.nrt1 * v.npt1 * taps1 * kstep_clk(mf1, v.pr1);
+                    // 4-channel groups of 4-pixel row pieces, or 8-channel groups of 64 pixels
+                    const int x_units_per_kg = v.pr1 ? 2 * ceil_div(c.ih * c.iw, 64) : gps_of(mf1) * c.ih * ceil_div(c.iw, 4);
+                    c.chunk_kg = dw ? 1 : pick_chunk(nkg1, px > 0 ? 0 : x_units_per_kg, w_per_kg, max_units, clk1, want_clk);
                     if (px > 0)     // planar chunk: kc x px x 16 quads per K step, at most PLANAR_SLOTS wave loads per wave
                         c.chunk_kg = std::min(c.chunk_kg, PLANAR_SLOTS * nw * 64 / (kc_of(mf1) * px * 16));
                     if (c.chunk_kg < 1) continue;
@@ -399,12 +423,17 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     c.w_off1 = c.chunk_kg * x_per_kg * 4 + 16;        // + slack for a left-edge unit running past the last row
                     if (px > 0) c.w_off1 = c.chunk_kg * kc_of(mf1) * px * 64;
                     int buf1 = c.w_off1 + c.chunk_kg * w_per_kg * 4;
-                    c.mid_floats = b.kind == KIND_SINGLE ? 0 : nrt1 * mf1 / 4 * c.mh * c.mw * 4;
+                    // floats of the LDS tile: 4 bytes per element, or one bf16 per part in planes of 8 channels
+                    const bool split_mid = v.pr && two;
+                    auto mid_size = [&](int channels) {
+                        return (split_mid ? channels / 8 * parts_of(v.pr) : channels / 4) * c.mh * c.mw * 4;
+                    };
+                    c.mid_floats = b.kind == KIND_SINGLE ? 0 : mid_size(nrt1 * mf1);
                     if (dw) {       // the whole input tile, every channel, staged once; no filter chunk
                         const int ncg = ceil_div(b.Cin, 4);
                         c.w_off1 = 0;
                         buf1 = ncg * c.ih * ((c.iw + 3) / 4 * 4) * 4;
-                        c.mid_floats = ceil_div(b.Cin, 16) * 4 * c.mh * c.mw * 4;     // whole K steps of the pointwise stage
+                        c.mid_floats = mid_size(ceil_div(b.Cin, 16) * 16);      // whole K steps of the pointwise stage
                     }
 
                     std::vector<int> splits, wr2s, vws;
@@ -438,6 +467,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                                 // staging buffers: passes with several chunks ping-pong between two buffers
                                 // `multi` floats apart, a single-chunk pass only ever touches the first one
                                 int multi = 0, single = 0;
+                                c.tile2_floats = 0;
                                 ((!dw && ceil_div(nkg1, c.chunk_kg) > 1) ? multi : single) = buf1;
                                 bool fits = true;
                                 if (two) {
@@ -450,14 +480,16 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                                         // one pass must cover every pixel of the stage-2 tile, and its result
                                         // (row tiles of the pass x tile pixels) is pooled from the staging area
                                         if (ceil_div(c.th * vw, v.mf2) > (nw / w2) * NPT2) continue;
-                                        single = std::max(single, w2 * NRT2 * v.mf2 * c.th * c.tw);
+                                        // (split operands: an area of its own, the next pass reads the LDS tile)
+                                        int &area = v.pr ? c.tile2_floats : single;
+                                        area = std::max(area, w2 * NRT2 * v.mf2 * c.th * c.tw);
                                     }
-                                    for (int i = 0; i < b.n2; ++i) {
+                                    for (int i = 0; i < b.n2 && !v.pr; ++i) {
                                         const int nkg2 = ceil_div(b.c2[i].cin, kc_of(v.mf2, v.pr));
-                                        const int w2_per_kg = b.c2[i].k * b.c2[i].k * w2 * NRT2 * 64 * frows;
+                                        const int w2_per_kg = b.c2[i].k * b.c2[i].k * w2 * NRT2 * 64;
                                         const double clk2 = (double)(nw / 4.0) * NRT2 * NPT2 * b.c2[i].k * b.c2[i].k *
                                                             kstep_clk(v.mf2, v.pr);
-                                        c.chunk_kg2[i] = pick_chunk(nkg2, 0, w2_per_kg, threads, clk2, want_clk);
+                                        c.chunk_kg2[i] = pick_chunk(nkg2, 0, w2_per_kg, 0, clk2, want_clk);
                                         if (c.chunk_kg2[i] < 1) {
                                             fits = false;
                                             break;
@@ -469,14 +501,25 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                                 }
                                 if (!fits) continue;
                                 c.buf_floats = multi;
-                                c.lds_bytes = (c.mid_floats + std::max(single, 2 * multi)) * 4;
+                                if (b.gap && v.pr) single = std::max(single, nw / wr * wg_rt * mf1);     // store_gap's partial sums
+                                const int staging = std::max(single, 2 * multi);
+                                // split operands stage nothing once layer 1 is done: the LDS tile takes the place of
+                                // its buffers, except where both are in use together
+                                c.mid_over_staging = v.pr && !dw && b.n1 == 1;
+                                c.lds_bytes = (c.mid_over_staging ? std::max(c.mid_floats + c.tile2_floats, staging)
+                                                                  : c.mid_floats + staging + c.tile2_floats) * 4;
+                                c.tile2_off = c.mid_floats + (c.mid_over_staging ? 0 : staging);
+                                c.flag_off = c.lds_bytes / 4;
+                                if (v.pr == 2) c.lds_bytes += 16;
                                 if (c.lds_bytes > pl.lds_budget) {
                                     any_lds_reject = true;
                                     continue;
                                 }
                                 // waves per SIMD the registers allow: the conv -> pool kernels are built for 4
-                                // (at most 128 registers), the others for 2
-                                const int reg_waves = b.kind == KIND_POOL ? 16 : 8;
+                                // (at most 128 registers), the others for 2; split-bf16 kernels of one tile per wave
+                                // need fewer than 128, of two at most 168 unless they stage their input
+                                const int tiles_wave = v.pr ? std::max(v.pr1 ? v.nrt1 * v.npt1 : 1, two ? v.nrt2 * v.npt2 : 1) : 0;
+                                const int reg_waves = b.kind == KIND_POOL || tiles_wave == 1 ? 16 : (tiles_wave == 2 && !v.pr1) ? 12 : 8;
                                 c.occ = std::max(1, std::min({pl.lds_per_cu / std::max(c.lds_bytes, 1), 2048 / threads,
                                                               reg_waves / nw}));
                                 evaluate(b, pl, c);
@@ -683,6 +726,11 @@ struct Builder {
         for (size_t i = 0; i < pl.packed.size(); ++i)
             if (pl.packed[i].layer == layer && pl.packed[i].mf == mf && pl.packed[i].pairs == pairs && pl.packed[i].pr == pr)
                 return (int)i;
+        pl.packed.push_back(packed_form(layer, mf, pairs, pr));
+        return (int)pl.packed.size() - 1;
+    }
+    PackedFilter packed_form(int layer, int mf, bool pairs, int pr) const
+    {
         const xl_layer &L = pl.layers[layer];
         PackedFilter p;
         p.layer = layer;
@@ -700,40 +748,57 @@ struct Builder {
         } else {
             p.nkg = pairs ? 1 : ceil_div(L.cin, kc_of(mf, pr));
             p.nrt = ceil_div(L.cout, mf);
-            p.bytes = (size_t)p.nkg * L.k * L.k * p.nrt * 64 * 16 * (pr ? 2 : 1);
-            p.aff_bytes = (size_t)p.nrt * (mf == 32 ? 4 : 1) * 64 * 16;
+            p.bytes = packed_filter_bytes(p.nkg, L.k * L.k, p.nrt, pr);
+            p.aff_bytes = packed_affine_bytes(p.nrt, mf);
         }
         p.offset = 0;
         p.aff_offset = 0;
-        pl.packed.push_back(p);
-        return (int)pl.packed.size() - 1;
+        return p;
+    }
+
+    // Filter forms (layer, tile, pairs) that the fp32 candidates of the plan's launches would use, were there no others:
+    // xl_run_static accepts a plan by their size, so that what fits its array does not depend on which kernels rank well.
+    std::set<std::tuple<int, int, bool>> fp32_forms;
+    void count_fp32_forms(const BlockSpec &b, const Choice &c)
+    {
+        fp32_forms.insert(std::make_tuple(b.c1.layer, b.kind == KIND_DW ? 0 : (c.v.kind == KIND_THIN ? -1 : c.v.mf1), c.v.px1 < 0));
+        if (b.n1 == 2) fp32_forms.insert(std::make_tuple(b.c1b.layer, c.v.mf1, false));
+        if (b.kind == KIND_FUSED2 || b.kind == KIND_DW || b.kind == KIND_FUSED2P)
+            for (int i = 0; i < b.n2; ++i) fp32_forms.insert(std::make_tuple(b.c2[i].layer, c.v.mf2, false));
     }
 
     // Turn a searched choice into a launch step.
     xl_status make_block_step(const BlockSpec &b, int x_id, int y_id, int sc_id, int coff1, Step &st, Choice &ch,
                               const std::string &what)
     {
-        bool lds_rejected = false;
-        // split-bf16 kernels where the plan asks for them and a variant covers the block, fp32 ones otherwise
+        // Whether a block can be planned at all is decided by the fp32 kernels alone (the others need less LDS).
+        bool lds_rejected = false, ignored = false;
         std::vector<Choice> ranked = search(b, pl, lds_rejected, 0);
-        if (pl.opts.precision == XL_PRECISION_BF16X3) {
-            // the split-bf16 candidates first (the cost model cannot rank the two kinds against each other
-            // well: blocks that are not bound by the matrix cores gain nothing from the split), then the
-            // best fp32 ones, for xl_tune to choose from
-            bool rej1 = false;
-            std::vector<Choice> split = search(b, pl, rej1, 1);
-            if (!split.empty()) {
-                const size_t keep32 = MAX_ALTERNATIVES / 4;
-                if (split.size() > MAX_ALTERNATIVES - keep32) split.resize(MAX_ALTERNATIVES - keep32);
-                if (ranked.size() > keep32) ranked.resize(keep32);
-                split.insert(split.end(), ranked.begin(), ranked.end());
-                ranked.swap(split);
-                lds_rejected = false;
-            }
-        }
         if (ranked.empty())
             return fail(lds_rejected ? XL_E_LDS_BUDGET : XL_E_UNSUPPORTED,
                         what + (lds_rejected ? ": no tile fits the LDS budget" : ": no kernel variant covers this block"));
+        for (const Choice &c : ranked) count_fp32_forms(b, c);
+        // fp32 arithmetic: the kernels on fp32 matrix operations and those on operands in three bf16 parts, whose results
+        // are no less exact (split_conv.h), ranked together
+        std::vector<Choice> parts3 = search(b, pl, ignored, 2);
+        const size_t keep_fp32 = MAX_ALTERNATIVES / 3;
+        if (parts3.size() > MAX_ALTERNATIVES - keep_fp32) parts3.resize(MAX_ALTERNATIVES - keep_fp32);
+        if (ranked.size() > MAX_ALTERNATIVES - parts3.size()) ranked.resize(MAX_ALTERNATIVES - parts3.size());
+        ranked.insert(ranked.end(), parts3.begin(), parts3.end());
+        std::stable_sort(ranked.begin(), ranked.end(), [](const Choice &x, const Choice &y) { return x.cost < y.cost; });
+        if (pl.opts.precision == XL_PRECISION_BF16X3) {
+            // the candidates on two bf16 parts first (the cost model cannot rank the two kinds against each other
+            // well: blocks that are not bound by the matrix cores gain nothing from the split), then the
+            // best of the others, for xl_tune to choose from
+            std::vector<Choice> split = search(b, pl, ignored, 1);
+            if (!split.empty()) {
+                const size_t keep = MAX_ALTERNATIVES / 2;
+                if (split.size() > MAX_ALTERNATIVES - keep) split.resize(MAX_ALTERNATIVES - keep);
+                if (ranked.size() > keep) ranked.resize(keep);
+                split.insert(split.end(), ranked.begin(), ranked.end());
+                ranked.swap(split);
+            }
+        }
         ch = ranked[0];
         fill_step(b, ch, x_id, y_id, sc_id, coff1, st);
         // the other candidates, for xl_tune to time on the device
@@ -762,7 +827,7 @@ struct Builder {
         st.sc_id = sc_id;
         st.conv_layer[0] = b.c1.layer;
         st.conv_layer[1] = st.conv_layer[2] = -1;
-        st.packed[0] = packed_index(b.c1.layer, b.kind == KIND_DW ? 0 : (ch.v.kind == KIND_THIN ? -1 : ch.v.mf1), ch.v.px1 < 0, ch.v.pr);
+        st.packed[0] = packed_index(b.c1.layer, b.kind == KIND_DW ? 0 : (ch.v.kind == KIND_THIN ? -1 : ch.v.mf1), ch.v.px1 < 0, ch.v.pr1);
         st.packed[1] = st.packed[2] = -1;
         BlockParams &p = st.bp;
         memset(&p, 0, sizeof p);
@@ -778,7 +843,7 @@ struct Builder {
         const Storage &ys = pl.storage[y_id];
         p.Cy = ys.ctot;
         p.Csc = sc_id >= 0 ? pl.shapes[sc_id].c : 0;
-        auto fill = [&](ConvW &w, const ConvSpec &s, int mf) {
+        auto fill = [&](ConvW &w, const ConvSpec &s, int mf, int pr) {
             w.wp = nullptr;
             w.aff = nullptr;
             w.cin = s.cin;
@@ -787,25 +852,25 @@ struct Builder {
             w.stride = s.stride;
             w.pad = s.pad;
             w.relu = s.relu;
-            w.nkg = ceil_div(s.cin, kc_of(mf, ch.v.pr));
+            w.nkg = ceil_div(s.cin, kc_of(mf, pr));
             w.nrt = ceil_div(s.cout, mf);
         };
-        fill(p.c1, b.c1, ch.v.mf1);
+        fill(p.c1, b.c1, ch.v.mf1, ch.v.pr1);
         p.n1 = b.n1;
         p.relu_mid = b.relu_mid;
         st.conv_layer[3] = -1;
         st.packed[3] = -1;
         if (b.n1 == 2) {
-            fill(p.c1b, b.c1b, ch.v.mf1);
+            fill(p.c1b, b.c1b, ch.v.mf1, ch.v.pr1);
             st.conv_layer[3] = b.c1b.layer;
-            st.packed[3] = packed_index(b.c1b.layer, ch.v.mf1, false, ch.v.pr);
+            st.packed[3] = packed_index(b.c1b.layer, ch.v.mf1, false, ch.v.pr1);
         }
         p.coff1 = ys.coff + coff1;
         const bool two = b.kind == KIND_FUSED2 || b.kind == KIND_DW || b.kind == KIND_FUSED2P;
         p.n2 = two ? b.n2 : 0;
         int P2 = 0;
         for (int i = 0; i < p.n2; ++i) {
-            fill(p.c2[i], b.c2[i], ch.v.mf2);
+            fill(p.c2[i], b.c2[i], ch.v.mf2, ch.v.pr);
             p.coff2[i] = ys.coff + b.coff2[i];
             st.conv_layer[1 + i] = b.c2[i].layer;
             st.packed[1 + i] = packed_index(b.c2[i].layer, ch.v.mf2, false, ch.v.pr);
@@ -827,7 +892,7 @@ struct Builder {
         p.mw = ch.mw;
         p.ih = ch.ih;
         p.iw = ch.iw;
-        p.iws = (ch.iw + 3) / 4 * 4;
+        p.iws = ch.v.pr1 ? ch.iw : (ch.iw + 3) / 4 * 4;
         p.tiles_x = ch.tiles_x;
         p.tiles_y = ch.tiles_y;
         p.csplit = ch.csplit;
@@ -841,7 +906,7 @@ struct Builder {
         auto rcp = [](int d) { return d <= 1 ? 0u : (unsigned)((1ull << 32) / (unsigned)d + 1); };
         p.rcp_mw = rcp(ch.mw);
         p.rcp_vw2 = rcp(ch.vw2);
-        p.rcp_qrow = rcp(p.iws / 4);
+        p.rcp_qrow = rcp(ch.v.pr1 ? p.iws : p.iws / 4);
         p.rcp_tiles = rcp(ch.tiles_x * ch.tiles_y);
         p.rcp_tcs = rcp(ch.tiles_x * ch.tiles_y * ch.csplit);
         p.rcp_csplit = rcp(ch.csplit);
@@ -864,7 +929,9 @@ struct Builder {
         }
         p.mid_gstride = ch.mh * ch.mw * 4;
         p.in_gstride = ch.ih * p.iws * 4;
-        p.lds_buf_off = ch.mid_floats;
+        p.lds_buf_off = ch.mid_over_staging ? 0 : ch.mid_floats;
+        p.tile2_off = ch.tile2_off;
+        p.flag_off = ch.flag_off;
         p.buf_stride = ch.buf_floats;
         p.w_off1 = ch.w_off1;
         p.stream_wgs = ch.v.kind == KIND_POOLS ? std::min(p.nblocks, pl.num_cus * std::max(ch.occ, 1)) : 0;
@@ -886,9 +953,9 @@ struct Builder {
         gi.threads = ch.threads;
         gi.lds_bytes = ch.lds_bytes;
         gi.workgroups_per_cu = ch.occ;
-        gi.chunk_channels = ch.v.kind == KIND_THIN ? b.c1.cin : ch.chunk_kg * kc_of(ch.v.mf1, ch.v.pr);
+        gi.chunk_channels = ch.v.kind == KIND_THIN ? b.c1.cin : ch.chunk_kg * kc_of(ch.v.mf1, ch.v.pr1);
         gi.flops_executed = ch.flops_exec;
-        gi.precision = ch.v.pr ? XL_PRECISION_BF16X3 : XL_PRECISION_FP32;
+        gi.precision = ch.v.pr == 1 ? XL_PRECISION_BF16X3 : XL_PRECISION_FP32;
         if (b.kind == KIND_SINGLE) {
             gi.redundancy = 1.0;
         } else {
@@ -1212,7 +1279,7 @@ struct Builder {
         size_t off = 0;
         for (PackedFilter &p : pl.packed) {
             p.offset = off;
-            off = align_up(off + p.bytes, 256);
+            off += packed_affine_offset(p.bytes);
             p.aff_offset = off;
             off = align_up(off + p.aff_bytes, 256);
         }
@@ -1236,6 +1303,13 @@ struct Builder {
             }
         }
         pl.workspace_bytes = std::max<size_t>(off, 256);
+        size_t forms = 0, forms_fp32 = 0;
+        for (const PackedFilter &p : pl.packed) forms += packed_affine_offset(p.bytes) + align_up(p.aff_bytes, 256);
+        for (const auto &[layer, mf, pairs] : fp32_forms) {
+            const PackedFilter p = packed_form(layer, mf, pairs, 0);
+            forms_fp32 += packed_affine_offset(p.bytes) + align_up(p.aff_bytes - (mf == 32 ? 16 : 0), 256);
+        }
+        pl.static_bytes = pl.workspace_bytes - forms + forms_fp32;
         return XL_OK;
     }
 };

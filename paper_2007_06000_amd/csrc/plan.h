@@ -66,6 +66,9 @@ struct GroupPlan {
     std::vector<int> layers;
 };
 
+// xl_run_static takes plans that need up to XL_STATIC_SCRATCH_BYTES with the filters of their fp32 candidates alone; its
+// array holds as much again, for the filters in bf16 parts (at most 1.5 times the fp32 ones).
+constexpr size_t STATIC_SPLIT_BYTES = XL_STATIC_SCRATCH_BYTES;
 }  // namespace xl
 
 struct xl_plan;
@@ -86,6 +89,7 @@ struct xl_plan {
     std::vector<char> layerwise;
     std::vector<xl::Step *> fused_active;
     size_t workspace_bytes = 0;
+    size_t static_bytes = 0;    // the same with the filter forms of the fp32 candidates only (xl_run_static)
     int device = -1;
     int lds_budget = 160 * 1024;
     int lds_per_cu = 160 * 1024;

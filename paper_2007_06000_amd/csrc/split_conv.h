@@ -1,0 +1,411 @@
+// Convolutions on split-bf16 operands (included by kernels.hip).
+//
+// A float is held as PR + 1 bf16 parts, each the rounding of what the parts before it leave:
+//   PR = 1: x ~ hi + lo (16 bits), a product is hi*hi + hi*lo + lo*hi: at most 3 * 2^-16 of |a||b| is left out;
+//   PR = 2: x = hi + mid + lo, all 24 bits of a float, exactly.  A product is six of the nine part products; mid*lo, lo*mid
+//           and lo*lo, at most 2^-23 and typically 2^-27 of |a||b| together, are left out.
+// bf16 products are exact in the fp32 accumulators, so what remains is the rounding of the sums, and there PR = 2
+// keeps TWO accumulators per tile: hi*hi in one, the five small products, which would lose their last bits against
+// the large sum, in the other; they are added once at the end.  Error against 64 bits (relative 2-norm, reductions of
+// 64 / 576 / 4608 non-negative x signed normal terms): fp32 matrix operations 1.0e-7 / 3.0e-7 / 8.8e-7, six products in
+// one accumulator 1.1e-7 / 3.5e-7 / 1.0e-6, in two 4.0e-8 / 1.0e-7 / 3.5e-7 -- so the second accumulator is what makes
+// PR = 2 a replacement for the fp32 operations.  Six 32x32x16 bf16 operations take 192 cycles for what takes the fp32
+// 32x32x2 operation 8 x 64.
+//
+// What cannot be taken apart: infinities and NaN (inf - inf) and values the first rounding takes to infinity (above
+// 3.39e38).  Such a value is kept in its parts all the same (hi + mid + lo gives it back exactly: value_parts) and raises a
+// flag -- the workgroup's in LDS for pixels, one behind the shift table for a filter -- on which the workgroup computes
+// the layer with fp32 matrix operations on the reassembled operands (conv_whole), as the fp32 kernels do.  Parts
+// below 2^-126 are flushed by the matrix operations: operands keep an absolute precision of 2^-126.
+//
+// The filter goes from memory to registers, one (K step, tap) or two ahead of the matrix operations, not
+// through LDS: six operations on one 3 KB row of parts last 192 cycles per pixel tile, so a wave with two or more pixel
+// tiles per row asks its vector cache for at most half of what it delivers; and a K loop that reads only pixels from LDS
+// has no barriers, no filter buffers and no chunks.  The LDS tile of the intermediate then takes the place of the
+// staging buffers of layer 1.
+//
+// What bounds it: power.  A K loop of this header alone keeps the matrix cores 86 to 90 % busy (36 to 37 cycles per
+// operation and SIMD where 32 are nominal), but with real operands the clock falls to 1.65 - 1.75 GHz: 1.55 PFLOP/s in
+// bf16, 258 TFLOP/s of fp32-exact products against 155 of the fp32 operations.  Time per pass, fp32 kernels -> PR = 2: the
+// residual block of 64 channels at 56 x 56, batch 32: 158.6 -> 94.4 us; two 1x1 producers 64 -> 256 and their consumer,
+// batch 32: 179 -> 126 us; 1x1 into 5x5, 28 x 28, batch 32: 17.6 -> 13.8 us; the batch-64 network: 688 -> 563 us.
+#pragma once
+
+namespace xl {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((vector_size(16)));     // what the 128-bit buffer load returns
+
+__device__ __forceinline__ float bf16_low(unsigned w) { return __builtin_bit_cast(float, w << 16); }
+__device__ __forceinline__ float bf16_high(unsigned w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
+
+// The parts of two floats, packed (first float in the low half of each word).  `odd` is raised when one of the two
+// does not come apart (PR = 2).
+template <int PR>
+__device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[PR + 1], bool &odd)
+{
+#pragma unroll
+    for (int i = 0; i <= PR; ++i) {
+        w[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+        if (i < PR || PR == 2) {
+            a -= bf16_low(w[i]);
+            b -= bf16_high(w[i]);
+        }
+    }
+    // what is left is 0, or NaN where a part was infinite or NaN
+    if constexpr (PR == 2) odd |= __builtin_isunordered(a, b);
+}
+
+// The same for values of which some do not come apart (PR = 2): parts by truncation, whose sum is the value for every
+// finite float; infinities and NaN are their own first part.
+__device__ __forceinline__ void value_parts(float a, float b, unsigned (&w)[3])
+{
+    unsigned p[2][3];
+    const float v[2] = {a, b};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const unsigned bits = __builtin_bit_cast(unsigned, v[h]);
+        if ((bits & 0x7f800000u) == 0x7f800000u) {
+            p[h][0] = (bits >> 16) | ((bits & 0x7fffffu) ? 0x40u : 0u);
+            p[h][1] = p[h][2] = 0u;
+        } else {
+            float r = v[h];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const unsigned top = __builtin_bit_cast(unsigned, r) & 0xffff0000u;
+                p[h][i] = top >> 16;
+                r -= __builtin_bit_cast(float, top);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) w[i] = p[0][i] | (p[1][i] << 16);
+}
+
+// Four consecutive channels of one pixel into the part planes: part p goes 8 bytes wide to dst + p * plane.
+template <int PR>
+__device__ __forceinline__ void store_parts(const f32x4 &v, float *dst, int plane, bool &odd)
+{
+    unsigned a[PR + 1], b[PR + 1];
+    split_pair<PR>(v[0], v[1], a, odd);
+    split_pair<PR>(v[2], v[3], b, odd);
+#pragma unroll
+    for (int i = 0; i <= PR; ++i) *(uint2 *)(dst + i * plane) = uint2{a[i], b[i]};
+}
+__device__ __forceinline__ void store_value_parts(const f32x4 &v, float *dst, int plane)
+{
+    unsigned a[3], b[3];
+    value_parts(v[0], v[1], a);
+    value_parts(v[2], v[3], b);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) *(uint2 *)(dst + i * plane) = uint2{a[i], b[i]};
+}
+
+// Whether a filter in three parts holds a value that does not come apart.
+__device__ __forceinline__ bool weights_flag(const ConvW &c) { return *(const int *)(c.aff + c.nrt * 256) != 0; }
+
+// Workgroup barrier for data in LDS: waits for this wave's LDS operations only, so that loads of the next chunk and
+// of the next filter rows stay in flight (__syncthreads would wait for nothing less than the compiler's fence asks).
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// ----------------------------------------------------------------------------
+// K loop: acc (+ accl) [r][p] += filter (row tile rt0 + r) x pixels (pixel tile p), K steps kg0 .. kg0 + nkg - 1, for the
+// first LIVE of the wave's pixel tiles.
+// Pixels in LDS: 16-byte planes [8-channel group][part][row][col][8 bf16], `gstride` floats apart; `off` is the lane's
+// pixel plus the planes of its lane half; `bsrc` starts at K step kg0.  Filter in memory:
+// [K step][tap][row tile][part][lane] 16 bytes.  The operands of the next (K step, tap) steps are requested before the
+// matrix operations of the current one: filter rows PD steps ahead, pixels one.  `hook` runs once the first filter
+// rows have been requested: what it requests (the next input chunk) comes after them in the queue.
+// ----------------------------------------------------------------------------
+template <int KS, int NRT, int NPT, int PR, int LIVE, typename Hook>
+__device__ __forceinline__ void conv_tiles(f32x16 (&acc)[NRT][NPT], f32x16 (&accl)[NRT][NPT], const float *bsrc,
+                                           const int (&off)[NPT], int src_w, int gstride, const ConvW &c, int rt0,
+                                           int kg0, int nkg, Hook hook)
+{
+    constexpr int T = KS * KS, NP = PR + 1, GROUPS = 2 * NP;     // planes per K step
+    constexpr int PD = NRT >= 2 ? 1 : 2;                        // steps the filter rows are requested ahead
+    constexpr int R = PD + 1;
+    const __amdgpu_buffer_rsrc_t wr = make_rsrc(c.wp, (unsigned long long)c.nkg * T * c.nrt * (NP * 1024));
+    // Addresses are kept as few running values that the compiler cannot see through: left to itself it keeps one
+    // induction variable per tap and part in vector registers, 60 to 100 of them.
+    int w_lane = (threadIdx.x & 63) * 16;
+    const int w_step = c.nrt * (NP * 1024);
+    int w_next = __builtin_amdgcn_readfirstlane((kg0 * T * c.nrt + rt0) * (NP * 1024));     // the step requested next
+    int px[LIVE];                                                                          // the K step read next
+#pragma unroll
+    for (int p = 0; p < LIVE; ++p) px[p] = off[p];
+    f32x4 a[R][NRT][NP], b[LIVE][NP];
+    auto fetch_a = [&](int slot) {                  // one (K step, tap) after the other
+        asm volatile("" : "+v"(w_lane), "+s"(w_next));
+#pragma unroll
+        for (int r = 0; r < NRT; ++r)
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+                a[slot][r][i] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(wr, w_lane + (r * NP + i) * 1024, w_next, 0));
+        w_next += w_step;
+    };
+    auto fetch_b = [&](int i, int t) {              // part i of tap t of the K step that px stands at
+        const float *s = bsrc + ((t / KS) * src_w + t % KS) * 4 + i * gstride;
+#pragma unroll
+        for (int p = 0; p < LIVE; ++p) {
+            asm volatile("" : "+v"(px[p]));
+            b[p][i] = *(const f32x4 *)(s + px[p]);
+        }
+    };
+    auto next_px = [&](bool more) {                 // (the last K step is read once more, in place of one past the end)
+#pragma unroll
+        for (int p = 0; p < LIVE; ++p) px[p] += more ? GROUPS * gstride : 0;
+    };
+    // (results are asked for where they are due: matrix operations have no side effect that would keep them in place)
+    auto pin = [&](f32x16 (&d)[NRT][NPT]) {
+#pragma unroll
+        for (int r = 0; r < NRT; ++r)
+#pragma unroll
+            for (int p = 0; p < LIVE; ++p) asm volatile("" : "+v"(d[r][p]));
+    };
+    auto mma = [&](int as, int ai, int bi, f32x16 (&d)[NRT][NPT]) {
+#pragma unroll
+        for (int r = 0; r < NRT; ++r)
+#pragma unroll
+            for (int p = 0; p < LIVE; ++p)
+                d[r][p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[as][r][ai]), __builtin_bit_cast(bf16x8, b[p][bi]), d[r][p], 0, 0, 0);
+    };
+    // One (K step, tap): the filter rows PD steps on are requested, then part by part, the smallest first, the products
+    // that need it and the request of the same part for the next tap `tn`, so that pixels need one register set.
+    auto step = [&](int as, bool more_a, int slot, int tn) {
+        if (more_a) fetch_a(slot);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 (&low)[NRT][NPT] = PR == 2 ? accl : acc;
+#pragma unroll
+        for (int i = NP - 1; i >= 0; --i) {
+#pragma unroll
+            for (int j = NP - 1 - i; j >= 0; --j) mma(as, j, i, i + j == 0 ? acc : low);
+            pin(low);
+            if (i == 0) pin(acc);
+            fetch_b(i, tn);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // A result of the matrix operations may be read 12 wait states after the last one.  The compiler counts them along
+    // one path to the reader only and falls short where paths of different length meet (seen: the first copy out
+    // of an accumulator took its old value), so they stand here; the matrix pipe is busy for longer anyway.
+    auto settle = [] { asm volatile("s_nop 15"); };
+    const int nsteps = nkg * T;
+#pragma unroll
+    for (int i = 0; i < PD; ++i)
+        if (i < nsteps) fetch_a(i);
+    hook();
+#pragma unroll
+    for (int i = NP - 1; i >= 0; --i) fetch_b(i, 0);
+    if constexpr (T == 1) {
+#pragma unroll 1
+        for (int kg = 0; kg < nkg; kg += R) {
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                if (kg + u < nkg) {
+                    next_px(kg + u + 1 < nkg);
+                    step(u, kg + u + PD < nkg, (u + PD) % R, 0);
+                    settle();
+                }
+        }
+    } else {
+#pragma unroll 1
+        for (int kg = 0; kg < nkg; ++kg) {
+            const bool last = kg + 1 >= nkg;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                if (t == T - 1) next_px(!last);
+                step(t % R, t + PD < T || !last, (t + PD) % R, (t + 1) % T);
+            }
+            settle();
+            // the next K step starts again from slot 0 of the ring
+            if constexpr (T % R != 0) {
+                f32x4 keep[PD][NRT][NP];
+#pragma unroll
+                for (int i = 0; i < PD; ++i)
+#pragma unroll
+                    for (int r = 0; r < NRT; ++r)
+#pragma unroll
+                        for (int q = 0; q < NP; ++q) keep[i][r][q] = a[(T + i) % R][r][q];
+#pragma unroll
+                for (int i = 0; i < PD; ++i)
+#pragma unroll
+                    for (int r = 0; r < NRT; ++r)
+#pragma unroll
+                        for (int q = 0; q < NP; ++q) a[i][r][q] = keep[i][r][q];
+            }
+        }
+    }
+}
+
+// conv_tiles for a wave of which all or only the first pixel tile holds pixels (`live`, wave-uniform): work on a tile of
+// padding costs as much power as any, and these kernels run at the power limit.
+template <int KS, int NRT, int NPT, int PR, typename Hook>
+__device__ __forceinline__ void conv_direct(f32x16 (&acc)[NRT][NPT], f32x16 (&accl)[NRT][NPT], const float *bsrc,
+                                            const int (&off)[NPT], int src_w, int gstride, const ConvW &c, int rt0,
+                                            int kg0, int nkg, int live, Hook hook)
+{
+    if (NPT == 1 || live > 1) conv_tiles<KS, NRT, NPT, PR, NPT>(acc, accl, bsrc, off, src_w, gstride, c, rt0, kg0, nkg, hook);
+    else conv_tiles<KS, NRT, NPT, PR, 1>(acc, accl, bsrc, off, src_w, gstride, c, rt0, kg0, nkg, hook);
+}
+
+// The same sums by fp32 matrix operations on whole operands, for a workgroup that met one that does not come apart:
+// rare, so it is short rather than fast, and it starts from the shift again instead of joining a sum that may be NaN
+// already.  Element e of a lane's 8 channels is K index `lane half` of the operation, for both operands alike;
+// value(p, kg, t, e) is that element of pixel tile p.
+template <int KS, int NRT, int NPT, typename Value>
+__device__ __forceinline__ void conv_whole(f32x16 (&acc)[NRT][NPT], const ConvW &c, int rt0, Value value)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll 1
+    for (int kg = 0; kg < c.nkg; ++kg)
+#pragma unroll 1
+        for (int t = 0; t < KS * KS; ++t)
+#pragma unroll 1
+            for (int e = 0; e < 8; ++e) {
+                float a[NRT];
+#pragma unroll
+                for (int r = 0; r < NRT; ++r) {
+                    const int rt = min(rt0 + r, c.nrt - 1);
+                    const unsigned short *w = (const unsigned short *)(c.wp + (size_t)((kg * KS * KS + t) * c.nrt + rt) * 192 + lane) + e;
+                    a[r] = bf16_low(w[0]) + (bf16_low(w[512]) + bf16_low(w[1024]));
+                }
+#pragma unroll
+                for (int p = 0; p < NPT; ++p) {
+                    const float x = value(p, kg, t, e);
+#pragma unroll
+                    for (int r = 0; r < NRT; ++r) acc[r][p] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[r], x, acc[r][p], 0, 0, 0);
+                }
+            }
+}
+
+// The two accumulators of a tile become one.
+template <int NRT, int NPT>
+__device__ __forceinline__ void add_small(f32x16 (&acc)[NRT][NPT], const f32x16 (&accl)[NRT][NPT])
+{
+#pragma unroll
+    for (int r = 0; r < NRT; ++r)
+#pragma unroll
+        for (int p = 0; p < NPT; ++p)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r][p][i] += accl[r][p][i];
+}
+
+// ----------------------------------------------------------------------------
+// Layer 1 on split operands: the halo-extended input tile goes through LDS in chunks of `chunk_kg` K steps, taken
+// apart on the way.  Two LDS buffers; the values of chunk i + 1 are in registers when chunk i begins and are written at
+// its start, the loads of chunk i + 2 follow the first filter rows of chunk i; one barrier per chunk.
+// A wave stages 64 consecutive pixels of the tile (row-major, no padding) times 8 channels: a lane loads its pixel's 8
+// values, consecutive lanes consecutive pixels, and writes 16 bytes per part, consecutive lanes consecutive addresses.
+// (Units of 4 channels x 4 pixels per lane load wider but write with a stride of 64 bytes: four bank groups of LDS for
+// 64 lanes; 55 % of the LDS cycles of the residual block were conflicts.)  The buffer ends with the image, and lanes
+// outside the image aim past it: zeros without a mask.
+// ----------------------------------------------------------------------------
+template <int KS, int NRT, int NPT, int PR, typename Init>
+__device__ __forceinline__ void conv_pass_split(f32x16 (&acc)[NRT][NPT], const BlockParams &P, const ConvW &c, int rt0,
+                                                int pt0, int live, const int (&off)[NPT], float *buf, int *flag,
+                                                const float *__restrict__ ximg, int iy0, int ix0, Init init)
+{
+    constexpr int NP = PR + 1, KC = 16;
+    const int tid = threadIdx.x;
+    const int HW = P.H * P.W;
+    const int plane = P.ih * P.iws;                                // pixels of the tile, and of an LDS plane
+    const int chunk = P.chunk_kg;
+    constexpr int NU = SPLIT_STAGE_UNITS;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = blockDim.x >> 6;
+    const int groups = chunk * 2, units = groups * ((plane + 63) >> 6);
+    int xgrp[NU];                   // 8-channel group of the chunk (wave-uniform)
+    unsigned xoff[NU];              // byte offset of the lane's pixel in its plane
+    int xdst[NU];                   // float offset in the LDS chunk; -1: no pixel
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+        const int u = i * nwaves + wave;
+        const int blk = u / groups;
+        xgrp[i] = u < units ? u - blk * groups : -1;
+        const int px = blk * 64 + (tid & 63);
+        const int r = fdiv(px, P.rcp_qrow), gy = iy0 + r, gx = ix0 + px - r * P.iws;
+        xdst[i] = px < plane ? (xgrp[i] * NP * plane + px) * 4 : -1;
+        const bool in = px < plane && gy >= 0 && gy < P.H && gx >= 0 && gx < P.W;
+        xoff[i] = in ? (unsigned)((gy * P.W + gx) * 4) : 0xfffffff0u;
+    }
+    float xst[NU][8];
+    auto load_x = [&](int c0) {                     // chunk whose first channel is c0
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+            if (xgrp[i] < 0) continue;
+            const int ch = c0 + xgrp[i] * 8, live = P.Cin - ch;     // channels that exist (wave-uniform)
+            const __amdgpu_buffer_rsrc_t xr = make_rsrc(ximg + (size_t)ch * HW, live > 0 ? (unsigned long long)live * HW * 4ull : 0ull);
+            if (live >= 8) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    xst[i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, xoff[i], j * HW * 4, 0));
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    xst[i][j] = j < live ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, xoff[i], j * HW * 4, 0)) : 0.f;
+            }
+        }
+    };
+    auto store_x = [&](float *dst) {
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+            if (xgrp[i] < 0 || xdst[i] < 0) continue;
+            unsigned w[4][NP];
+            bool odd = false;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) split_pair<PR>(xst[i][2 * j], xst[i][2 * j + 1], w[j], odd);
+            if constexpr (PR == 2) {
+                if (__builtin_expect(odd, 0)) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) value_parts(xst[i][2 * j], xst[i][2 * j + 1], w[j]);
+                    *flag = 1;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < NP; ++q) *(uint4 *)(dst + xdst[i] + q * plane * 4) = uint4{w[0][q], w[1][q], w[2][q], w[3][q]};
+        }
+    };
+    f32x16 accl[NRT][NPT];
+#pragma unroll
+    for (int r = 0; r < NRT; ++r)
+#pragma unroll
+        for (int p = 0; p < NPT; ++p) zero_acc(accl[r][p]);
+    const int nchunks = (c.nkg + chunk - 1) / chunk;
+    load_x(0);
+    store_x(buf);
+    if (nchunks > 1) load_x(chunk * KC);
+    lds_barrier();
+    for (int ch = 0; ch < nchunks; ++ch) {
+        const int kg0 = ch * chunk;
+        if (ch + 1 < nchunks) store_x(buf + ((ch + 1) & 1) * P.buf_stride);
+        auto next = [&]() {
+            if (ch + 2 < nchunks) load_x((kg0 + 2 * chunk) * KC);
+        };
+        if (live > 0)
+            conv_direct<KS, NRT, NPT, PR>(acc, accl, buf + (ch & 1) * P.buf_stride, off, P.iws, P.in_gstride, c, rt0, kg0,
+                                          min(chunk, c.nkg - kg0), live, next);
+        else
+            next();
+        lds_barrier();
+    }
+    if constexpr (PR == 2) {
+        add_small<NRT, NPT>(acc, accl);
+        if (live > 0 && (*flag != 0 || weights_flag(c))) {
+            init(acc);
+            const int lane = tid & 63, sub = lane >> 5;
+            conv_whole<KS, NRT, NPT>(acc, c, rt0, [&](int p, int kg, int t, int e) {
+                const int pidx = min((pt0 + p) * 32 + (lane & 31), P.mh * P.mw - 1);
+                const int my = fdiv(pidx, P.rcp_mw), mx = pidx - my * P.mw;
+                const int gy = iy0 + my * c.stride + t / KS, gx = ix0 + mx * c.stride + t % KS, ch = kg * 16 + sub * 8 + e;
+                return (ch < P.Cin && gy >= 0 && gy < P.H && gx >= 0 && gx < P.W) ? ximg[(ch * P.H + gy) * P.W + gx] : 0.f;
+            });
+        }
+    }
+}
+
+}  // namespace xl

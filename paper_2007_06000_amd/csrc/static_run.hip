@@ -6,7 +6,7 @@
 #include "plan.h"
 
 // One copy per GPU the library is loaded on, held until the process ends.
-static __device__ __align__(256) unsigned char scratch[XL_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[XL_STATIC_SCRATCH_BYTES + xl::STATIC_SPLIT_BYTES];
 
 namespace {
 
@@ -39,8 +39,8 @@ extern "C" xl_status xl_run_static(xl_plan *plan, const void *const *weights, in
                                    int ntensors, void *stream, int fused, int relayout)
 {
     if (!plan || !tensors) return XL_E_NULL;
-    if (plan->workspace_bytes > (size_t)XL_STATIC_SCRATCH_BYTES) {
-        plan->error = "the plan needs " + std::to_string(plan->workspace_bytes) + " bytes of workspace, the static scratch holds " +
+    if (plan->static_bytes > (size_t)XL_STATIC_SCRATCH_BYTES || plan->workspace_bytes > XL_STATIC_SCRATCH_BYTES + xl::STATIC_SPLIT_BYTES) {
+        plan->error = "the plan needs " + std::to_string(plan->static_bytes) + " bytes of workspace, the static scratch holds " +
                       std::to_string((size_t)XL_STATIC_SCRATCH_BYTES);
         return XL_E_SCRATCH;
     }

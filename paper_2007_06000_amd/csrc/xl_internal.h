@@ -17,16 +17,19 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // Matrix-core tile geometry.  MF = 32 uses V_MFMA_F32_32X32X2_F32 (one K step of
 // the packed filter covers 8 input channels: 2 lane halves x 4 components),
 // MF = 16 uses V_MFMA_F32_16X16X4_F32 (16 channels: 4 lane quarters x 4).
-// With split-bf16 operands (pr = 1: V_MFMA_F32_32X32X16_BF16 / V_MFMA_F32_16X16X32_BF16, three per
-// product) a lane holds 8 channels and a K step covers twice as many.
-constexpr int kc_of(int mf, int pr = 0) { return (mf == 32 ? 8 : 16) << pr; }      // channels per K step
-constexpr int gps_of(int mf, int pr = 0) { return (mf == 32 ? 2 : 4) << pr; }      // 4-channel groups per K step
+// Split-bf16 operands (pr > 0, MF = 32 only): a float is held as pr + 1 bf16 parts and a product is several
+// V_MFMA_F32_32X32X16_BF16; a lane holds 8 channels and a K step covers 16.
+constexpr int kc_of(int mf, int pr = 0) { return pr ? 16 : (mf == 32 ? 8 : 16); }      // channels per K step
+constexpr int gps_of(int mf, int pr = 0) { return kc_of(mf, pr) / 4; }                 // 4-channel groups per K step
+constexpr int parts_of(int pr) { return pr ? pr + 1 : 1; }      // bf16 parts of an operand (fp32: the value itself)
+constexpr int products_of(int pr) { return pr == 2 ? 6 : 3; }   // matrix operations per product of split operands
 
 // One convolution as the kernels see it.
 struct ConvW {
     const f32x4 *wp;        // filter, times the per-channel scale, re-laid out as [K step][tap][row tile][lane] of float4
-                            // (split-bf16 kernels: [K step][tap][row tile][hi, lo][lane] of 8 bf16)
-    const f32x4 *aff;       // shift in accumulator order: [row tile][quad][lane] float4
+                            // (split-bf16 kernels: [K step][tap][row tile][part][lane] of 8 bf16)
+    const f32x4 *aff;       // shift in accumulator order: [row tile][quad][lane] float4; filters in three bf16 parts
+                            // have an int behind it: 1 if a value cannot be taken apart (see split_conv.h)
     int cin, cout;
     int k, stride, pad;
     int relu;
@@ -83,7 +86,7 @@ struct BlockParams {
     int th, tw;             // output tile of the block
     int mh, mw;             // stage-1 output tile (incl. halo) -- equals th, tw for SINGLE
     int ih, iw;             // input tile (incl. halo)
-    int iws;                // pixels per row of the staged input in LDS: iw rounded up to 4
+    int iws;                // pixels per row of the staged input in LDS: iw rounded up to 4 (split-bf16 parts: iw)
     int tiles_x, tiles_y, csplit;
     int nblocks;            // logical workgroups = N * csplit * tiles_y * tiles_x
     int chunk_kg;           // stage 1: K steps staged per chunk
@@ -91,7 +94,7 @@ struct BlockParams {
     int waves_r1;           // stage-1 waves along the row-tile (Cout) direction
     int waves_r2;           // stage-2 waves along the row-tile direction
     int vw2;                // stage 2 lays output pixels out in virtual rows of vw2 >= tw columns
-    unsigned rcp_mw, rcp_vw2, rcp_qrow;   // 2^32 / d + 1 for d = mw, vw2, iws / 4 (0 when d is 1): x / d = mulhi(x, rcp) for x < 65536
+    unsigned rcp_mw, rcp_vw2, rcp_qrow;   // 2^32 / d + 1 for d = mw, vw2, iws / 4 (split-bf16 parts: iws) (0 when d is 1): x / d = mulhi(x, rcp) for x < 65536
     // The same multipliers for the other divisors of the index arithmetic (a division by a run-time value costs
     // about 30 vector instructions, and a vector instruction is paid for in matrix-core time):
     unsigned rcp_tiles, rcp_tcs, rcp_csplit, rcp_tiles_x;   // d = tiles_x * tiles_y, that times csplit, csplit, tiles_x
@@ -101,7 +104,10 @@ struct BlockParams {
                                     // start inside the image ([0]) and for the tx = 0 tiles ([1])
     int mid_gstride;        // floats between consecutive 4-channel groups of the LDS tile
     int in_gstride;         // same for the staged input
-    int lds_buf_off;        // float offset of the two staging buffers in LDS (after the tile)
+    int lds_buf_off;        // float offset of the two staging buffers in LDS (after the tile; 0 where the tile of a
+                            // split-bf16 kernel takes their place once layer 1 is done)
+    int tile2_off;          // KIND_FUSED2P: float offset of the stage-2 tile that is pooled
+    int flag_off;           // split-bf16 kernels with three parts: float offset of the workgroup's flag (split_conv.h)
     int buf_stride;         // floats per staging buffer
     int w_off1;             // stage 1: float offset of the filter chunk inside a buffer (after the input chunk)
     int stream_wgs;         // KIND_POOLS: resident workgroups wanted; the launch rounds it up to a multiple of 8 and
@@ -118,7 +124,9 @@ struct Variant {
     int sc;                     // 1: adds a shortcut tensor in the epilogue (merge mode)
     int px1;                    // > 0: stage 1 (1x1 filter) reads a planar input chunk, px1 * 64 floats per channel;
                                 // < 0: stage 1 uses only -px1 of the 4 channel slots (<= -2 * px1 input channels)
-    int pr;                     // 0: fp32 matrix operations; 1: split-bf16 operands (3 bf16 operations per product)
+    int pr;                     // 0: fp32 matrix operations; 1, 2: operands as two or three bf16 parts (3 or 6 bf16
+                                // operations per product), in stage 2 or, for a kernel of one convolution, in stage 1
+    int pr1;                    // the same for stage 1
 };
 
 // id, kind, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1
@@ -259,56 +267,78 @@ struct Variant {
     X(40, KIND_POOL, 16, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0)             \
     X(41, KIND_POOL, 16, 3, 1, 1, 0, 0, 0, 0, 0, 0, 0)
 
-// Variants with split-bf16 operands (ids from 200): same columns.  Stage 2 uses 32-row tiles only, so
-// that its K step (16 channels) divides what stage 1 writes into the LDS tile (whole 16- or 32-row tiles).
-#define XL_VARIANT_LIST_B3(X)                                      \
-    X(200, KIND_SINGLE, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0)          \
-    X(201, KIND_SINGLE, 32, 1, 2, 1, 0, 0, 0, 0, 0, 0, 0)          \
-    X(202, KIND_SINGLE, 32, 1, 2, 2, 0, 0, 0, 0, 0, 0, 0)          \
-    X(204, KIND_SINGLE, 16, 1, 1, 3, 0, 0, 0, 0, 0, 0, 0)          \
-    X(205, KIND_SINGLE, 32, 3, 1, 1, 0, 0, 0, 0, 0, 0, 0)          \
-    X(206, KIND_SINGLE, 32, 3, 2, 1, 0, 0, 0, 0, 0, 0, 0)          \
-    X(207, KIND_SINGLE, 32, 3, 2, 2, 0, 0, 0, 0, 0, 0, 0)          \
-    X(208, KIND_SINGLE, 32, 5, 1, 1, 0, 0, 0, 0, 0, 0, 0)          \
-    X(209, KIND_SINGLE, 32, 1, 2, 3, 0, 0, 0, 0, 0, 0, 0)          \
-    X(214, KIND_SINGLE, 32, 1, 4, 1, 0, 0, 0, 0, 0, 0, 0)          \
-    X(216, KIND_SINGLE, 32, 3, 4, 1, 0, 0, 0, 0, 0, 0, 0)          \
-    X(217, KIND_SINGLE, 32, 3, 1, 2, 0, 0, 0, 0, 0, 0, 0)          \
-    X(218, KIND_SINGLE, 16, 3, 1, 2, 0, 0, 0, 0, 0, 0, 0)          \
-    X(203, KIND_SINGLE, 32, 1, 2, 4, 0, 0, 0, 0, 0, 0, 0)          \
-    X(222, KIND_FUSED2, 32, 3, 2, 2, 32, 2, 2, 3, 0, 0, 0)         \
-    X(213, KIND_FUSED2, 32, 1, 2, 1, 32, 2, 2, 3, 1, 0, 0)         \
-    /* split */                                                    \
-    X(210, KIND_FUSED2, 32, 1, 1, 1, 32, 2, 1, 3, 1, 0, 0)         \
-    X(211, KIND_FUSED2, 32, 1, 2, 1, 32, 2, 1, 3, 1, 0, 0)         \
-    X(212, KIND_FUSED2, 16, 1, 1, 2, 32, 2, 1, 3, 1, 0, 0)         \
-    X(233, KIND_FUSED2, 16, 1, 1, 3, 32, 2, 1, 3, 1, 0, 0)         \
-    X(235, KIND_FUSED2, 16, 1, 3, 2, 32, 2, 1, 3, 1, 0, 0)         \
-    /* split -> max pooling */                                     \
-    X(250, KIND_FUSED2P, 32, 1, 1, 1, 32, 2, 1, 3, 1, 0, 0)        \
-    X(251, KIND_FUSED2P, 16, 1, 1, 3, 32, 2, 1, 3, 1, 0, 0)        \
-    X(252, KIND_FUSED2P, 16, 1, 2, 3, 32, 2, 1, 3, 1, 0, 0)        \
-    X(253, KIND_FUSED2P, 32, 1, 1, 2, 32, 2, 1, 3, 1, 0, 0)        \
-    /* straight and merge */                                       \
-    X(220, KIND_FUSED2, 32, 3, 2, 1, 32, 2, 1, 3, 0, 0, 0)         \
-    X(221, KIND_FUSED2, 32, 3, 2, 1, 32, 2, 1, 3, 0, 1, 0)         \
-    X(224, KIND_FUSED2, 32, 3, 1, 1, 32, 2, 1, 3, 0, 0, 0)         \
-    X(225, KIND_FUSED2, 32, 3, 1, 1, 32, 2, 1, 3, 0, 1, 0)         \
-    X(226, KIND_FUSED2, 32, 1, 1, 1, 32, 2, 1, 3, 0, 0, 0)         \
-    X(227, KIND_FUSED2, 32, 1, 1, 1, 32, 2, 1, 3, 0, 1, 0)         \
-    X(228, KIND_FUSED2, 32, 1, 1, 1, 32, 2, 1, 1, 0, 0, 0)         \
-    X(229, KIND_FUSED2, 32, 1, 1, 1, 32, 2, 1, 1, 0, 1, 0)         \
-    X(230, KIND_FUSED2, 32, 3, 1, 1, 32, 2, 1, 1, 0, 0, 0)         \
-    X(231, KIND_FUSED2, 16, 1, 1, 1, 32, 1, 1, 5, 0, 0, 0)         \
-    /* two producers -> add -> consumer, all 1x1 */                \
-    X(254, KIND_FUSED2, 32, 1, 2, 1, 32, 2, 1, 1, 0, 0, 0)         \
-    /* depthwise (vector ALU, fp32) -> convolution on split-bf16 operands */ \
-    X(255, KIND_DW, 32, 3, 1, 1, 32, 2, 1, 1, 0, 0, 0)             \
-    X(256, KIND_DW, 32, 3, 1, 1, 32, 1, 1, 1, 0, 0, 0)             \
-    X(257, KIND_DW, 32, 3, 1, 1, 32, 2, 1, 3, 0, 0, 0)             \
-    /* conv -> maxpool (the LDS tile stays fp32) */                \
-    X(240, KIND_POOL, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0)            \
-    X(241, KIND_POOL, 32, 3, 1, 1, 0, 0, 0, 0, 0, 0, 0)
+// Variants with split-bf16 operands, each compiled for two parts (pr = 1, ids from 200) and for three (pr = 2, ids
+// from 400): the columns above, then S1 = 1: stage 1 takes split operands too (0: fp32 matrix operations).  Where
+// operands are split the matrix-core tile is 32 wide.
+#define XL_SPLIT_LIST_A(X)                                            \
+    X(0, KIND_SINGLE, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
+    X(1, KIND_SINGLE, 32, 1, 2, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
+    X(2, KIND_SINGLE, 32, 1, 1, 2, 0, 0, 0, 0, 0, 0, 0, 1)            \
+    X(5, KIND_SINGLE, 32, 3, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
+    X(6, KIND_SINGLE, 32, 3, 2, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
+    X(7, KIND_SINGLE, 32, 3, 1, 2, 0, 0, 0, 0, 0, 0, 0, 1)            \
+    X(10, KIND_SINGLE, 32, 5, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)           \
+    X(11, KIND_SINGLE, 32, 5, 1, 2, 0, 0, 0, 0, 0, 0, 0, 1)           \
+    /* depthwise (vector ALU, fp32) -> convolution */                 \
+    X(12, KIND_DW, 32, 3, 1, 1, 32, 2, 1, 1, 0, 0, 0, 0)              \
+    X(13, KIND_DW, 32, 3, 1, 1, 32, 1, 1, 1, 0, 0, 0, 0)              \
+    X(14, KIND_DW, 32, 3, 1, 1, 32, 1, 2, 3, 0, 0, 0, 0)              \
+    /* conv -> maxpool (the LDS tile stays fp32) */                   \
+    X(15, KIND_POOL, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)             \
+    X(16, KIND_POOL, 32, 3, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)             \
+    /* straight and merge */                                          \
+    X(20, KIND_FUSED2, 32, 3, 2, 1, 32, 2, 1, 3, 0, 0, 0, 1)          \
+    X(21, KIND_FUSED2, 32, 3, 2, 1, 32, 2, 1, 3, 0, 1, 0, 1)          \
+    X(24, KIND_FUSED2, 32, 3, 1, 2, 32, 1, 2, 3, 0, 0, 0, 1)          \
+    X(25, KIND_FUSED2, 32, 3, 1, 2, 32, 1, 2, 3, 0, 1, 0, 1)          \
+    X(26, KIND_FUSED2, 32, 3, 1, 1, 32, 1, 1, 3, 0, 0, 0, 1)          \
+    X(27, KIND_FUSED2, 32, 3, 1, 1, 32, 1, 1, 3, 0, 1, 0, 1)          \
+    X(28, KIND_FUSED2, 32, 3, 1, 1, 32, 1, 2, 1, 0, 0, 0, 1)
+
+#define XL_SPLIT_LIST_B(X)                                            \
+    X(40, KIND_FUSED2, 16, 1, 1, 1, 32, 1, 2, 3, 0, 0, 0, 0)          \
+    X(41, KIND_FUSED2, 32, 1, 1, 1, 32, 1, 2, 3, 0, 0, 0, 0)          \
+    X(42, KIND_FUSED2, 32, 1, 1, 1, 32, 1, 2, 3, 0, 1, 0, 0)          \
+    X(43, KIND_FUSED2, 32, 1, 1, 1, 32, 1, 2, 1, 0, 1, 0, 0)          \
+    X(44, KIND_FUSED2, 16, 1, 1, 1, 32, 1, 1, 5, 0, 0, 4, 0)          \
+    X(45, KIND_FUSED2, 16, 1, 1, 2, 32, 1, 1, 5, 0, 0, 4, 0)          \
+    X(46, KIND_FUSED2, 16, 1, 1, 1, 32, 1, 2, 5, 0, 0, 0, 0)          \
+    X(47, KIND_FUSED2, 32, 3, 1, 1, 32, 1, 1, 5, 0, 0, 0, 1)          \
+    /* 1x1 -> 1x1, also two producers -> add -> consumer */           \
+    X(48, KIND_FUSED2, 32, 1, 1, 1, 32, 1, 2, 1, 0, 0, 0, 0)          \
+    X(49, KIND_FUSED2, 32, 1, 2, 1, 32, 1, 2, 1, 0, 0, 0, 1)          \
+    X(52, KIND_FUSED2, 32, 1, 1, 2, 32, 1, 2, 1, 0, 0, 0, 1)          \
+    /* split -> max pooling */                                        \
+    X(60, KIND_FUSED2P, 16, 1, 1, 3, 32, 2, 1, 3, 1, 0, 0, 0)         \
+    X(61, KIND_FUSED2P, 16, 1, 1, 3, 32, 2, 1, 3, 1, 0, 4, 0)         \
+    X(62, KIND_FUSED2P, 16, 1, 2, 3, 32, 2, 1, 3, 1, 0, 0, 0)         \
+    X(63, KIND_FUSED2P, 32, 1, 1, 1, 32, 2, 1, 3, 1, 0, 0, 0)         \
+    X(64, KIND_FUSED2P, 32, 1, 1, 2, 32, 2, 1, 3, 1, 0, 0, 0)         \
+    X(65, KIND_FUSED2P, 32, 1, 1, 2, 32, 1, 2, 3, 1, 0, 0, 0)         \
+    X(66, KIND_FUSED2P, 16, 1, 1, 3, 32, 1, 2, 3, 1, 0, 0, 0)         \
+    X(67, KIND_FUSED2P, 16, 1, 1, 3, 32, 1, 2, 3, 1, 0, 4, 0)         \
+    X(68, KIND_FUSED2P, 32, 1, 2, 1, 32, 1, 2, 3, 1, 0, 0, 0)
+
+#define XL_SPLIT_LIST_C(X)                                            \
+    X(80, KIND_FUSED2, 16, 1, 1, 1, 32, 2, 1, 3, 1, 0, 2, 0)          \
+    X(81, KIND_FUSED2, 16, 1, 1, 1, 32, 1, 2, 3, 1, 0, 2, 0)          \
+    X(82, KIND_FUSED2, 16, 1, 1, 2, 32, 2, 1, 3, 1, 0, 4, 0)          \
+    X(83, KIND_FUSED2, 16, 1, 1, 2, 32, 1, 2, 3, 1, 0, 4, 0)          \
+    X(84, KIND_FUSED2, 16, 1, 1, 3, 32, 2, 1, 3, 1, 0, 0, 0)          \
+    X(85, KIND_FUSED2, 16, 1, 1, 3, 32, 1, 2, 3, 1, 0, 4, 0)          \
+    X(86, KIND_FUSED2, 16, 1, 1, 3, 32, 2, 2, 3, 1, 0, 4, 0)          \
+    X(87, KIND_FUSED2, 16, 1, 3, 2, 32, 2, 1, 3, 1, 0, 4, 0)          \
+    X(88, KIND_FUSED2, 16, 1, 3, 2, 32, 1, 2, 3, 1, 0, 4, 0)          \
+    X(89, KIND_FUSED2, 32, 1, 1, 1, 32, 2, 1, 3, 1, 0, 4, 0)          \
+    X(90, KIND_FUSED2, 32, 1, 1, 1, 32, 1, 2, 3, 1, 0, 4, 0)          \
+    X(91, KIND_FUSED2, 32, 1, 2, 1, 32, 2, 2, 3, 1, 0, 4, 0)          \
+    X(92, KIND_FUSED2, 32, 1, 1, 1, 32, 2, 1, 3, 1, 0, 0, 0)          \
+    X(93, KIND_FUSED2, 32, 1, 1, 1, 32, 1, 2, 3, 1, 0, 0, 0)          \
+    X(94, KIND_FUSED2, 32, 1, 2, 1, 32, 2, 1, 3, 1, 0, 0, 1)          \
+    X(95, KIND_FUSED2, 32, 1, 1, 2, 32, 1, 2, 3, 1, 0, 0, 1)          \
+    X(96, KIND_FUSED2, 16, 1, 1, 1, 32, 1, 1, 3, 1, 0, 0, 0)
+
+constexpr int SPLIT_ID0[3] = {0, 200, 400};     // id of list entry 0, by pr
 
 const std::vector<Variant> &variants();
 
@@ -316,6 +346,7 @@ const std::vector<Variant> &variants();
 #define XL_STAGE_UNITS 1
 #endif
 constexpr int STAGE_UNITS = XL_STAGE_UNITS;      // input units (4 channels x 4 pixels) each thread stages per chunk
+constexpr int SPLIT_STAGE_UNITS = 2;    // split-bf16 kernels: units (64 pixels x 8 channels) each wave stages per chunk
 constexpr int MAX_W_CHUNK_BYTES = 52 * 1024;  // filter bytes staged per chunk (LDS-direct loads, no registers)
 constexpr int PLANAR_SLOTS = 8;     // LDS-direct loads per wave and chunk of a planar input chunk
 constexpr int MAX_THREADS = 512;
@@ -327,6 +358,13 @@ constexpr int MAX_ALTERNATIVES = 64;  // candidates per block kept for on-device
 #ifndef XL_MIN_WAVES
 #define XL_MIN_WAVES 2
 #endif
+
+// ---- re-laid-out filters in the workspace: the table, then (256-byte aligned) the shifts, then for 32-wide tiles 16
+// bytes whose first int launch_pack_affine clears and launch_pack_filter (pr = 2, launched after it) sets to 1 when a
+// value cannot be taken apart into bf16 parts (split_conv.h)
+constexpr size_t packed_filter_bytes(int nkg, int taps, int nrt, int pr) { return (size_t)nkg * taps * nrt * 1024 * parts_of(pr); }
+constexpr size_t packed_affine_bytes(int nrt, int mf) { return (size_t)nrt * (mf == 32 ? 4 : 1) * 1024 + (mf == 32 ? 16 : 0); }
+constexpr size_t packed_affine_offset(size_t filter_bytes) { return (filter_bytes + 255) / 256 * 256; }
 
 // ---- launchers (kernels.hip) -------------------------------------------------
 hipError_t launch_block(int variant, const BlockParams &p, int threads, size_t lds_bytes, hipStream_t s);

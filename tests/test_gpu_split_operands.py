@@ -1,0 +1,84 @@
+"""Kernels on operands in three bf16 parts (variants from 400 in a plan of fp32 precision) against the kernels on fp32
+matrix operations: no less exact, and the same results for values that do not come apart into bf16 parts."""
+import numpy as np
+import pytest
+
+import xl_workloads as W
+from oracle import xlo
+
+pytestmark = pytest.mark.gpu
+
+FIRST, END = 400, 600       # variant ids of the kernels under test
+
+WORKLOADS = [
+    W.single_conv(2, 40, 9, 31, 70, 3, 1, 1), W.single_conv(1, 17, 13, 11, 40, 5, 1, 2), W.single_conv(3, 90, 7, 9, 33, 1),
+    W.straight_generic(2, 24, 17, 19, 40, 3, 1, 1, 48, 3, 1, 1), W.straight_generic(1, 24, 17, 19, 40, 1, 0, 1, 48, 1, 0, 1),
+    W.straight_generic(1, 40, 14, 15, 16, 1, 0, 1, 32, 5, 2, 1), W.config(4, n=1, hw=17, c=40), W.config(3, n=1, hw=19, cin=48),
+    W.split_fire_pool(n=1, cin=32, hw=15, s=16, e=64), W.merge_two_producers(1, c=24, h=9, w=11, cmid=40, cout=20),
+    W.conv_gap_generic(2, 40, 9, 9, 70, 1, 0, 1), W.depthwise_pointwise(1, 18, 13, 9, 40),
+    W.conv_pool_generic(1, 24, 19, 23, 40, 3, 1, 1, 3, 2, 1),
+]
+
+
+def run_candidates(wl, x, params):
+    """{variant: output} of the fused launch, one candidate per variant, and the fp32 variants' ids first."""
+    from paper_2007_06000_amd.session import Session
+    s = Session(wl, x, params)
+    out = {}
+    for c in range(s.plan.num_candidates(True, 0)):
+        v = s.plan.candidate_info(True, 0, c)["variant"]
+        if v in out:
+            continue
+        s.plan.select_candidate(True, 0, c)
+        print(f"[case] {wl.name} variant {v} candidate {c}", flush=True)
+        out[v] = s.output(True)
+    fp32 = {v: y for v, y in out.items() if v < FIRST}
+    split = {v: y for v, y in out.items() if FIRST <= v < END}
+    assert fp32 and split, sorted(out)
+    return fp32, split
+
+
+@pytest.mark.parametrize("wl", WORKLOADS, ids=lambda w: w.name)
+def test_error_is_no_larger_than_with_fp32_operations(wl):
+    # The reference is float64 with one rounding per layer output: both kernels share those roundings (2^-24 per element
+    # and layer), hence the floor below which neither is told apart.
+    x, params = W.make_tensors(wl)
+    ref = xlo.forward(wl, x, params).astype(np.float64)
+    fp32, split = run_candidates(wl, x, params)
+
+    def err(y):
+        return np.linalg.norm(y.astype(np.float64) - ref) / np.linalg.norm(ref)
+    worst = max(err(y) for y in fp32.values())
+    for v, y in split.items():
+        assert err(y) <= max(worst, 2.0 ** -23), (v, err(y), worst)
+
+
+@pytest.mark.parametrize("special", [np.inf, -np.inf, np.nan, 3.4e38])
+@pytest.mark.parametrize("wl", WORKLOADS, ids=lambda w: w.name)
+def test_values_without_bf16_parts(wl, special):
+    # one such value: whatever it reaches is what the fp32 kernels make of it, everything else is untouched
+    x, params = W.make_tensors(wl)
+    x[0, 1, x.shape[2] // 2, x.shape[3] // 2] = special
+    fp32, split = run_candidates(wl, x, params)
+    ref = next(iter(fp32.values()))
+    fin = np.isfinite(ref)
+    assert fin.any() or wl.name.startswith("convgap")
+    for v, y in split.items():
+        assert (np.isnan(y) == np.isnan(ref)).all(), v
+        assert (np.isposinf(y) == np.isposinf(ref)).all() and (np.isneginf(y) == np.isneginf(ref)).all(), v
+        a, b = y[fin].astype(np.float64), ref[fin].astype(np.float64)
+        d, reached = np.abs(a - b), np.maximum(np.abs(a), np.abs(b)) > 1e20
+        assert (d <= 1e-4 + 1e-4 * np.abs(b))[~reached].all(), (v, d[~reached].max())
+        # sums that hold 3.4e38 * w: up to a few hundred roundings of 2^-24 of that magnitude
+        assert (d[reached] <= 2.0 ** -16 * 3.4e38).all(), (v, d[reached].max())
+
+
+@pytest.mark.parametrize("special", [np.inf, 3.4e38])
+def test_filters_without_bf16_parts(special):
+    wl = W.config(4, n=1, hw=17, c=40)
+    x, params = W.make_tensors(wl)
+    params[2 if 2 in params else 1]["w"][3, 5, 1, 1] = special
+    fp32, split = run_candidates(wl, x, params)
+    ref = next(iter(fp32.values()))
+    for v, y in split.items():
+        assert (np.isfinite(y) == np.isfinite(ref)).all() and (np.isnan(y) == np.isnan(ref)).all(), v
