@@ -207,7 +207,7 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     const long long nwg = (long long)c.tiles_x * c.tiles_y * c.csplit * b.N;
     const double rounds = std::ceil((double)nwg / pl.num_cus);
     double t_mfma = rounds * wg_clk * (c.occ >= 2 ? 1.0 : 1.08) / 2.4e9;
-    if (v.pr) {
+    if (v.pr && b.kind != KIND_DW) {
         // `occ` workgroups of a compute unit share the matrix cores while each waits for its own loads, barriers and
         // stores: they finish after the matrix work of all or the whole life of one, whichever is longer.  (The three
         // latencies are fitted to 36 blocks of 600 timed candidates each: the first choice is 5.5 % behind the best one on
@@ -533,6 +533,38 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             }
         }
     }
+    if (best.ok && b.kind == KIND_DW && pr == 0 && b.n2 == 1 && b.c2[0].k == 1 && b.c1.stride == 1 && !pl.opts.force_tile_h &&
+        !pl.opts.force_threads && !pl.opts.force_cout_split && !pl.opts.paper_tuner_only)
+        for (const Variant &v : variants()) {
+            // depthwise -> pointwise wave by wave (whether the block can be planned is decided by the kernels above)
+            if (v.kind != KIND_DWP) continue;
+            const int nrt = ceil_div(b.c2[0].cout, v.mf2);
+            if (v.nrt2 > nrt) continue;
+            Choice c;
+            c.v = v;
+            c.threads = 256;
+            c.waves_r1 = c.waves_r2 = 1;
+            c.tw = c.vw2 = c.mw = v.px1;
+            c.th = c.mh = v.mf2 / v.px1 * v.npt2;
+            c.ih = c.th + 2;
+            c.iw = c.tw + 2;
+            c.tiles_y = ceil_div(b.Ho, c.th);
+            c.tiles_x = ceil_div(b.Wo, c.tw);
+            c.csplit = ceil_div(nrt, v.nrt2);
+            c.chunk_kg = 1;
+            c.occ = v.mf2 * v.nrt2 * v.npt2 > 64 ? 2 : 3;     // waves per SIMD (212 / 128 to 164 registers)
+            // a trip to memory per K step and round of waves; per wave and K step loads, multiply-adds and matrix
+            // operations; the memory side is the algorithmic bytes at what a copy reaches
+            const int nkg = ceil_div(b.Cin, kc_of(v.mf2));
+            const double waves = (double)c.tiles_x * c.tiles_y * c.csplit * b.N, rows = v.npt2, simds = 4.0 * pl.num_cus;
+            const double step = (12.0 * (rows + 2.0) + 11.0) * 8.0 + 36.0 * rows * 2.5 + kstep_clk(v.mf2, 0) * v.nrt2 * rows;
+            const double t_cu = (std::max(1.0, waves / (simds * c.occ)) * nkg * 5000.0 +
+                                 std::ceil(waves / simds) * (nkg * step + 4.0 * (v.mf2 / 16) * (v.mf2 / 16) * v.nrt2 * rows * 8.0)) / 2.4e9;
+            c.cost = 2.0e-6 + std::max(t_cu, (double)b.alg_bytes / 5.4e12) + 0.3 * std::min(t_cu, (double)b.alg_bytes / 5.4e12);
+            c.flops_exec = (long long)(waves * nkg * rows * (2.0 * 64 * 36 + 2.0 * v.mf2 * v.mf2 * kc_of(v.mf2) * v.nrt2));
+            c.ok = true;
+            per_key[std::make_tuple(v.id, c.threads, c.th, c.tw)] = c;
+        }
     lds_rejected = !best.ok && any_lds_reject;
     // ranked list: the model's best first, then the best of other (variant, threads, tile) combinations
     std::vector<Choice> ranked;
@@ -897,6 +929,7 @@ struct Builder {
         p.tiles_y = ch.tiles_y;
         p.csplit = ch.csplit;
         p.nblocks = ch.tiles_x * ch.tiles_y * ch.csplit * b.N;
+        if (ch.v.kind == KIND_DWP) p.nblocks = ceil_div(p.nblocks, 4);      // four waves with a tile each
         p.chunk_kg = ch.chunk_kg;
         p.chunk_kg2[0] = ch.chunk_kg2[0];
         p.chunk_kg2[1] = ch.chunk_kg2[1];
@@ -950,6 +983,7 @@ struct Builder {
         gi.tiles_x = ch.tiles_x;
         gi.cout_split = ch.csplit;
         gi.workgroups = ch.tiles_x * ch.tiles_y * ch.csplit * b.N;
+        if (ch.v.kind == KIND_DWP) gi.workgroups = ceil_div(gi.workgroups, 4);
         gi.threads = ch.threads;
         gi.lds_bytes = ch.lds_bytes;
         gi.workgroups_per_cu = ch.occ;
@@ -961,6 +995,7 @@ struct Builder {
         } else {
             const double unique = (double)b.H1 * b.W1;
             gi.redundancy = (double)ch.mh * ch.mw * ch.tiles_x * ch.tiles_y * ch.csplit / unique;
+            if (ch.v.kind == KIND_DWP) gi.redundancy = ch.csplit;
         }
     }
 

@@ -331,7 +331,7 @@ __device__ __forceinline__ void conv_pass_split(f32x16 (&acc)[NRT][NPT], const B
         const int r = fdiv(px, P.rcp_qrow), gy = iy0 + r, gx = ix0 + px - r * P.iws;
         xdst[i] = px < plane ? (xgrp[i] * NP * plane + px) * 4 : -1;
         const bool in = px < plane && gy >= 0 && gy < P.H && gx >= 0 && gx < P.W;
-        xoff[i] = in ? (unsigned)((gy * P.W + gx) * 4) : 0xfffffff0u;
+        xoff[i] = in ? (unsigned)((gy * P.W + gx) * 4) : 0xfffffffcu;
     }
     float xst[NU][8];
     auto load_x = [&](int c0) {                     // chunk whose first channel is c0

@@ -37,7 +37,7 @@ struct ConvW {
     int nrt;                // row tiles = ceil(cout / MF)
 };
 
-enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6 };
+enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7 };
 
 // Kernel argument of every convolution-stage kernel.
 //   KIND_SINGLE: stage 1 writes its result to global memory (one layer, the
@@ -58,6 +58,7 @@ enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_P
 //   KIND_DW:     stage 1 is a depthwise convolution (one filter per channel, vector ALU) into the
 //                LDS tile; stage 2 as KIND_FUSED2.  c1.wp / c1.aff then hold the plain depthwise
 //                tables ([channel group][tap] and [channel group][scale, shift] float4).
+//   KIND_DWP:    KIND_DW with stride 1 and a pointwise stage 2, wave by wave without LDS (dw_conv.h).
 struct BlockParams {
     const float *x;         // block input  [N, Cin, H, W]
     float *y;               // tensor the block writes into [N, Cy, Ho, Wo]
@@ -236,6 +237,13 @@ struct Variant {
     X(57, KIND_DW, 32, 3, 1, 1, 16, 1, 2, 1, 0, 0, 0)                \
     X(58, KIND_DW, 32, 3, 1, 1, 32, 2, 1, 3, 0, 0, 0)                \
     X(59, KIND_DW, 32, 3, 1, 1, 16, 1, 2, 3, 0, 0, 0)                \
+    /* ... wave by wave without LDS: columns 7 (NRT2), 8 and 13 are cout tiles, rows and columns of a wave's tile */ \
+    X(161, KIND_DWP, 32, 3, 1, 1, 32, 1, 4, 1, 0, 0, 32)             \
+    X(162, KIND_DWP, 32, 3, 1, 1, 32, 1, 4, 1, 0, 0, 16)             \
+    X(164, KIND_DWP, 32, 3, 1, 1, 16, 1, 2, 1, 0, 0, 16)             \
+    X(165, KIND_DWP, 32, 3, 1, 1, 16, 1, 4, 1, 0, 0, 16)             \
+    X(167, KIND_DWP, 32, 3, 1, 1, 16, 2, 4, 1, 0, 0, 16)             \
+    X(168, KIND_DWP, 32, 3, 1, 1, 16, 4, 2, 1, 0, 0, 16)             \
     /* conv -> maxpool as a stream of tiles (first layer of one chunk) */ \
     X(94, KIND_POOLS, 32, 3, 1, 1, 0, 0, 0, 0, 0, 0, 0)           \
     X(95, KIND_POOLS, 32, 3, 2, 1, 0, 0, 0, 0, 0, 0, 0)           \
