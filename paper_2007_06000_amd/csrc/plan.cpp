@@ -211,8 +211,9 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
         // `occ` workgroups of a compute unit share the matrix cores while each waits for its own loads, barriers and
         // stores: they finish after the matrix work of all or the whole life of one, whichever is longer.  (The three
         // latencies are fitted to 36 blocks of 600 timed candidates each: the first choice is 5.5 % behind the best one on
-        // average, 14 % with the formula above; the best of the 64 kept ones 0.6 %.)
-        const double lat = 5000.0 + 700.0 * barriers + 2000.0 * passes, mat = t1 + t2 - 2500.0 * passes;
+        // average, 14 % with the formula above.  The fourth stands for a second producer's pass over the tile: 168 -> 139 us for
+        // the choice at 64 channels of 56 x 56, batch 32, and the fp32 kernel's 16.4 us instead of 18 at 19 of 14 x 29, batch 58.)
+        const double lat = 5000.0 + 12000.0 * (b.n1 - 1) + 700.0 * barriers + 2000.0 * passes, mat = t1 + t2 - 2500.0 * passes;
         const int per_cu = (int)rounds, full = per_cu / c.occ, rest = per_cu % c.occ;
         const double life = mat + lat;
         t_mfma = (full * std::max(c.occ * mat, life) + (rest ? std::max(rest * mat, life) : 0.0)) / 2.4e9;
@@ -799,6 +800,17 @@ struct Builder {
             for (int i = 0; i < b.n2; ++i) fp32_forms.insert(std::make_tuple(b.c2[i].layer, c.v.mf2, false));
     }
 
+    // The first n of a list by cost, with at most six of one variant before others had theirs; by cost again.
+    static void keep_best(std::vector<Choice> &l, size_t n)
+    {
+        auto by_cost = [](const Choice &x, const Choice &y) { return x.cost < y.cost; };
+        std::map<int, int> seen;
+        std::stable_sort(l.begin(), l.end(), by_cost);
+        std::stable_partition(l.begin(), l.end(), [&](const Choice &c) { return ++seen[c.v.id] <= 6; });
+        if (l.size() > n) l.resize(n);
+        std::stable_sort(l.begin(), l.end(), by_cost);
+    }
+
     // Turn a searched choice into a launch step.
     xl_status make_block_step(const BlockSpec &b, int x_id, int y_id, int sc_id, int coff1, Step &st, Choice &ch,
                               const std::string &what)
@@ -810,27 +822,23 @@ struct Builder {
             return fail(lds_rejected ? XL_E_LDS_BUDGET : XL_E_UNSUPPORTED,
                         what + (lds_rejected ? ": no tile fits the LDS budget" : ": no kernel variant covers this block"));
         for (const Choice &c : ranked) count_fp32_forms(b, c);
-        // fp32 arithmetic: the kernels on fp32 matrix operations and those on operands in three bf16 parts, whose results
-        // are no less exact (split_conv.h), ranked together
-        std::vector<Choice> parts3 = search(b, pl, ignored, 2);
-        const size_t keep_fp32 = MAX_ALTERNATIVES / 3;
-        if (parts3.size() > MAX_ALTERNATIVES - keep_fp32) parts3.resize(MAX_ALTERNATIVES - keep_fp32);
-        if (ranked.size() > MAX_ALTERNATIVES - parts3.size()) ranked.resize(MAX_ALTERNATIVES - parts3.size());
-        ranked.insert(ranked.end(), parts3.begin(), parts3.end());
-        std::stable_sort(ranked.begin(), ranked.end(), [](const Choice &x, const Choice &y) { return x.cost < y.cost; });
-        if (pl.opts.precision == XL_PRECISION_BF16X3) {
-            // the candidates on two bf16 parts first (the cost model cannot rank the two kinds against each other
-            // well: blocks that are not bound by the matrix cores gain nothing from the split), then the
-            // best of the others, for xl_tune to choose from
-            std::vector<Choice> split = search(b, pl, ignored, 1);
-            if (!split.empty()) {
-                const size_t keep = MAX_ALTERNATIVES / 2;
-                if (split.size() > MAX_ALTERNATIVES - keep) split.resize(MAX_ALTERNATIVES - keep);
-                if (ranked.size() > keep) ranked.resize(keep);
-                split.insert(split.end(), ranked.begin(), ranked.end());
-                ranked.swap(split);
-            }
+        // Next to them the kernels on operands in bf16 parts: three, whose results are no less exact (split_conv.h), ranked
+        // together with the fp32 ones; two where the caller asks for that, before the fp32 ones (blocks that are not bound
+        // by the matrix cores gain nothing from the split, and the cost model ranks the two kinds against each other badly).
+        // Each kind gets half of the places (more where the other has less), every variant its six best before a seventh of
+        // any: with one list by cost, 3 -> 23 channels at stride 2 with pooling, batch 14, lost the 9.2 us candidate of
+        // another variant and took 11.2 us.  (The best of the 64 is 0.6 % behind the best of 600 over 36 blocks; of 64 and 48
+        // without the cap 0.5 %.)
+        std::vector<Choice> split = search(b, pl, ignored, pl.opts.precision == XL_PRECISION_BF16X3 ? 1 : 2);
+        if (!split.empty()) {
+            const size_t half = MAX_ALTERNATIVES / 2, fp32 = ranked.size();
+            keep_best(ranked, std::max(half, MAX_ALTERNATIVES - std::min(split.size(), (size_t)MAX_ALTERNATIVES)));
+            keep_best(split, std::max(half, MAX_ALTERNATIVES - std::min(fp32, (size_t)MAX_ALTERNATIVES)));
+            split.insert(split.end(), ranked.begin(), ranked.end());
+            ranked.swap(split);
         }
+        if (pl.opts.precision != XL_PRECISION_BF16X3)
+            std::stable_sort(ranked.begin(), ranked.end(), [](const Choice &x, const Choice &y) { return x.cost < y.cost; });
         ch = ranked[0];
         fill_step(b, ch, x_id, y_id, sc_id, coff1, st);
         // the other candidates, for xl_tune to time on the device
