@@ -1651,18 +1651,43 @@ hipError_t launch_add(const float *a, const float *b, float *y, long long count,
                        relu);
 }
 
-// one wavefront per (image, channel): mean over H*W
-__global__ void gap_kernel(const float *__restrict__ x, float *__restrict__ y, int NC, int HW)
+// Mean over H*W: a wavefront per NP consecutive (image, channel) planes.  Bound by memory; a wave's life is one trip to it
+// and the sums across the wave, so what counts is the loads in flight: all NU * NP of them are issued before the first sum.
+// Per plane the order of the sums does not depend on NU or NP.
+// 64000 planes of 13 x 13: 14.5 us with a loop over one plane's loads, 10.5 with NP = 1, 8.5 with 2 (5.1 TB/s), 8.7 with 4.
+template <int NU, int NP>
+__global__ void __launch_bounds__(256) gap_kernel(const float *__restrict__ x, float *__restrict__ y, int NC, int HW)
 {
-    const int wave = (int)((blockIdx.x * (long long)blockDim.x + threadIdx.x) >> 6);
+    const int plane = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * (long long)blockDim.x + threadIdx.x) >> 6)) * NP;
     const int lane = threadIdx.x & 63;
-    if (wave >= NC) return;
-    const float *xc = x + (size_t)wave * HW;
-    float s = 0.f;
-    for (int i = lane; i < HW; i += 64) s += xc[i];
+    if (plane >= NC) return;
+    const float *xc[NP];
+    float s[NP];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) y[wave] = s / (float)HW;
+    for (int p = 0; p < NP; ++p) {
+        xc[p] = x + (size_t)min(plane + p, NC - 1) * HW;
+        s[p] = 0.f;
+    }
+    for (int i0 = 0; i0 < HW; i0 += NU * 64) {
+        float v[NP][NU];
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int u = 0; u < NU; ++u) v[p][u] = xc[p][min(i0 + u * 64 + lane, HW - 1)];
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int u = 0; u < NU; ++u) s[p] += i0 + u * 64 + lane < HW ? v[p][u] : 0.f;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) s[p] += __shfl_xor(s[p], o, 64);
+    if (lane == 0) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (plane + p < NC) y[plane + p] = s[p] / (float)HW;
+    }
 }
 
 hipError_t launch_gap(const float *x, float *y, int NC, int HW, hipStream_t s)
@@ -1670,7 +1695,12 @@ hipError_t launch_gap(const float *x, float *y, int NC, int HW, hipStream_t s)
     if (NC == 0) return hipSuccess;
     const int threads = 256;
     const int wpb = threads / 64;
-    return launch(gap_kernel, dim3((NC + wpb - 1) / wpb), dim3(threads), 0, s, x, y, NC, HW);
+    auto go = [&](auto kernel, int np) { return launch(kernel, dim3((NC + wpb * np - 1) / (wpb * np)), dim3(threads), 0, s, x, y, NC, HW); };
+    // Two planes per wave once one each would fill the chip's wave slots (13 x 13: 2.6 and 2.6 us at 8000 planes, 3.85 and
+    // 3.35 at 16000; 2.42 and 2.45 at 4000).
+    if (NC < 8192)
+        return HW <= 64 ? go(gap_kernel<1, 1>, 1) : HW <= 128 ? go(gap_kernel<2, 1>, 1) : HW <= 192 ? go(gap_kernel<3, 1>, 1) : go(gap_kernel<4, 1>, 1);
+    return HW <= 64 ? go(gap_kernel<1, 2>, 2) : HW <= 128 ? go(gap_kernel<2, 2>, 2) : HW <= 192 ? go(gap_kernel<3, 2>, 2) : go(gap_kernel<4, 2>, 2);
 }
 
 // ----------------------------------------------------------------------------
