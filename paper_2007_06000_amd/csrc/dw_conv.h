@@ -1,4 +1,4 @@
-// Depthwise 3x3 (stride 1) -> 1x1 convolution without LDS (included by kernels.hip; paper Table 1, a.2).
+// Depthwise 3x3 (stride 1) -> 1x1 convolution (stride 1) without LDS (included by kernels.hip; paper Table 1, a.2).
 //
 // The block moves its input and output once and does little else (16 channels of 80 x 80, batch 32: 26 MB, 164 MFLOP), so
 // it is bound by memory as long as enough requests are in flight.  The general kernel (KIND_DW in block_kernel) runs in

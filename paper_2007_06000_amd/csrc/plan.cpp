@@ -538,8 +538,8 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             }
         }
     }
-    if (best.ok && b.kind == KIND_DW && pr == 0 && b.n2 == 1 && b.c2[0].k == 1 && b.c1.stride == 1 && !pl.opts.force_tile_h &&
-        !pl.opts.force_threads && !pl.opts.force_cout_split && !pl.opts.paper_tuner_only)
+    if (best.ok && b.kind == KIND_DW && pr == 0 && b.n2 == 1 && b.c2[0].k == 1 && b.c2[0].stride == 1 && b.c1.stride == 1 &&
+        !pl.opts.force_tile_h && !pl.opts.force_threads && !pl.opts.force_cout_split && !pl.opts.paper_tuner_only)
         for (const Variant &v : variants()) {
             // depthwise -> pointwise wave by wave (whether the block can be planned is decided by the kernels above)
             if (v.kind != KIND_DWP) continue;

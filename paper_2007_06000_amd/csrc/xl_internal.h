@@ -58,7 +58,7 @@ enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_P
 //   KIND_DW:     stage 1 is a depthwise convolution (one filter per channel, vector ALU) into the
 //                LDS tile; stage 2 as KIND_FUSED2.  c1.wp / c1.aff then hold the plain depthwise
 //                tables ([channel group][tap] and [channel group][scale, shift] float4).
-//   KIND_DWP:    KIND_DW with stride 1 and a pointwise stage 2, wave by wave without LDS (dw_conv.h).
+//   KIND_DWP:    KIND_DW with a pointwise stage 2, both of stride 1, wave by wave without LDS (dw_conv.h).
 struct BlockParams {
     const float *x;         // block input  [N, Cin, H, W]
     float *y;               // tensor the block writes into [N, Cy, Ho, Wo]

@@ -79,6 +79,15 @@ def test_grouped_convolutions_other_than_depthwise_are_rejected():
     assert e.value.status == B.XL_E_UNSUPPORTED
 
 
+@pytest.mark.parametrize("s2", [1, 2, 3])
+@pytest.mark.parametrize("n,c,h,w,c2", [(32, 16, 80, 80, 16), (64, 8, 100, 100, 24), (24, 13, 41, 50, 24)])
+def test_depthwise_kernels_without_lds_are_offered_for_pointwise_layers_of_stride_one_only(n, c, h, w, c2, s2):
+    for precision in (0, 1):
+        p = B.Plan(W.depthwise_pointwise(n, c, h, w, c2, s2=s2), precision=precision)
+        ids = {p.candidate_info(True, 0, i)["variant"] for i in range(p.num_candidates(True, 0))}
+        assert bool(ids & set(range(161, 169))) == (s2 == 1), ids
+
+
 def test_two_producer_merge_block_plans_as_one_launch():
     """Table 1, c.1: {1x1 64->256, 1x1 64->256} -> add -> 1x1 256->64 on [64,56,56]."""
     p = B.Plan(W.merge_two_producers(1))

@@ -41,3 +41,23 @@ def test_against_the_oracle(wl, expected):
         others = [i for i in range(x.shape[0]) if i != 1]
         assert (y[others] == z[others]).all() and not np.isfinite(z[1]).all(), v
     assert seen >= expected and (expected or not seen), seen
+
+
+@pytest.mark.parametrize("wl,tune", [
+    (W.depthwise_pointwise(32, 16, 80, 80, 16, s2=2), False), (W.depthwise_pointwise(24, 13, 41, 50, 24, s2=3), False),
+    (W.depthwise_pointwise(64, 8, 100, 100, 24, s2=2), True), (W.depthwise_pointwise(24, 13, 41, 50, 24, s2=3), True),
+], ids=lambda a: getattr(a, "name", str(a)))
+def test_a_strided_second_layer_runs_on_the_general_kernel(wl, tune):
+    from paper_2007_06000_amd.session import Session
+    x, params = W.make_tensors(wl)
+    ref = xlo.forward(wl, x, params)
+    s = Session(wl, x, params, tune=tune)
+    assert np.linalg.norm(s.output(True) - ref) <= 2.0 ** -20 * np.linalg.norm(ref)
+    seen = set()
+    for c in range(s.plan.num_candidates(True, 0)):
+        v = s.plan.candidate_info(True, 0, c)["variant"]
+        if v not in seen:
+            seen.add(v)
+            print(f"[case] {wl.name} variant {v} candidate {c}", flush=True)
+            s.plan.select_candidate(True, 0, c)
+            assert np.linalg.norm(s.output(True) - ref) <= 2.0 ** -20 * np.linalg.norm(ref), v
