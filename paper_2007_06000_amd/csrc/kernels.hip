@@ -997,6 +997,7 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
                         if constexpr (PR) {
                             // the filter comes from memory: a wave needs nothing of the others, and a pass whose
                             // result stays in registers has no barrier
+                            bool redo = whole;
                             if (g2.active && !whole) {
                                 f32x16 small[NRT2][NPT2];
 #pragma unroll
@@ -1005,8 +1006,13 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
                                     for (int p = 0; p < NPT2; ++p) zero_acc(small[r][p]);
                                 conv_direct<KS2, NRT2, NPT2, PR>(acc2, small, mid, off2, P.mw, P.mid_gstride, c, r0, 0,
                                                                  c.nkg, __builtin_amdgcn_readfirstlane(npt2 - p0), [] {});
-                                if constexpr (PR == 2) add_small<NRT2, NPT2>(acc2, small);
-                            } else if (g2.active) {
+                                if constexpr (PR == 2) {
+                                    add_small<NRT2, NPT2>(acc2, small);
+                                    redo = any_not_finite<NRT2, NPT2>(acc2);
+                                    if (redo) init_acc<MF2, NRT2, NPT2>(acc2, c, r0);
+                                }
+                            }
+                            if (g2.active && redo) {
                                 conv_whole<KS2, NRT2, NPT2>(acc2, c, r0, [&](int p, int kg, int t, int e) {
                                     const int at = kg * 6 * P.mid_gstride + off2[p] + (t / KS2 * P.mw + t % KS2) * 4;
                                     const unsigned short *v = (const unsigned short *)(mid + at) + e;

@@ -284,6 +284,20 @@ __device__ __forceinline__ void conv_whole(f32x16 (&acc)[NRT][NPT], const ConvW 
             }
 }
 
+// Whether a sum of the wave is infinite or NaN.
+template <int NRT, int NPT>
+__device__ __forceinline__ bool any_not_finite(const f32x16 (&acc)[NRT][NPT])
+{
+    float t = 0.f;
+#pragma unroll
+    for (int r = 0; r < NRT; ++r)
+#pragma unroll
+        for (int p = 0; p < NPT; ++p)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) t = fmaf(acc[r][p][i], 0.f, t);
+    return __builtin_amdgcn_ballot_w64(t != 0.f) != 0;
+}
+
 // The two accumulators of a tile become one.
 template <int NRT, int NPT>
 __device__ __forceinline__ void add_small(f32x16 (&acc)[NRT][NPT], const f32x16 (&accl)[NRT][NPT])
@@ -395,7 +409,7 @@ __device__ __forceinline__ void conv_pass_split(f32x16 (&acc)[NRT][NPT], const B
     }
     if constexpr (PR == 2) {
         add_small<NRT, NPT>(acc, accl);
-        if (live > 0 && (*flag != 0 || weights_flag(c))) {
+        if (live > 0 && (*flag != 0 || weights_flag(c) || any_not_finite<NRT, NPT>(acc))) {
             init(acc);
             const int lane = tid & 63, sub = lane >> 5;
             conv_whole<KS, NRT, NPT>(acc, c, rt0, [&](int p, int kg, int t, int e) {

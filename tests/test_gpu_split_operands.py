@@ -82,3 +82,31 @@ def test_filters_without_bf16_parts(special):
     ref = next(iter(fp32.values()))
     for v, y in split.items():
         assert (np.isfinite(y) == np.isfinite(ref)).all() and (np.isnan(y) == np.isnan(ref)).all(), v
+
+
+@pytest.mark.parametrize("wl", WORKLOADS, ids=lambda w: w.name)
+def test_products_just_below_the_largest_float(wl):
+    # (2 - 2^-9)^2 * 2^126 is below FLT_MAX, while the product of the factors rounded to bf16 is 2^128: one pixel and one
+    # filter value of the first layer, so that one of its sums is within 2^-8 of FLT_MAX.
+    big = np.float32(2.0 - 2.0 ** -9) * np.float32(2.0 ** 63)
+    x, params = W.make_tensors(wl)
+    x[0, 1, x.shape[2] // 2, x.shape[3] // 2] = big
+    first = wl.layers[0]
+    w = params[0]["w"]
+    k = first.k // 2
+    w[0, 1 if first.groups == 1 else 0, k, k] = big
+    if first.groups != 1:
+        x[0, 0, x.shape[2] // 2, x.shape[3] // 2] = big
+    if params[0]["scale"] is not None:
+        params[0]["scale"][0] = 1.0
+    fp32, split = run_candidates(wl, x, params)
+    ref = next(iter(fp32.values()))
+    assert all((np.isfinite(y) == np.isfinite(ref)).all() for y in fp32.values())
+    for v, y in split.items():
+        assert (np.isfinite(y) == np.isfinite(ref)).all(), v
+        fin = np.isfinite(ref)
+        # sums that hold a term near FLT_MAX: up to a few hundred roundings of 2^-24 of that magnitude
+        d = np.abs(y[fin].astype(np.float64) - ref[fin].astype(np.float64))
+        reached = np.abs(ref[fin]) > 1e10
+        assert (d <= 1e-4 + 1e-4 * np.abs(ref[fin]))[~reached].all(), (v, d[~reached].max())
+        assert (d <= 2.0 ** -16 * 3.4e38)[reached].all(), (v, d[reached].max())
