@@ -614,12 +614,11 @@ __device__ __forceinline__ void store_gap(const typename MM<MF>::Acc (&acc)[NRT]
 // must see outside the image: 0 for a convolution, -FLT_MAX for max pooling.
 // With `add` the result is added to what the tile already holds (the first of two producer layers
 // of a merge block, written by this same lane) and `relu_sum` is applied to the sum.
-// PR > 0: the tile is written as planes of bf16 parts (split_conv.h), `flag` raised where a value does not come apart;
-// `add` reads the sum of the parts back.
+// PR > 0: the tile is written as planes of bf16 parts (split_conv.h); `add` reads the sum of the parts back.
 template <int MF, int NRT, int NPT, int PR = 0>
 __device__ __forceinline__ void store_mid(const typename MM<MF>::Acc (&acc)[NRT][NPT], const BlockParams &P,
                                           const ConvW &c, float *mid, int my0, int mx0, int rt0, int rt_end, int pt0,
-                                          int npx, float fill, int *flag, bool add = false, bool relu_sum = false)
+                                          int npx, float fill, bool add = false, bool relu_sum = false)
 {
     typedef MM<MF> M;
     const int lane = threadIdx.x & 63;
@@ -655,6 +654,13 @@ __device__ __forceinline__ void store_mid(const typename MM<MF>::Acc (&acc)[NRT]
                             old[2] += bf16_low(w.y);
                             old[3] += bf16_high(w.y);
                         }
+                        if constexpr (PR == 2) {
+                            if (__builtin_expect((*(const unsigned *)dst & 0xffffu) == WHOLE_MARK, 0)) {   // (all four alike)
+                                const unsigned short *w = (const unsigned short *)dst;
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) old[i] = whole_value(w[i], w[2 * P.mid_gstride + i], w[4 * P.mid_gstride + i]);
+                            }
+                        }
                     } else {
                         old = *(const f32x4 *)dst;
                     }
@@ -672,10 +678,7 @@ __device__ __forceinline__ void store_mid(const typename MM<MF>::Acc (&acc)[NRT]
                         bool odd = false;
                         store_parts<PR>(v, dst, P.mid_gstride, odd);
                         if constexpr (PR == 2) {
-                            if (__builtin_expect(odd, 0)) {
-                                store_value_parts(v, dst, P.mid_gstride);
-                                *flag = 1;
-                            }
+                            if (__builtin_expect(odd, 0)) store_whole_parts(v, dst, P.mid_gstride);
                         }
                     }
                 } else {
@@ -733,7 +736,7 @@ __device__ __forceinline__ void store_tile(const typename MM<MF>::Acc (&acc)[NRT
 // Filter: [channel group][tap] float4, scale / shift: [channel group][2] float4 (re-laid out once).
 // ----------------------------------------------------------------------------
 template <int PR>
-__device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mid, float *xs, int *flag, const float *ximg,
+__device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mid, float *xs, const float *ximg,
                                                  unsigned long long x_bytes, int my0, int mx0, int iy0, int ix0)
 {
     const ConvW &c = P.c1;
@@ -792,10 +795,7 @@ __device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mi
             bool odd = false;
             store_parts<PR>(o, dst, P.mid_gstride, odd);
             if constexpr (PR == 2) {
-                if (__builtin_expect(odd, 0)) {
-                    store_value_parts(o, dst, P.mid_gstride);
-                    *flag = 1;
-                }
+                if (__builtin_expect(odd, 0)) store_whole_parts(o, dst, P.mid_gstride);
             }
         } else {
             *(f32x4 *)(mid + g * P.mid_gstride + pidx * 4) = o;
@@ -838,15 +838,10 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
     float *mid = lds;
     float *buf = lds + P.lds_buf_off;
     const float *ximg = P.x + (size_t)n * P.Cin * P.H * P.W;
-    int *flag = (int *)(lds + P.flag_off);          // some pixel in LDS does not come apart (three parts only)
-    if constexpr (PR == 2) {
-        if (threadIdx.x == 0) *flag = 0;
-        if constexpr (PR1 == 2) lds_barrier();      // (stage 1 on fp32 operands has barriers before it could be raised)
-    }
 
     if constexpr (KIND == KIND_DW) {
         // ---- S1/S2 for a depthwise first layer: vector ALU from a staged input tile into the LDS tile
-        depthwise_stage1<PR>(P, mid, buf, flag, ximg, (unsigned long long)(P.N - n) * P.Cin * P.H * P.W * 4ull, my0, mx0, iy0, ix0);
+        depthwise_stage1<PR>(P, mid, buf, ximg, (unsigned long long)(P.N - n) * P.Cin * P.H * P.W * 4ull, my0, mx0, iy0, ix0);
     } else {
     // ---- S1: layer 1 over the (halo-extended) tile
     const int npx1 = P.mh * P.mw;
@@ -883,7 +878,7 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
         if constexpr (PR1)
             conv_pass_split<K1, NRT1, NPT1, PR1>(acc, P, c, rt0, pt0,
                                                  g1.active ? __builtin_amdgcn_readfirstlane((npx1 - pt0 * MF1 + MF1 - 1) / MF1) : 0,
-                                                 off1, buf, flag, ximg, iy0, ix0, init);
+                                                 off1, buf, ximg, iy0, ix0, init);
         else
             conv_pass<MF1, K1, NRT1, NPT1, true, PX1>(acc, P, c, g1, nullptr, off1, buf, ximg, x_bytes, iy0, ix0);
     };
@@ -902,13 +897,13 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
     } else {
         // ---- S2: epilogue of layer 1 into the LDS tile
         store_mid<MF1, NRT1, NPT1, (KIND == KIND_POOL ? 0 : PR)>(acc, P, P.c1, mid, my0, mx0, rt0, rt_end1, pt0, npx1,
-                                                                 KIND == KIND_POOL ? -FLT_MAX : 0.f, flag);
+                                                                 KIND == KIND_POOL ? -FLT_MAX : 0.f);
         if constexpr (KIND == KIND_FUSED2 && K1 == 1 && K2A == 1 && K2B == 0 && !SC) {
             if (P.n1 == 2) {
                 // second producer of a merge block (paper Fig. 4c): same input, same geometry, its own
                 // filter; its result is added to the first one's in the LDS tile
                 stage1(P.c1b);
-                store_mid<MF1, NRT1, NPT1, PR>(acc, P, P.c1b, mid, my0, mx0, rt0, rt_end1, pt0, npx1, 0.f, flag, true,
+                store_mid<MF1, NRT1, NPT1, PR>(acc, P, P.c1b, mid, my0, mx0, rt0, rt_end1, pt0, npx1, 0.f, true,
                                                P.relu_mid != 0);
             }
         }
@@ -958,16 +953,13 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
             // ---- S4/S5: sibling convolutions from the LDS tile, heavier one first.  Every pass covers
             // (row waves x NRT2) row tiles by (pixel waves x NPT2) pixel tiles; all waves stream the
             // same filter chunks.
-            const int sub = lane / MF2, col = lane % MF2;
             const int npt2 = (P.th * P.vw2 + MF2 - 1) / MF2;
             const int lg_r2 = __builtin_ctz(P.waves_r2);
             const int wr2 = wave & (P.waves_r2 - 1), wp2 = wave >> lg_r2;
             const int wg_pt2 = (nwaves >> lg_r2) * NPT2;
             float *tile2 = PR ? lds + P.tile2_off : buf;        // KIND_FUSED2P: what is pooled
-            const bool whole_px = PR == 2 && __builtin_amdgcn_readfirstlane(*flag) != 0;
             auto run_conv = [&](auto ks_tag, const ConvW &c, int coff, int chunk_kg2) {
                 constexpr int KS2 = decltype(ks_tag)::value;
-                const bool whole = PR == 2 && (whole_px || weights_flag(c));
                 const int per = udiv(c.nrt + P.csplit - 1, P.csplit, P.rcp_csplit);     // row tiles of this workgroup
                 const int rtb = cs * per, rte = min(c.nrt, rtb + per);
                 PassGeom g2;
@@ -987,18 +979,18 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
                         typename MM<MF2>::Acc acc2[NRT2][NPT2];
                         int off2[NPT2];
                         init_acc<MF2, NRT2, NPT2>(acc2, c, r0);
-#pragma unroll
-                        for (int p = 0; p < NPT2; ++p) {
-                            const int pidx = (p0 + p) * MF2 + col;
+                        auto pixel_offset = [&](int p, int ln) {
+                            const int pidx = (p0 + p) * MF2 + ln % MF2;
                             const int oyu = fdiv(pidx, P.rcp_vw2);
                             const int oy = min(oyu, P.th - 1), ox = min(pidx - oyu * P.vw2, P.tw - 1);
-                            off2[p] = ((oy * P.s2 + d) * P.mw + ox * P.s2 + d) * 4 + sub * (PR + 1) * P.mid_gstride;
-                        }
+                            return ((oy * P.s2 + d) * P.mw + ox * P.s2 + d) * 4 + ln / MF2 * (PR + 1) * P.mid_gstride;
+                        };
+#pragma unroll
+                        for (int p = 0; p < NPT2; ++p) off2[p] = pixel_offset(p, lane);
                         if constexpr (PR) {
                             // the filter comes from memory: a wave needs nothing of the others, and a pass whose
                             // result stays in registers has no barrier
-                            bool redo = whole;
-                            if (g2.active && !whole) {
+                            if (g2.active) {
                                 f32x16 small[NRT2][NPT2];
 #pragma unroll
                                 for (int r = 0; r < NRT2; ++r)
@@ -1008,16 +1000,17 @@ __global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_W
                                                                  c.nkg, __builtin_amdgcn_readfirstlane(npt2 - p0), [] {});
                                 if constexpr (PR == 2) {
                                     add_small<NRT2, NPT2>(acc2, small);
-                                    redo = any_not_finite<NRT2, NPT2>(acc2);
-                                    if (redo) init_acc<MF2, NRT2, NPT2>(acc2, c, r0);
+                                    if (any_not_finite<NRT2, NPT2>(acc2)) {
+                                        int ln = lane;      // (offsets are worked out again: no registers for them in the K loop)
+                                        asm volatile("" : "+v"(ln));
+                                        init_acc<MF2, NRT2, NPT2>(acc2, c, r0);
+                                        conv_whole<KS2, NRT2, NPT2>(acc2, c, r0, [&](int p, int kg, int t, int e) {
+                                            const int at = kg * 6 * P.mid_gstride + pixel_offset(p, ln) + (t / KS2 * P.mw + t % KS2) * 4;
+                                            const unsigned short *v = (const unsigned short *)(mid + at) + e;
+                                            return whole_value(v[0], v[2 * P.mid_gstride], v[4 * P.mid_gstride]);
+                                        });
+                                    }
                                 }
-                            }
-                            if (g2.active && redo) {
-                                conv_whole<KS2, NRT2, NPT2>(acc2, c, r0, [&](int p, int kg, int t, int e) {
-                                    const int at = kg * 6 * P.mid_gstride + off2[p] + (t / KS2 * P.mw + t % KS2) * 4;
-                                    const unsigned short *v = (const unsigned short *)(mid + at) + e;
-                                    return bf16_low(v[0]) + (bf16_low(v[2 * P.mid_gstride]) + bf16_low(v[4 * P.mid_gstride]));
-                                });
                             }
                         } else {
                             conv_pass<MF2, KS2, NRT2, NPT2, false>(acc2, P, c, g2, mid, off2, buf, nullptr, 0ull, 0, 0);
@@ -1457,11 +1450,10 @@ __global__ void pack_filter_kernel(const float *__restrict__ w, const float *__r
 }
 
 // Split-bf16 form (32-wide tiles): [K step][tap][row tile][part][lane] of 8 bf16;
-//   lane l holds cout = rt*32 + l%32, cin = kg*16 + (l/32)*8 + e.  `flag` (three parts) is raised by a value that does
-// not come apart (split_conv.h); launch_pack_affine has cleared it.
+//   lane l holds cout = rt*32 + l%32, cin = kg*16 + (l/32)*8 + e.
 template <int PR>
 __global__ void pack_filter_split_kernel(const float *__restrict__ w, const float *__restrict__ scale,
-                                         uint4 *__restrict__ wp, int *flag, int cout, int cin, int k, int nkg, int nrt)
+                                         uint4 *__restrict__ wp, int cout, int cin, int k, int nkg, int nrt)
 {
     const int taps = k * k;
     const long long total = (long long)nkg * taps * nrt * 64;
@@ -1476,7 +1468,6 @@ __global__ void pack_filter_split_kernel(const float *__restrict__ w, const floa
     const int o = rt * 32 + lane % 32;
     const int sub = lane / 32;
     unsigned out[PR + 1][4];
-    bool odd = false;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         float v[2];
@@ -1486,16 +1477,14 @@ __global__ void pack_filter_split_kernel(const float *__restrict__ w, const floa
             v[h] = (o < cout && ci < cin) ? w[((size_t)o * cin + ci) * taps + t] * (scale ? scale[o] : 1.f) : 0.f;
         }
         unsigned p[PR + 1];
-        bool here = false;
-        split_pair<PR>(v[0], v[1], p, here);
+        bool odd = false;
+        split_pair<PR>(v[0], v[1], p, odd);
         if constexpr (PR == 2) {
-            if (here) value_parts(v[0], v[1], p);
+            if (odd) whole_parts(v[0], v[1], p);
         }
-        odd |= here;
 #pragma unroll
         for (int i = 0; i <= PR; ++i) out[i][e] = p[i];
     }
-    if (PR == 2 && odd) atomicOr(flag, 1);
     uint4 *dst = wp + (idx >> 6) * (64 * (PR + 1)) + lane;
 #pragma unroll
     for (int i = 0; i <= PR; ++i) dst[i * 64] = uint4{out[i][0], out[i][1], out[i][2], out[i][3]};
@@ -1507,12 +1496,9 @@ hipError_t launch_pack_filter(const float *w, const float *scale, f32x4 *wp, int
     const long long total = (long long)nkg * k * k * nrt * 64;
     const int threads = 256;
     const int grid = (int)((total + threads - 1) / threads);
-    if (pr) {
-        const size_t bytes = packed_filter_bytes(nkg, k * k, nrt, pr);
-        int *flag = reinterpret_cast<int *>(reinterpret_cast<char *>(wp) + packed_affine_offset(bytes) + packed_affine_bytes(nrt, mf) - 16);
+    if (pr)
         return launch(pr == 2 ? pack_filter_split_kernel<2> : pack_filter_split_kernel<1>, dim3(grid), dim3(threads), 0, s,
-                      w, scale, (uint4 *)wp, flag, cout, cin, k, nkg, nrt);
-    }
+                      w, scale, (uint4 *)wp, cout, cin, k, nkg, nrt);
     return launch(pack_filter_kernel, dim3(grid), dim3(threads), 0, s, w, scale, wp, cout, cin, k, mf, nkg, nrt, pairs);
 }
 
@@ -1528,7 +1514,6 @@ __global__ void pack_affine_kernel(const float *__restrict__ shift, f32x4 *__res
 {
     const int nq = mf == 32 ? 4 : 1;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;     // over nrt * nq * 64
-    if (mf == 32 && idx == 0) *reinterpret_cast<int *>(out + nrt * nq * 64) = 0;     // see packed_affine_bytes
     if (idx >= nrt * nq * 64) return;
     const int lane = idx & 63, q = (idx >> 6) % nq, rt = (idx >> 6) / nq;
     const int sub = lane / mf;

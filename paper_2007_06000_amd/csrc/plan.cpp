@@ -104,7 +104,7 @@ struct Choice {
     int tiles_y = 0, tiles_x = 0;
     int chunk_kg = 0, chunk_kg2[2] = {1, 1};
     int mid_floats = 0, buf_floats = 0, w_off1 = 0;
-    int tile2_floats = 0, tile2_off = 0, flag_off = 0;      // KIND_FUSED2P on split operands: the tile that is pooled; the flag
+    int tile2_floats = 0, tile2_off = 0;      // KIND_FUSED2P on split operands: the tile that is pooled
     bool mid_over_staging = false;
     int lds_bytes = 0, occ = 1;
     long long flops_exec = 0;
@@ -514,8 +514,6 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                                 c.lds_bytes = (c.mid_over_staging ? std::max(c.mid_floats + c.tile2_floats, staging)
                                                                   : c.mid_floats + staging + c.tile2_floats) * 4;
                                 c.tile2_off = c.mid_floats + (c.mid_over_staging ? 0 : staging);
-                                c.flag_off = c.lds_bytes / 4;
-                                if (v.pr == 2) c.lds_bytes += 16;
                                 if (c.lds_bytes > pl.lds_budget) {
                                     any_lds_reject = true;
                                     continue;
@@ -976,7 +974,6 @@ struct Builder {
         p.in_gstride = ch.ih * p.iws * 4;
         p.lds_buf_off = ch.mid_over_staging ? 0 : ch.mid_floats;
         p.tile2_off = ch.tile2_off;
-        p.flag_off = ch.flag_off;
         p.buf_stride = ch.buf_floats;
         p.w_off1 = ch.w_off1;
         p.stream_wgs = ch.v.kind == KIND_POOLS ? std::min(p.nblocks, pl.num_cus * std::max(ch.occ, 1)) : 0;
@@ -1354,7 +1351,7 @@ struct Builder {
         for (const PackedFilter &p : pl.packed) forms += packed_affine_offset(p.bytes) + align_up(p.aff_bytes, 256);
         for (const auto &[layer, mf, pairs] : fp32_forms) {
             const PackedFilter p = packed_form(layer, mf, pairs, 0);
-            forms_fp32 += packed_affine_offset(p.bytes) + align_up(p.aff_bytes - (mf == 32 ? 16 : 0), 256);
+            forms_fp32 += packed_affine_offset(p.bytes) + align_up(p.aff_bytes, 256);
         }
         pl.static_bytes = pl.workspace_bytes - forms + forms_fp32;
         return XL_OK;

@@ -13,9 +13,10 @@
 // 32x32x2 operation 8 x 64.
 //
 // What cannot be taken apart: infinities and NaN (inf - inf) and values the first rounding takes to infinity (above
-// 3.39e38).  Such a value is kept in its parts all the same (hi + mid + lo gives it back exactly: value_parts) and raises a
-// flag -- the workgroup's in LDS for pixels, one behind the shift table for a filter -- on which the workgroup computes
-// the layer with fp32 matrix operations on the reassembled operands (conv_whole), as the fp32 kernels do.  Parts
+// 3.39e38).  In place of the parts of such a value stand a NaN and its upper and lower half (whole_parts), so that every
+// sum it goes into is NaN.  A wave whose sums are not all finite after the K loop computes them again with fp32 matrix
+// operations on the reassembled operands (conv_whole), as the fp32 kernels do.  That also covers sums that overflow: hi*hi may
+// round a product just below FLT_MAX up to infinity.  What a wave does depends on its own sums alone.  Parts
 // below 2^-126 are flushed by the matrix operations: operands keep an absolute precision of 2^-126.
 //
 // The filter goes from memory to registers, one (K step, tap) or two ahead of the matrix operations, not
@@ -58,30 +59,20 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[PR + 
     if constexpr (PR == 2) odd |= __builtin_isunordered(a, b);
 }
 
-// The same for values of which some do not come apart (PR = 2): parts by truncation, whose sum is the value for every
-// finite float; infinities and NaN are their own first part.
-__device__ __forceinline__ void value_parts(float a, float b, unsigned (&w)[3])
+// What is held in place of the parts of two values of which one does not come apart (PR = 2).
+constexpr unsigned WHOLE_MARK = 0x7fc0u;        // no part of a value that comes apart is NaN
+__device__ __forceinline__ void whole_parts(float a, float b, unsigned (&w)[3])
 {
-    unsigned p[2][3];
-    const float v[2] = {a, b};
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const unsigned bits = __builtin_bit_cast(unsigned, v[h]);
-        if ((bits & 0x7f800000u) == 0x7f800000u) {
-            p[h][0] = (bits >> 16) | ((bits & 0x7fffffu) ? 0x40u : 0u);
-            p[h][1] = p[h][2] = 0u;
-        } else {
-            float r = v[h];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const unsigned top = __builtin_bit_cast(unsigned, r) & 0xffff0000u;
-                p[h][i] = top >> 16;
-                r -= __builtin_bit_cast(float, top);
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 3; ++i) w[i] = p[0][i] | (p[1][i] << 16);
+    const unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
+    w[0] = WHOLE_MARK | WHOLE_MARK << 16;
+    w[1] = x >> 16 | (y & 0xffff0000u);
+    w[2] = (x & 0xffffu) | y << 16;
+}
+
+// The value of three parts, whichever way it is held.
+__device__ __forceinline__ float whole_value(unsigned hi, unsigned mid, unsigned lo)
+{
+    return hi == WHOLE_MARK ? __builtin_bit_cast(float, mid << 16 | lo) : bf16_low(hi) + (bf16_low(mid) + bf16_low(lo));
 }
 
 // Four consecutive channels of one pixel into the part planes: part p goes 8 bytes wide to dst + p * plane.
@@ -94,17 +85,14 @@ __device__ __forceinline__ void store_parts(const f32x4 &v, float *dst, int plan
 #pragma unroll
     for (int i = 0; i <= PR; ++i) *(uint2 *)(dst + i * plane) = uint2{a[i], b[i]};
 }
-__device__ __forceinline__ void store_value_parts(const f32x4 &v, float *dst, int plane)
+__device__ __forceinline__ void store_whole_parts(const f32x4 &v, float *dst, int plane)
 {
     unsigned a[3], b[3];
-    value_parts(v[0], v[1], a);
-    value_parts(v[2], v[3], b);
+    whole_parts(v[0], v[1], a);
+    whole_parts(v[2], v[3], b);
 #pragma unroll
     for (int i = 0; i < 3; ++i) *(uint2 *)(dst + i * plane) = uint2{a[i], b[i]};
 }
-
-// Whether a filter in three parts holds a value that does not come apart.
-__device__ __forceinline__ bool weights_flag(const ConvW &c) { return *(const int *)(c.aff + c.nrt * 256) != 0; }
 
 // Workgroup barrier for data in LDS: waits for this wave's LDS operations only, so that loads of the next chunk and
 // of the next filter rows stay in flight (__syncthreads would wait for nothing less than the compiler's fence asks).
@@ -254,9 +242,8 @@ __device__ __forceinline__ void conv_direct(f32x16 (&acc)[NRT][NPT], f32x16 (&ac
     else conv_tiles<KS, NRT, NPT, PR, 1>(acc, accl, bsrc, off, src_w, gstride, c, rt0, kg0, nkg, hook);
 }
 
-// The same sums by fp32 matrix operations on whole operands, for a workgroup that met one that does not come apart:
-// rare, so it is short rather than fast, and it starts from the shift again instead of joining a sum that may be NaN
-// already.  Element e of a lane's 8 channels is K index `lane half` of the operation, for both operands alike;
+// The same sums by fp32 matrix operations on whole operands, for a wave whose sums are not all finite: rare, so it is
+// short rather than fast, and it starts from the shift again.  Element e of a lane's 8 channels is K index `lane half` of the operation, for both operands alike;
 // value(p, kg, t, e) is that element of pixel tile p.
 template <int KS, int NRT, int NPT, typename Value>
 __device__ __forceinline__ void conv_whole(f32x16 (&acc)[NRT][NPT], const ConvW &c, int rt0, Value value)
@@ -273,7 +260,7 @@ __device__ __forceinline__ void conv_whole(f32x16 (&acc)[NRT][NPT], const ConvW 
                 for (int r = 0; r < NRT; ++r) {
                     const int rt = min(rt0 + r, c.nrt - 1);
                     const unsigned short *w = (const unsigned short *)(c.wp + (size_t)((kg * KS * KS + t) * c.nrt + rt) * 192 + lane) + e;
-                    a[r] = bf16_low(w[0]) + (bf16_low(w[512]) + bf16_low(w[1024]));
+                    a[r] = whole_value(w[0], w[512], w[1024]);
                 }
 #pragma unroll
                 for (int p = 0; p < NPT; ++p) {
@@ -322,7 +309,7 @@ __device__ __forceinline__ void add_small(f32x16 (&acc)[NRT][NPT], const f32x16 
 // ----------------------------------------------------------------------------
 template <int KS, int NRT, int NPT, int PR, typename Init>
 __device__ __forceinline__ void conv_pass_split(f32x16 (&acc)[NRT][NPT], const BlockParams &P, const ConvW &c, int rt0,
-                                                int pt0, int live, const int (&off)[NPT], float *buf, int *flag,
+                                                int pt0, int live, const int (&off)[NPT], float *buf,
                                                 const float *__restrict__ ximg, int iy0, int ix0, Init init)
 {
     constexpr int NP = PR + 1, KC = 16;
@@ -376,8 +363,7 @@ __device__ __forceinline__ void conv_pass_split(f32x16 (&acc)[NRT][NPT], const B
             if constexpr (PR == 2) {
                 if (__builtin_expect(odd, 0)) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) value_parts(xst[i][2 * j], xst[i][2 * j + 1], w[j]);
-                    *flag = 1;
+                    for (int j = 0; j < 4; ++j) whole_parts(xst[i][2 * j], xst[i][2 * j + 1], w[j]);
                 }
             }
 #pragma unroll
@@ -409,7 +395,7 @@ __device__ __forceinline__ void conv_pass_split(f32x16 (&acc)[NRT][NPT], const B
     }
     if constexpr (PR == 2) {
         add_small<NRT, NPT>(acc, accl);
-        if (live > 0 && (*flag != 0 || weights_flag(c) || any_not_finite<NRT, NPT>(acc))) {
+        if (live > 0 && any_not_finite<NRT, NPT>(acc)) {
             init(acc);
             const int lane = tid & 63, sub = lane >> 5;
             conv_whole<KS, NRT, NPT>(acc, c, rt0, [&](int p, int kg, int t, int e) {

@@ -28,8 +28,7 @@ constexpr int products_of(int pr) { return pr == 2 ? 6 : 3; }   // matrix operat
 struct ConvW {
     const f32x4 *wp;        // filter, times the per-channel scale, re-laid out as [K step][tap][row tile][lane] of float4
                             // (split-bf16 kernels: [K step][tap][row tile][part][lane] of 8 bf16)
-    const f32x4 *aff;       // shift in accumulator order: [row tile][quad][lane] float4; filters in three bf16 parts
-                            // have an int behind it: 1 if a value cannot be taken apart (see split_conv.h)
+    const f32x4 *aff;       // shift in accumulator order: [row tile][quad][lane] float4
     int cin, cout;
     int k, stride, pad;
     int relu;
@@ -108,7 +107,6 @@ struct BlockParams {
     int lds_buf_off;        // float offset of the two staging buffers in LDS (after the tile; 0 where the tile of a
                             // split-bf16 kernel takes their place once layer 1 is done)
     int tile2_off;          // KIND_FUSED2P: float offset of the stage-2 tile that is pooled
-    int flag_off;           // split-bf16 kernels with three parts: float offset of the workgroup's flag (split_conv.h)
     int buf_stride;         // floats per staging buffer
     int w_off1;             // stage 1: float offset of the filter chunk inside a buffer (after the input chunk)
     int stream_wgs;         // KIND_POOLS: resident workgroups wanted; the launch rounds it up to a multiple of 8 and
@@ -367,11 +365,9 @@ constexpr int MAX_ALTERNATIVES = 64;  // candidates per block kept for on-device
 #define XL_MIN_WAVES 2
 #endif
 
-// ---- re-laid-out filters in the workspace: the table, then (256-byte aligned) the shifts, then for 32-wide tiles 16
-// bytes whose first int launch_pack_affine clears and launch_pack_filter (pr = 2, launched after it) sets to 1 when a
-// value cannot be taken apart into bf16 parts (split_conv.h)
+// ---- re-laid-out filters in the workspace: the table, then (256-byte aligned) the shifts
 constexpr size_t packed_filter_bytes(int nkg, int taps, int nrt, int pr) { return (size_t)nkg * taps * nrt * 1024 * parts_of(pr); }
-constexpr size_t packed_affine_bytes(int nrt, int mf) { return (size_t)nrt * (mf == 32 ? 4 : 1) * 1024 + (mf == 32 ? 16 : 0); }
+constexpr size_t packed_affine_bytes(int nrt, int mf) { return (size_t)nrt * (mf == 32 ? 4 : 1) * 1024; }
 constexpr size_t packed_affine_offset(size_t filter_bytes) { return (filter_bytes + 255) / 256 * 256; }
 
 // ---- launchers (kernels.hip) -------------------------------------------------

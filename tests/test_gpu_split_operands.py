@@ -110,3 +110,27 @@ def test_products_just_below_the_largest_float(wl):
         reached = np.abs(ref[fin]) > 1e10
         assert (d <= 1e-4 + 1e-4 * np.abs(ref[fin]))[~reached].all(), (v, d[~reached].max())
         assert (d <= 2.0 ** -16 * 3.4e38)[reached].all(), (v, d[reached].max())
+
+
+@pytest.mark.parametrize("wl", [w for w in WORKLOADS if len([ly for ly in w.layers if ly.op == "conv"]) > 1], ids=lambda w: w.name)
+def test_passes_repeat_bit_for_bit_around_an_infinite_intermediate(wl):
+    # one sum of the first layer overflows: what a wave then does must not depend on how far the others are
+    from paper_2007_06000_amd.session import Session
+    x, params = W.make_tensors(wl)
+    x[0, 0, x.shape[2] // 2, x.shape[3] // 2] = 3e38
+    k = wl.layers[0].k // 2
+    params[0]["w"][0, 0, k, k] = 4.0
+    s = Session(wl, x, params)
+    seen = set()
+    for c in range(s.plan.num_candidates(True, 0)):
+        v = s.plan.candidate_info(True, 0, c)["variant"]
+        if v < FIRST or v in seen:
+            continue
+        seen.add(v)
+        s.plan.select_candidate(True, 0, c)
+        print(f"[case] {wl.name} variant {v} candidate {c}", flush=True)
+        first = s.output(True)
+        assert not np.isfinite(first).all(), v
+        for _ in range(10):
+            assert s.output(True).tobytes() == first.tobytes(), v
+    assert seen
