@@ -120,8 +120,12 @@ typedef struct xl_options {
     int force_threads;      /* >0: fix the workgroup size (256 or 512) of every block         */
     int precision;          /* XL_PRECISION_FP32 (0, default): fp32 matrix operations, or operands taken apart
                                exactly into three bf16 numbers and multiplied by six bf16 matrix operations
-                               per product, accumulated in fp32: no less exact (the sums meet fewer
-                               roundings), same results for infinities, NaN and values near FLT_MAX.
+                               per product, accumulated in fp32.  The three smallest part products are left
+                               out (together at most 2^-23, typically 2^-27 of |a||b|), and the sums meet fewer
+                               roundings: the error against 64 bits is no larger than with fp32 operations.
+                               Sums that are infinite or NaN that way, and sums over values that cannot be taken
+                               apart (infinities, NaN, above 3.39e38, bits below 2^-133), are computed by
+                               fp32 matrix operations.
                                XL_PRECISION_BF16X3: every operand of a convolution is split into
                                two bf16 numbers, hi = bf16(x) and lo = bf16(x - hi), and a product
                                is hi*hi + hi*lo + lo*hi on the bf16 matrix cores, accumulated in

@@ -808,7 +808,8 @@ __device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mi
 // ----------------------------------------------------------------------------
 // PR: bf16 parts of the operands of stage 2 (0: fp32 operands), PR1: of stage 1 (split_conv.h).
 template <int KIND, int MF1, int K1, int NRT1, int NPT1, int MF2, int NRT2, int NPT2, int K2A, int K2B, bool SC, int PX1, int PR = 0, int PR1 = 0>
-__global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL ? 4 : XL_MIN_WAVES)) block_kernel(const BlockParams P)
+__global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL || (KIND == KIND_SINGLE && PR1 == 2 && NRT1 * NPT1 == 1) ? 4 : XL_MIN_WAVES))
+block_kernel(const BlockParams P)
 {
     static_assert(PR1 == 0 || (PX1 == 0 && MF1 == 32), "split operands are staged through registers");
     static_assert(PR == 0 || MF2 == 32, "split operands use 32-wide matrix-core tiles");

@@ -12,12 +12,13 @@
 // PR = 2 a replacement for the fp32 operations.  Six 32x32x16 bf16 operations take 192 cycles for what takes the fp32
 // 32x32x2 operation 8 x 64.
 //
-// What cannot be taken apart: infinities and NaN (inf - inf) and values the first rounding takes to infinity (above
-// 3.39e38).  In place of the parts of such a value stand a NaN and its upper and lower half (whole_parts), so that every
-// sum it goes into is NaN.  A wave whose sums are not all finite after the K loop computes them again with fp32 matrix
-// operations on the reassembled operands (conv_whole), as the fp32 kernels do.  That also covers sums that overflow: hi*hi may
-// round a product just below FLT_MAX up to infinity.  What a wave does depends on its own sums alone.  Parts
-// below 2^-126 are flushed by the matrix operations: operands keep an absolute precision of 2^-126.
+// What cannot be taken apart: infinities and NaN (inf - inf), values the first rounding takes to infinity (above
+// 3.39e38), and values with bits below 2^-133, the smallest bf16 number (many of those below 2^-110 = 7.7e-34; the matrix
+// operations themselves keep parts, products and sums below 2^-126).  In place of the parts of such a value stand a NaN and
+// its upper and lower half (whole_parts), so that every sum it goes into is NaN.  A wave whose sums are not all finite
+// after the K loop computes them again with fp32 matrix operations on the reassembled operands (conv_whole), as the fp32
+// kernels do.  That also covers sums that overflow: hi*hi may round a product just below FLT_MAX up to infinity.  What a
+// wave does depends on its own sums alone.
 //
 // The filter goes from memory to registers, one (K step, tap) or two ahead of the matrix operations, not
 // through LDS: six operations on one 3 KB row of parts last 192 cycles per pixel tile, so a wave with two or more pixel
@@ -55,8 +56,8 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[PR + 
             b -= bf16_high(w[i]);
         }
     }
-    // what is left is 0, or NaN where a part was infinite or NaN
-    if constexpr (PR == 2) odd |= __builtin_isunordered(a, b);
+    // what is left is 0, except where a part was infinite or NaN (NaN) or bits lie below the smallest bf16 number
+    if constexpr (PR == 2) odd |= (__builtin_bit_cast(unsigned, a) | __builtin_bit_cast(unsigned, b)) != 0u;
 }
 
 // What is held in place of the parts of two values of which one does not come apart (PR = 2).

@@ -134,3 +134,36 @@ def test_passes_repeat_bit_for_bit_around_an_infinite_intermediate(wl):
         for _ in range(10):
             assert s.output(True).tobytes() == first.tobytes(), v
     assert seen
+
+
+@pytest.mark.parametrize("where", ["input", "filter 1", "filter 2"])
+@pytest.mark.parametrize("wl", WORKLOADS, ids=lambda w: w.name)
+def test_error_on_small_operands_is_no_larger_than_with_fp32_operations(wl, where):
+    # Values around 2^-118 have bits below 2^-133, the smallest bf16 number; the other operand is scaled up so that the
+    # results are ordinary floats.  ("filter 2" makes the filters of the later layers small and the intermediate large.)
+    x, params = W.make_tensors(wl)
+    convs = [i for i, ly in enumerate(wl.layers) if ly.op == "conv"]
+    small, large = np.float32(2.0 ** -118), np.float32(2.0 ** 60)
+    if where == "filter 2" and len(convs) == 1:
+        pytest.skip("one layer")
+    x *= small if where == "input" else large
+    for i in convs:
+        first = wl.layers[i].inputs[0] == wl.input_id
+        if where == "filter 1" and first or where == "filter 2" and not first:
+            params[i]["w"] *= small
+        if params[i]["shift"] is not None:
+            params[i]["shift"] *= np.float32(0.0)
+    if where == "input":
+        for i in convs[-1:]:
+            params[i]["w"] *= large
+    ref = xlo.forward(wl, x, params).astype(np.float64)
+    fp32, split = run_candidates(wl, x, params)
+
+    def err(y):
+        scale = np.abs(ref).max()
+        return float(np.linalg.norm(y / scale - ref / scale) / np.linalg.norm(ref / scale))
+    # The same fp32 operations with the K steps in another order: as many roundings, other ones.  The norm over the 200 or
+    # more outputs of a case varies by about 1 / sqrt(200) = 7 % between orders; 25 % is more than three times that.
+    worst = max(err(y) for y in fp32.values())
+    for v, y in split.items():
+        assert err(y) <= max(1.25 * worst, 2.0 ** -23), (v, err(y), worst)
