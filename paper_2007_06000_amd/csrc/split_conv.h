@@ -180,9 +180,10 @@ __device__ __forceinline__ void conv_tiles(f32x16 (&acc)[NRT][NPT], f32x16 (&acc
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // A result of the matrix operations may be read 12 wait states after the last one.  The compiler counts them along
-    // one path to the reader only and falls short where paths of different length meet (seen: the first copy out
-    // of an accumulator took its old value), so they stand here; the matrix pipe is busy for longer anyway.
+    // A result of the matrix operations may be read 12 wait states after the last one.  An earlier form of this loop read an
+    // accumulator too early where paths of different length met behind it, so they stand here; the matrix pipe is busy for
+    // longer anyway.  As the kernels are now the compiler's own count holds on every path, with these states and without
+    // them, behind conv_whole too (tests/test_matrix_operation_waits.py follows them in the built library).
     auto settle = [] { asm volatile("s_nop 15"); };
     const int nsteps = nkg * T;
 #pragma unroll
