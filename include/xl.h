@@ -260,12 +260,15 @@ xl_status xl_tune(xl_plan *plan, const void *const *tensors, int ntensors,
 /*
  * xl_prepare + xl_run for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  The workspace is not the caller's but a
- * static device array inside the library, XL_STATIC_SCRATCH_BYTES long, which every GPU the library
- * runs on holds from the first call on that GPU until the process ends.  The call allocates no
- * device memory and frees none; it enqueues kernels on `stream` and returns without synchronising.
- *   - XL_E_SCRATCH when the plan's workspace, with filters re-laid out for the fp32 matrix operations alone (the array
- *     has room of its own for the other forms), exceeds XL_STATIC_SCRATCH_BYTES (configs 1-4 at their full sizes
- *     fit; config 5 up to batch 4).
+ * static device array inside the library, twice XL_STATIC_SCRATCH_BYTES long (the second half for what filters in bf16
+ * parts need beyond fp32 ones), which every GPU the library runs on holds from the first call on that GPU until the
+ * process ends.  The call allocates no device memory and frees none; it enqueues kernels on `stream` and returns without
+ * synchronising.
+ *   - XL_E_SCRATCH when the plan's workspace, with filters re-laid out for the fp32 matrix operations alone, exceeds
+ *     XL_STATIC_SCRATCH_BYTES (configs 1-4 at their full sizes fit; config 5 up to batch 4).  Plans of precision
+ *     XL_PRECISION_FP32 that pass this always fit the array: the planner leaves kernels on bf16 parts out of the blocks with
+ *     the largest filters where they would not.  With XL_PRECISION_BF16X3 also when the whole workspace exceeds twice
+ *     XL_STATIC_SCRATCH_BYTES.
  *   - relayout != 0: the filters are re-laid out into the array first (as xl_prepare does), from
  *     `weights` / `nweights`; needed on the first call and whenever filter values change.
  *     relayout == 0: the filters are re-laid out only if the array's last user on this GPU was another

@@ -802,6 +802,15 @@ struct Builder {
             for (int i = 0; i < b.n2; ++i) fp32_forms.insert(std::make_tuple(b.c2[i].layer, c.v.mf2, false));
     }
 
+    std::set<int> fp32_layers;      // layers whose blocks get no kernels on split operands (build_plan)
+    bool has_fp32_layer(const BlockSpec &b) const
+    {
+        bool found = fp32_layers.count(b.c1.layer) || (b.n1 == 2 && fp32_layers.count(b.c1b.layer));
+        if (b.kind == KIND_FUSED2 || b.kind == KIND_DW || b.kind == KIND_FUSED2P)
+            for (int i = 0; i < b.n2; ++i) found = found || fp32_layers.count(b.c2[i].layer);
+        return found;
+    }
+
     // The first n of a list by cost, with at most six of one variant before others had theirs; by cost again.
     static void keep_best(std::vector<Choice> &l, size_t n)
     {
@@ -831,7 +840,8 @@ struct Builder {
         // any: with one list by cost, 3 -> 23 channels at stride 2 with pooling, batch 14, lost the 9.2 us candidate of
         // another variant and took 11.2 us.  (The best of the 64 is 0.6 % behind the best of 600 over 36 blocks; of 64 and 48
         // without the cap 0.5 %.)
-        std::vector<Choice> split = search(b, pl, ignored, pl.opts.precision == XL_PRECISION_BF16X3 ? 1 : 2);
+        std::vector<Choice> split;
+        if (!has_fp32_layer(b)) split = search(b, pl, ignored, pl.opts.precision == XL_PRECISION_BF16X3 ? 1 : 2);
         if (!split.empty()) {
             const size_t half = MAX_ALTERNATIVES / 2, fp32 = ranked.size();
             keep_best(ranked, std::max(half, MAX_ALTERNATIVES - std::min(split.size(), (size_t)MAX_ALTERNATIVES)));
@@ -1360,9 +1370,32 @@ struct Builder {
 
 xl_status build_plan(xl_plan &pl, const xl_group *groups, int ngroups)
 {
-    Builder b(pl);
-    const xl_status s = b.build(groups, ngroups);
-    if (s != XL_OK) return s;
+    // A plan that xl_run_static takes with the filters of fp32 kernels alone has to fit its array with all of its filters.
+    // Three bf16 parts take 1.5 times the bytes of the fp32 form, up to 3 times where channels fill a 16-channel K step or a
+    // 32-row tile badly; where that is too much (2500 -> 700 channels, 3x3: 60.8 MB, 151.9 MB with three parts) the blocks
+    // of the layers with the largest filters stay on fp32 kernels.
+    std::set<int> fp32_layers;
+    for (;;) {
+        Builder b(pl);
+        b.fp32_layers = fp32_layers;
+        const xl_status s = b.build(groups, ngroups);
+        if (s != XL_OK) return s;
+        const size_t room = XL_STATIC_SCRATCH_BYTES + STATIC_SPLIT_BYTES;
+        if (pl.opts.precision != XL_PRECISION_FP32 || pl.static_bytes > XL_STATIC_SCRATCH_BYTES || pl.workspace_bytes <= room) break;
+        std::vector<std::pair<size_t, int>> split;
+        for (const PackedFilter &p : pl.packed)
+            if (p.pr == 2) split.push_back({p.bytes, p.layer});
+        std::sort(split.rbegin(), split.rend());
+        size_t saved = 0;
+        for (size_t i = 0; i < split.size() && pl.workspace_bytes - saved > room; ++i) {
+            fp32_layers.insert(split[i].second);
+            saved += split[i].first;
+        }
+        pl.packed.clear();
+        pl.unfused_steps.clear();
+        pl.fused_steps.clear();
+        pl.groups.clear();
+    }
     pl.layerwise.assign(pl.groups.size(), 0);
     refresh_fused_path(pl);
     return XL_OK;

@@ -67,7 +67,7 @@ struct GroupPlan {
 };
 
 // xl_run_static takes plans that need up to XL_STATIC_SCRATCH_BYTES with the filters of their fp32 candidates alone; its
-// array holds as much again, for the filters in bf16 parts (at most 1.5 times the fp32 ones).
+// array holds as much again for the filters in bf16 parts, and build_plan keeps such a plan within both.
 constexpr size_t STATIC_SPLIT_BYTES = XL_STATIC_SCRATCH_BYTES;
 }  // namespace xl
 

@@ -39,9 +39,12 @@ extern "C" xl_status xl_run_static(xl_plan *plan, const void *const *weights, in
                                    int ntensors, void *stream, int fused, int relayout)
 {
     if (!plan || !tensors) return XL_E_NULL;
-    if (plan->static_bytes > (size_t)XL_STATIC_SCRATCH_BYTES || plan->workspace_bytes > XL_STATIC_SCRATCH_BYTES + xl::STATIC_SPLIT_BYTES) {
-        plan->error = "the plan needs " + std::to_string(plan->static_bytes) + " bytes of workspace, the static scratch holds " +
-                      std::to_string((size_t)XL_STATIC_SCRATCH_BYTES);
+    const size_t fp32_room = XL_STATIC_SCRATCH_BYTES, room = XL_STATIC_SCRATCH_BYTES + xl::STATIC_SPLIT_BYTES;
+    if (plan->static_bytes > fp32_room || plan->workspace_bytes > room) {
+        const bool fp32 = plan->static_bytes > fp32_room;
+        plan->error = "the plan needs " + std::to_string(fp32 ? plan->static_bytes : plan->workspace_bytes) + " bytes of workspace" +
+                      (fp32 ? " with fp32 kernels alone, the static scratch takes " : ", the static scratch holds ") +
+                      std::to_string(fp32 ? fp32_room : room);
         return XL_E_SCRATCH;
     }
     int dev = -1;

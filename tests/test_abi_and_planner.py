@@ -161,6 +161,22 @@ def test_oversized_tensors_are_rejected_cleanly():
     assert e.value.status == B.XL_E_UNSUPPORTED
 
 
+def test_the_static_scratch_takes_plans_by_the_size_of_their_fp32_filters():
+    # A 3x3 layer of 63 MB, one with 8 channels in a 16-channel K step, and two layers of which only one has to give way.
+    # (The size is looked at before the device and the weights: any other error is as good as accepted.)
+    pair = W.straight_generic(4, 2500, 7, 7, 600, 3, 1, 1, 150, 3, 1, 1)
+    pair.groups = []
+    for wl in (W.single_conv(4, 2500, 7, 7, 700, 3, pad=1), W.single_conv(8, 8, 20, 20, 150000, 3, pad=1), pair):
+        p = B.Plan(wl)
+        assert p.workspace_bytes() <= 2 * B.XL_STATIC_SCRATCH_BYTES, wl.name
+        with pytest.raises(B.XlError) as e:
+            p.run_static(None, {})
+        assert e.value.status != B.XL_E_SCRATCH, wl.name
+    split = [any(p.candidate_info(False, layer, c)["variant"] >= 400 for c in range(p.num_candidates(False, layer)))
+             for layer in range(2)]
+    assert split == [False, True]
+
+
 def test_global_average_pooling_block_needs_the_image_in_one_tile():
     ok = B.Plan(W.conv_gap_generic(2, 16, 13, 13, 64, 1, 0, 1))
     q = ok.query(0)
