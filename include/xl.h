@@ -246,9 +246,9 @@ xl_status xl_run(const xl_plan *plan, const void *const *tensors, int ntensors,
  * xl_plan_query reports the adopted tiles.  Needs xl_prepare on this workspace first.  Contents of
  * the tensors do not matter but every graph input/output pointer must be valid; outputs and the
  * workspace intermediates are overwritten.  Unlike xl_run this call SYNCHRONISES the stream
- * repeatedly; call it once, outside any timed region.  Every candidate is timed three times (fastest
- * kept) and the six fastest again `reps` times each (reps < 5 means 5), ranked by their MEDIAN
- * time; ties go to the lower candidate index.  xl_plan_candidate_info(.., -1, ..) names the winner.
+ * repeatedly; call it once, outside any timed region.  Every candidate is timed (the fastest of
+ * three launches counts, of two where those are more than half as slow again as the best so far) and the
+ * six fastest again `reps` times each (reps < 5 means 5), ranked by their MEDIAN time; ties go to the lower candidate index.  xl_plan_candidate_info(.., -1, ..) names the winner.
  * Last, a block whose layers, run back to back one kernel each, take less than 0.97 of the time of its fused
  * kernel (both medians of this call) is switched to layer-by-layer execution inside the fused path, as by
  * xl_plan_set_block_fused(.., 0), and every other block is (re)set to fused; options.keep_blocks_fused = 1

@@ -600,19 +600,22 @@ xl_status xl_tune(xl_plan *plan, const void *const *tensors, int ntensors, void 
                 }
                 std::sort(t.begin(), t.end());
             };
-            // a quick look at every candidate (fastest of 3 after a warm-up launch; one launch settles those that are
-            // not within half as much again of the best so far) ...
+            // a quick look at every candidate (fastest of 3 after a warm-up launch; two launches, as one may have met a
+            // stall, settle those that are not within half as much again of the best so far) ...
             float quick_ms = 1e30f;
             std::vector<std::pair<float, int>> quick;
             std::vector<float> t;
             for (size_t a = 0; a < st.alts.size() && rc == XL_OK; ++a) {
                 rc = launch_step(plan, st.alts[a], tensors, ws, s);         // warm-up (code, filters in L2)
                 if (rc != XL_OK) break;
-                time_alt(a, 1, t);
-                if (rc == XL_OK && t.front() <= 1.5f * quick_ms) time_alt(a, 3, t);
+                time_alt(a, 2, t);
                 if (rc != XL_OK) break;
-                quick.push_back({t.front(), (int)a});
-                quick_ms = std::min(quick_ms, t.front());
+                float ms = t.front();
+                if (ms <= 1.5f * quick_ms) time_alt(a, 1, t);
+                if (rc != XL_OK) break;
+                ms = std::min(ms, t.front());
+                quick.push_back({ms, (int)a});
+                quick_ms = std::min(quick_ms, ms);
             }
             // ... then the six fastest again, ranked by the median of `reps` launches (ties: lower index)
             int best = 0;

@@ -93,6 +93,20 @@ def test_planner_and_c_abi_under_address_and_undefined_behaviour_sanitizers():
     assert " 0 failures" in r.stdout.splitlines()[-1]
 
 
+def test_a_stalled_launch_does_not_cost_a_candidate_its_place():
+    if not os.path.exists(CLANG):
+        pytest.skip("no clang++ with sanitizer runtimes in this image")
+    os.makedirs(OUT, exist_ok=True)
+    exe = os.path.join(OUT, "tuner_stalls")
+    csrc = os.path.join(ROOT, "paper_2007_06000_amd", "csrc")
+    cmd = [CLANG, "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+           "-I" + csrc, "-Wno-unused-value", *SAN, os.path.join(csrc, "plan.cpp"), os.path.join(csrc, "api.cpp"),
+           os.path.join(HERE, "tuner_stalls.cpp"), "-o", exe]
+    subprocess.run(cmd, check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, env=ENV, timeout=120)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
 def test_oracle_loops_under_address_and_undefined_behaviour_sanitizers():
     os.makedirs(OUT, exist_ok=True)
     exe = os.path.join(OUT, "oracle_asan")
