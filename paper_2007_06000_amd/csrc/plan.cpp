@@ -182,22 +182,25 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
             const int nrt = ceil_div(s.cout, mf2), nkg = ceil_div(s.cin, kc_of(mf2, v.pr));
             const int per = std::min(nrt, ceil_div(nrt, c.csplit));
             const double wave2 = (double)NRT2 * NPT2 * nkg * s.k * s.k * kstep_clk(mf2, v.pr);
-            for (int rp = 0; rp < per; rp += wg_rt2)
-                for (int pp = 0; pp < npt2; pp += wg_pt2) {
-                    double s2[4] = {0, 0, 0, 0};
-                    for (int w = 0; w < nw; ++w) {
-                        const int r0 = rp + (w % c.waves_r2) * NRT2, p0 = pp + (w / c.waves_r2) * NPT2;
-                        if (r0 < per && p0 < npt2) s2[w % 4] += wave2;
-                    }
-                    t2 += *std::max_element(s2, s2 + 4) + 2500.0;       // + epilogue / prologue of the pass
-                    ++passes;
+            // the passes are alike except for the last of the row tiles and the last of the pixel tiles
+            const int rows_last = (per - 1) % wg_rt2 + 1, px_last = (npt2 - 1) % wg_pt2 + 1;       // tiles of those
+            const int row_passes = ceil_div(per, wg_rt2), px_passes = ceil_div(npt2, wg_pt2);
+            for (int lr = 0; lr < 2; ++lr)
+                for (int lp = 0; lp < 2; ++lp) {
+                    const int n = (lr ? 1 : row_passes - 1) * (lp ? 1 : px_passes - 1);
+                    if (n == 0) continue;
+                    const int rows = lr ? rows_last : wg_rt2, px = lp ? px_last : wg_pt2;
+                    int active[4] = {0, 0, 0, 0};
+                    for (int w = 0; w < nw; ++w)
+                        if (w % c.waves_r2 * NRT2 < rows && w / c.waves_r2 * NPT2 < px) ++active[w % 4];
+                    double t = *std::max_element(active, active + 4) * wave2 + 2500.0;       // + epilogue / prologue of the pass
                     if (b.kind == KIND_FUSED2P)     // pooling of the pass from LDS: two barriers, one float4 window per item
-                        t2 += 700.0 + (double)std::min(wg_rt2, per - rp) * mf2 / 4 * c.pth * c.ptw * b.pool_k * b.pool_k * 8.0 /
-                                          c.threads * 4;
-                    if (!v.pr) barriers += ceil_div(nkg, c.chunk_kg2[ci]);      // (split operands: no filter chunks)
-                    flops2 += 2LL * std::min(wg_rt2, per - rp) * mf2 * std::min(wg_pt2, npt2 - pp) * mf2 * nkg *
-                              kc_of(mf2, v.pr) * s.k * s.k;
+                        t += 700.0 + (double)rows * mf2 / 4 * c.pth * c.ptw * b.pool_k * b.pool_k * 8.0 / c.threads * 4;
+                    t2 += n * t;
                 }
+            passes += row_passes * px_passes;
+            if (!v.pr) barriers += row_passes * px_passes * ceil_div(nkg, c.chunk_kg2[ci]);      // (split operands: no filter chunks)
+            flops2 += 2LL * per * mf2 * npt2 * mf2 * nkg * kc_of(mf2, v.pr) * s.k * s.k;
         }
     } else if (b.kind == KIND_POOL) {
         t2 = (double)ceil_div(b.c1.cout, 4) * c.th * c.tw * b.pool_k * b.pool_k * 8.0 / c.threads * 4;
@@ -240,9 +243,18 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     c.flops_exec = tiles * (b.kind == KIND_SINGLE ? 1 : c.csplit) * s1 * b.n1 + tiles * c.csplit * flops2;
 }
 
+// A list of at most four numbers.
+struct Few {
+    int n = 0, v[4];
+    void add(int x) { v[n++] = x; }
+    int back() const { return v[n - 1]; }
+    const int *begin() const { return v; }
+    const int *end() const { return v + n; }
+};
+
 static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &lds_rejected, int pr)
 {
-    Choice best;
+    bool any_ok = false;
     std::map<std::tuple<int, int, int, int>, Choice> per_key;     // best per (variant, threads, tile)
     const std::vector<int> ths = tile_candidates(b.Ho), tws = tile_candidates(b.Wo);
     std::vector<std::pair<int, int>> tiles;
@@ -310,7 +322,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                         c.cost = std::max(t_alu, t_mem) + 0.15 * std::min(t_alu, t_mem);
                         c.flops_exec = (long long)(nwg * threads * rows16 * taps * 8.0);
                         c.ok = true;
-                        if (!best.ok || c.cost < best.cost) best = c;
+                        any_ok = true;
                         per_key[std::make_tuple(v.id, threads, th, tw)] = c;
                         continue;
                     }
@@ -342,7 +354,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     c.cost = std::max(t_alu, t_mem) + 0.15 * std::min(t_alu, t_mem);
                     c.flops_exec = (long long)(nwg * threads * rows16 * taps * 2.0);
                     c.ok = true;
-                    if (!best.ok || c.cost < best.cost) best = c;
+                    any_ok = true;
                     per_key[std::make_tuple(v.id, threads, th, tw)] = c;
                 }
             }
@@ -376,7 +388,9 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                 if (!dw && b.kind != KIND_SINGLE && wg_rt < nrt1) continue;     // stage 1 must produce every channel
                 if (!dw && wr > 1 && (wr / 2) * v.nrt1 >= nrt1) continue;       // more row waves than row tiles
                 const int px_cap = dw ? (1 << 30) : (nw / wr) * v.npt1 * mf1;
-                for (auto [th, tw] : tiles)
+                for (auto [th, tw] : tiles) {
+                Choice *kept = nullptr;         // the best of this variant, workgroup size and tile so far
+                int first_chunk = 0;
                 for (double want_clk : {16000.0, 8000.0}) {     // longer chunks = fewer barriers, if LDS allows
                     Choice c;
                     c.v = v;
@@ -424,6 +438,9 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     if (px > 0)     // planar chunk: kc x px x 16 quads per K step, at most PLANAR_SLOTS wave loads per wave
                         c.chunk_kg = std::min(c.chunk_kg, PLANAR_SLOTS * nw * 64 / (kc_of(mf1) * px * 16));
                     if (c.chunk_kg < 1) continue;
+                    // (the second length is the first one again, and stage 2 has no chunks either)
+                    if ((!two || v.pr) && c.chunk_kg == first_chunk) continue;
+                    first_chunk = c.chunk_kg;
                     if (stream && c.chunk_kg < nkg1) continue;        // the stream kernel keeps the whole reduction in one chunk
                     c.w_off1 = c.chunk_kg * x_per_kg * 4 + 16;        // + slack for a left-edge unit running past the last row
                     if (px > 0) c.w_off1 = c.chunk_kg * kc_of(mf1) * px * 64;
@@ -441,27 +458,27 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                         c.mid_floats = mid_size(ceil_div(b.Cin, 16) * 16);      // whole K steps of the pointwise stage
                     }
 
-                    std::vector<int> splits, wr2s, vws;
+                    Few splits, wr2s, vws;
                     if (two) {
                         if (pl.opts.force_cout_split > 0) {
-                            splits.push_back(pl.opts.force_cout_split);
+                            splits.add(pl.opts.force_cout_split);
                         } else {
                             int min_nrt = 1 << 30;
                             for (int i = 0; i < b.n2; ++i) min_nrt = std::min(min_nrt, ceil_div(b.c2[i].cout, v.mf2));
-                            for (int s = 1; s <= 8 && s <= min_nrt; s *= 2) splits.push_back(s);
+                            for (int s = 1; s <= 8 && s <= min_nrt; s *= 2) splits.add(s);
                         }
-                        for (int w2 = 1; w2 <= nw; w2 *= 2) wr2s.push_back(w2);
+                        for (int w2 = 1; w2 <= nw; w2 *= 2) wr2s.add(w2);
                         const int tw2 = c.tw;
-                        vws.push_back(tw2);
+                        vws.add(tw2);
                         if (!pool2) {       // (the pooled form writes its tile to LDS pixel by pixel: no padded rows)
-                            if (tw2 % 16 && (tw2 + 15) / 16 * 16 - tw2 <= 4) vws.push_back((tw2 + 15) / 16 * 16);
+                            if (tw2 % 16 && (tw2 + 15) / 16 * 16 - tw2 <= 4) vws.add((tw2 + 15) / 16 * 16);
                             // rows of a multiple of 4 pixels let the epilogue move 4 pixels per access
-                            if (tw2 % 4 && (tw2 + 3) / 4 * 4 != vws.back()) vws.push_back((tw2 + 3) / 4 * 4);
+                            if (tw2 % 4 && (tw2 + 3) / 4 * 4 != vws.back()) vws.add((tw2 + 3) / 4 * 4);
                         }
                     } else {
-                        splits.push_back(b.kind == KIND_SINGLE ? ceil_div(nrt1, wg_rt) : 1);
-                        wr2s.push_back(1);
-                        vws.push_back(c.tw);
+                        splits.add(b.kind == KIND_SINGLE ? ceil_div(nrt1, wg_rt) : 1);
+                        wr2s.add(1);
+                        vws.add(c.tw);
                     }
                     for (int cs : splits)
                         for (int w2 : wr2s)
@@ -527,16 +544,16 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                                                               reg_waves / nw}));
                                 evaluate(b, pl, c);
                                 c.ok = true;
-                                if (!best.ok || c.cost < best.cost) best = c;
-                                auto key = std::make_tuple(v.id, threads, th, tw);
-                                auto it = per_key.find(key);
-                                if (it == per_key.end() || c.cost < it->second.cost) per_key[key] = c;
+                                any_ok = true;
+                                if (!kept) kept = &per_key[std::make_tuple(v.id, threads, th, tw)];
+                                if (!kept->ok || c.cost < kept->cost) *kept = c;
                             }
+                }
                 }
             }
         }
     }
-    if (best.ok && b.kind == KIND_DW && pr == 0 && b.n2 == 1 && b.c2[0].k == 1 && b.c2[0].stride == 1 && b.c1.stride == 1 &&
+    if (any_ok && b.kind == KIND_DW && pr == 0 && b.n2 == 1 && b.c2[0].k == 1 && b.c2[0].stride == 1 && b.c1.stride == 1 &&
         !pl.opts.force_tile_h && !pl.opts.force_threads && !pl.opts.force_cout_split && !pl.opts.paper_tuner_only)
         for (const Variant &v : variants()) {
             // depthwise -> pointwise wave by wave (whether the block can be planned is decided by the kernels above)
@@ -568,7 +585,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             c.ok = true;
             per_key[std::make_tuple(v.id, c.threads, c.th, c.tw)] = c;
         }
-    lds_rejected = !best.ok && any_lds_reject;
+    lds_rejected = !any_ok && any_lds_reject;
     // ranked list: the model's best first, then the best of other (variant, threads, tile) combinations
     std::vector<Choice> ranked;
     for (auto &kv : per_key) ranked.push_back(kv.second);
