@@ -1430,14 +1430,15 @@ __global__ void pack_filter_kernel(const float *__restrict__ w, const float *__r
 {
     const int taps = k * k;
     const long long total = (long long)nkg * taps * nrt * 64;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int lane = (int)(idx & 63);
-    long long r = idx >> 6;
-    const int rt = (int)(r % nrt);
-    r /= nrt;
+    const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= total) return;
+    const int lane = (int)(id & 63);
+    long long r = id >> 6;              // (taps are neighbours in w: the waves of a workgroup take them one after the other)
     const int t = (int)(r % taps);
-    const int kg = (int)(r / taps);
+    r /= taps;
+    const int rt = (int)(r % nrt);
+    const int kg = (int)(r / nrt);
+    const long long row = ((long long)kg * taps + t) * nrt + rt;
     const int o = rt * mf + lane % mf;
     const int sub = lane / mf;
     const int kc = mf == 32 ? 8 : 16;
@@ -1447,7 +1448,7 @@ __global__ void pack_filter_kernel(const float *__restrict__ w, const float *__r
         const int ci = pairs ? 2 * j + sub : kg * kc + sub * 4 + j;
         v[j] = (o < cout && ci < cin) ? w[((size_t)o * cin + ci) * taps + t] * (scale ? scale[o] : 1.f) : 0.f;
     }
-    wp[idx] = v;
+    wp[row * 64 + lane] = v;
 }
 
 // Split-bf16 form (32-wide tiles): [K step][tap][row tile][part][lane] of 8 bf16;
@@ -1458,14 +1459,15 @@ __global__ void pack_filter_split_kernel(const float *__restrict__ w, const floa
 {
     const int taps = k * k;
     const long long total = (long long)nkg * taps * nrt * 64;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int lane = (int)(idx & 63);
-    long long r = idx >> 6;
-    const int rt = (int)(r % nrt);
-    r /= nrt;
+    const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= total) return;
+    const int lane = (int)(id & 63);
+    long long r = id >> 6;              // (taps are neighbours in w: the waves of a workgroup take them one after the other)
     const int t = (int)(r % taps);
-    const int kg = (int)(r / taps);
+    r /= taps;
+    const int rt = (int)(r % nrt);
+    const int kg = (int)(r / nrt);
+    const long long row = ((long long)kg * taps + t) * nrt + rt;
     const int o = rt * 32 + lane % 32;
     const int sub = lane / 32;
     unsigned out[PR + 1][4];
@@ -1486,7 +1488,7 @@ __global__ void pack_filter_split_kernel(const float *__restrict__ w, const floa
 #pragma unroll
         for (int i = 0; i <= PR; ++i) out[i][e] = p[i];
     }
-    uint4 *dst = wp + (idx >> 6) * (64 * (PR + 1)) + lane;
+    uint4 *dst = wp + row * (64 * (PR + 1)) + lane;
 #pragma unroll
     for (int i = 0; i <= PR; ++i) dst[i * 64] = uint4{out[i][0], out[i][1], out[i][2], out[i][3]};
 }
@@ -1494,8 +1496,11 @@ __global__ void pack_filter_split_kernel(const float *__restrict__ w, const floa
 hipError_t launch_pack_filter(const float *w, const float *scale, f32x4 *wp, int cout, int cin, int k, int mf, int nkg,
                               int nrt, hipStream_t s, int pairs, int pr)
 {
+    // Workgroups of 16 waves hold most of the taps of a K step and row tile, so that a line of w is fetched by one of the
+    // chip's L2 caches (1024 -> 1024 channels, 3x3, its three forms: 152 -> 104 us); smaller ones where those would not
+    // fill the chip.
     const long long total = (long long)nkg * k * k * nrt * 64;
-    const int threads = 256;
+    const int threads = total >= 256 * 1024 ? 1024 : 256;
     const int grid = (int)((total + threads - 1) / threads);
     if (pr)
         return launch(pr == 2 ? pack_filter_split_kernel<2> : pack_filter_split_kernel<1>, dim3(grid), dim3(threads), 0, s,

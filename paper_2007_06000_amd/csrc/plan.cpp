@@ -1352,6 +1352,11 @@ struct Builder {
             p.offset = off;
             off += packed_affine_offset(p.bytes);
             p.aff_offset = off;
+            for (const PackedFilter *q = pl.packed.data(); q != &p && p.aff_bytes; ++q)
+                if (p.mf > 0 && q->layer == p.layer && q->mf == p.mf) {
+                    p.aff_offset = q->aff_offset;
+                    p.aff_bytes = 0;
+                }
             off = align_up(off + p.aff_bytes, 256);
         }
         for (size_t t = 0; t < pl.shapes.size(); ++t) {

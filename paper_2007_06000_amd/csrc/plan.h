@@ -17,13 +17,13 @@ struct PackedFilter {
     int layer;
     int mf;             // 32 or 16; 0 = depthwise tables ([channel group][tap], [channel group][scale, shift]);
                         // -1 = thin first layer ([Cout rounded up to 16][Cin*K*K] floats, as many shifts)
-    int pr = 0;         // 1: split-bf16 form ([K step][tap][row tile][hi, lo][lane] of 8 bf16)
+    int pr = 0;         // 1, 2: form in two or three bf16 parts ([K step][tap][row tile][part][lane] of 8 bf16)
     bool pairs = false; // channels packed two per channel slot (c -> lane half c % 2, slot c / 2), one K step
     int nkg, nrt;
     size_t offset;      // bytes into the workspace
     size_t bytes;
     size_t aff_offset;  // scale / shift table in accumulator order
-    size_t aff_bytes;
+    size_t aff_bytes;   // 0: the table of an earlier form of the layer (it depends on mf alone)
 };
 
 // Where a tensor lives: itself, or a channel slice of a concatenated tensor.
