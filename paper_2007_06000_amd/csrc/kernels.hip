@@ -1655,14 +1655,15 @@ hipError_t launch_add(const float *a, const float *b, float *y, long long count,
 template <int NU, int NP>
 __global__ void __launch_bounds__(256) gap_kernel(const float *__restrict__ x, float *__restrict__ y, int NC, int HW)
 {
-    const int plane = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * (long long)blockDim.x + threadIdx.x) >> 6)) * NP;
+    // (unsigned: the planes of the last workgroup may lie past 2^31)
+    const unsigned plane = (unsigned)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * (long long)blockDim.x + threadIdx.x) >> 6)) * NP;
     const int lane = threadIdx.x & 63;
-    if (plane >= NC) return;
+    if (plane >= (unsigned)NC) return;
     const float *xc[NP];
     float s[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        xc[p] = x + (size_t)min(plane + p, NC - 1) * HW;
+        xc[p] = x + (size_t)min(plane + p, (unsigned)NC - 1u) * HW;
         s[p] = 0.f;
     }
     for (int i0 = 0; i0 < HW; i0 += NU * 64) {
@@ -1683,7 +1684,7 @@ __global__ void __launch_bounds__(256) gap_kernel(const float *__restrict__ x, f
     if (lane == 0) {
 #pragma unroll
         for (int p = 0; p < NP; ++p)
-            if (plane + p < NC) y[plane + p] = s[p] / (float)HW;
+            if (plane + p < (unsigned)NC) y[plane + p] = s[p] / (float)HW;
     }
 }
 
@@ -1692,7 +1693,7 @@ hipError_t launch_gap(const float *x, float *y, int NC, int HW, hipStream_t s)
     if (NC == 0) return hipSuccess;
     const int threads = 256;
     const int wpb = threads / 64;
-    auto go = [&](auto kernel, int np) { return launch(kernel, dim3((NC + wpb * np - 1) / (wpb * np)), dim3(threads), 0, s, x, y, NC, HW); };
+    auto go = [&](auto kernel, int np) { return launch(kernel, dim3(((long long)NC + wpb * np - 1) / (wpb * np)), dim3(threads), 0, s, x, y, NC, HW); };
     // Two planes per wave once one each would fill the chip's wave slots (13 x 13: 2.6 and 2.6 us at 8000 planes, 3.85 and
     // 3.35 at 16000; 2.42 and 2.45 at 4000).
     if (NC < 8192)
