@@ -88,6 +88,17 @@ def test_depthwise_kernels_without_lds_are_offered_for_pointwise_layers_of_strid
         assert bool(ids & set(range(161, 169))) == (s2 == 1), ids
 
 
+def test_every_kernel_on_three_parts_is_a_candidate_in_the_tests_of_its_special_values():
+    from test_gpu_split_operands import OPTIONS, WORKLOADS
+    source = open(os.path.join(ROOT, "paper_2007_06000_amd", "csrc", "xl_internal.h")).read()
+    listed = {400 + int(m) for m in re.findall(r"X\((\d+), KIND", source[source.index("#define XL_SPLIT_LIST_A"):])}
+    seen = set()
+    for wl in WORKLOADS:
+        p = B.Plan(wl, **OPTIONS.get(wl.name, {}))
+        seen |= {p.candidate_info(True, 0, c)["variant"] for c in range(p.num_candidates(True, 0))}
+    assert len(listed) > 50 and listed <= seen, listed - seen
+
+
 def test_two_producer_merge_block_plans_as_one_launch():
     """Table 1, c.1: {1x1 64->256, 1x1 64->256} -> add -> 1x1 256->64 on [64,56,56]."""
     p = B.Plan(W.merge_two_producers(1))

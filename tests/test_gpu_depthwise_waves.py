@@ -17,6 +17,8 @@ IDS = range(161, 169)
     (W.depthwise_pointwise(24, 16, 50, 50, 16, p1=0, relu1=False, bn2=True), {164, 165}),
     (W.depthwise_pointwise(300, 3, 17, 1, 5, bn1=True), {161, 162, 164, 165}),
     (W.depthwise_pointwise(64, 16, 66, 67, 30, s1=2), set()),
+    (W.depthwise_pointwise(24, 16, 66, 67, 64), {161, 162, 165, 167, 168}),
+    (W.depthwise_pointwise(24, 13, 33, 47, 70), {161, 162, 165, 167, 168}),
 ], ids=lambda a: getattr(a, "name", ""))
 def test_against_the_oracle(wl, expected):
     from paper_2007_06000_amd.session import Session

@@ -20,10 +20,40 @@ WORKLOADS = [
 ]
 
 
+def named(wl, name):
+    wl.name = name
+    return wl
+
+
+def pointwise_residual(k2):
+    """Merge block whose first layer is 1x1."""
+    b = W._Builder(f"residual_1_{k2}", 2, 24, 15, 14)
+    t = b.conv(0, 40, 1, bn=True, relu=True, name="conv1")
+    t = b.conv(t, 24, k2, pad=k2 // 2, bn=True, relu=False, name="conv2")
+    b.add(t, 0, relu=True, name="add")
+    b.group("merge", 0)
+    return b.done(len(b.shapes) - 1, "relu_normal", 31)
+
+
+# ... with these every kernel on three parts is a candidate of some block (test_abi_and_planner.py counts them)
+WORKLOADS += [
+    W.single_conv(2, 17, 13, 7, 52, 3, 1, 1), W.single_conv(1, 26, 6, 15, 20, 5, 1, 2),
+    W.conv_pool_generic(1, 11, 10, 10, 20, 1, 0, 1, 3, 2, 1), W.depthwise_pointwise(1, 22, 11, 11, 16, k2=3, p2=1),
+    W.straight_generic(2, 14, 12, 9, 12, 3, 1, 1, 32, 3, 1, 1), W.straight_generic(1, 12, 9, 18, 10, 1, 0, 1, 25, 3, 1, 1),
+    W.straight_generic(1, 48, 34, 27, 8, 1, 0, 1, 23, 5, 2, 1), W.straight_generic(1, 9, 15, 11, 9, 3, 1, 1, 22, 5, 2, 1),
+    W.straight_generic(1, 35, 8, 41, 13, 3, 1, 1, 80, 1, 0, 1), pointwise_residual(3), pointwise_residual(1),
+    named(W.config(4, n=1, c=21, hw=9), "residual_21x9"),
+    named(W.split_fire_pool(n=1, cin=23, hw=10, s=16, e=48), "firepool_23x10"),
+    named(W.config(3, n=1, cin=419, hw=10, s=48, e=128), "fire_419x10"), named(W.config(3, n=2, cin=336, hw=18, s=48, e=48), "fire_336x18"),
+    named(W.config(3, n=1, cin=32, hw=10, s=16, e=48), "fire_32x10"),
+]
+OPTIONS = {"fire_32x10": {"force_tile_h": 10, "force_tile_w": 8}}
+
+
 def run_candidates(wl, x, params):
     """{variant: output} of the fused launch, one candidate per variant, and the fp32 variants' ids first."""
     from paper_2007_06000_amd.session import Session
-    s = Session(wl, x, params)
+    s = Session(wl, x, params, **OPTIONS.get(wl.name, {}))
     out = {}
     for c in range(s.plan.num_candidates(True, 0)):
         v = s.plan.candidate_info(True, 0, c)["variant"]
@@ -51,6 +81,11 @@ def test_error_is_no_larger_than_with_fp32_operations(wl):
     worst = max(err(y) for y in fp32.values())
     for v, y in split.items():
         assert err(y) <= max(worst, 2.0 ** -23), (v, err(y), worst)
+    # Not only than the worst of them.  The fp32 kernels differ in the order of their sums alone; over 200 or more outputs the
+    # norm varies by about 1 / sqrt(200) = 7 % between orders, so that the best is the same error up to three times that.
+    best = min(err(y) for y in fp32.values())
+    for v, y in split.items():
+        assert err(y) <= max(1.25 * best, 2.0 ** -23), (v, err(y), best)
 
 
 @pytest.mark.parametrize("special", [np.inf, -np.inf, np.nan, 3.4e38])
@@ -71,6 +106,22 @@ def test_values_without_bf16_parts(wl, special):
         assert (d <= 1e-4 + 1e-4 * np.abs(b))[~reached].all(), (v, d[~reached].max())
         # sums that hold 3.4e38 * w: up to a few hundred roundings of 2^-24 of that magnitude
         assert (d[reached] <= 2.0 ** -16 * 3.4e38).all(), (v, d[reached].max())
+
+
+@pytest.mark.parametrize("special", [np.inf, 3.4e38])
+@pytest.mark.parametrize("wl", WORKLOADS, ids=lambda w: w.name)
+def test_a_filter_value_without_bf16_parts_in_each_layer(wl, special):
+    for layer in [i for i, ly in enumerate(wl.layers) if ly.op == "conv"]:
+        x, params = W.make_tensors(wl)
+        w = params[layer]["w"]
+        w[3, min(5, w.shape[1] - 1), w.shape[2] // 2, w.shape[3] // 2] = special
+        fp32, split = run_candidates(wl, x, params)
+        ref = next(iter(fp32.values()))
+        # what it does not reach is untouched
+        fin = np.isfinite(ref) & (np.abs(ref) < 1e20)
+        for v, y in split.items():
+            assert (np.isfinite(y) == np.isfinite(ref)).all() and (np.isnan(y) == np.isnan(ref)).all(), (layer, v)
+            assert (np.abs(y[fin] - ref[fin]) <= 1e-4 + 1e-4 * np.abs(ref[fin])).all(), (layer, v)
 
 
 @pytest.mark.parametrize("special", [np.inf, 3.4e38])
@@ -120,7 +171,7 @@ def test_passes_repeat_bit_for_bit_around_an_infinite_intermediate(wl):
     x[0, 0, x.shape[2] // 2, x.shape[3] // 2] = 3e38
     k = wl.layers[0].k // 2
     params[0]["w"][0, 0, k, k] = 4.0
-    s = Session(wl, x, params)
+    s = Session(wl, x, params, **OPTIONS.get(wl.name, {}))
     seen = set()
     for c in range(s.plan.num_candidates(True, 0)):
         v = s.plan.candidate_info(True, 0, c)["variant"]
