@@ -4,10 +4,12 @@
 One "step" is one pass of the whole hot path over one batch of the workload:
 every fusion block of the network executed once by `xl_run(fused=1)`, inputs
 already resident in HBM.  The same step with `fused=0` (one kernel per layer,
-intermediates through HBM) is timed beside it for the speedup.  Prints ONE JSON
-line.  Inputs are seeded synthetic tensors (xl_workloads.py).
+intermediates through HBM) is timed beside it for the speedup.  Prints ONE short JSON
+line on stdout, and the whole record with its tables on stderr or to --rows FILE.
+Inputs are seeded synthetic tensors (xl_workloads.py).
 
-What the line holds besides the contract fields:
+What the whole record holds besides the contract fields (the line: the same without the rows of `per_launch`, and
+of `blocks` the few columns of BLOCK_COLUMNS):
   per_launch   one row per kernel launch of the fused step of the headline workload, in launch order:
                layers, adopted launch configuration (kernel variant, tile, workgroup size, split),
                average duration from events around that launch (xl_profile), FLOPs, algorithmic bytes,
@@ -277,6 +279,7 @@ def main():
                     help="after tuning, write the adopted candidate of every launch of the headline workload to FILE")
     ap.add_argument("--load-candidates", metavar="FILE",
                     help="adopt the candidates listed in FILE instead of tuning (for profiler runs: no candidate launches)")
+    ap.add_argument("--rows", metavar="FILE", help="write the whole record, with its tables, to FILE instead of stderr")
     ap.add_argument("--fused-only", action="store_true", help="time the fused step only (for profiler runs)")
     args = ap.parse_args()
     global TUNE
@@ -414,7 +417,39 @@ def main():
             out["bf16x3"] = {"error": repr(e)}
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(args.workload, W, np)
-    print(json.dumps(out))
+    if args.rows:
+        with open(args.rows, "w") as f:
+            json.dump(out, f)
+    else:
+        print(json.dumps(out), file=sys.stderr)
+    print(json.dumps(short_line(out)))
+
+
+BLOCK_COLUMNS = ("batch", "ms_fused", "speedup_vs_unfused", "frac")
+
+
+def short_line(out):
+    """The record without its tables, short enough for whoever keeps only the end of the output."""
+    def brief(v):
+        return float(f"{v:.5g}") if isinstance(v, float) else v
+
+    def columns(rows):
+        return {r["workload"].split(":")[0]: r["error"][:60] if "error" in r else [brief(r[k]) for k in BLOCK_COLUMNS] for r in rows}
+    line = {k: brief(v) for k, v in out.items() if k not in ("per_launch", "per_launch_note", "target_60pct", "peaks", "paper_context")}
+    for key in ("value", "ms_per_step"):
+        line[key] = out[key]
+    if "peaks" in out:
+        line["measured_peaks"] = {k: brief(v) for k, v in out["peaks"]["measured"].items()}
+    line["roofline"] = {k: brief(v) for k, v in out["roofline"].items()}
+    if "blocks" in out:
+        line["blocks_columns"] = BLOCK_COLUMNS
+        line["blocks"] = columns(out["blocks"])
+    if "bf16x3" in out:
+        b3 = {k: brief(v) for k, v in out["bf16x3"].items() if k not in ("arithmetic", "per_launch", "roofline", "blocks")}
+        if "blocks" in out["bf16x3"]:
+            b3["blocks"] = columns(out["bf16x3"]["blocks"])
+        line["bf16x3"] = b3
+    return line
 
 
 def traffic_probe(cfg, torch, np, W, Session, candidates):
