@@ -1,5 +1,6 @@
 // HIP kernels of libxl for gfx950 (CDNA4): tiled implicit-GEMM convolution on the
-// fp32 matrix cores, with the block's intermediate feature map held in LDS.
+// matrix cores -- fp32 operations, or bf16 ones on operands taken apart into bf16
+// parts (split_conv.h) -- with the block's intermediate feature map held in LDS.
 //
 // Structure of one workgroup (paper section 2.2, Fig. 3b; section 3.2):
 //   S1  stage a halo-extended input tile through LDS in channel chunks
@@ -19,7 +20,9 @@
 // pixels of the tile, flattened row-major (B operand = one float4 LDS read per
 // lane giving 4 input channels of one pixel and tap).  Accumulator registers
 // of a lane therefore hold 4 consecutive output channels of one pixel, which
-// is exactly one float4 of the LDS tile layout.
+// is exactly one float4 of the LDS tile layout.  (On operands in
+// parts a lane reads 16 bytes per part, 8 input channels, the filter comes from
+// memory without LDS, and the tile is kept as planes of parts.)
 #include <float.h>
 #include <limits.h>
 

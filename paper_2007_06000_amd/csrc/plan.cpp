@@ -231,7 +231,6 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
                                                  : out_ch * c.th * lines(c.tw) * (b.shortcut ? 2.0 : 1.0);
     const double t_mem = (double)b.alg_bytes / 8.0e12 + (in_wg + out_wg) * c.tiles_x * c.tiles_y * b.N / 24.0e12;
     c.cost = std::max(t_mfma, t_mem) + 0.15 * std::min(t_mfma, t_mem);
-    // Taking the depthwise results apart is not in t1: without this the choice was 11.1, 8.2 and 11.6 us against 8.7, 6.7 and
     // Taking the depthwise results apart is not in t1: without this the choice was a split kernel of 11.1 and 8.2 us (30 -> 63
     // channels of 104 x 46, batch 4; 30 -> 35 of 109 x 38, batch 3) where the fp32 kernels take 8.7 to 10.1 and 6.7 to 7.6.
     if (v.pr && b.kind == KIND_DW) c.cost *= 1.2;

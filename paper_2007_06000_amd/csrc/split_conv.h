@@ -29,8 +29,8 @@
 // What bounds it: power.  A K loop of this header alone keeps the matrix cores 86 to 90 % busy (36 to 37 cycles per
 // operation and SIMD where 32 are nominal), but with real operands the clock falls to 1.65 - 1.75 GHz: 1.55 PFLOP/s in
 // bf16, 258 TFLOP/s of fp32-exact products against 155 of the fp32 operations.  Time per pass, fp32 kernels -> PR = 2: the
-// residual block of 64 channels at 56 x 56, batch 32: 158.6 -> 94.4 us; two 1x1 producers 64 -> 256 and their consumer,
-// batch 32: 179 -> 126 us; 1x1 into 5x5, 28 x 28, batch 32: 17.6 -> 13.8 us; the batch-64 network: 688 -> 563 us.
+// residual block of 64 channels at 56 x 56, batch 32: 158.6 -> 94 to 99 us from card to card; two 1x1 producers 64 -> 256 and
+// their consumer, batch 32: 179 -> 124 us; 1x1 into 5x5, 28 x 28, batch 32: 17.6 -> 13.5 us; the batch-64 network: 688 -> 552 us.
 #pragma once
 
 namespace xl {
