@@ -1008,10 +1008,11 @@ block_kernel(const BlockParams P)
                                         int ln = lane;      // (offsets are worked out again: no registers for them in the K loop)
                                         asm volatile("" : "+v"(ln));
                                         init_acc<MF2, NRT2, NPT2>(acc2, c, r0);
-                                        conv_whole<KS2, NRT2, NPT2>(acc2, c, r0, [&](int p, int kg, int t, int e) {
-                                            const int at = kg * 6 * P.mid_gstride + pixel_offset(p, ln) + (t / KS2 * P.mw + t % KS2) * 4;
-                                            const unsigned short *v = (const unsigned short *)(mid + at) + e;
-                                            return whole_value(v[0], v[2 * P.mid_gstride], v[4 * P.mid_gstride]);
+                                        conv_whole<KS2, NRT2, NPT2>(acc2, c, r0, [&](int p, int kg, int t, float (&x)[8]) {
+                                            const float *at = mid + kg * 6 * P.mid_gstride + pixel_offset(p, ln) + (t / KS2 * P.mw + t % KS2) * 4;
+                                            const uint4 w[3] = {*(const uint4 *)at, *(const uint4 *)(at + P.mid_gstride), *(const uint4 *)(at + 2 * P.mid_gstride)};
+#pragma unroll
+                                            for (int e = 0; e < 8; ++e) x[e] = whole_value(w, e);
                                         });
                                     }
                                 }
