@@ -1,5 +1,5 @@
 """Depthwise -> pointwise blocks wave by wave (variants 161 to 168) against the oracle, at partial tiles, partial channel
-groups, one-pixel-wide images, no padding and several cout tiles."""
+groups, one-pixel-wide images, paddings 0 to 3 and several cout tiles."""
 import numpy as np
 import pytest
 
@@ -17,6 +17,7 @@ IDS = range(161, 169)
     (W.depthwise_pointwise(24, 16, 50, 50, 16, p1=0, relu1=False, bn2=True), {164, 165}),
     (W.depthwise_pointwise(300, 3, 17, 1, 5, bn1=True), {161, 162, 164, 165}),
     (W.depthwise_pointwise(64, 16, 66, 67, 30, s1=2), set()),
+    (W.depthwise_pointwise(64, 13, 33, 30, 24, p1=2), {161, 162, 164, 165}), (W.depthwise_pointwise(64, 6, 35, 33, 40, p1=3), {161, 162, 165, 167}),
     (W.depthwise_pointwise(24, 16, 66, 67, 64), {161, 162, 165, 167, 168}),
     (W.depthwise_pointwise(24, 13, 33, 47, 70), {161, 162, 165, 167, 168}),
 ], ids=lambda a: getattr(a, "name", ""))

@@ -46,6 +46,13 @@ WORKLOADS += [
     named(W.split_fire_pool(n=1, cin=23, hw=10, s=16, e=48), "firepool_23x10"),
     named(W.config(3, n=1, cin=419, hw=10, s=48, e=128), "fire_419x10"), named(W.config(3, n=2, cin=336, hw=18, s=48, e=48), "fire_336x18"),
     named(W.config(3, n=1, cin=32, hw=10, s=16, e=48), "fire_32x10"),
+    # strides in either layer, and paddings beyond half of the filter
+    W.single_conv(2, 40, 19, 23, 70, 3, 2, 1), W.single_conv(1, 20, 17, 14, 33, 5, 3, 4),
+    named(W.straight_generic(2, 24, 17, 19, 40, 3, 1, 2, 48, 3, 1, 1), "straight_s2_s1"),
+    named(W.straight_generic(2, 24, 19, 21, 40, 3, 2, 1, 48, 3, 0, 2), "straight_s1_s2"),
+    named(W.straight_generic(2, 40, 19, 21, 16, 1, 0, 1, 32, 5, 3, 2), "straight_1x1_5x5_s2"),
+    named(W.conv_pool_generic(1, 24, 29, 23, 40, 3, 1, 2, 2, 2, 0), "convpool_s2"),
+    named(W.depthwise_pointwise(2, 18, 23, 19, 40, s2=2), "dwpw_s2"),
 ]
 OPTIONS = {"fire_32x10": {"force_tile_h": 10, "force_tile_w": 8}}
 
@@ -168,8 +175,11 @@ def test_passes_repeat_bit_for_bit_around_an_infinite_intermediate(wl):
     # one sum of the first layer overflows: what a wave then does must not depend on how far the others are
     from paper_2007_06000_amd.session import Session
     x, params = W.make_tensors(wl)
-    x[0, 0, x.shape[2] // 2, x.shape[3] // 2] = 3e38
-    k = wl.layers[0].k // 2
+    # (the input pixel under the centre tap of an even position of the intermediate, which a strided second layer reads too)
+    first = wl.layers[0]
+    k = first.k // 2
+    y0, x0 = [wl.shapes[first.out][d] // 4 * 2 * first.stride - first.pad + k for d in (2, 3)]
+    x[0, 0, y0, x0] = 3e38
     params[0]["w"][0, 0, k, k] = 4.0
     s = Session(wl, x, params, **OPTIONS.get(wl.name, {}))
     seen = set()
