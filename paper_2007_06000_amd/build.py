@@ -18,11 +18,11 @@ LIB = os.path.join(HERE, "libxl.so")
 # (source, object name, extra defines): kernels.hip is compiled once for the fp32 variants and once for each part of the
 # split-bf16 ones
 SOURCES = [("kernels.hip", "kernels", []),
-           *[("kernels.hip", f"kernels_split_{part}{pr}", [f"-DXL_TU_SPLIT={part}", f"-DXL_TU_PR={pr}"])
-             for part in "ABC" for pr in (1, 2)],
+           *[("kernels.hip", f"kernels_split_{part}{pr}", [f"-DXL_TU_SPLIT={part}", f"-DXL_TU_PR={pr}"] + extra)
+             for part, extra in (("A", []), ("B", []), ("C", []), ("D", ["-DXL_TU_CHAIN"])) for pr in (1, 2)],
            ("plan.cpp", "plan", []), ("api.cpp", "api", []), ("static_run.hip", "static_run", [])]
 HEADERS = [os.path.join(CSRC, "xl_internal.h"), os.path.join(CSRC, "plan.h"), os.path.join(CSRC, "thin_conv.h"),
-           os.path.join(CSRC, "split_conv.h"), os.path.join(CSRC, "dw_conv.h"),
+           os.path.join(CSRC, "split_conv.h"), os.path.join(CSRC, "dw_conv.h"), os.path.join(CSRC, "chain_conv.h"),
            os.path.join(ROOT, "include", "xl.h")]
 
 # packed-fp32 instructions are switched off for all device code

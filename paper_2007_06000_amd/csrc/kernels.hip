@@ -1330,6 +1330,9 @@ __global__ void __launch_bounds__(MAX_THREADS, 4) pool_stream_kernel(const Block
 #include "thin_conv.h"
 #include "dw_conv.h"
 #endif
+#if defined(XL_TU_SPLIT) && defined(XL_TU_CHAIN)
+#include "chain_conv.h"
+#endif
 namespace xl {
 
 // ----------------------------------------------------------------------------
@@ -1350,20 +1353,30 @@ static hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, size_
 // This file is compiled several times, in parallel: once for the fp32 variants and everything else, and once for each
 // part of the split-bf16 variants (XL_TU_SPLIT = the list, XL_TU_PR = parts - 1).
 typedef void (*BlockKernel)(const BlockParams);
-BlockKernel split_kernel_A1(int), split_kernel_B1(int), split_kernel_C1(int);
-BlockKernel split_kernel_A2(int), split_kernel_B2(int), split_kernel_C2(int);
+BlockKernel split_kernel_A1(int), split_kernel_B1(int), split_kernel_C1(int), split_kernel_D1(int);
+BlockKernel split_kernel_A2(int), split_kernel_B2(int), split_kernel_C2(int), split_kernel_D2(int);
 
 #ifdef XL_TU_SPLIT
 #define XL_CAT_(a, b, c) a##b##c
 #define XL_CAT(a, b, c) XL_CAT_(a, b, c)
+template <int KIND, int MF1, int K1, int NRT1, int NPT1, int MF2, int NRT2, int NPT2, int K2A, int K2B, bool SC, int PX1, int PR, int PR1>
+static BlockKernel select_split_kernel()
+{
+#ifdef XL_TU_CHAIN
+    return chain_kernel<PR, NPT1, NRT1, NRT2>;        // producers, K steps of layer 1, row tiles of layer 2
+#else
+    return block_kernel<KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, PR, PR1>;
+#endif
+}
+
 BlockKernel XL_CAT(split_kernel_, XL_TU_SPLIT, XL_TU_PR)(int variant)
 {
     switch (variant - SPLIT_ID0[XL_TU_PR]) {
 #define X(ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, S1)                                     \
     case ID:                                                                                                         \
-        return block_kernel<KIND, MF1, K1, NRT1, NPT1, (MF2 == 0 ? 32 : MF2), (NRT2 == 0 ? 1 : NRT2),                \
-                            (NPT2 == 0 ? 1 : NPT2), (K2A == 0 ? 1 : K2A), K2B, (SC != 0), PX1, XL_TU_PR,             \
-                            (S1 ? XL_TU_PR : 0)>;
+        return select_split_kernel<KIND, MF1, K1, NRT1, NPT1, (MF2 == 0 ? 32 : MF2), (NRT2 == 0 ? 1 : NRT2),         \
+                                   (NPT2 == 0 ? 1 : NPT2), (K2A == 0 ? 1 : K2A), K2B, (SC != 0), PX1, XL_TU_PR,      \
+                                   (S1 ? XL_TU_PR : 0)>();
         XL_CAT(XL_SPLIT_LIST, _, XL_TU_SPLIT)(X)
 #undef X
     }
@@ -1396,7 +1409,7 @@ static BlockKernel kernel_of(int variant)
 #undef X
     }
     if (variant >= SPLIT_ID0[1]) {
-        for (auto part : {split_kernel_A1, split_kernel_B1, split_kernel_C1, split_kernel_A2, split_kernel_B2, split_kernel_C2})
+        for (auto part : {split_kernel_A1, split_kernel_B1, split_kernel_C1, split_kernel_D1, split_kernel_A2, split_kernel_B2, split_kernel_C2, split_kernel_D2})
             if (BlockKernel k = part(variant)) return k;
     }
     return nullptr;

@@ -27,6 +27,7 @@ const std::vector<Variant> &variants()
         XL_SPLIT_LIST_A(X)
         XL_SPLIT_LIST_B(X)
         XL_SPLIT_LIST_C(X)
+        XL_SPLIT_LIST_D(X)
 #undef X
     };
     return v;
@@ -89,6 +90,7 @@ struct BlockSpec {
     int H1 = 0, W1 = 0, Ho = 0, Wo = 0;
     int H2 = 0, W2 = 0;             // KIND_FUSED2P: stage-2 output extent, pooled (pool_k, pool_s) into Ho x Wo
     int relu_out = 0;
+    int ctot = 0;                   // channels of the tensor the block writes into
     bool shortcut = false;
     bool gap = false;               // KIND_SINGLE followed by a global average pooling: one tile per image
     long long alg_bytes = 0;        // algorithmic HBM bytes of the fused block
@@ -250,6 +252,9 @@ struct Few {
     const int *begin() const { return v; }
     const int *end() const { return v + n; }
 };
+
+// A variant with one tile and workgroup size per block.
+static bool one_candidate(const Variant &v) { return v.kind == KIND_CHAIN; }
 
 static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &lds_rejected, int pr)
 {
@@ -584,6 +589,41 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             c.ok = true;
             per_key[std::make_tuple(v.id, c.threads, c.th, c.tw)] = c;
         }
+    if (any_ok && b.kind == KIND_FUSED2 && pr != 0 && b.n2 == 1 && !b.shortcut && b.c1.k == 1 && b.c2[0].k == 1 && b.c1.stride == 1 &&
+        b.c2[0].stride == 1 && !pl.opts.force_tile_h && !pl.opts.force_threads && !pl.opts.force_cout_split && !pl.opts.paper_tuner_only)
+        for (const Variant &v : variants()) {
+            // pointwise -> pointwise with the intermediate in registers, 32 pixels per wave;
+            // pixels of neighbouring images are addressed from one base with 32-bit offsets
+            const long long hw = (long long)b.H * b.W, px = hw * b.N, reach = 31 / hw + 2;
+            const int nkg1 = ceil_div(b.c1.cin, 16), nrt1 = ceil_div(b.c1.cout, 32), nkg2 = ceil_div(b.c2[0].cin, 16);
+            if (v.kind != KIND_CHAIN || v.pr != pr || v.npt1 != b.n1 || v.nrt1 != nkg1 || v.nrt2 != ceil_div(b.c2[0].cout, 32)) continue;
+            if (px >= (1LL << 31) - 256 || reach * hw * std::max(b.c1.cin, b.ctot) >= (1LL << 29)) continue;
+            Choice c;
+            c.v = v;
+            c.threads = 256;
+            c.waves_r1 = c.waves_r2 = 1;
+            c.th = c.mh = c.ih = c.tiles_y = c.csplit = 1;
+            c.tw = c.vw2 = c.mw = c.iw = 128;
+            c.tiles_x = (int)((hw + 127) / 128);
+            c.chunk_kg = nkg1;
+            c.mid_floats = b.n1 * nrt1 * 32;        // the shifts of layer 1
+            c.buf_floats = (b.n1 * nkg1 + 2 * v.nrt2) * parts_of(pr) * 256;
+            c.lds_bytes = (c.mid_floats + c.buf_floats * std::min(nrt1, 2)) * 4;
+            if (c.lds_bytes > pl.lds_budget) continue;
+            c.occ = std::max(1, std::min(2, pl.lds_per_cu / c.lds_bytes));
+            // matrix operations of a wave; a life adds the trip to memory, and per 32 intermediate channels a barrier and the
+            // vector instructions, a third of which a second workgroup of the compute unit does not hide; loads, life and stores
+            // of a round overlap little (64 -> 256 twice -> 64 channels of 56 x 56, batches 8 / 31 / 32: 22 / 56 / 66 us)
+            const double mat = (double)nrt1 * (b.n1 * nkg1 + 2 * v.nrt2) * kstep_clk(32, pr), lat = 5000.0 + 1300.0 * b.n1 * nrt1;
+            const int per_cu = (int)((px + 127) / 128 + pl.num_cus - 1) / pl.num_cus;
+            const int full = per_cu / c.occ, rest = per_cu % c.occ;
+            const double t_cu = (full * std::max(c.occ * mat * 1.5, mat + lat) + (rest ? std::max(rest * mat, mat + lat) : 0.0)) / 2.4e9;
+            const double t_mem = (double)b.alg_bytes / 5.4e12;
+            c.cost = std::max(t_cu, t_mem) + 0.5 * std::min(t_cu, t_mem);
+            c.flops_exec = (px + 127) / 128 * 128 * 2LL * (b.n1 * nkg1 * 16 * nrt1 * 32 + nkg2 * 16LL * v.nrt2 * 32);
+            c.ok = true;
+            per_key[std::make_tuple(v.id, c.threads, c.th, c.tw)] = c;
+        }
     lds_rejected = !any_ok && any_lds_reject;
     // ranked list: the model's best first, then the best of other (variant, threads, tile) combinations
     std::vector<Choice> ranked;
@@ -595,10 +635,17 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
         // the best of those among the candidates, for xl_tune to time.
         const size_t reserve = MAX_ALTERNATIVES / 5;
         std::vector<Choice> small;
+        // (and the kinds with one candidate per block)
+        std::vector<bool> taken(ranked.size());
         for (size_t i = MAX_ALTERNATIVES - reserve; i < ranked.size() && small.size() < reserve; ++i)
-            if (ranked[i].threads == 256 && ranked[i].lds_bytes * 3 <= pl.lds_per_cu) small.push_back(ranked[i]);
-        ranked.resize(MAX_ALTERNATIVES - small.size());
-        ranked.insert(ranked.end(), small.begin(), small.end());
+            if (one_candidate(ranked[i].v)) small.push_back(ranked[i]), taken[i] = true;
+        for (size_t i = MAX_ALTERNATIVES - reserve; i < ranked.size() && small.size() < reserve; ++i)
+            if (!taken[i] && ranked[i].threads == 256 && ranked[i].lds_bytes * 3 <= pl.lds_per_cu) small.push_back(ranked[i]), taken[i] = true;
+        std::vector<Choice> kept;
+        for (size_t i = 0; i < ranked.size() && kept.size() < MAX_ALTERNATIVES - small.size(); ++i)
+            if (!taken[i]) kept.push_back(ranked[i]);
+        kept.insert(kept.end(), small.begin(), small.end());
+        ranked.swap(kept);
     }
     return ranked;
 }
@@ -827,13 +874,15 @@ struct Builder {
         return found;
     }
 
-    // The first n of a list by cost, with at most six of one variant before others had theirs; by cost again.
+    // The first n of a list by cost, with at most six of one variant before others had theirs, and before all the kinds with one
+    // candidate per block; by cost again.
     static void keep_best(std::vector<Choice> &l, size_t n)
     {
         auto by_cost = [](const Choice &x, const Choice &y) { return x.cost < y.cost; };
         std::map<int, int> seen;
         std::stable_sort(l.begin(), l.end(), by_cost);
-        std::stable_partition(l.begin(), l.end(), [&](const Choice &c) { return ++seen[c.v.id] <= 6; });
+        auto others = std::stable_partition(l.begin(), l.end(), [&](const Choice &c) { return one_candidate(c.v); });
+        std::stable_partition(others, l.end(), [&](const Choice &c) { return ++seen[c.v.id] <= 6; });
         if (l.size() > n) l.resize(n);
         std::stable_sort(l.begin(), l.end(), by_cost);
     }
@@ -966,6 +1015,7 @@ struct Builder {
         p.csplit = ch.csplit;
         p.nblocks = ch.tiles_x * ch.tiles_y * ch.csplit * b.N;
         if (ch.v.kind == KIND_DWP) p.nblocks = ceil_div(p.nblocks, 4);      // four waves with a tile each
+        if (ch.v.kind == KIND_CHAIN) p.nblocks = (int)(((long long)b.N * b.H * b.W + 127) / 128);      // pixels of all images in one row
         p.chunk_kg = ch.chunk_kg;
         p.chunk_kg2[0] = ch.chunk_kg2[0];
         p.chunk_kg2[1] = ch.chunk_kg2[1];
@@ -1019,6 +1069,7 @@ struct Builder {
         gi.cout_split = ch.csplit;
         gi.workgroups = ch.tiles_x * ch.tiles_y * ch.csplit * b.N;
         if (ch.v.kind == KIND_DWP) gi.workgroups = ceil_div(gi.workgroups, 4);
+        if (ch.v.kind == KIND_CHAIN) gi.workgroups = (int)(((long long)b.N * b.H * b.W + 127) / 128);
         gi.threads = ch.threads;
         gi.lds_bytes = ch.lds_bytes;
         gi.workgroups_per_cu = ch.occ;
@@ -1030,7 +1081,7 @@ struct Builder {
         } else {
             const double unique = (double)b.H1 * b.W1;
             gi.redundancy = (double)ch.mh * ch.mw * ch.tiles_x * ch.tiles_y * ch.csplit / unique;
-            if (ch.v.kind == KIND_DWP) gi.redundancy = ch.csplit;
+            if (ch.v.kind == KIND_DWP || ch.v.kind == KIND_CHAIN) gi.redundancy = ch.csplit;
         }
     }
 
@@ -1236,6 +1287,7 @@ struct Builder {
         const xl_shape &ys = pl.shapes[y_id];
         b.Ho = ys.h;
         b.Wo = ys.w;
+        b.ctot = pl.storage[y_id].ctot;
         if (b.gap) {
             // the kernel sees the convolution's own output extent; a pointwise one as a single row
             b.Ho = ms.h;

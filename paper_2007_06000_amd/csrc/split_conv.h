@@ -43,10 +43,10 @@ typedef unsigned u32x4 __attribute__((vector_size(16)));     // what the 128-bit
 __device__ __forceinline__ float bf16_low(unsigned w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float bf16_high(unsigned w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
 
-// The parts of two floats, packed (first float in the low half of each word).  `odd` is raised when one of the two
+// The parts of two floats, packed (first float in the low half of each word).  `odd` is raised (is not 0) when one of the two
 // does not come apart (PR = 2).
 template <int PR>
-__device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[PR + 1], bool &odd)
+__device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[PR + 1], unsigned &odd)
 {
 #pragma unroll
     for (int i = 0; i <= PR; ++i) {
@@ -57,7 +57,14 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[PR + 
         }
     }
     // what is left is 0, except where a part was infinite or NaN (NaN) or bits lie below the smallest bf16 number
-    if constexpr (PR == 2) odd |= (__builtin_bit_cast(unsigned, a) | __builtin_bit_cast(unsigned, b)) != 0u;
+    if constexpr (PR == 2) odd |= __builtin_bit_cast(unsigned, a) | __builtin_bit_cast(unsigned, b);
+}
+template <int PR>
+__device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[PR + 1], bool &odd)
+{
+    unsigned left = 0;
+    split_pair<PR>(a, b, w, left);
+    if constexpr (PR == 2) odd |= left != 0u;
 }
 
 // What is held in place of the parts of two values of which one does not come apart (PR = 2).

@@ -36,7 +36,7 @@ struct ConvW {
     int nrt;                // row tiles = ceil(cout / MF)
 };
 
-enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7 };
+enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7, KIND_CHAIN = 8 };
 
 // Kernel argument of every convolution-stage kernel.
 //   KIND_SINGLE: stage 1 writes its result to global memory (one layer, the
@@ -58,6 +58,7 @@ enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_P
 //                LDS tile; stage 2 as KIND_FUSED2.  c1.wp / c1.aff then hold the plain depthwise
 //                tables ([channel group][tap] and [channel group][scale, shift] float4).
 //   KIND_DWP:    KIND_DW with a pointwise stage 2, both of stride 1, wave by wave without LDS (dw_conv.h).
+//   KIND_CHAIN:  KIND_FUSED2 of pointwise layers on split operands, the intermediate in registers (chain_conv.h).
 struct BlockParams {
     const float *x;         // block input  [N, Cin, H, W]
     float *y;               // tensor the block writes into [N, Cy, Ho, Wo]
@@ -276,6 +277,33 @@ struct Variant {
 // Variants with split-bf16 operands, each compiled for two parts (pr = 1, ids from 200) and for three (pr = 2, ids
 // from 400): the columns above, then S1 = 1: stage 1 takes split operands too (0: fp32 matrix operations).  Where
 // operands are split the matrix-core tile is 32 wide.
+// KIND_CHAIN: columns 5, 6 and 8 are K steps of layer 1, producers and row tiles of layer 2
+#define XL_SPLIT_LIST_D(X)                                            \
+    X(120, KIND_CHAIN, 32, 1, 1, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(121, KIND_CHAIN, 32, 1, 1, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(122, KIND_CHAIN, 32, 1, 1, 1, 32, 3, 1, 1, 0, 0, 0, 1)          \
+    X(123, KIND_CHAIN, 32, 1, 2, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(124, KIND_CHAIN, 32, 1, 2, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(125, KIND_CHAIN, 32, 1, 2, 1, 32, 3, 1, 1, 0, 0, 0, 1)          \
+    X(126, KIND_CHAIN, 32, 1, 3, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(127, KIND_CHAIN, 32, 1, 3, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(128, KIND_CHAIN, 32, 1, 3, 1, 32, 3, 1, 1, 0, 0, 0, 1)          \
+    X(129, KIND_CHAIN, 32, 1, 4, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(130, KIND_CHAIN, 32, 1, 4, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(131, KIND_CHAIN, 32, 1, 4, 1, 32, 3, 1, 1, 0, 0, 0, 1)          \
+    X(132, KIND_CHAIN, 32, 1, 5, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(133, KIND_CHAIN, 32, 1, 5, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(134, KIND_CHAIN, 32, 1, 6, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(135, KIND_CHAIN, 32, 1, 6, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(136, KIND_CHAIN, 32, 1, 1, 2, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(137, KIND_CHAIN, 32, 1, 1, 2, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(138, KIND_CHAIN, 32, 1, 2, 2, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(139, KIND_CHAIN, 32, 1, 2, 2, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(140, KIND_CHAIN, 32, 1, 3, 2, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(141, KIND_CHAIN, 32, 1, 3, 2, 32, 2, 1, 1, 0, 0, 0, 1)          \
+    X(142, KIND_CHAIN, 32, 1, 4, 2, 32, 1, 1, 1, 0, 0, 0, 1)          \
+    X(143, KIND_CHAIN, 32, 1, 4, 2, 32, 2, 1, 1, 0, 0, 0, 1)
+
 #define XL_SPLIT_LIST_A(X)                                            \
     X(0, KIND_SINGLE, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
     X(1, KIND_SINGLE, 32, 1, 2, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
