@@ -104,6 +104,7 @@ __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
     constexpr int NP = PR + 1, ROWS1 = NKG1 * NP;        // filter rows of 1 KB per producer and row tile
     constexpr int GROUPS = N1 * NKG1 + 2 * NRT2;       // K steps per row tile of layer 1: of the producers, then of layer 2
     extern __shared__ __attribute__((aligned(16))) float lds[];
+    touch_arguments();
     const int L = logical_block();
     if (L >= P.nblocks) return;
     const int lane = threadIdx.x & 63, sub = lane >> 5;

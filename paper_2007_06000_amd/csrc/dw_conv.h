@@ -24,6 +24,7 @@ template <int MF, int NRT, int R, int PW>
 __global__ void __launch_bounds__(256) dw_pointwise_kernel(const BlockParams P)
 {
     typedef MM<MF> M;
+    touch_arguments();
     const int L = logical_block() * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tiles = P.tiles_x * P.tiles_y;
     if (L >= P.N * P.csplit * tiles) return;        // (wave-uniform; nothing below waits for another wave)

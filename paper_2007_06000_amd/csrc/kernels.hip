@@ -78,6 +78,21 @@ __device__ __forceinline__ float relu_from(float v, int lo)
 }
 __device__ __forceinline__ int relu_bound(int on) { return on ? 0 : INT_MIN; }
 
+// The kernel argument (BlockParams and the workgroup size behind it) is ten cache lines that no launch before has read.  Loaded
+// where its numbers are first used, line after line, each costs a trip to memory, which the first waves of a launch
+// wait for one by one; this asks for one number of every line at once.  Called first in every kernel.
+__device__ __forceinline__ void touch_arguments()
+{
+    static_assert(sizeof(BlockParams) > 448 && sizeof(BlockParams) <= 576, "lines 0 to 9 hold the argument and the workgroup size");
+    const unsigned long long p = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+    unsigned t[10];
+    asm volatile("s_load_dword %0, %10, 0x0\n\ts_load_dword %1, %10, 0x40\n\ts_load_dword %2, %10, 0x80\n\ts_load_dword %3, %10, 0xc0\n\t"
+                 "s_load_dword %4, %10, 0x100\n\ts_load_dword %5, %10, 0x140\n\ts_load_dword %6, %10, 0x180\n\ts_load_dword %7, %10, 0x1c0\n\t"
+                 "s_load_dword %8, %10, 0x200\n\ts_load_dword %9, %10, 0x240\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(t[0]), "=&s"(t[1]), "=&s"(t[2]), "=&s"(t[3]), "=&s"(t[4]), "=&s"(t[5]), "=&s"(t[6]), "=&s"(t[7]), "=&s"(t[8]), "=&s"(t[9])
+                 : "s"(p));
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
 // Map hardware block id -> logical id so that consecutive logical ids (tiles of
 // one image, which share halo rows and cache lines of the output) land on the
@@ -817,6 +832,7 @@ block_kernel(const BlockParams P)
     static_assert(PR1 == 0 || (PX1 == 0 && MF1 == 32), "split operands are staged through registers");
     static_assert(PR == 0 || MF2 == 32, "split operands use 32-wide matrix-core tiles");
     extern __shared__ __attribute__((aligned(16))) float lds[];
+    touch_arguments();
     const int L = logical_block();
     if (L >= P.nblocks) return;
     const int tiles = P.tiles_x * P.tiles_y;
@@ -1095,6 +1111,7 @@ __global__ void __launch_bounds__(MAX_THREADS, 4) pool_stream_kernel(const Block
     constexpr int T = K1 * K1;
     static_assert(STAGE_UNITS == 1, "every thread of the stream kernel stages exactly one input unit per tile");
     extern __shared__ __attribute__((aligned(16))) float lds[];
+    touch_arguments();
     float *mid = lds;
     float *xbuf = lds + P.lds_buf_off;
     float *wbuf = xbuf + P.w_off1;

@@ -41,6 +41,7 @@ __global__ void __launch_bounds__(MAX_THREADS) thin_conv_kernel(const BlockParam
     constexpr int OCB = THIN_OCB;
     typedef const float __attribute__((address_space(4))) cfloat;    // read-only, wave-uniform: scalar loads
     extern __shared__ __attribute__((aligned(16))) float lds[];
+    touch_arguments();
 
     const int L = logical_block();
     if (L >= P.nblocks) return;
@@ -206,6 +207,7 @@ __global__ void __launch_bounds__(256) thin_conv_pool_kernel(const BlockParams P
     typedef const float __attribute__((address_space(4))) cfloat;
     typedef unsigned u32x4 __attribute__((vector_size(16)));
     extern __shared__ __attribute__((aligned(16))) float lds[];
+    touch_arguments();
 
     const int L = logical_block();
     if (L >= P.nblocks) return;
