@@ -17,7 +17,7 @@
 // the block below), and the last round: 3136 waves of 32 pixels on 1024 SIMDs take four rounds instead of 3.06.  A wave alone on
 // its SIMD takes 1.7 us per row tile, 1.0 of it operations; staging and barriers cost 5 % (measured without them).  Time per
 // pass, before (three passes of the general kernel with the intermediate in LDS) -> here: {64 -> 256, 64 -> 256} -> 64 channels of
-// 56 x 56, batch 32: 123 -> 59 us (two parts: 68 -> 37), batch 8: 40 -> 22; {20 -> 45, 20 -> 45} -> 19 of 44 x 49, batch 45: 28 ->
+// 56 x 56, batch 32: 123 -> 59 us (layer 2 on two parts: 68 -> 55), batch 8: 40 -> 22; {20 -> 45, 20 -> 45} -> 19 of 44 x 49, batch 45: 28 ->
 // 11; 20 -> 16 -> 16 of 50 x 50, batch 64: 17.5 -> 10.6; 64 -> 64 -> 64 of 56 x 56, batch 32: 27.8 -> 21.  Below about 100 waves the
 // general kernel's smaller tiles are faster ({64 -> 256, 64 -> 256} -> 64 of one image: 17.1 and 18.9 us), so both stay.
 #pragma once
@@ -44,7 +44,7 @@ struct ChainInput {
 
 // The whole chain again with fp32 matrix operations on whole operands, for a wave that met a sum that is not finite
 // (conv_whole of split_conv.h: values without bf16 parts, sums that overflow).  The intermediate stays in fp32.
-template <int NRT2>
+template <int NRT2, int PR>
 __device__ __forceinline__ void chain_whole(f32x16 (&acc2)[NRT2][1], const BlockParams &P, const ChainInput &in, int lane)
 {
     const int from = (lane & 32) + row_channel(lane & 31);
@@ -84,24 +84,25 @@ __device__ __forceinline__ void chain_whole(f32x16 (&acc2)[NRT2][1], const Block
             if (kg >= P.c2[0].nkg) continue;
 #pragma unroll
             for (int r = 0; r < NRT2; ++r) {
-                uint4 w[3];
+                uint4 w[PR + 1];
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    w[i] = reinterpret_cast<const uint4 *>(P.c2[0].wp)[(size_t)(kg * NRT2 + r) * 192 + i * 64 + lane];
+                for (int i = 0; i <= PR; ++i)
+                    w[i] = reinterpret_cast<const uint4 *>(P.c2[0].wp)[(size_t)(kg * NRT2 + r) * (64 * (PR + 1)) + i * 64 + lane];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc2[r][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(whole_value(w, e), v[s * 8 + e], acc2[r][0], 0, 0, 0);
+                for (int e = 0; e < 8; ++e) acc2[r][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(held_value<PR>(w, e), v[s * 8 + e], acc2[r][0], 0, 0, 0);
             }
         }
     }
 }
 
-// N1: producers, NKG1: K steps of layer 1, NRT2: row tiles of layer 2.
+// N1: producers, NKG1: K steps of layer 1, NRT2: row tiles of layer 2.  Layer 1 takes three parts in either precision (the general
+// kernel it stands for may run it on fp32 operations); PR: of layer 2.
 // BlockParams used: x, y, N, Cin, H, W, Cy, c1, c1b (N1 == 2), n1, relu_mid, c2[0], coff2[0], relu_out, nblocks, and buf_stride
 // (floats per filter buffer), lds_buf_off (floats of the shift tables before them).
 template <int PR, int N1, int NKG1, int NRT2>
 __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
 {
-    constexpr int NP = PR + 1, ROWS1 = NKG1 * NP;        // filter rows of 1 KB per producer and row tile
+    constexpr int PR1 = 2, NP1 = PR1 + 1, NP = PR + 1, ROWS1 = NKG1 * NP1;      // filter rows of 1 KB per producer and row tile
     constexpr int GROUPS = N1 * NKG1 + 2 * NRT2;       // K steps per row tile of layer 1: of the producers, then of layer 2
     extern __shared__ __attribute__((aligned(16))) float lds[];
     touch_arguments();
@@ -145,8 +146,8 @@ __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
     int at1[R1];
 #pragma unroll
     for (int i = 0; i < R1; ++i) {
-        const int r = i * 4 + wave, kg = r / NP;
-        at1[i] = (kg * P.c1.nrt * NP + r - kg * NP) * 1024;
+        const int r = i * 4 + wave, kg = r / NP1;
+        at1[i] = (kg * P.c1.nrt * NP1 + r - kg * NP1) * 1024;
     }
     auto stage = [&](int rt, float *to) {
         auto row = [&](__amdgpu_buffer_rsrc_t from, int lane_at, int at, int r) {
@@ -155,8 +156,8 @@ __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
 #pragma unroll
         for (int i = 0; i < R1; ++i) {
             if (ROWS1 % 4 && i * 4 + wave >= ROWS1) continue;
-            row(wa, permuted, at1[i] + rt * (NP * 1024), i * 4 + wave);
-            if (N1 == 2) row(wb, permuted, at1[i] + rt * (NP * 1024), ROWS1 + i * 4 + wave);
+            row(wa, permuted, at1[i] + rt * (NP1 * 1024), i * 4 + wave);
+            if (N1 == 2) row(wb, permuted, at1[i] + rt * (NP1 * 1024), ROWS1 + i * 4 + wave);
         }
         const int live = min(2, c2.nkg - rt * 2) * (NRT2 * NP);        // rows of K steps that exist
 #pragma unroll
@@ -178,15 +179,15 @@ __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
     // ---- the input in parts.  Bits that are left raise `odd` (split_pair), as those of the intermediate do below: the wave then
     // starts again with whole operands, so nothing needs to stand for such a value here.
     unsigned odd = 0;
-    u32x4 xp[NKG1][NP];
+    u32x4 xp[NKG1][NP1];
 #pragma unroll
     for (int kg = 0; kg < NKG1; ++kg)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            unsigned w[NP];
-            split_pair<PR>(xv[kg][2 * j], xv[kg][2 * j + 1], w, odd);
+            unsigned w[NP1];
+            split_pair<PR1>(xv[kg][2 * j], xv[kg][2 * j + 1], w, odd);
 #pragma unroll
-            for (int q = 0; q < NP; ++q) xp[kg][q][j] = w[q];
+            for (int q = 0; q < NP1; ++q) xp[kg][q][j] = w[q];
         }
     // The largest sum of layer 1 as an unsigned number: 0xff800000 and above are -inf and NaN with the sign set, which an activation
     // turns to 0 (+inf and NaN do not come apart).
@@ -199,21 +200,23 @@ __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
     for (int rt = 0; rt < P.c1.nrt; ++rt) {
         const float *w = buf + (rt & 1) * P.buf_stride + lane * 4;
         // the filter rows of K step g + 2 of the tile are read before the matrix operations of K step g
-        f32x4 a[3][NP];
+        f32x4 a[3][NP1];
         auto fetch = [&](int g) {
             if (g >= GROUPS) return;
+            constexpr int G1 = N1 * NKG1;
 #pragma unroll
-            for (int i = 0; i < NP; ++i) a[g % 3][i] = *(const f32x4 *)(w + (g * NP + i) * 256);
+            for (int i = 0; i < (g < G1 ? NP1 : NP); ++i) a[g % 3][i] = *(const f32x4 *)(w + (g < G1 ? g * NP1 + i : G1 * NP1 + (g - G1) * NP + i) * 256);
         };
         // acc gets the large products, low the small ones; `beside(i)` are vector instructions for the time of the i-th operation
-        auto mma = [&](f32x16 &acc, f32x16 &low, int g, const u32x4 (&b)[NP], auto beside) {
+        auto mma = [&](f32x16 &acc, f32x16 &low, int g, const auto &b, auto beside) {
+            constexpr int parts = sizeof(b) / 16;
             fetch(g + 2);
             int at = 0;
 #pragma unroll
-            for (int i = NP - 1; i >= 0; --i)
+            for (int i = parts - 1; i >= 0; --i)
 #pragma unroll
-                for (int j = NP - 1 - i; j >= 0; --j) {
-                    f32x16 &d = PR == 2 && i + j > 0 ? low : acc;
+                for (int j = parts - 1 - i; j >= 0; --j) {
+                    f32x16 &d = parts == 3 && i + j > 0 ? low : acc;
                     d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[g % 3][j]), __builtin_bit_cast(bf16x8, b[i]), d, 0, 0, 0);
                     beside(at++);
                     __builtin_amdgcn_sched_barrier(0);
@@ -234,12 +237,12 @@ __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
             }
         }
         if (rt + 1 < P.c1.nrt) stage(rt + 1, buf + ((rt + 1) & 1) * P.buf_stride);
-        constexpr int OPS = PR == 2 ? 6 : 3;
+        constexpr int OPS1 = products_of(PR1), OPS = products_of(PR);
         f32x16 v;
         u32x4 mp[2][NP];
         auto sum = [&](int pr, int i) {
-            const float t = PR == 2 ? acc[pr][i] + low[pr][i] : acc[pr][i];
-            if constexpr (PR == 2) least = max(least, __builtin_bit_cast(unsigned, t));
+            const float t = acc[pr][i] + low[pr][i];
+            least = max(least, __builtin_bit_cast(unsigned, t));
             v[i] = pr == 0 ? relu_from(t, lo1) : relu_from(v[i] + relu_from(t, lo1b), lo_sum);
         };
         auto split = [&](u32x4 (&to)[NP], int from, int j) {
@@ -259,7 +262,7 @@ __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
         if constexpr (N1 == 2) {
 #pragma unroll
             for (int kg = 0; kg < NKG1; ++kg)
-                mma(acc[1], low[1], NKG1 + kg, xp[kg], [&](int k) { share(kg * OPS + k, NKG1 * OPS, 16, [&](int i) { sum(0, i); }); });
+                mma(acc[1], low[1], NKG1 + kg, xp[kg], [&](int k) { share(kg * OPS1 + k, NKG1 * OPS1, 16, [&](int i) { sum(0, i); }); });
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) sum(N1 - 1, i);
@@ -273,11 +276,9 @@ __global__ void __launch_bounds__(256, 2) chain_kernel(const BlockParams P)
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     }
-    if constexpr (PR == 2) {
-        add_small<NRT2, 1>(acc2, small2);
-        const bool again = __builtin_amdgcn_ballot_w64(odd != 0u || least >= 0xff800000u) != 0;
-        if (again || any_not_finite<NRT2, 1>(acc2)) chain_whole<NRT2>(acc2, P, in, lane);
-    }
+    if constexpr (PR == 2) add_small<NRT2, 1>(acc2, small2);
+    const bool again = __builtin_amdgcn_ballot_w64(odd != 0u || least >= 0xff800000u) != 0;
+    if (again || any_not_finite<NRT2, 1>(acc2)) chain_whole<NRT2, PR>(acc2, P, in, lane);
     if (!own) return;
     const __amdgpu_buffer_rsrc_t yr = make_rsrc(P.y + ((size_t)n0 * P.Cy + P.coff2[0]) * HW,
                                                 ((unsigned long long)reach * P.Cy - P.coff2[0]) * HW * 4ull);

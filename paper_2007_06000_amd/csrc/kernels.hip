@@ -1393,7 +1393,7 @@ BlockKernel XL_CAT(split_kernel_, XL_TU_SPLIT, XL_TU_PR)(int variant)
     case ID:                                                                                                         \
         return select_split_kernel<KIND, MF1, K1, NRT1, NPT1, (MF2 == 0 ? 32 : MF2), (NRT2 == 0 ? 1 : NRT2),         \
                                    (NPT2 == 0 ? 1 : NPT2), (K2A == 0 ? 1 : K2A), K2B, (SC != 0), PX1, XL_TU_PR,      \
-                                   (S1 ? XL_TU_PR : 0)>();
+                                   (S1 == 2 ? 2 : S1 ? XL_TU_PR : 0)>();
         XL_CAT(XL_SPLIT_LIST, _, XL_TU_SPLIT)(X)
 #undef X
     }

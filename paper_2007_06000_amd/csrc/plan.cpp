@@ -22,7 +22,7 @@ const std::vector<Variant> &variants()
         XL_VARIANT_LIST(X)
 #undef X
 #define X(ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, S1) \
-    Variant{SPLIT_ID0[1] + ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, 1, S1 ? 1 : 0}, \
+    Variant{SPLIT_ID0[1] + ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, 1, S1}, \
     Variant{SPLIT_ID0[2] + ID, KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, 2, S1 ? 2 : 0},
         XL_SPLIT_LIST_A(X)
         XL_SPLIT_LIST_B(X)
@@ -607,14 +607,14 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             c.tiles_x = (int)((hw + 127) / 128);
             c.chunk_kg = nkg1;
             c.mid_floats = b.n1 * nrt1 * 32;        // the shifts of layer 1
-            c.buf_floats = (b.n1 * nkg1 + 2 * v.nrt2) * parts_of(pr) * 256;
+            c.buf_floats = (b.n1 * nkg1 * parts_of(v.pr1) + 2 * v.nrt2 * parts_of(pr)) * 256;
             c.lds_bytes = (c.mid_floats + c.buf_floats * std::min(nrt1, 2)) * 4;
             if (c.lds_bytes > pl.lds_budget) continue;
             c.occ = std::max(1, std::min(2, pl.lds_per_cu / c.lds_bytes));
             // matrix operations of a wave; a life adds the trip to memory, and per 32 intermediate channels a barrier and the
             // vector instructions, a third of which a second workgroup of the compute unit does not hide; loads, life and stores
             // of a round overlap little (64 -> 256 twice -> 64 channels of 56 x 56, batches 8 / 31 / 32: 22 / 56 / 66 us)
-            const double mat = (double)nrt1 * (b.n1 * nkg1 + 2 * v.nrt2) * kstep_clk(32, pr), lat = 5000.0 + 1300.0 * b.n1 * nrt1;
+            const double mat = (double)nrt1 * (b.n1 * nkg1 * kstep_clk(32, v.pr1) + 2 * v.nrt2 * kstep_clk(32, pr)), lat = 5000.0 + 1300.0 * b.n1 * nrt1;
             const int per_cu = (int)((px + 127) / 128 + pl.num_cus - 1) / pl.num_cus;
             const int full = per_cu / c.occ, rest = per_cu % c.occ;
             const double t_cu = (full * std::max(c.occ * mat * 1.5, mat + lat) + (rest ? std::max(rest * mat, mat + lat) : 0.0)) / 2.4e9;

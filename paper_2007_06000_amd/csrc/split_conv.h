@@ -93,6 +93,15 @@ __device__ __forceinline__ float whole_value(const uint4 (&w)[3], int e)
     return whole_value(part[0], part[1], part[2]);
 }
 
+// The same for a value of PR + 1 parts (two parts hold every value as their sum).
+template <int PR>
+__device__ __forceinline__ float held_value(const uint4 (&w)[PR + 1], int e)
+{
+    if constexpr (PR == 2) return whole_value(w, e);
+    const unsigned hi = e < 2 ? w[0].x : e < 4 ? w[0].y : e < 6 ? w[0].z : w[0].w, lo = e < 2 ? w[1].x : e < 4 ? w[1].y : e < 6 ? w[1].z : w[1].w;
+    return e & 1 ? bf16_high(hi) + bf16_high(lo) : bf16_low(hi) + bf16_low(lo);
+}
+
 // Four consecutive channels of one pixel into the part planes: part p goes 8 bytes wide to dst + p * plane.
 template <int PR>
 __device__ __forceinline__ void store_parts(const f32x4 &v, float *dst, int plane, bool &odd)

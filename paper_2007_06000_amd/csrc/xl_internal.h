@@ -275,34 +275,34 @@ struct Variant {
     X(41, KIND_POOL, 16, 3, 1, 1, 0, 0, 0, 0, 0, 0, 0)
 
 // Variants with split-bf16 operands, each compiled for two parts (pr = 1, ids from 200) and for three (pr = 2, ids
-// from 400): the columns above, then S1 = 1: stage 1 takes split operands too (0: fp32 matrix operations).  Where
-// operands are split the matrix-core tile is 32 wide.
+// from 400): the columns above, then S1 = 1: stage 1 takes split operands too (0: fp32 matrix operations; 2: three parts in
+// either).  Where operands are split the matrix-core tile is 32 wide.
 // KIND_CHAIN: columns 5, 6 and 8 are K steps of layer 1, producers and row tiles of layer 2
 #define XL_SPLIT_LIST_D(X)                                            \
-    X(120, KIND_CHAIN, 32, 1, 1, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(121, KIND_CHAIN, 32, 1, 1, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(122, KIND_CHAIN, 32, 1, 1, 1, 32, 3, 1, 1, 0, 0, 0, 1)          \
-    X(123, KIND_CHAIN, 32, 1, 2, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(124, KIND_CHAIN, 32, 1, 2, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(125, KIND_CHAIN, 32, 1, 2, 1, 32, 3, 1, 1, 0, 0, 0, 1)          \
-    X(126, KIND_CHAIN, 32, 1, 3, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(127, KIND_CHAIN, 32, 1, 3, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(128, KIND_CHAIN, 32, 1, 3, 1, 32, 3, 1, 1, 0, 0, 0, 1)          \
-    X(129, KIND_CHAIN, 32, 1, 4, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(130, KIND_CHAIN, 32, 1, 4, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(131, KIND_CHAIN, 32, 1, 4, 1, 32, 3, 1, 1, 0, 0, 0, 1)          \
-    X(132, KIND_CHAIN, 32, 1, 5, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(133, KIND_CHAIN, 32, 1, 5, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(134, KIND_CHAIN, 32, 1, 6, 1, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(135, KIND_CHAIN, 32, 1, 6, 1, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(136, KIND_CHAIN, 32, 1, 1, 2, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(137, KIND_CHAIN, 32, 1, 1, 2, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(138, KIND_CHAIN, 32, 1, 2, 2, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(139, KIND_CHAIN, 32, 1, 2, 2, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(140, KIND_CHAIN, 32, 1, 3, 2, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(141, KIND_CHAIN, 32, 1, 3, 2, 32, 2, 1, 1, 0, 0, 0, 1)          \
-    X(142, KIND_CHAIN, 32, 1, 4, 2, 32, 1, 1, 1, 0, 0, 0, 1)          \
-    X(143, KIND_CHAIN, 32, 1, 4, 2, 32, 2, 1, 1, 0, 0, 0, 1)
+    X(120, KIND_CHAIN, 32, 1, 1, 1, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(121, KIND_CHAIN, 32, 1, 1, 1, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(122, KIND_CHAIN, 32, 1, 1, 1, 32, 3, 1, 1, 0, 0, 0, 2)          \
+    X(123, KIND_CHAIN, 32, 1, 2, 1, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(124, KIND_CHAIN, 32, 1, 2, 1, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(125, KIND_CHAIN, 32, 1, 2, 1, 32, 3, 1, 1, 0, 0, 0, 2)          \
+    X(126, KIND_CHAIN, 32, 1, 3, 1, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(127, KIND_CHAIN, 32, 1, 3, 1, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(128, KIND_CHAIN, 32, 1, 3, 1, 32, 3, 1, 1, 0, 0, 0, 2)          \
+    X(129, KIND_CHAIN, 32, 1, 4, 1, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(130, KIND_CHAIN, 32, 1, 4, 1, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(131, KIND_CHAIN, 32, 1, 4, 1, 32, 3, 1, 1, 0, 0, 0, 2)          \
+    X(132, KIND_CHAIN, 32, 1, 5, 1, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(133, KIND_CHAIN, 32, 1, 5, 1, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(134, KIND_CHAIN, 32, 1, 6, 1, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(135, KIND_CHAIN, 32, 1, 6, 1, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(136, KIND_CHAIN, 32, 1, 1, 2, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(137, KIND_CHAIN, 32, 1, 1, 2, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(138, KIND_CHAIN, 32, 1, 2, 2, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(139, KIND_CHAIN, 32, 1, 2, 2, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(140, KIND_CHAIN, 32, 1, 3, 2, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(141, KIND_CHAIN, 32, 1, 3, 2, 32, 2, 1, 1, 0, 0, 0, 2)          \
+    X(142, KIND_CHAIN, 32, 1, 4, 2, 32, 1, 1, 1, 0, 0, 0, 2)          \
+    X(143, KIND_CHAIN, 32, 1, 4, 2, 32, 2, 1, 1, 0, 0, 0, 2)
 
 #define XL_SPLIT_LIST_A(X)                                            \
     X(0, KIND_SINGLE, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
