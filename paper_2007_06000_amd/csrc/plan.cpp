@@ -28,6 +28,7 @@ const std::vector<Variant> &variants()
         XL_SPLIT_LIST_B(X)
         XL_SPLIT_LIST_C(X)
         XL_SPLIT_LIST_D(X)
+        XL_SPLIT_LIST_E(X)
 #undef X
     };
     return v;
@@ -101,6 +102,7 @@ struct Choice {
     double cost = 0;
     Variant v{};
     int threads = 0, waves_r1 = 0, waves_r2 = 1, csplit = 1;
+    int pw1 = 1, pw2 = 1;           // KIND_KSPLIT
     int th = 0, tw = 0, mh = 0, mw = 0, ih = 0, iw = 0, vw2 = 0;
     int pth = 0, ptw = 0;           // KIND_FUSED2P: tile of the pooled output (th x tw: the stage-2 tile under it)
     int tiles_y = 0, tiles_x = 0;
@@ -253,13 +255,9 @@ struct Few {
     const int *end() const { return v + n; }
 };
 
-// A variant with one tile and workgroup size per block.
-static bool one_candidate(const Variant &v) { return v.kind == KIND_CHAIN; }
-
-static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &lds_rejected, int pr)
+// The tiles of the block's output to choose from.
+static std::vector<std::pair<int, int>> tiles_of(const BlockSpec &b, const xl_plan &pl)
 {
-    bool any_ok = false;
-    std::map<std::tuple<int, int, int, int>, Choice> per_key;     // best per (variant, threads, tile)
     const std::vector<int> ths = tile_candidates(b.Ho), tws = tile_candidates(b.Wo);
     std::vector<std::pair<int, int>> tiles;
     if (b.gap) {
@@ -275,6 +273,124 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
         for (int th : ths)
             for (int tw : tws) tiles.push_back({th, tw});
     }
+    return tiles;
+}
+
+// Kernels whose waves divide the reductions (ksplit_conv.h).
+static std::vector<Choice> search_ksplit(const BlockSpec &b, const xl_plan &pl, int pr)
+{
+    std::map<std::tuple<int, int, int, int>, Choice> per_key;
+    std::vector<Choice> ranked;
+    const bool pool2 = b.kind == KIND_FUSED2P;
+    if ((b.kind != KIND_FUSED2 && !pool2) || b.n1 != 1) return ranked;
+    const std::vector<std::pair<int, int>> tiles = tiles_of(b, pl);
+    const int pr1 = b.c1.k == 1 ? 2 : pr, np1 = parts_of(pr1), np = parts_of(pr), nkg1 = ceil_div(b.c1.cin, 16), nrt1 = ceil_div(b.c1.cout, 32), taps1 = b.c1.k * b.c1.k;
+    int halo = 0, ext = 0, min_nrt = 1 << 30;
+    for (int i = 0; i < b.n2; ++i) {
+        halo = std::max(halo, b.c2[i].pad);
+        ext = std::max(ext, b.c2[i].k - b.c2[i].pad);
+        min_nrt = std::min(min_nrt, ceil_div(b.c2[i].cout, 32));
+    }
+    // (the kernel divides step numbers by 9 and 25 with short multipliers)
+    if (nkg1 * taps1 > 4096 || nrt1 * 2 * 25 > 4096) return ranked;
+    const int s2 = b.c2[0].stride;
+    auto pow2 = [](int v) { int p = 1; while (p < v) p *= 2; return p; };
+    for (auto [th, tw] : tiles) {
+        Choice t;
+        t.th = pool2 ? required_extent(th, b.pool_k, b.pool_s) : th;
+        t.tw = t.vw2 = pool2 ? required_extent(tw, b.pool_k, b.pool_s) : tw;
+        t.pth = pool2 ? th : 0;
+        t.ptw = pool2 ? tw : 0;
+        t.mh = (t.th - 1) * s2 + ext + halo;
+        t.mw = (t.tw - 1) * s2 + ext + halo;
+        const int npt1 = ceil_div(t.mh * t.mw, 32), npt2 = ceil_div(t.th * t.tw, 32);
+        if (npt1 > 8) continue;
+        t.ih = required_extent(t.mh, b.c1.k, b.c1.stride);
+        t.iw = required_extent(t.mw, b.c1.k, b.c1.stride);
+        t.tiles_y = ceil_div(b.Ho, th);
+        t.tiles_x = ceil_div(b.Wo, tw);
+        t.chunk_kg = nkg1;
+        const int mid = nrt1 * 4 * np * t.mh * t.mw * 4, input = b.c1.k == 1 ? 0 : nkg1 * 2 * np1 * t.ih * t.iw * 4;
+        if ((mid + input) * 4 > pl.lds_budget) continue;
+        for (const Variant &v : variants()) {
+            if (v.kind != KIND_KSPLIT || v.pr != pr || (v.px1 != 0) != pool2 || (v.k1 == 1) != (b.c1.k == 1)) continue;
+            if (v.nrt1 > nrt1 || v.npt1 > npt1 || v.npt2 > npt2) continue;
+            for (int threads : {256, 512}) {
+                if (pl.opts.force_threads > 0 && pl.opts.force_threads != threads) continue;
+                const int nw = threads / 64, rw1 = pow2(ceil_div(nrt1, v.nrt1)), pw1 = pow2(ceil_div(npt1, v.npt1));
+                if (rw1 * pw1 > nw) continue;
+                const int kw1 = nw / (rw1 * pw1);
+                Choice *kept = nullptr;
+                for (int cs = 1; cs <= 16 && cs <= min_nrt; cs *= 2) {
+                    if (pl.opts.force_cout_split > 0 && cs != 1) break;
+                    const int csplit = pl.opts.force_cout_split > 0 ? pl.opts.force_cout_split : cs;
+                    for (int rw2 = 1; rw2 <= nw; rw2 *= 2) {
+                        int max_per = 0;
+                        for (int i = 0; i < b.n2; ++i) max_per = std::max(max_per, ceil_div(ceil_div(b.c2[i].cout, 32), csplit));
+                        if (rw2 > 1 && rw2 / 2 * v.nrt2 >= max_per) continue;
+                        const int pw2 = std::min(pow2(ceil_div(npt2, v.npt2)), nw / rw2);
+                        const int px_passes = ceil_div(npt2, pw2 * v.npt2), kw2 = nw / (rw2 * pw2);
+                        if (pool2 && px_passes > 1) continue;
+                        Choice c = t;
+                        c.v = v;
+                        c.threads = threads;
+                        c.waves_r1 = rw1;
+                        c.pw1 = pw1;
+                        c.waves_r2 = rw2;
+                        c.pw2 = pw2;
+                        c.csplit = csplit;
+                        c.mid_floats = mid;
+                        const int part = nw * std::max(v.nrt1 * v.npt1, v.nrt2 * v.npt2) * 1024;
+                        c.w_off1 = mid + part;
+                        c.tile2_off = c.w_off1 + input;
+                        c.tile2_floats = pool2 ? rw2 * v.nrt2 * 32 * t.th * t.tw : 0;
+                        c.lds_bytes = (c.tile2_off + c.tile2_floats) * 4;
+                        if (c.lds_bytes > pl.lds_budget) continue;
+                        c.occ = std::max(1, std::min(pl.lds_per_cu / c.lds_bytes, 8 / nw));
+                        // Cycles: matrix operations of the busiest SIMD (nw / 4 waves each) or filter rows at 64 bytes per cycle, a
+                        // start, trips to memory behind the first, and for every quad of a tile that a wave adds up and stores, and
+                        // every pass.  (The numbers are fitted to 700 candidates of 25 blocks, both precisions, 6 to 40 us: 10 % off
+                        // in the mean, first choice 2.5 % behind the best.)
+                        const double op1 = products_of(pr1) * 34.0 * 1.61, row1 = np1 * 16.0 * 1.57, op = products_of(pr) * 34.0 * 1.61, row = np * 16.0 * 1.57;
+                        const int sw1 = ceil_div(nkg1 * taps1, kw1);
+                        double busy = std::max(sw1 * v.nrt1 * v.npt1 * op1 * (nw / 4), sw1 * v.nrt1 * row1 * nw);
+                        double life = 5300.0 + 1800.0 * ceil_div(rw1 * v.nrt1 * pw1 * v.npt1 * 4, nw) + (b.c1.k == 1 ? 2300.0 * std::max(0, sw1 - 3) : 0.0);
+                        long long flops2 = 0;
+                        for (int i = 0; i < b.n2; ++i) {
+                            const ConvSpec &s = b.c2[i];
+                            const int nrt = ceil_div(s.cout, 32), per = std::min(nrt, ceil_div(nrt, csplit)), nkg = ceil_div(s.cin, 16);
+                            const int passes = ceil_div(per, rw2 * v.nrt2) * px_passes, sw2 = ceil_div(nkg * s.k * s.k, kw2);
+                            busy += passes * std::max(sw2 * v.nrt2 * v.npt2 * op * (nw / 4), sw2 * v.nrt2 * row * nw);
+                            life += passes * (2900.0 + 1600.0 * ceil_div(rw2 * v.nrt2 * pw2 * v.npt2 * 4, nw));
+                            flops2 += 2LL * per * 32 * npt2 * 32 * nkg * 16 * s.k * s.k;
+                        }
+                        life += busy;
+                        const long long wgs = (long long)c.tiles_x * c.tiles_y * csplit * b.N;
+                        const int per_cu = (int)((wgs + pl.num_cus - 1) / pl.num_cus), full = per_cu / c.occ, rest = per_cu % c.occ;
+                        const double t_cu = (full * std::max(c.occ * busy * 2.0, life) + (rest ? std::max(rest * busy * 2.0, life) : 0.0)) / 2.4e9;
+                        const double t_mem = (double)b.alg_bytes / 5.4e12;
+                        c.cost = 1.05 * std::max(t_cu, t_mem);      // (of equals, the one that holds its tile in a wave)
+                        c.flops_exec = wgs * (2LL * nrt1 * 32 * npt1 * 32 * nkg1 * 16 * taps1 + flops2);
+                        c.ok = true;
+                        if (!kept) kept = &per_key[std::make_tuple(v.id, threads, th, tw)];
+                        if (!kept->ok || c.cost < kept->cost) *kept = c;
+                    }
+                }
+            }
+        }
+    }
+    for (auto &kv : per_key) ranked.push_back(kv.second);
+    return ranked;
+}
+
+// A variant with one tile and workgroup size per block.
+static bool one_candidate(const Variant &v) { return v.kind == KIND_CHAIN; }
+
+static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &lds_rejected, int pr)
+{
+    bool any_ok = false;
+    std::map<std::tuple<int, int, int, int>, Choice> per_key;     // best per (variant, threads, tile)
+    const std::vector<std::pair<int, int>> tiles = tiles_of(b, pl);
     bool any_lds_reject = false;
     for (const Variant &v : variants()) {
         if (v.kind == KIND_THIN) {
@@ -876,13 +992,13 @@ struct Builder {
 
     // The first n of a list by cost, with at most six of one variant before others had theirs, and before all the kinds with one
     // candidate per block; by cost again.
-    static void keep_best(std::vector<Choice> &l, size_t n)
+    static void keep_best(std::vector<Choice> &l, size_t n, int of_a_variant = 6)
     {
         auto by_cost = [](const Choice &x, const Choice &y) { return x.cost < y.cost; };
         std::map<int, int> seen;
         std::stable_sort(l.begin(), l.end(), by_cost);
         auto others = std::stable_partition(l.begin(), l.end(), [&](const Choice &c) { return one_candidate(c.v); });
-        std::stable_partition(others, l.end(), [&](const Choice &c) { return ++seen[c.v.id] <= 6; });
+        std::stable_partition(others, l.end(), [&](const Choice &c) { return ++seen[c.v.id] <= of_a_variant; });
         if (l.size() > n) l.resize(n);
         std::stable_sort(l.begin(), l.end(), by_cost);
     }
@@ -906,11 +1022,21 @@ struct Builder {
         // another variant and took 11.2 us.  (The best of the 64 is 0.6 % behind the best of 600 over 36 blocks; of 64 and 48
         // without the cap 0.5 %.)
         std::vector<Choice> split;
-        if (!has_fp32_layer(b)) split = search(b, pl, ignored, pl.opts.precision == XL_PRECISION_BF16X3 ? 1 : 2);
+        std::vector<Choice> ksplit;
+        if (!has_fp32_layer(b)) {
+            const int pr = pl.opts.precision == XL_PRECISION_BF16X3 ? 1 : 2;
+            split = search(b, pl, ignored, pr);
+            if (!split.empty()) ksplit = search_ksplit(b, pl, pr);
+        }
         if (!split.empty()) {
-            const size_t half = MAX_ALTERNATIVES / 2, fp32 = ranked.size();
-            keep_best(ranked, std::max(half, MAX_ALTERNATIVES - std::min(split.size(), (size_t)MAX_ALTERNATIVES)));
+            // (the kernels that divide the reductions have places of their own, taken from the fp32 ones', which are seldom the
+            // fastest where these exist)
+            keep_best(ksplit, KSPLIT_PLACES, 3);
+            const size_t half = MAX_ALTERNATIVES / 2, fp32 = ranked.size() + ksplit.size();
+            keep_best(ranked, std::max(half, MAX_ALTERNATIVES - std::min(split.size(), (size_t)MAX_ALTERNATIVES)) - ksplit.size());
             keep_best(split, std::max(half, MAX_ALTERNATIVES - std::min(fp32, (size_t)MAX_ALTERNATIVES)));
+            split.insert(split.end(), ksplit.begin(), ksplit.end());
+            std::stable_sort(split.begin(), split.end(), [](const Choice &x, const Choice &y) { return x.cost < y.cost; });
             split.insert(split.end(), ranked.begin(), ranked.end());
             ranked.swap(split);
         }
@@ -1021,6 +1147,8 @@ struct Builder {
         p.chunk_kg2[1] = ch.chunk_kg2[1];
         p.waves_r1 = ch.waves_r1;
         p.waves_r2 = ch.waves_r2;
+        p.pw1 = ch.pw1;
+        p.pw2 = ch.pw2;
         p.vw2 = ch.vw2;
         auto rcp = [](int d) { return d <= 1 ? 0u : (unsigned)((1ull << 32) / (unsigned)d + 1); };
         p.rcp_mw = rcp(ch.mw);

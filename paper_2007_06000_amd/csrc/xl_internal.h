@@ -36,7 +36,7 @@ struct ConvW {
     int nrt;                // row tiles = ceil(cout / MF)
 };
 
-enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7, KIND_CHAIN = 8 };
+enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7, KIND_CHAIN = 8, KIND_KSPLIT = 9 };
 
 // Kernel argument of every convolution-stage kernel.
 //   KIND_SINGLE: stage 1 writes its result to global memory (one layer, the
@@ -59,6 +59,7 @@ enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_P
 //                tables ([channel group][tap] and [channel group][scale, shift] float4).
 //   KIND_DWP:    KIND_DW with a pointwise stage 2, both of stride 1, wave by wave without LDS (dw_conv.h).
 //   KIND_CHAIN:  KIND_FUSED2 of pointwise layers on split operands, the intermediate in registers (chain_conv.h).
+//   KIND_KSPLIT: KIND_FUSED2 and KIND_FUSED2P on split operands, the waves of a workgroup dividing the reductions (ksplit_conv.h).
 struct BlockParams {
     const float *x;         // block input  [N, Cin, H, W]
     float *y;               // tensor the block writes into [N, Cy, Ho, Wo]
@@ -94,6 +95,7 @@ struct BlockParams {
     int chunk_kg2[2];       // stage 2: K steps of filter staged per chunk, per convolution
     int waves_r1;           // stage-1 waves along the row-tile (Cout) direction
     int waves_r2;           // stage-2 waves along the row-tile direction
+    int pw1, pw2;           // KIND_KSPLIT: waves along the pixel tiles of either stage (the rest divide the K steps)
     int vw2;                // stage 2 lays output pixels out in virtual rows of vw2 >= tw columns
     unsigned rcp_mw, rcp_vw2, rcp_qrow;   // 2^32 / d + 1 for d = mw, vw2, iws / 4 (split-bf16 parts: iws) (0 when d is 1): x / d = mulhi(x, rcp) for x < 65536
     // The same multipliers for the other divisors of the index arithmetic (a division by a run-time value costs
@@ -304,6 +306,22 @@ struct Variant {
     X(142, KIND_CHAIN, 32, 1, 4, 2, 32, 1, 1, 1, 0, 0, 0, 2)          \
     X(143, KIND_CHAIN, 32, 1, 4, 2, 32, 2, 1, 1, 0, 0, 0, 2)
 
+// KIND_KSPLIT: column 4 = 1: layer 1 is pointwise, 3: any filter size from LDS; column 13 = 1: followed by a max pooling
+#define XL_SPLIT_LIST_E(X)                                            \
+    X(150, KIND_KSPLIT, 32, 1, 1, 1, 32, 1, 1, 0, 0, 0, 0, 2)         \
+    X(151, KIND_KSPLIT, 32, 1, 2, 1, 32, 1, 1, 0, 0, 0, 0, 2)         \
+    X(152, KIND_KSPLIT, 32, 1, 1, 2, 32, 1, 1, 0, 0, 0, 0, 2)         \
+    X(153, KIND_KSPLIT, 32, 1, 1, 2, 32, 1, 2, 0, 0, 0, 0, 2)         \
+    X(154, KIND_KSPLIT, 32, 1, 2, 2, 32, 1, 2, 0, 0, 0, 0, 2)         \
+    X(155, KIND_KSPLIT, 32, 1, 1, 1, 32, 1, 1, 0, 0, 0, 1, 2)         \
+    X(156, KIND_KSPLIT, 32, 1, 2, 1, 32, 1, 1, 0, 0, 0, 1, 2)         \
+    X(157, KIND_KSPLIT, 32, 1, 1, 2, 32, 1, 2, 0, 0, 0, 1, 2)         \
+    X(158, KIND_KSPLIT, 32, 1, 2, 2, 32, 1, 2, 0, 0, 0, 1, 2)         \
+    X(159, KIND_KSPLIT, 32, 3, 1, 1, 32, 1, 1, 0, 0, 0, 0, 1)         \
+    X(160, KIND_KSPLIT, 32, 3, 1, 2, 32, 1, 1, 0, 0, 0, 0, 1)         \
+    X(161, KIND_KSPLIT, 32, 3, 1, 2, 32, 1, 2, 0, 0, 0, 0, 1)         \
+    X(162, KIND_KSPLIT, 32, 3, 2, 2, 32, 2, 2, 0, 0, 0, 0, 1)
+
 #define XL_SPLIT_LIST_A(X)                                            \
     X(0, KIND_SINGLE, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
     X(1, KIND_SINGLE, 32, 1, 2, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
@@ -389,6 +407,7 @@ constexpr int MAX_THREADS = 512;
 constexpr int thin_row_floats(int taps) { return (taps + 15) / 16 * 16; }
 constexpr int THIN_PCB = 4;         // thin_conv_pool_kernel: output channels per LDS tile (per barrier)
 constexpr int MAX_ALTERNATIVES = 64;  // candidates per block kept for on-device tuning
+constexpr int KSPLIT_PLACES = 14;     // ... of which kernels that divide the reductions take at most these
 #ifndef XL_MIN_WAVES
 #define XL_MIN_WAVES 2
 #endif
