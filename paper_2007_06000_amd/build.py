@@ -23,7 +23,7 @@ SOURCES = [("kernels.hip", "kernels", []),
            ("plan.cpp", "plan", []), ("api.cpp", "api", []), ("static_run.hip", "static_run", [])]
 HEADERS = [os.path.join(CSRC, "xl_internal.h"), os.path.join(CSRC, "plan.h"), os.path.join(CSRC, "thin_conv.h"),
            os.path.join(CSRC, "split_conv.h"), os.path.join(CSRC, "dw_conv.h"), os.path.join(CSRC, "chain_conv.h"),
-           os.path.join(CSRC, "ksplit_conv.h"),
+           os.path.join(CSRC, "ksplit_conv.h"), os.path.join(CSRC, "stem_conv.h"),
            os.path.join(ROOT, "include", "xl.h")]
 
 # packed-fp32 instructions are switched off for all device code

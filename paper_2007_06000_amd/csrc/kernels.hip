@@ -1346,6 +1346,7 @@ __global__ void __launch_bounds__(MAX_THREADS, 4) pool_stream_kernel(const Block
 #ifndef XL_TU_SPLIT
 #include "thin_conv.h"
 #include "dw_conv.h"
+#include "stem_conv.h"
 #endif
 #ifdef XL_TU_CHAIN
 #include "chain_conv.h"
@@ -1410,6 +1411,8 @@ static BlockKernel select_kernel()
 {
     if constexpr (KIND == KIND_POOLS)
         return pool_stream_kernel<MF1, K1, NRT1, NPT1, (PX1 < 0 ? -PX1 : 4)>;
+    else if constexpr (KIND == KIND_STEM)
+        return stem_pool_kernel;
     else if constexpr (KIND == KIND_DWP)
         return dw_pointwise_kernel<MF2, NRT2, NPT2, PX1>;    // cout tiles, rows, columns of a wave's tile
     else if constexpr (KIND == KIND_THIN && NPT1 == 2)

@@ -238,6 +238,8 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     // Taking the depthwise results apart is not in t1: without this the choice was a split kernel of 11.1 and 8.2 us (30 -> 63
     // channels of 104 x 46, batch 4; 30 -> 35 of 109 x 38, batch 3) where the fp32 kernels take 8.7 to 10.1 and 6.7 to 7.6.
     if (v.pr && b.kind == KIND_DW) c.cost *= 1.2;
+    // (3 -> 64 channels at 224 x 224 with pooling, batch 8 / 1: 7.6 / 2.2 us without it, 13.5 / 4.2 measured)
+    if (v.kind == KIND_POOLS) c.cost *= 1.8;
     // executed multiply-adds: stage 1 covers every row tile once per tile (per cout slice when fused),
     // with pixels and channels rounded up to whole matrix-core tiles
     const long long tiles = (long long)c.tiles_x * c.tiles_y * b.N;
@@ -383,8 +385,11 @@ static std::vector<Choice> search_ksplit(const BlockSpec &b, const xl_plan &pl, 
     return ranked;
 }
 
-// A variant with one tile and workgroup size per block.
-static bool one_candidate(const Variant &v) { return v.kind == KIND_CHAIN; }
+// Kernels that take the filter table of thin first layers.
+static bool thin_table(const Variant &v) { return v.kind == KIND_THIN || v.kind == KIND_STEM; }
+
+// A variant with a handful of candidates per block.
+static bool few_candidates(const Variant &v) { return v.kind == KIND_CHAIN || v.kind == KIND_STEM; }
 
 static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &lds_rejected, int pr)
 {
@@ -435,9 +440,10 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                         }
                         c.occ = std::max(1, std::min({pl.lds_per_cu / c.lds_bytes, 2048 / threads, 20 / (threads / 64)}));
                         const double nwg = (double)c.tiles_x * c.tiles_y * b.N;
-                        // four multiply-adds per filter value, channel and lane, about 2.3 cycles each at full occupancy
-                        const double wave_clk = rows16 * (4.0 * taps + 24.0) * 2.3 + 1500.0;
-                        const double t_alu = nwg * (threads / 64) / (4.0 * pl.num_cus) * wave_clk / 2.4e9;
+                        // four multiply-adds per filter value, channel and lane: 4.4 cycles of the SIMD each, 6 for a wave alone on
+                        // it (to 64 channels at 224 x 224, batch 64 / 8: 64 / 25 us)
+                        const double ops = rows16 * (4.0 * taps + 24.0);
+                        const double t_alu = std::max(nwg * (threads / 64) / (4.0 * pl.num_cus) * ops * 4.4, ops * 6.0 + 1500.0) / 2.4e9;
                         const double t_mem = (double)b.alg_bytes / 8.0e12;
                         c.cost = std::max(t_alu, t_mem) + 0.15 * std::min(t_alu, t_mem);
                         c.flops_exec = (long long)(nwg * threads * rows16 * taps * 8.0);
@@ -468,7 +474,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     // one multiply-add instruction (4 cycles per wavefront) per filter value and output channel, every
                     // wavefront of the workgroup; 4 SIMDs per compute unit
                     const double nwg = (double)c.tiles_x * c.tiles_y * b.N;
-                    const double wave_clk = rows16 * (taps + (pooled ? 4.0 : 2.0)) * 4.0 + 1500.0;
+                    const double wave_clk = rows16 * (taps + (pooled ? 4.0 : 2.0)) * (pooled ? 6.8 : 4.0) + 1500.0;
                     const double t_alu = std::ceil(nwg / pl.num_cus) * (threads / 64) / 4.0 * wave_clk / 2.4e9;
                     const double t_mem = (double)b.alg_bytes / 8.0e12;
                     c.cost = std::max(t_alu, t_mem) + 0.15 * std::min(t_alu, t_mem);
@@ -478,6 +484,41 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     per_key[std::make_tuple(v.id, threads, th, tw)] = c;
                 }
             }
+            continue;
+        }
+        if (v.kind == KIND_STEM) {
+            if (pr != 0 || b.kind != KIND_POOL || b.c1.cin != 3 || b.c1.k != 3 || b.c1.stride != 2 || b.c1.pad != 0 || b.pool_k != 3 ||
+                b.pool_s != 2 || b.pool_p != 0 || pl.opts.force_tile_h > 0 || pl.opts.paper_tuner_only || (pl.opts.force_threads > 0 && pl.opts.force_threads != 256))
+                continue;
+            std::vector<Choice> few;
+            for (int th : tile_candidates(b.Ho)) {
+                if (th > 28 || (th > 8 && th % 2)) continue;
+                Choice c;
+                c.v = v;
+                c.threads = 256;
+                c.waves_r1 = c.waves_r2 = 1;
+                c.th = th;
+                c.tw = c.vw2 = 31;
+                c.mh = 2 * th + 1;
+                c.mw = 63;
+                c.ih = 4 * th + 3;
+                c.iw = 127;
+                c.tiles_y = ceil_div(b.Ho, th);
+                c.tiles_x = ceil_div(b.Wo, 31);
+                c.csplit = ceil_div(b.c1.cout, 32);
+                c.chunk_kg = 1;
+                c.occ = 3;
+                // a wave takes its rows and half of one more, alone on its SIMD at 6500 cycles a row, with others at 5200
+                const double waves = (double)c.tiles_x * c.tiles_y * c.csplit * b.N, rows = th + 0.5;
+                const double t_cu = std::max(std::ceil(waves / (4.0 * pl.num_cus)) * rows * 5200.0, 5000.0 + rows * 6500.0) / 2.4e9;
+                c.cost = std::max(t_cu, (double)b.alg_bytes / 5.4e12);
+                c.flops_exec = (long long)(waves * rows * 4 * 2.0 * 32 * 32 * 32);
+                c.ok = true;
+                few.push_back(c);
+            }
+            std::sort(few.begin(), few.end(), [](const Choice &x, const Choice &y) { return x.cost < y.cost; });
+            for (size_t i = 0; i < few.size() && i < 5; ++i) per_key[std::make_tuple(v.id, few[i].threads, few[i].th, few[i].tw)] = few[i];
+            any_ok = any_ok || !few.empty();
             continue;
         }
         const bool stream = v.kind == KIND_POOLS;          // conv -> pool as a stream of tiles: same block kind
@@ -751,10 +792,13 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
         // the best of those among the candidates, for xl_tune to time.
         const size_t reserve = MAX_ALTERNATIVES / 5;
         std::vector<Choice> small;
-        // (and the kinds with one candidate per block)
+        // (and the kinds with few candidates per block, and the best of every kernel for thin layers)
+        std::set<int> thin;
+        for (size_t i = 0; i < MAX_ALTERNATIVES - reserve; ++i) thin.insert(ranked[i].v.id);
         std::vector<bool> taken(ranked.size());
         for (size_t i = MAX_ALTERNATIVES - reserve; i < ranked.size() && small.size() < reserve; ++i)
-            if (one_candidate(ranked[i].v)) small.push_back(ranked[i]), taken[i] = true;
+            if (few_candidates(ranked[i].v) || (ranked[i].v.kind == KIND_THIN && thin.insert(ranked[i].v.id).second))
+                small.push_back(ranked[i]), taken[i] = true;
         for (size_t i = MAX_ALTERNATIVES - reserve; i < ranked.size() && small.size() < reserve; ++i)
             if (!taken[i] && ranked[i].threads == 256 && ranked[i].lds_bytes * 3 <= pl.lds_per_cu) small.push_back(ranked[i]), taken[i] = true;
         std::vector<Choice> kept;
@@ -975,7 +1019,7 @@ struct Builder {
     std::set<std::tuple<int, int, bool>> fp32_forms;
     void count_fp32_forms(const BlockSpec &b, const Choice &c)
     {
-        fp32_forms.insert(std::make_tuple(b.c1.layer, b.kind == KIND_DW ? 0 : (c.v.kind == KIND_THIN ? -1 : c.v.mf1), c.v.px1 < 0));
+        fp32_forms.insert(std::make_tuple(b.c1.layer, b.kind == KIND_DW ? 0 : (thin_table(c.v) ? -1 : c.v.mf1), c.v.px1 < 0));
         if (b.n1 == 2) fp32_forms.insert(std::make_tuple(b.c1b.layer, c.v.mf1, false));
         if (b.kind == KIND_FUSED2 || b.kind == KIND_DW || b.kind == KIND_FUSED2P)
             for (int i = 0; i < b.n2; ++i) fp32_forms.insert(std::make_tuple(b.c2[i].layer, c.v.mf2, false));
@@ -990,14 +1034,15 @@ struct Builder {
         return found;
     }
 
-    // The first n of a list by cost, with at most six of one variant before others had theirs, and before all the kinds with one
-    // candidate per block; by cost again.
+    // The first n of a list by cost, with at most six of one variant before others had theirs, and before all the kinds with few
+    // candidates per block and the best of every kernel for thin layers; by cost again.
     static void keep_best(std::vector<Choice> &l, size_t n, int of_a_variant = 6)
     {
         auto by_cost = [](const Choice &x, const Choice &y) { return x.cost < y.cost; };
         std::map<int, int> seen;
         std::stable_sort(l.begin(), l.end(), by_cost);
-        auto others = std::stable_partition(l.begin(), l.end(), [&](const Choice &c) { return one_candidate(c.v); });
+        std::set<int> thin;
+        auto others = std::stable_partition(l.begin(), l.end(), [&](const Choice &c) { return few_candidates(c.v) || (c.v.kind == KIND_THIN && thin.insert(c.v.id).second); });
         std::stable_partition(others, l.end(), [&](const Choice &c) { return ++seen[c.v.id] <= of_a_variant; });
         if (l.size() > n) l.resize(n);
         std::stable_sort(l.begin(), l.end(), by_cost);
@@ -1070,7 +1115,7 @@ struct Builder {
         st.sc_id = sc_id;
         st.conv_layer[0] = b.c1.layer;
         st.conv_layer[1] = st.conv_layer[2] = -1;
-        st.packed[0] = packed_index(b.c1.layer, b.kind == KIND_DW ? 0 : (ch.v.kind == KIND_THIN ? -1 : ch.v.mf1), ch.v.px1 < 0, ch.v.pr1);
+        st.packed[0] = packed_index(b.c1.layer, b.kind == KIND_DW ? 0 : (thin_table(ch.v) ? -1 : ch.v.mf1), ch.v.px1 < 0, ch.v.pr1);
         st.packed[1] = st.packed[2] = -1;
         BlockParams &p = st.bp;
         memset(&p, 0, sizeof p);
@@ -1140,7 +1185,7 @@ struct Builder {
         p.tiles_y = ch.tiles_y;
         p.csplit = ch.csplit;
         p.nblocks = ch.tiles_x * ch.tiles_y * ch.csplit * b.N;
-        if (ch.v.kind == KIND_DWP) p.nblocks = ceil_div(p.nblocks, 4);      // four waves with a tile each
+        if (ch.v.kind == KIND_DWP || ch.v.kind == KIND_STEM) p.nblocks = ceil_div(p.nblocks, 4);      // four waves with a tile each
         if (ch.v.kind == KIND_CHAIN) p.nblocks = (int)(((long long)b.N * b.H * b.W + 127) / 128);      // pixels of all images in one row
         p.chunk_kg = ch.chunk_kg;
         p.chunk_kg2[0] = ch.chunk_kg2[0];
@@ -1196,12 +1241,12 @@ struct Builder {
         gi.tiles_x = ch.tiles_x;
         gi.cout_split = ch.csplit;
         gi.workgroups = ch.tiles_x * ch.tiles_y * ch.csplit * b.N;
-        if (ch.v.kind == KIND_DWP) gi.workgroups = ceil_div(gi.workgroups, 4);
+        if (ch.v.kind == KIND_DWP || ch.v.kind == KIND_STEM) gi.workgroups = ceil_div(gi.workgroups, 4);
         if (ch.v.kind == KIND_CHAIN) gi.workgroups = (int)(((long long)b.N * b.H * b.W + 127) / 128);
         gi.threads = ch.threads;
         gi.lds_bytes = ch.lds_bytes;
         gi.workgroups_per_cu = ch.occ;
-        gi.chunk_channels = ch.v.kind == KIND_THIN ? b.c1.cin : ch.chunk_kg * kc_of(ch.v.mf1, ch.v.pr1);
+        gi.chunk_channels = thin_table(ch.v) ? b.c1.cin : ch.chunk_kg * kc_of(ch.v.mf1, ch.v.pr1);
         gi.flops_executed = ch.flops_exec;
         gi.precision = ch.v.pr == 1 ? XL_PRECISION_BF16X3 : XL_PRECISION_FP32;
         if (b.kind == KIND_SINGLE) {

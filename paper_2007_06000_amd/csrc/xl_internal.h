@@ -36,7 +36,7 @@ struct ConvW {
     int nrt;                // row tiles = ceil(cout / MF)
 };
 
-enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7, KIND_CHAIN = 8, KIND_KSPLIT = 9 };
+enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7, KIND_CHAIN = 8, KIND_KSPLIT = 9, KIND_STEM = 10 };
 
 // Kernel argument of every convolution-stage kernel.
 //   KIND_SINGLE: stage 1 writes its result to global memory (one layer, the
@@ -59,6 +59,7 @@ enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_P
 //                tables ([channel group][tap] and [channel group][scale, shift] float4).
 //   KIND_DWP:    KIND_DW with a pointwise stage 2, both of stride 1, wave by wave without LDS (dw_conv.h).
 //   KIND_CHAIN:  KIND_FUSED2 of pointwise layers on split operands, the intermediate in registers (chain_conv.h).
+//   KIND_STEM:   KIND_POOL for 3 input channels, 3x3 with stride 2 -> pooling 3x3 with stride 2, on the bf16 matrix cores (stem_conv.h).
 //   KIND_KSPLIT: KIND_FUSED2 and KIND_FUSED2P on split operands, the waves of a workgroup dividing the reductions (ksplit_conv.h).
 struct BlockParams {
     const float *x;         // block input  [N, Cin, H, W]
@@ -268,6 +269,8 @@ struct Variant {
     /* ... 3x3 stride 2 -> pooling 3x3 stride 2 with a 2x2 block of convolution outputs per lane (column 6 = 2) */ \
     X(140, KIND_THIN, 32, 3, 3, 2, 0, 0, 0, 0, 3, 0, 0)           \
     X(141, KIND_THIN, 32, 3, 1, 2, 0, 0, 0, 0, 3, 0, 0)           \
+    /* ... the same shape with 3 channels on the bf16 matrix cores */ \
+    X(170, KIND_STEM, 32, 3, 1, 1, 0, 0, 0, 0, 0, 0, 0)           \
     /* conv -> maxpool */                                 \
     X(36, KIND_POOL, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0)             \
     X(37, KIND_POOL, 32, 1, 2, 1, 0, 0, 0, 0, 0, 0, 0)             \
