@@ -226,6 +226,7 @@ class Plan:
         self.handle = handle
         self.nweights = 3 * nl
         self.ntensors = nt
+        self._tensor_array = ctypes.c_void_p * nt
 
     def close(self):
         if getattr(self, "handle", None):
@@ -280,11 +281,12 @@ class Plan:
                                      ctypes.c_void_p(stream)))
 
     def run(self, tensor_ptrs: Dict[int, int], workspace_ptr: int, stream: int = 0, fused: bool = True):
-        arr = (ctypes.c_void_p * self.ntensors)()
+        arr = self._tensor_array()
         for t, p in tensor_ptrs.items():
             arr[t] = p
-        self._check(lib().xl_run(self.handle, arr, self.ntensors, ctypes.c_void_p(workspace_ptr),
-                                 ctypes.c_void_p(stream), int(fused)))
+        st = _lib.xl_run(self.handle, arr, self.ntensors, workspace_ptr, stream, fused)     # (the plan has loaded the library)
+        if st != XL_OK:
+            self._check(st)
 
     def run_static(self, weight_ptrs: Optional[Sequence[Optional[int]]], tensor_ptrs: Dict[int, int], stream: int = 0,
                    fused: bool = True, relayout: bool = True):

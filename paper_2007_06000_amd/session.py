@@ -43,7 +43,8 @@ class Session:
 
     @property
     def stream(self) -> int:
-        return torch.cuda.current_stream(self.dev).cuda_stream
+        # (the handle alone, without a Stream object around it: 0.2 instead of 1.8 us of a pass's submission)
+        return torch._C._cuda_getCurrentRawStream(self.dev.index)
 
     def add_workspace(self) -> int:
         """One more prepared workspace (for callers that rotate over several, e.g. cache-cold timing); returns its index."""
@@ -53,11 +54,13 @@ class Session:
         return len(self.workspaces) - 1
 
     def run(self, fused: bool = True, x: Optional[torch.Tensor] = None, y: Optional[torch.Tensor] = None, ws: int = 0):
-        ptrs = dict(self.tensor_ptrs)
-        if x is not None:
-            ptrs[self.workload.input_id] = x.data_ptr()
-        if y is not None:
-            ptrs[self.workload.output_id] = y.data_ptr()
+        ptrs = self.tensor_ptrs
+        if x is not None or y is not None:
+            ptrs = dict(ptrs)
+            if x is not None:
+                ptrs[self.workload.input_id] = x.data_ptr()
+            if y is not None:
+                ptrs[self.workload.output_id] = y.data_ptr()
         self.plan.run(ptrs, self.workspaces[ws].data_ptr(), self.stream, fused)
         return self.y if y is None else y
 
