@@ -296,6 +296,9 @@ static std::vector<Choice> search_ksplit(const BlockSpec &b, const xl_plan &pl, 
     // (the kernel divides step numbers by 9 and 25 with short multipliers)
     if (nkg1 * taps1 > 4096 || nrt1 * 2 * 25 > 4096) return ranked;
     const int s2 = b.c2[0].stride;
+    std::vector<const Variant *> fit;
+    for (const Variant &v : variants())
+        if (v.kind == KIND_KSPLIT && v.pr == pr && (v.px1 != 0) == pool2 && (v.k1 == 1) == (b.c1.k == 1) && v.nrt1 <= nrt1) fit.push_back(&v);
     auto pow2 = [](int v) { int p = 1; while (p < v) p *= 2; return p; };
     for (auto [th, tw] : tiles) {
         Choice t;
@@ -314,9 +317,9 @@ static std::vector<Choice> search_ksplit(const BlockSpec &b, const xl_plan &pl, 
         t.chunk_kg = nkg1;
         const int mid = nrt1 * 4 * np * t.mh * t.mw * 4, input = b.c1.k == 1 ? 0 : nkg1 * 2 * np1 * t.ih * t.iw * 4;
         if ((mid + input) * 4 > pl.lds_budget) continue;
-        for (const Variant &v : variants()) {
-            if (v.kind != KIND_KSPLIT || v.pr != pr || (v.px1 != 0) != pool2 || (v.k1 == 1) != (b.c1.k == 1)) continue;
-            if (v.nrt1 > nrt1 || v.npt1 > npt1 || v.npt2 > npt2) continue;
+        for (const Variant *variant : fit) {
+            const Variant &v = *variant;
+            if (v.npt1 > npt1 || v.npt2 > npt2) continue;
             for (int threads : {256, 512}) {
                 if (pl.opts.force_threads > 0 && pl.opts.force_threads != threads) continue;
                 const int nw = threads / 64, rw1 = pow2(ceil_div(nrt1, v.nrt1)), pw1 = pow2(ceil_div(npt1, v.npt1));
@@ -783,31 +786,33 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
         }
     lds_rejected = !any_ok && any_lds_reject;
     // ranked list: the model's best first, then the best of other (variant, threads, tile) combinations
-    std::vector<Choice> ranked;
-    for (auto &kv : per_key) ranked.push_back(kv.second);
-    std::sort(ranked.begin(), ranked.end(), [](const Choice &a, const Choice &b) { return a.cost < b.cost; });
+    std::vector<const Choice *> ranked;         // (a Choice is hundreds of bytes: sorted themselves they were a tenth of the time a plan takes)
+    for (auto &kv : per_key) ranked.push_back(&kv.second);
+    std::sort(ranked.begin(), ranked.end(), [](const Choice *a, const Choice *b) { return a->cost < b->cost; });
     if (ranked.size() > (size_t)MAX_ALTERNATIVES) {
         // The model assumes at most two waves per SIMD; kernels that need fewer registers run three
         // 256-thread workgroups per CU when their LDS share allows it, which the model cannot rank.  Keep
         // the best of those among the candidates, for xl_tune to time.
         const size_t reserve = MAX_ALTERNATIVES / 5;
-        std::vector<Choice> small;
+        std::vector<const Choice *> small;
         // (and the kinds with few candidates per block, and the best of every kernel for thin layers)
         std::set<int> thin;
-        for (size_t i = 0; i < MAX_ALTERNATIVES - reserve; ++i) thin.insert(ranked[i].v.id);
+        for (size_t i = 0; i < MAX_ALTERNATIVES - reserve; ++i) thin.insert(ranked[i]->v.id);
         std::vector<bool> taken(ranked.size());
         for (size_t i = MAX_ALTERNATIVES - reserve; i < ranked.size() && small.size() < reserve; ++i)
-            if (few_candidates(ranked[i].v) || (ranked[i].v.kind == KIND_THIN && thin.insert(ranked[i].v.id).second))
+            if (few_candidates(ranked[i]->v) || (ranked[i]->v.kind == KIND_THIN && thin.insert(ranked[i]->v.id).second))
                 small.push_back(ranked[i]), taken[i] = true;
         for (size_t i = MAX_ALTERNATIVES - reserve; i < ranked.size() && small.size() < reserve; ++i)
-            if (!taken[i] && ranked[i].threads == 256 && ranked[i].lds_bytes * 3 <= pl.lds_per_cu) small.push_back(ranked[i]), taken[i] = true;
-        std::vector<Choice> kept;
+            if (!taken[i] && ranked[i]->threads == 256 && ranked[i]->lds_bytes * 3 <= pl.lds_per_cu) small.push_back(ranked[i]), taken[i] = true;
+        std::vector<const Choice *> kept;
         for (size_t i = 0; i < ranked.size() && kept.size() < MAX_ALTERNATIVES - small.size(); ++i)
             if (!taken[i]) kept.push_back(ranked[i]);
         kept.insert(kept.end(), small.begin(), small.end());
         ranked.swap(kept);
     }
-    return ranked;
+    std::vector<Choice> out;
+    for (const Choice *c : ranked) out.push_back(*c);
+    return out;
 }
 
 // ----------------------------------------------------------------------------
