@@ -412,8 +412,11 @@ __global__ void __launch_bounds__(MAX_THREADS, 2) ksplit_kernel(const BlockParam
     };
     auto open2 = [&](const ConvW &c, int rp) { k2.open(c, rp + w2.r * NRT2, w2.k, w2.lk); };
     {
+        // (siblings of 5 and 8 row tiles in four slices: the last slice has none of the first sibling's)
         const BlockParams &P = block_params();
-        open2(P.c2[0], rows_of(P.c2[0].nrt).first);
+        const Rows rows0 = rows_of(P.c2[0].nrt);
+        const ConvW &c = P.c2[rows0.first >= rows0.end && convs > 1 ? 1 : 0];
+        open2(c, rows_of(c.nrt).first);
     }
 
     // ---- epilogue of layer 1: the LDS tile of the intermediate

@@ -97,3 +97,34 @@ def test_values_without_bf16_parts(wl, special):
             y = s.output(True)
             assert (np.isnan(y) == np.isnan(ref)).all() and (np.isfinite(y) == np.isfinite(ref)).all(), (where, v)
             assert (np.abs(y[fin] - ref[fin]) <= 1e-4 + 1e-4 * np.abs(ref[fin])).all(), (where, v)
+
+
+def siblings(cin, hw, s, e1, e3):
+    b = W._Builder(f"siblings_{cin}_{s}_{e1}_{e3}", 1, cin, hw, hw)
+    sq = b.conv(0, s, 1, bias=True, relu=True, name="squeeze")
+    a = b.conv(sq, e1, 1, bias=True, relu=True, name="expand1x1")
+    c = b.conv(sq, e3, 3, pad=1, bias=True, relu=True, name="expand3x3")
+    t = b.concat(a, c, name="concat")
+    b.group("split", 0)
+    return b.done(t, "relu_normal", 37)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("wl", [siblings(64, 9, 32, 160, 256), siblings(64, 9, 32, 256, 160), siblings(40, 11, 48, 33, 300)],
+                         ids=lambda a: getattr(a, "name", ""))
+def test_slices_without_rows_of_one_sibling(wl, precision):
+    """Four slices of 5 and 8, or 2 and 10, row tiles: a workgroup that has rows of one sibling only."""
+    from paper_2007_06000_amd.session import Session
+    x, params = W.make_tensors(wl)
+    ref = xlo.forward(wl, x, params)
+    s = Session(wl, x, params, precision=precision, force_cout_split=4)
+    found = candidates(s.plan, 350 if precision else 550)
+    assert found
+    for v, cs in found.items():
+        for c in cs:
+            print(f"[case] {wl.name} kernel {v} candidate {s.plan.candidate_info(True, 0, c)}", flush=True)
+            s.plan.select_candidate(True, 0, c)
+            y = s.output(True)
+            # (bounds as in test_against_the_oracle)
+            assert np.linalg.norm(y - ref) <= (2.0 ** -12 if precision else 2.0 ** -20) * np.linalg.norm(ref), (v, c)
