@@ -284,7 +284,7 @@ class Plan:
         arr = self._tensor_array()
         for t, p in tensor_ptrs.items():
             arr[t] = p
-        st = _lib.xl_run(self.handle, arr, self.ntensors, workspace_ptr, stream, fused)     # (the plan has loaded the library)
+        st = _lib.xl_run(self.handle, arr, self.ntensors, workspace_ptr, stream, int(fused))     # (the plan has loaded the library)
         if st != XL_OK:
             self._check(st)
 

@@ -188,6 +188,14 @@ def test_the_static_scratch_takes_plans_by_the_size_of_their_fp32_filters():
     assert split == [False, True]
 
 
+@pytest.mark.parametrize("fused", [True, 1, 1.0, "1"])
+def test_run_takes_every_number_for_its_mode(fused):
+    # (the workspace is looked at before the device: the call reaches the library)
+    with pytest.raises(B.XlError) as e:
+        B.Plan(W.config(1)).run({}, 256, 0, fused)
+    assert e.value.status == B.XL_E_STATE
+
+
 def test_global_average_pooling_block_needs_the_image_in_one_tile():
     ok = B.Plan(W.conv_gap_generic(2, 16, 13, 13, 64, 1, 0, 1))
     q = ok.query(0)
