@@ -268,7 +268,8 @@ xl_status xl_tune(xl_plan *plan, const void *const *tensors, int ntensors,
  *     XL_STATIC_SCRATCH_BYTES (configs 1-4 at their full sizes fit; config 5 up to batch 4).  Plans of precision
  *     XL_PRECISION_FP32 that pass this always fit the array: the planner leaves kernels on bf16 parts out of the blocks with
  *     the largest filters where they would not.  With XL_PRECISION_BF16X3 also when the whole workspace exceeds twice
- *     XL_STATIC_SCRATCH_BYTES.
+ *     XL_STATIC_SCRATCH_BYTES, the three-part filters of pointwise first layers aside: the kernels that read those are left
+ *     out where they alone would not fit.
  *   - relayout != 0: the filters are re-laid out into the array first (as xl_prepare does), from
  *     `weights` / `nweights`; needed on the first call and whenever filter values change.
  *     relayout == 0: the filters are re-laid out only if the array's last user on this GPU was another

@@ -1030,7 +1030,9 @@ struct Builder {
             for (int i = 0; i < b.n2; ++i) fp32_forms.insert(std::make_tuple(b.c2[i].layer, c.v.mf2, false));
     }
 
-    std::set<int> fp32_layers;      // layers whose blocks get no kernels on split operands (build_plan)
+    // Layers whose blocks get no kernels on split operands, or, in a plan on two parts, none that take the layer on three
+    // (build_plan).
+    std::set<int> fp32_layers;
     bool has_fp32_layer(const BlockSpec &b) const
     {
         bool found = fp32_layers.count(b.c1.layer) || (b.n1 == 2 && fp32_layers.count(b.c1b.layer));
@@ -1073,10 +1075,15 @@ struct Builder {
         // without the cap 0.5 %.)
         std::vector<Choice> split;
         std::vector<Choice> ksplit;
-        if (!has_fp32_layer(b)) {
-            const int pr = pl.opts.precision == XL_PRECISION_BF16X3 ? 1 : 2;
+        const int pr = pl.opts.precision == XL_PRECISION_BF16X3 ? 1 : 2;
+        if (pr == 1 || !has_fp32_layer(b)) {
             split = search(b, pl, ignored, pr);
             if (!split.empty()) ksplit = search_ksplit(b, pl, pr);
+        }
+        if (pr == 1 && has_fp32_layer(b)) {
+            auto on_three = [](const Choice &c) { return c.v.pr1 == 2; };
+            split.erase(std::remove_if(split.begin(), split.end(), on_three), split.end());
+            ksplit.erase(std::remove_if(ksplit.begin(), ksplit.end(), on_three), ksplit.end());
         }
         if (!split.empty()) {
             // (the kernels that divide the reductions have places of their own, taken from the fp32 ones', which are seldom the
@@ -1624,7 +1631,9 @@ xl_status build_plan(xl_plan &pl, const xl_group *groups, int ngroups)
     // A plan that xl_run_static takes with the filters of fp32 kernels alone has to fit its array with all of its filters.
     // Three bf16 parts take 1.5 times the bytes of the fp32 form, up to 3 times where channels fill a 16-channel K step or a
     // 32-row tile badly; where that is too much (2500 -> 700 channels, 3x3: 60.8 MB, 151.9 MB with three parts) the blocks
-    // of the layers with the largest filters stay on fp32 kernels.
+    // of the layers with the largest filters stay on fp32 kernels.  In a plan on two parts (XL_PRECISION_BF16X3) the kernels that
+    // take a pointwise first layer on three are left out in the same way, as long as that makes it fit (15000 -> 512 -> {32, 32}
+    // channels: 94.4 MB, 140.5 with them).
     std::set<int> fp32_layers;
     for (;;) {
         Builder b(pl);
@@ -1632,10 +1641,12 @@ xl_status build_plan(xl_plan &pl, const xl_group *groups, int ngroups)
         const xl_status s = b.build(groups, ngroups);
         if (s != XL_OK) return s;
         const size_t room = XL_STATIC_SCRATCH_BYTES + STATIC_SPLIT_BYTES;
-        if (pl.opts.precision != XL_PRECISION_FP32 || pl.static_bytes > XL_STATIC_SCRATCH_BYTES || pl.workspace_bytes <= room) break;
+        if (pl.static_bytes > XL_STATIC_SCRATCH_BYTES || pl.workspace_bytes <= room) break;
         std::vector<std::pair<size_t, int>> split;
+        size_t all = 0;
         for (const PackedFilter &p : pl.packed)
-            if (p.pr == 2) split.push_back({p.bytes, p.layer});
+            if (p.pr == 2) split.push_back({p.bytes, p.layer}), all += p.bytes;
+        if (pl.opts.precision != XL_PRECISION_FP32 && (split.empty() || pl.workspace_bytes - all > room)) break;
         std::sort(split.rbegin(), split.rend());
         size_t saved = 0;
         for (size_t i = 0; i < split.size() && pl.workspace_bytes - saved > room; ++i) {

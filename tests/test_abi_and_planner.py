@@ -188,6 +188,26 @@ def test_the_static_scratch_takes_plans_by_the_size_of_their_fp32_filters():
     assert split == [False, True]
 
 
+@pytest.mark.parametrize("wl", [W.config(3, n=1, cin=15000, hw=7, s=512, e=32), W.config(3, n=1, cin=30000, hw=7, s=256, e=32),
+                                W.split_fire_pool(n=1, cin=60000, hw=9, s=128, e=32)], ids=["512", "256", "128_pool"])
+def test_the_static_scratch_takes_plans_on_two_parts_whose_first_layer_fits_without_a_third(wl):
+    p = B.Plan(wl, precision=1)
+    ids = {p.candidate_info(True, 0, c)["variant"] for c in range(p.num_candidates(True, 0))}
+    assert ids & set(range(200, 320)) and not ids & set(range(350, 359)), ids
+    assert p.workspace_bytes() <= 2 * B.XL_STATIC_SCRATCH_BYTES
+    with pytest.raises(B.XlError) as e:
+        p.run_static(None, {})
+    assert e.value.status != B.XL_E_SCRATCH
+
+
+def test_plans_on_two_parts_that_fit_keep_their_kernels_on_three():
+    # (the last takes more than the static scratch holds whatever is left out)
+    for wl in (W.config(3, n=1, cin=8192, hw=7, s=512, e=512), W.config(3, n=64, cin=64, hw=112, s=16, e=64), W.config(3, n=1, cin=24000, hw=7, s=512, e=32)):
+        p = B.Plan(wl, precision=1)
+        ids = {p.candidate_info(True, 0, c)["variant"] for c in range(p.num_candidates(True, 0))}
+        assert ids & set(range(350, 359)), ids
+
+
 @pytest.mark.parametrize("fused", [True, 1, 1.0, "1"])
 def test_run_takes_every_number_for_its_mode(fused):
     # (the workspace is looked at before the device: the call reaches the library)
