@@ -491,7 +491,8 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
         }
         if (v.kind == KIND_STEM) {
             if (pr != 0 || b.kind != KIND_POOL || b.c1.cin != 3 || b.c1.k != 3 || b.c1.stride != 2 || b.c1.pad != 0 || b.pool_k != 3 ||
-                b.pool_s != 2 || b.pool_p != 0 || pl.opts.force_tile_h > 0 || pl.opts.paper_tuner_only || (pl.opts.force_threads > 0 && pl.opts.force_threads != 256))
+                b.pool_s != 2 || b.pool_p != 0 || pl.opts.force_tile_h > 0 || pl.opts.paper_tuner_only || (pl.opts.force_threads > 0 && pl.opts.force_threads != 256) ||
+                (pl.opts.force_cout_split > 0 && pl.opts.force_cout_split != ceil_div(b.c1.cout, 32)))
                 continue;
             std::vector<Choice> few;
             for (int th : tile_candidates(b.Ho)) {

@@ -34,6 +34,15 @@ def test_where_the_kernels_are_planned():
         assert not candidates(B.Plan(wl)), wl.name
 
 
+@pytest.mark.parametrize("cout", [32, 64])
+def test_a_fixed_number_of_workgroups_per_tile_is_kept(cout):
+    from paper_2007_06000_amd import binding as B
+    for split in (1, 2, 3):
+        p = B.Plan(stem(8, 224, 224, cout), force_cout_split=split)
+        mine = {p.candidate_info(True, 0, c)["cout_split"] for cs in candidates(p).values() for c in cs}
+        assert mine == ({split} if split == cout // 32 else set()), split
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("wl", CASES, ids=lambda w: w.name)
 def test_against_the_oracle(wl):
