@@ -142,6 +142,12 @@ static int pick_chunk(int nkg, int x_units_per_kg, int w_items_per_kg, int max_u
     return std::min(cap, ceil_div(nkg, nchunks));       // balance the chunks
 }
 
+// The block that KIND_STEM takes: 3x3 of 3 channels with stride 2 -> pooling 3x3 with stride 2, neither padded.
+static bool stem_shape(const BlockSpec &b)
+{
+    return b.kind == KIND_POOL && b.c1.cin == 3 && b.c1.k == 3 && b.c1.stride == 2 && b.c1.pad == 0 && b.pool_k == 3 && b.pool_s == 2 && b.pool_p == 0;
+}
+
 // Model of one candidate.  Times in seconds on a nominal MI355X (2.4 GHz, 8 TB/s).
 static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
 {
@@ -238,8 +244,12 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     // Taking the depthwise results apart is not in t1: without this the choice was a split kernel of 11.1 and 8.2 us (30 -> 63
     // channels of 104 x 46, batch 4; 30 -> 35 of 109 x 38, batch 3) where the fp32 kernels take 8.7 to 10.1 and 6.7 to 7.6.
     if (v.pr && b.kind == KIND_DW) c.cost *= 1.2;
-    // (3 -> 64 channels at 224 x 224 with pooling, batch 8 / 1: 7.6 / 2.2 us without it, 13.5 / 4.2 measured)
-    if (v.kind == KIND_POOLS) c.cost *= 1.8;
+    // The stream kernels' estimate is short of the truth: against the stem kernel (3 -> 64 channels at 224 x 224, batch 8 / 4 / 1: 7.6 /
+    // 3.8 / 2.3 us without the factor against 6.5 / 6.2 / 6.2; xl_profile: 17.9 / 12.3 / 8.6 us and 12.2 / 10.0 / 9.5) and for
+    // pointwise layers of more than 4 channels (23 blocks whose choice it changes: 5 % faster, from 0.79 to 1.15 times the time).
+    // Not elsewhere: it made the choice of 3x3 blocks slower (21: by 8 %, up to 51 %), and of pointwise ones of up to 4
+    // channels (15) no better, with xl_tune 11 % behind in one whose list lost its stream kernels.
+    if (v.kind == KIND_POOLS && (stem_shape(b) || (b.c1.k == 1 && b.c1.cin > 4))) c.cost *= 1.8;
     // executed multiply-adds: stage 1 covers every row tile once per tile (per cout slice when fused),
     // with pixels and channels rounded up to whole matrix-core tiles
     const long long tiles = (long long)c.tiles_x * c.tiles_y * b.N;
@@ -490,8 +500,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             continue;
         }
         if (v.kind == KIND_STEM) {
-            if (pr != 0 || b.kind != KIND_POOL || b.c1.cin != 3 || b.c1.k != 3 || b.c1.stride != 2 || b.c1.pad != 0 || b.pool_k != 3 ||
-                b.pool_s != 2 || b.pool_p != 0 || pl.opts.force_tile_h > 0 || pl.opts.paper_tuner_only || (pl.opts.force_threads > 0 && pl.opts.force_threads != 256) ||
+            if (pr != 0 || !stem_shape(b) || pl.opts.force_tile_h > 0 || pl.opts.paper_tuner_only || (pl.opts.force_threads > 0 && pl.opts.force_threads != 256) ||
                 (pl.opts.force_cout_split > 0 && pl.opts.force_cout_split != ceil_div(b.c1.cout, 32)))
                 continue;
             std::vector<Choice> few;

@@ -20,7 +20,8 @@
 // pixels apart.  Time per pass, before -> here: to 64 channels at 224 x 224, batch 64: 67 -> 40 us, batch 8: 16 -> 10.8; to 96 at
 // 150 x 200, batch 16: 29.5 -> 15.5; to 32 at 224 x 224, batch 50: 32 -> 21.  64 channels per wave, which takes a pixel apart once,
 // was slower (46 us at batch 64: 248 registers, two waves per SIMD), as was holding a third of the filter in LDS (equal).
-// Where the chip is not filled (batch 1: 6.7 us) the stream kernel stays ahead.
+// Where the chip is not filled the stream kernel stays ahead (to 64 channels at 224 x 224, xl_profile with its 2 to 3 us of events, batch 1:
+// 8.6 us there, 9.5 here; batch 2: 9.5 and 9.6; batch 4: 12.3 and 10.0).
 // A wave in which a value has no bf16 parts, or one is so large that a sum might overflow, takes fp32 matrix operations instead.
 //
 // BlockParams used: x, y, N, H, W, Ho, Wo, Cy, coff1, c1 (wp, aff: the tables of thin_conv_kernel; cout, relu), th (pooled rows of a
