@@ -78,19 +78,22 @@ __device__ __forceinline__ float relu_from(float v, int lo)
 }
 __device__ __forceinline__ int relu_bound(int on) { return on ? 0 : INT_MIN; }
 
-// The kernel argument (BlockParams and the workgroup size behind it) is ten cache lines that no launch before has read.  Loaded
-// where its numbers are first used, line after line, each costs a trip to memory, which the first waves of a launch
-// wait for one by one; this asks for one number of every line at once.  Called first in every kernel.
+// The kernel argument is eight cache lines that no launch before has read: BlockParams and, in the last one, the block count and
+// the workgroup size that the compiler puts behind it (6 numbers of 2 and 3 of 4 bytes).  Loaded where its numbers are first used, line after
+// line, each costs a trip to memory, which the first waves of a launch wait for one by one; this asks for one number of every line at
+// once.  Every number is one of BlockParams: nothing is read that a kernel might not have been given.  Called first in every kernel.
 __device__ __forceinline__ void touch_arguments()
 {
-    static_assert(sizeof(BlockParams) > 448 && sizeof(BlockParams) <= 576, "lines 0 to 9 hold the argument and the workgroup size");
+    static_assert(sizeof(BlockParams) >= 0x1c0 + 4, "the loads read BlockParams");
+    static_assert((sizeof(BlockParams) + 7) / 8 * 8 + 18 <= 0x200, "eight lines hold the argument and what stands behind it");
     const unsigned long long p = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
-    unsigned t[10];
-    asm volatile("s_load_dword %0, %10, 0x0\n\ts_load_dword %1, %10, 0x40\n\ts_load_dword %2, %10, 0x80\n\ts_load_dword %3, %10, 0xc0\n\t"
-                 "s_load_dword %4, %10, 0x100\n\ts_load_dword %5, %10, 0x140\n\ts_load_dword %6, %10, 0x180\n\ts_load_dword %7, %10, 0x1c0\n\t"
-                 "s_load_dword %8, %10, 0x200\n\ts_load_dword %9, %10, 0x240\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&s"(t[0]), "=&s"(t[1]), "=&s"(t[2]), "=&s"(t[3]), "=&s"(t[4]), "=&s"(t[5]), "=&s"(t[6]), "=&s"(t[7]), "=&s"(t[8]), "=&s"(t[9])
+    unsigned t[8];
+    asm volatile("s_load_dword %0, %8, 0x0\n\ts_load_dword %1, %8, 0x40\n\ts_load_dword %2, %8, 0x80\n\ts_load_dword %3, %8, 0xc0\n\t"
+                 "s_load_dword %4, %8, 0x100\n\ts_load_dword %5, %8, 0x140\n\ts_load_dword %6, %8, 0x180\n\ts_load_dword %7, %8, 0x1c0\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(t[0]), "=&s"(t[1]), "=&s"(t[2]), "=&s"(t[3]), "=&s"(t[4]), "=&s"(t[5]), "=&s"(t[6]), "=&s"(t[7])
                  : "s"(p));
+    asm volatile("" : : "s"(t[0]), "s"(t[1]), "s"(t[2]), "s"(t[3]), "s"(t[4]), "s"(t[5]), "s"(t[6]), "s"(t[7]));
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
