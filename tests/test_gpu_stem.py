@@ -34,6 +34,17 @@ def test_where_the_kernels_are_planned():
         assert not candidates(B.Plan(wl)), wl.name
 
 
+@pytest.mark.parametrize("n,h,w,c", [(8, 224, 224, 64), (64, 224, 224, 64), (16, 150, 200, 96)])
+def test_the_choice_where_the_chip_is_filled_in_either_precision(n, h, w, c):
+    from paper_2007_06000_amd import binding as B
+    for precision in (0, 1):
+        p = B.Plan(stem(n, h, w, c), precision=precision)
+        assert p.candidate_info(True, 0, 0)["variant"] == 170, precision
+        # (two parts: the kernels on fp32 operations stay behind)
+        costs = [(p.candidate_info(True, 0, i)["variant"] < 170, p.candidate_info(True, 0, i)["model_cost_us"]) for i in range(p.num_candidates(True, 0))]
+        assert costs == (sorted(costs) if precision else sorted(costs, key=lambda t: t[1]))
+
+
 @pytest.mark.parametrize("cout", [32, 64])
 def test_a_fixed_number_of_workgroups_per_tile_is_kept(cout):
     from paper_2007_06000_amd import binding as B
