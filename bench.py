@@ -138,11 +138,23 @@ def launch_rows(s, mfma_peak, reps):
 
 def apply_candidates(plan, saved):
     """Adopt a saved launch configuration: first which blocks run layer by layer (that fixes the launch list of
-    the fused path), then the candidate of every launch."""
+    the fused path), then the candidate of every launch.  A candidate is saved by its place in the planner's list, which another
+    build may order differently, and by what it was there: one that is something else now ends the run (a file without the second
+    part is taken as it stands)."""
     for g in range(plan.num_groups):
         plan.set_block_fused(g, g not in saved["layer_by_layer_blocks"])
-    for fused, launch, cand in saved["candidates"]:
+    for fused, launch, cand, *was in saved["candidates"]:
+        if was and was[0] != configuration(plan, bool(fused), launch, cand):
+            raise SystemExit(f"bench.py: candidate {cand} of launch {launch} (fused={fused}) is not the one that was saved: the file is of another build")
         plan.select_candidate(bool(fused), launch, cand)
+
+
+def configuration(plan, fused, launch, cand):
+    """Kernel variant, workgroup size, tile and output-channel split of a candidate; None if there is no such candidate."""
+    if cand >= plan.num_candidates(fused, launch):
+        return None
+    info = plan.candidate_info(fused, launch, cand)
+    return [info[k] for k in ("variant", "threads", "tile_h", "tile_w", "cout_split")]
 
 
 def bench_workload(cfg, steps, warmup, torch, np, W, Session, cold=True, precision=0, candidates=None, fused_only=False,
@@ -318,7 +330,8 @@ def main():
         cands = []
         for fused in (1, 0):
             for l in range(s.plan.num_launches(bool(fused))):
-                cands.append([fused, l, s.plan.candidate_info(bool(fused), l)["candidate"]])
+                cand = s.plan.candidate_info(bool(fused), l)["candidate"]
+                cands.append([fused, l, cand, configuration(s.plan, bool(fused), l, cand)])
         json.dump({"workload": wl.name, "batch": wl.batch, "precision": args.precision,
                    "layer_by_layer_blocks": switched_blocks(s.plan, wl),
                    "candidates": cands}, open(args.save_candidates, "w"))

@@ -1,6 +1,8 @@
 """bench.py's line on stdout: complete in what names the run and its figures, and short."""
 import json
 
+import pytest
+
 import bench
 
 
@@ -35,3 +37,19 @@ def test_the_line_of_a_run_without_the_extra_rows():
     for key in ("blocks", "bf16x3", "cpu_baseline"):
         del out[key]
     assert bench.short_line(out)["value"] == out["value"]
+
+
+def test_saved_candidates_are_taken_only_where_they_are_what_they_were():
+    import xl_workloads as W
+    from paper_2007_06000_amd import binding as B
+    p = B.Plan(W.config(4))
+    saved = {"layer_by_layer_blocks": [], "candidates": [[1, 0, 3, bench.configuration(p, True, 0, 3)], [0, 1, 2, bench.configuration(p, False, 1, 2)]]}
+    bench.apply_candidates(p, saved)
+    assert (p.candidate_info(True, 0)["candidate"], p.candidate_info(False, 1)["candidate"]) == (3, 2)
+    # a list in another order, and one without the candidate
+    first = saved["candidates"][0]
+    for place in (4, 64):
+        with pytest.raises(SystemExit):
+            bench.apply_candidates(p, dict(saved, candidates=[first[:2] + [place, first[3]]]))
+    bench.apply_candidates(p, dict(saved, candidates=[[1, 0, 5]]))
+    assert p.candidate_info(True, 0)["candidate"] == 5
