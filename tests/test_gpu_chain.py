@@ -99,3 +99,92 @@ def test_errors_and_extremes(wl):
     S.test_passes_repeat_bit_for_bit_around_an_infinite_intermediate(wl)
     for where in ("input", "filter 1", "filter 2"):
         S.test_error_on_small_operands_is_no_larger_than_with_fp32_operations(wl, where)
+
+
+def first_candidates(s, wanted):
+    """{variant: candidate} of the fused launch, the first of every variant that `wanted` takes."""
+    out = {}
+    for c in range(s.plan.num_candidates(True, 0)):
+        v = s.plan.candidate_info(True, 0, c)["variant"]
+        if wanted(v):
+            out.setdefault(v, c)
+    return out
+
+
+def against_fp32_operations_on_two_parts(wl, x, params, base, count, what):
+    """The kernels of a plan on two parts from id `base` on, against a kernel on fp32 operations of the same plan: the same infinities
+    and NaN, and everything else within what two parts give."""
+    from paper_2007_06000_amd.session import Session
+    s = Session(wl, x, params, precision=1)
+    s.plan.select_candidate(True, 0, min(first_candidates(s, lambda v: v < 200).values()))
+    ref = s.output(True)
+    fin = np.isfinite(ref)
+    large = fin & (np.abs(ref) > 1e20)
+    found = first_candidates(s, lambda v: base <= v < base + count)
+    for v, c in found.items():
+        print(f"[case] {wl.name} {what} variant {v} candidate {c}", flush=True)
+        s.plan.select_candidate(True, 0, c)
+        y = s.output(True)
+        assert (np.isnan(y) == np.isnan(ref)).all() and (np.isposinf(y) == np.isposinf(ref)).all() and (np.isneginf(y) == np.isneginf(ref)).all(), (v, what)
+        d = np.abs(np.where(fin, y, 0).astype(np.float64) - np.where(fin, ref, 0).astype(np.float64))
+        # 3 * 2^-16 of the absolute sums of the last layer at most: at the scale of these blocks the library's bar, and where a
+        # large value is part of the sums (up to 256 terms of random sign, their absolute sum within four times the largest
+        # result) 2^-12 of the largest
+        assert (d <= 1e-4 + 1e-4 * np.abs(ref))[fin & ~large].all(), (v, what, d[fin & ~large].max())
+        assert not large.any() or d[large].max() <= 2.0 ** -12 * np.abs(ref[large]).max(), (v, what)
+    return set(found)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("special", [np.inf, -np.inf, np.nan, 3.4e38, 2.0 ** -134])
+@pytest.mark.parametrize("wl,k", CASES, ids=lambda a: getattr(a, "name", ""))
+def test_values_without_bf16_parts_on_two_parts(wl, k, special):
+    """Layer 1 takes three parts there too, and the whole operands of the wave that starts again are filters of two in layer 2: such a
+    value in the input and in the filter of every layer 1."""
+    value = np.float32(special) * np.float32(1 + 2.0 ** -10 if special == 2.0 ** -134 else 1)
+    for where in [None] + [i for i, ly in enumerate(wl.layers) if ly.op == "conv" and ly.inputs[0] == wl.input_id]:
+        x, params = W.make_tensors(wl)
+        if where is None:
+            x[0, 1, x.shape[2] // 2, x.shape[3] // 2] = value
+        else:
+            params[where]["w"][3, 5, 0, 0] = value
+            if params[where]["scale"] is not None:
+                params[where]["scale"][3] = 1.0
+        assert against_fp32_operations_on_two_parts(wl, x, params, 320, len(KERNELS), f"{special} in {where}") >= {320 + k}
+
+
+def beside(blocks, name):
+    """Blocks on one input, their results next to each other in one tensor."""
+    n, c, h, w = blocks[0].shapes[0]
+    b = W._Builder(name, n, c, h, w)
+    t = None
+    for wl in blocks:
+        first, of = len(b.layers), {0: 0}
+        for ly in wl.layers:
+            ins = [of[i] for i in ly.inputs]
+            of[ly.out] = (b.conv(ins[0], ly.cout, ly.k, ly.stride, ly.pad, bias=ly.bias, bn=ly.bn, relu=ly.relu, name=ly.name) if ly.op == "conv"
+                          else b.maxpool(ins[0], ly.k, ly.stride, ly.pad) if ly.op == "maxpool" else b.add(*ins, relu=ly.relu))
+        b.group(wl.groups[0].mode, first)
+        t = of[wl.output_id] if t is None else b.concat(t, of[wl.output_id])
+    return b.done(t, blocks[0].input_dist, 41)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("blocks", [[one(2, 40, 9, 11, 48, 20), one(2, 40, 9, 11, 33, 70)], [two(3, 24, 7, 9, 40, 33), one(3, 24, 7, 9, 20, 31)],
+                                    [one(1, 24, 13, 10, 16, 64), two(1, 24, 13, 10, 50, 17)]], ids=["one_one", "two_one", "one_two"])
+def test_channel_slices_of_a_wider_tensor(blocks, precision):
+    from paper_2007_06000_amd.session import Session
+    wl = beside(blocks, "chains_beside")
+    x, params = W.make_tensors(wl)
+    ref = xlo.forward(wl, x, params)
+    s = Session(wl, x, params, precision=precision)
+    base = 320 if precision else 520
+    for launch in range(2):
+        chain = [c for c in range(s.plan.num_candidates(True, launch)) if base <= s.plan.candidate_info(True, launch, c)["variant"] < base + len(KERNELS)]
+        assert len(chain) == 1
+        s.plan.select_candidate(True, launch, chain[0])
+    y = s.output(True)
+    first = blocks[0].shapes[blocks[0].output_id][1]
+    for part in (slice(0, first), slice(first, None)):      # (bounds as in test_against_the_oracle)
+        assert np.linalg.norm((y - ref)[:, part]) <= (2.0 ** -12 if precision else 2.0 ** -20) * np.linalg.norm(ref[:, part])

@@ -99,6 +99,26 @@ def test_values_without_bf16_parts(wl, special):
             assert (np.abs(y[fin] - ref[fin]) <= 1e-4 + 1e-4 * np.abs(ref[fin])).all(), (where, v)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("special", [3.4e38, 2.0 ** -134])
+@pytest.mark.parametrize("wl", [wl for wl in CASES if wl.layers[0].k == 1], ids=lambda a: getattr(a, "name", ""))
+def test_values_without_bf16_parts_in_pointwise_first_layers_on_two_parts(wl, special):
+    """Layer 1 takes three parts there too: such a value in the input and in its filter, with finite sums, which is what two parts hold."""
+    from test_gpu_chain import against_fp32_operations_on_two_parts
+    value = np.float32(special) * np.float32(1 + 2.0 ** -10 if special < 1 else 1)
+    for where in ("x", "w"):
+        x, params = W.make_tensors(wl)
+        if where == "x":
+            x[0, 1, x.shape[2] // 2, x.shape[3] // 2] = value
+            params[0]["w"] *= np.float32(0.25)          # sums below 2^127
+        else:
+            x *= np.float32(0.1)
+            params[0]["w"][3, 5, 0, 0] = value
+        if params[0]["scale"] is not None:
+            params[0]["scale"][:] = 1.0
+        assert against_fp32_operations_on_two_parts(wl, x, params, 350, 9, f"{special} in {where}")
+
+
 def siblings(cin, hw, s, e1, e3):
     b = W._Builder(f"siblings_{cin}_{s}_{e1}_{e3}", 1, cin, hw, hw)
     sq = b.conv(0, s, 1, bias=True, relu=True, name="squeeze")
