@@ -137,6 +137,9 @@ typedef struct xl_options {
                                stays under 1e-4); on inputs scaled by s the absolute part of the bar has to
                                scale with s as well, i.e. the guarantee is |err| <= 1e-4 * max|out| there.
                                Tensors in memory stay fp32.
+                               Kernels that take a layer on three parts (pointwise first layers of some blocks, a 3-channel
+                               stem) serve this mode too; the filter of such a pointwise layer is held in three parts as well,
+                               which adds up to half to the workspace of a block whose first filter is most of it.
                                A depthwise first layer stays on the vector ALU in fp32; xl_tune may
                                keep an fp32 kernel for a block where it measures faster. */
     int keep_blocks_fused;  /* 1: xl_tune never switches a block to layer-by-layer execution (see

@@ -282,7 +282,10 @@ struct Variant {
 // Variants with split-bf16 operands, each compiled for two parts (pr = 1, ids from 200) and for three (pr = 2, ids
 // from 400): the columns above, then S1 = 1: stage 1 takes split operands too (0: fp32 matrix operations; 2: three parts in
 // either).  Where operands are split the matrix-core tile is 32 wide.
-// KIND_CHAIN: columns 5, 6 and 8 are K steps of layer 1, producers and row tiles of layer 2
+// KIND_CHAIN: columns 5, 6 and 8 are K steps of layer 1, producers and row tiles of layer 2.  The list ends at the channel counts
+// that were timed: 96 in and 64 out or 64 in and 96 out for one producer, 64 and 64 for two.  Registers, of 256: 235 (6 K steps, 2 row
+// tiles), 249 (4, 3) and 242 (two producers, 4, 2), 12 to 24 per K step and 18 to 52 per row tile, so that a step more might fit
+// here and there; wider blocks take the general kernels.
 #define XL_SPLIT_LIST_D(X)                                            \
     X(120, KIND_CHAIN, 32, 1, 1, 1, 32, 1, 1, 1, 0, 0, 0, 2)          \
     X(121, KIND_CHAIN, 32, 1, 1, 1, 32, 2, 1, 1, 0, 0, 0, 2)          \
