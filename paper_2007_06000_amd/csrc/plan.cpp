@@ -3,6 +3,7 @@
 #include "plan.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdlib>
 #include <cstdio>
@@ -320,13 +321,17 @@ static std::vector<Choice> search_ksplit(const BlockSpec &b, const xl_plan &pl, 
         t.mw = (t.tw - 1) * s2 + ext + halo;
         const int npt1 = ceil_div(t.mh * t.mw, 32), npt2 = ceil_div(t.th * t.tw, 32);
         if (npt1 > 8) continue;
-        t.ih = required_extent(t.mh, b.c1.k, b.c1.stride);
-        t.iw = required_extent(t.mw, b.c1.k, b.c1.stride);
+        // (in 64 bits: the input tile of a layer with a long stride may be larger than 32 hold)
+        const long long tile_h = (t.mh - 1LL) * b.c1.stride + b.c1.k, tile_w = (t.mw - 1LL) * b.c1.stride + b.c1.k;
+        if (b.c1.k != 1 && std::max(tile_h, tile_w) * np1 * 32 > pl.lds_budget) continue;
+        t.ih = (int)std::min(tile_h, (long long)INT_MAX);
+        t.iw = (int)std::min(tile_w, (long long)INT_MAX);
         t.tiles_y = ceil_div(b.Ho, th);
         t.tiles_x = ceil_div(b.Wo, tw);
         t.chunk_kg = nkg1;
-        const int mid = nrt1 * 4 * np * t.mh * t.mw * 4, input = b.c1.k == 1 ? 0 : nkg1 * 2 * np1 * t.ih * t.iw * 4;
-        if ((mid + input) * 4 > pl.lds_budget) continue;
+        const long long lds_floats = nrt1 * 4LL * np * t.mh * t.mw * 4 + (b.c1.k == 1 ? 0 : nkg1 * 2LL * np1 * tile_h * tile_w * 4);
+        if (lds_floats * 4 > pl.lds_budget) continue;
+        const int mid = nrt1 * 4 * np * t.mh * t.mw * 4, input = (int)lds_floats - mid;
         for (const Variant *variant : fit) {
             const Variant &v = *variant;
             if (v.npt1 > npt1 || v.npt2 > npt2) continue;

@@ -114,6 +114,16 @@ def test_stream_kernels_are_candidates_of_thin_pointwise_blocks():
     assert (97, 256, 4, 4) in {(i["variant"], i["threads"], i["tile_h"], i["tile_w"]) for i in found}
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("cin,hw,stride", [(256, 1600, 100), (64, 3200, 200), (4, 15900, 1000), (8, 200, 12)])
+def test_tiles_of_layers_with_long_strides_fit_the_lds(cin, hw, stride, precision):
+    p = B.Plan(W.straight_generic(1, cin, hw, hw, 32, 3, 0, stride, 32, 1, 0, 1), precision=precision)
+    found = [p.candidate_info(True, 0, c) for c in range(p.num_candidates(True, 0))]
+    assert all(0 < i["lds_bytes"] <= 160 * 1024 for i in found), [(i["variant"], i["lds_bytes"]) for i in found]
+    # (with a stride of 12 some tiles do fit)
+    assert stride > 12 or any(i["variant"] % 200 in range(150, 163) and i["variant"] >= 350 for i in found)
+
+
 def test_two_producer_merge_block_plans_as_one_launch():
     """Table 1, c.1: {1x1 64->256, 1x1 64->256} -> add -> 1x1 256->64 on [64,56,56]."""
     p = B.Plan(W.merge_two_producers(1))
