@@ -96,6 +96,15 @@ __device__ __forceinline__ void touch_arguments()
     asm volatile("" : : "s"(t[0]), "s"(t[1]), "s"(t[2]), "s"(t[3]), "s"(t[4]), "s"(t[5]), "s"(t[6]), "s"(t[7]));
 }
 
+// The kernel's argument.  Every phase asks for it anew, through a pointer that the compiler cannot see through: left to itself it
+// loads some 60 numbers before the first phase and spends hundreds of instructions on keeping them in vector lanes.
+__device__ __forceinline__ const BlockParams &block_params()
+{
+    unsigned long long p = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const BlockParams *)(const __attribute__((address_space(4))) BlockParams *)p;
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
 // Map hardware block id -> logical id so that consecutive logical ids (tiles of
 // one image, which share halo rows and cache lines of the output) land on the
@@ -824,18 +833,24 @@ __device__ __forceinline__ void depthwise_stage1(const BlockParams &P, float *mi
     }
 }
 
+}  // namespace xl
+#include "direct_conv.h"
+namespace xl {
+
 // ----------------------------------------------------------------------------
 // The block kernel
 // ----------------------------------------------------------------------------
 // PR: bf16 parts of the operands of stage 2 (0: fp32 operands), PR1: of stage 1 (split_conv.h).
 template <int KIND, int MF1, int K1, int NRT1, int NPT1, int MF2, int NRT2, int NPT2, int K2A, int K2B, bool SC, int PX1, int PR = 0, int PR1 = 0>
-__global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL || (KIND == KIND_SINGLE && PR1 == 2 && NRT1 * NPT1 == 1) ? 4 : XL_MIN_WAVES))
-block_kernel(const BlockParams P)
+__global__ void __launch_bounds__(MAX_THREADS, (KIND == KIND_POOL || (KIND == KIND_SINGLE && PR1 == 2 && NRT1 * NPT1 == 1) || (PR1 == 2 && MF1 == 16 && NRT1 * NRT2 * NPT2 == 1) ? 4 : XL_MIN_WAVES))
+block_kernel(const BlockParams args)
 {
-    static_assert(PR1 == 0 || (PX1 == 0 && MF1 == 32), "split operands are staged through registers");
+    constexpr bool DIRECT = PR1 == 2 && MF1 == 16;          // stage 1 reads memory (direct_conv.h)
+    static_assert(PR1 == 0 || (PX1 == 0 && (MF1 == 32 || (DIRECT && K1 == 1 && (KIND == KIND_FUSED2 || KIND == KIND_FUSED2P)))), "split operands are staged through registers");
     static_assert(PR == 0 || MF2 == 32, "split operands use 32-wide matrix-core tiles");
     extern __shared__ __attribute__((aligned(16))) float lds[];
     touch_arguments();
+    const BlockParams &P = DIRECT ? block_params() : args;
     const int L = logical_block();
     if (L >= P.nblocks) return;
     const int tiles = P.tiles_x * P.tiles_y;
@@ -865,6 +880,8 @@ block_kernel(const BlockParams P)
     if constexpr (KIND == KIND_DW) {
         // ---- S1/S2 for a depthwise first layer: vector ALU from a staged input tile into the LDS tile
         depthwise_stage1<PR>(P, mid, buf, ximg, (unsigned long long)(P.N - n) * P.Cin * P.H * P.W * 4ull, my0, mx0, iy0, ix0);
+    } else if constexpr (DIRECT) {
+        direct_stage1<NRT1, NPT1, PR>(P, P.c1, mid, buf, ximg, my0, mx0, iy0, ix0);
     } else {
     // ---- S1: layer 1 over the (halo-extended) tile
     const int npx1 = P.mh * P.mw;
@@ -933,6 +950,7 @@ block_kernel(const BlockParams P)
     }
     }
     if constexpr (KIND != KIND_SINGLE) {
+        const BlockParams &P = DIRECT ? block_params() : args;
         // ---- S3: barrier between producing and consuming the LDS tile
         __syncthreads();
 
@@ -1377,8 +1395,8 @@ static hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, size_
 // This file is compiled several times, in parallel: once for the fp32 variants and everything else, and once for each
 // part of the split-bf16 variants (XL_TU_SPLIT = the list, XL_TU_PR = parts - 1).
 typedef void (*BlockKernel)(const BlockParams);
-BlockKernel split_kernel_A1(int), split_kernel_B1(int), split_kernel_C1(int), split_kernel_D1(int), split_kernel_E1(int);
-BlockKernel split_kernel_A2(int), split_kernel_B2(int), split_kernel_C2(int), split_kernel_D2(int), split_kernel_E2(int);
+BlockKernel split_kernel_A1(int), split_kernel_B1(int), split_kernel_C1(int), split_kernel_D1(int), split_kernel_E1(int), split_kernel_F1(int);
+BlockKernel split_kernel_A2(int), split_kernel_B2(int), split_kernel_C2(int), split_kernel_D2(int), split_kernel_E2(int), split_kernel_F2(int);
 
 #ifdef XL_TU_SPLIT
 #define XL_CAT_(a, b, c) a##b##c
@@ -1437,8 +1455,8 @@ static BlockKernel kernel_of(int variant)
 #undef X
     }
     if (variant >= SPLIT_ID0[1]) {
-        for (auto part : {split_kernel_A1, split_kernel_B1, split_kernel_C1, split_kernel_D1, split_kernel_E1, split_kernel_A2,
-                          split_kernel_B2, split_kernel_C2, split_kernel_D2, split_kernel_E2})
+        for (auto part : {split_kernel_A1, split_kernel_B1, split_kernel_C1, split_kernel_D1, split_kernel_E1, split_kernel_F1, split_kernel_A2,
+                          split_kernel_B2, split_kernel_C2, split_kernel_D2, split_kernel_E2, split_kernel_F2})
             if (BlockKernel k = part(variant)) return k;
     }
     return nullptr;
@@ -1497,11 +1515,11 @@ __global__ void pack_filter_kernel(const float *__restrict__ w, const float *__r
     wp[row * 64 + lane] = v;
 }
 
-// Split-bf16 form (32-wide tiles): [K step][tap][row tile][part][lane] of 8 bf16;
-//   lane l holds cout = rt*32 + l%32, cin = kg*16 + (l/32)*8 + e.
+// Split-bf16 form: [K step][tap][row tile][part][lane] of 8 bf16;
+//   lane l holds cout = rt*MF + l%MF, cin = kg*KC + (l/MF)*8 + e  (MF = 32: KC = 16; MF = 16: KC = 32).
 template <int PR>
 __global__ void pack_filter_split_kernel(const float *__restrict__ w, const float *__restrict__ scale,
-                                         uint4 *__restrict__ wp, int cout, int cin, int k, int nkg, int nrt)
+                                         uint4 *__restrict__ wp, int cout, int cin, int k, int mf, int nkg, int nrt)
 {
     const int taps = k * k;
     const long long total = (long long)nkg * taps * nrt * 64;
@@ -1514,15 +1532,15 @@ __global__ void pack_filter_split_kernel(const float *__restrict__ w, const floa
     const int rt = (int)(r % nrt);
     const int kg = (int)(r / nrt);
     const long long row = ((long long)kg * taps + t) * nrt + rt;
-    const int o = rt * 32 + lane % 32;
-    const int sub = lane / 32;
+    const int o = rt * mf + lane % mf;
+    const int sub = lane / mf, kc = 512 / mf;
     unsigned out[PR + 1][4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         float v[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int ci = kg * 16 + sub * 8 + 2 * e + h;
+            const int ci = kg * kc + sub * 8 + 2 * e + h;
             v[h] = (o < cout && ci < cin) ? w[((size_t)o * cin + ci) * taps + t] * (scale ? scale[o] : 1.f) : 0.f;
         }
         unsigned p[PR + 1];
@@ -1550,7 +1568,7 @@ hipError_t launch_pack_filter(const float *w, const float *scale, f32x4 *wp, int
     const int grid = (int)((total + threads - 1) / threads);
     if (pr)
         return launch(pr == 2 ? pack_filter_split_kernel<2> : pack_filter_split_kernel<1>, dim3(grid), dim3(threads), 0, s,
-                      w, scale, (uint4 *)wp, cout, cin, k, nkg, nrt);
+                      w, scale, (uint4 *)wp, cout, cin, k, mf, nkg, nrt);
     return launch(pack_filter_kernel, dim3(grid), dim3(threads), 0, s, w, scale, wp, cout, cin, k, mf, nkg, nrt, pairs);
 }
 

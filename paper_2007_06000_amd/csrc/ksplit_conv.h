@@ -215,15 +215,6 @@ struct KPart {
     }
 };
 
-// The kernel's argument.  Every phase asks for it anew, through a pointer that the compiler cannot see through: left to itself it
-// loads some 60 numbers before the first phase and spends hundreds of instructions on keeping them in vector lanes.
-__device__ __forceinline__ const BlockParams &block_params()
-{
-    unsigned long long p = (unsigned long long)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *(const BlockParams *)(const __attribute__((address_space(4))) BlockParams *)p;
-}
-
 // Numbers of the argument that a phase uses, loaded together: where each is loaded at its use, behind branches, a wave waits for
 // every one of them (a tile of the epilogue took 1.5 us like that).
 template <typename T>

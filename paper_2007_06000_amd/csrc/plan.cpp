@@ -30,6 +30,7 @@ const std::vector<Variant> &variants()
         XL_SPLIT_LIST_C(X)
         XL_SPLIT_LIST_D(X)
         XL_SPLIT_LIST_E(X)
+        XL_SPLIT_LIST_F(X)
 #undef X
     };
     return v;
@@ -161,18 +162,28 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     const int wg_rt = c.waves_r1 * v.nrt1;
     const double wave1 = (double)v.nrt1 * v.npt1 * nkg1 * taps1 * kstep_clk(mf1, v.pr1);
     double simd[4] = {0, 0, 0, 0};
-    for (int w = 0; w < nw; ++w) {
+    double life1 = 0;
+    for (int w = 0; w < nw && v.direct(); ++w) {
+        // pixel groups of the wave: matrix operations, taking the pixels apart (60 vector instructions per tile and K step), epilogue
+        const int pw = nw / c.waves_r1, groups = ceil_div(ceil_div(npx1, 16), v.npt1), wp = w / c.waves_r1;
+        const int mine = wp < groups ? (groups - wp + pw - 1) / pw : 0;
+        const double steps = (double)mine * ceil_div(nkg1, c.waves_r1) * v.npt1, mat = steps * nrt1 * 6 * 22.0, alu = steps * 60 + mine * 60.0 * v.npt1 * nrt1;
+        simd[w % 4] += std::max(mat, alu * 2.6);
+        life1 = std::max(life1, mat + alu * 5.3 + mine * ceil_div(nkg1, c.waves_r1) * 400.0);
+    }
+    for (int w = 0; w < nw && !v.direct(); ++w) {
         const int wr = w % c.waves_r1, wp = w / c.waves_r1;
         const int rt0 = wr * v.nrt1, pt0 = wp * v.npt1;
         const int rt_end = std::min(nrt1, wg_rt);
         if (rt0 < rt_end && pt0 * mf1 < npx1) simd[w % 4] += wave1;
     }
-    double t1 = *std::max_element(simd, simd + 4) * b.n1;
+    double t1 = std::max(*std::max_element(simd, simd + 4), life1) * b.n1;
     if (v.px1 < 0) t1 *= -v.px1 / 4.0;      // only -px1 of the 4 channel slots carry matrix operations
     if (v.px1 > 0) t1 *= 0.9;       // planar input chunks: no register staging, no vector-ALU work in the K loop
     // taking the input apart: about 110 vector instructions per 64 pixels x 8 channels
-    if (v.pr1) t1 += b.n1 * ceil_div(b.c1.cin, 8) * ceil_div(c.ih * c.iw, 64) / 4.0 * 500.0;
+    if (v.pr1 && !v.direct()) t1 += b.n1 * ceil_div(b.c1.cin, 8) * ceil_div(c.ih * c.iw, 64) / 4.0 * 500.0;
     int barriers = ceil_div(nkg1, c.chunk_kg) * b.n1;
+    if (v.direct()) t1 += c.waves_r1 > 1 ? 1000.0 + 700.0 * ceil_div(nrt1 * ceil_div(npx1, 16), nw) : 0.0;
     if (b.kind == KIND_DW) {
         // vector ALU: staging one float4 per (channel group, input pixel), then per (channel group,
         // intermediate pixel) one LDS read and 4 multiply-adds per tap; ~8 issue cycles per wave instruction
@@ -564,9 +575,22 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             for (int wr = 1; wr <= nw; wr *= 2) {
                 const int wg_rt = wr * v.nrt1;
                 if (dw && wr > 1) continue;
-                if (!dw && b.kind != KIND_SINGLE && wg_rt < nrt1) continue;     // stage 1 must produce every channel
-                if (!dw && wr > 1 && (wr / 2) * v.nrt1 >= nrt1) continue;       // more row waves than row tiles
-                const int px_cap = dw ? (1 << 30) : (nw / wr) * v.npt1 * mf1;
+                if (v.direct()) {
+                    // all row tiles in a wave (the smallest kernel that holds them); wr: waves that divide the reduction
+                    if (nrt1 > v.nrt1 || (v.nrt1 > 1 && nrt1 <= v.nrt1 / 2) || b.n1 == 2 || wr > nkg1) continue;
+                    if ((b.c1.cin + 32LL * 32) * b.H * b.W >= (1LL << 29)) continue;        // (32-bit offsets past the end of an image)
+                } else if (!dw && b.kind != KIND_SINGLE && wg_rt < nrt1) continue;     // stage 1 must produce every channel
+                if (!dw && !v.direct() && wr > 1 && (wr / 2) * v.nrt1 >= nrt1) continue;       // more row waves than row tiles
+                const int px_cap = dw ? (1 << 30) : v.direct() && wr == 1 ? 32768 : (nw / wr) * v.npt1 * mf1;
+                // K steps whose filter rows lie in LDS together: all, or as many as 96 KB hold where a wave has one group of pixels
+                auto direct_chunk = [&](const Choice &c, const Variant &v, int kw) {
+                    const int all = nkg1 * nrt1 * 3072, turn = (DIRECT_AHEAD + 1) * kw, groups = ceil_div(c.mh * c.mw, 16 * v.npt1);
+                    if (groups * 2 <= nw / kw && kw * 2 <= nkg1) return 0;         // (half of the waves without pixels)
+                    if (all + c.mh * c.mw * nrt1 * 16 * 2 * parts_of(v.pr) <= pl.lds_budget) return nkg1;
+                    if (groups > nw / kw) return 0;
+                    const int chunk = 96 * 1024 / (nrt1 * 3072) / turn * turn;
+                    return chunk < 1 ? 0 : std::min(nkg1, ceil_div(ceil_div(nkg1, ceil_div(nkg1, chunk)), turn) * turn);
+                };
                 for (auto [th, tw] : tiles) {
                 Choice *kept = nullptr;         // the best of this variant, workgroup size and tile so far
                 int first_chunk = 0;
@@ -613,7 +637,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     const double clk1 = (double)(nw / 4.0) * v.nrt1 * v.npt1 * taps1 * kstep_clk(mf1, v.pr1);
                     // 4-channel groups of 4-pixel row pieces, or 8-channel groups of 64 pixels
                     const int x_units_per_kg = v.pr1 ? 2 * ceil_div(c.ih * c.iw, 64) : gps_of(mf1) * c.ih * ceil_div(c.iw, 4);
-                    c.chunk_kg = dw ? 1 : pick_chunk(nkg1, px > 0 ? 0 : x_units_per_kg, w_per_kg, max_units, clk1, want_clk);
+                    c.chunk_kg = dw ? 1 : v.direct() ? direct_chunk(c, v, wr) : pick_chunk(nkg1, px > 0 ? 0 : x_units_per_kg, w_per_kg, max_units, clk1, want_clk);
                     if (px > 0)     // planar chunk: kc x px x 16 quads per K step, at most PLANAR_SLOTS wave loads per wave
                         c.chunk_kg = std::min(c.chunk_kg, PLANAR_SLOTS * nw * 64 / (kc_of(mf1) * px * 16));
                     if (c.chunk_kg < 1) continue;
@@ -624,6 +648,11 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     c.w_off1 = c.chunk_kg * x_per_kg * 4 + 16;        // + slack for a left-edge unit running past the last row
                     if (px > 0) c.w_off1 = c.chunk_kg * kc_of(mf1) * px * 64;
                     int buf1 = c.w_off1 + c.chunk_kg * w_per_kg * 4;
+                    if (v.direct()) {       // no staging: the filter and the shifts, then the partial sums of divided reductions
+                        c.w_off1 = 0;
+                        buf1 = (c.chunk_kg * nrt1 + v.nrt1 - nrt1) * 768 + nrt1 * 256;
+                        if (wr > 1) buf1 = std::max(buf1, nrt1 * ceil_div(c.mh * c.mw, 16) * wr * 256);
+                    }
                     // floats of the LDS tile: 4 bytes per element, or one bf16 per part in planes of 8 channels
                     const bool split_mid = v.pr && two;
                     auto mid_size = [&](int channels) {
@@ -669,7 +698,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                                 // `multi` floats apart, a single-chunk pass only ever touches the first one
                                 int multi = 0, single = 0;
                                 c.tile2_floats = 0;
-                                ((!dw && ceil_div(nkg1, c.chunk_kg) > 1) ? multi : single) = buf1;
+                                ((!dw && !v.direct() && ceil_div(nkg1, c.chunk_kg) > 1) ? multi : single) = buf1;
                                 bool fits = true;
                                 if (two) {
                                     const int NRT2 = v.nrt2, NPT2 = v.npt2;
@@ -706,10 +735,11 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                                 const int staging = std::max(single, 2 * multi);
                                 // split operands stage nothing once layer 1 is done: the LDS tile takes the place of
                                 // its buffers, except where both are in use together
-                                c.mid_over_staging = v.pr && !dw && b.n1 == 1;
+                                c.mid_over_staging = v.pr && !dw && b.n1 == 1 && !v.direct();
                                 c.lds_bytes = (c.mid_over_staging ? std::max(c.mid_floats + c.tile2_floats, staging)
                                                                   : c.mid_floats + staging + c.tile2_floats) * 4;
-                                c.tile2_off = c.mid_floats + (c.mid_over_staging ? 0 : staging);
+                                c.tile2_off = c.mid_floats + (c.mid_over_staging || v.direct() ? 0 : staging);
+                                if (v.direct()) c.lds_bytes = (c.mid_floats + std::max(staging, c.tile2_floats)) * 4;
                                 if (c.lds_bytes > pl.lds_budget) {
                                     any_lds_reject = true;
                                     continue;
@@ -717,8 +747,8 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                                 // waves per SIMD the registers allow: the conv -> pool kernels are built for 4
                                 // (at most 128 registers), the others for 2; split-bf16 kernels of one tile per wave
                                 // need fewer than 128, of two at most 168 unless they stage their input
-                                const int tiles_wave = v.pr ? std::max(v.pr1 ? v.nrt1 * v.npt1 : 1, two ? v.nrt2 * v.npt2 : 1) : 0;
-                                const int reg_waves = b.kind == KIND_POOL || tiles_wave == 1 ? 16 : (tiles_wave == 2 && !v.pr1) ? 12 : 8;
+                                const int tiles_wave = v.pr ? std::max(v.direct() ? (v.nrt1 == 4 || v.nrt2 == 2 ? 4 : v.nrt1) : v.pr1 ? v.nrt1 * v.npt1 : 1, two ? v.nrt2 * v.npt2 : 1) : 0;
+                                const int reg_waves = b.kind == KIND_POOL || tiles_wave == 1 ? 16 : (tiles_wave == 2 && (!v.pr1 || v.direct())) ? 12 : 8;
                                 c.occ = std::max(1, std::min({pl.lds_per_cu / std::max(c.lds_bytes, 1), 2048 / threads,
                                                               reg_waves / nw}));
                                 evaluate(b, pl, c);
@@ -802,7 +832,8 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
     lds_rejected = !any_ok && any_lds_reject;
     // ranked list: the model's best first, then the best of other (variant, threads, tile) combinations
     std::vector<const Choice *> ranked;         // (a Choice is hundreds of bytes: sorted themselves they were a tenth of the time a plan takes)
-    for (auto &kv : per_key) ranked.push_back(&kv.second);
+    std::vector<const Choice *> direct;         // (kernels with places of their own: make_block_step)
+    for (auto &kv : per_key) (kv.second.v.direct() ? direct : ranked).push_back(&kv.second);
     std::sort(ranked.begin(), ranked.end(), [](const Choice *a, const Choice *b) { return a->cost < b->cost; });
     if (ranked.size() > (size_t)MAX_ALTERNATIVES) {
         // The model assumes at most two waves per SIMD; kernels that need fewer registers run three
@@ -827,6 +858,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
     }
     std::vector<Choice> out;
     for (const Choice *c : ranked) out.push_back(*c);
+    for (const Choice *c : direct) out.push_back(*c);
     return out;
 }
 
@@ -1089,21 +1121,27 @@ struct Builder {
         // another variant and took 11.2 us.  (The best of the 64 is 0.6 % behind the best of 600 over 36 blocks; of 64 and 48
         // without the cap 0.5 %.)
         std::vector<Choice> split;
-        std::vector<Choice> ksplit;
+        std::vector<Choice> ksplit, direct;
         const int pr = pl.opts.precision == XL_PRECISION_BF16X3 ? 1 : 2;
         if (pr == 1 || !has_fp32_layer(b)) {
             split = search(b, pl, ignored, pr);
             if (!split.empty()) ksplit = search_ksplit(b, pl, pr);
+            for (const Choice &c : split)
+                if (c.v.direct()) direct.push_back(c);
+            split.erase(std::remove_if(split.begin(), split.end(), [](const Choice &c) { return c.v.direct(); }), split.end());
         }
         if (pr == 1 && has_fp32_layer(b)) {
             auto on_three = [](const Choice &c) { return c.v.pr1 == 2; };
             split.erase(std::remove_if(split.begin(), split.end(), on_three), split.end());
             ksplit.erase(std::remove_if(ksplit.begin(), ksplit.end(), on_three), ksplit.end());
+            direct.clear();
         }
         if (!split.empty()) {
-            // (the kernels that divide the reductions have places of their own, taken from the fp32 ones', which are seldom the
+            // (the kernels that divide the reductions and those whose first layer reads memory have places of their own, taken from the fp32 ones', which are seldom the
             // fastest where these exist)
             keep_best(ksplit, KSPLIT_PLACES, 3);
+            keep_best(direct, DIRECT_PLACES, 3);
+            ksplit.insert(ksplit.end(), direct.begin(), direct.end());
             const size_t half = MAX_ALTERNATIVES / 2, fp32 = ranked.size() + ksplit.size();
             keep_best(ranked, std::max(half, MAX_ALTERNATIVES - std::min(split.size(), (size_t)MAX_ALTERNATIVES)) - ksplit.size());
             keep_best(split, std::max(half, MAX_ALTERNATIVES - std::min(fp32, (size_t)MAX_ALTERNATIVES)));

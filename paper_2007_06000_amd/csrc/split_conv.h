@@ -67,6 +67,22 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned (&w)[PR + 
     if constexpr (PR == 2) odd |= left != 0u;
 }
 
+// The three parts of two values for sums that are looked at afterwards and computed again from the values themselves: nothing is marked.
+// `left` collects, in its lower 16 bits, what the parts do not hold (bits below the smallest bf16 number); parts of values that are infinite, NaN or too large are
+// infinite or NaN, and so are their sums.  What is left for the third part has 8 bits: it is cut off, not rounded.
+__device__ __forceinline__ void split_exact(float a, float b, unsigned (&w)[3], unsigned &left)
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(w[i]) : "v"(a), "v"(b));      // (a vector of the two costs a move)
+        a -= bf16_low(w[i]);
+        b -= bf16_high(w[i]);
+    }
+    const unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
+    w[2] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+    left |= x | y;
+}
+
 // What is held in place of the parts of two values of which one does not come apart (PR = 2).
 constexpr unsigned WHOLE_MARK = 0x7fc0u;        // no part of a value that comes apart is NaN
 __device__ __forceinline__ void whole_parts(float a, float b, unsigned (&w)[3])

@@ -19,7 +19,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // MF = 16 uses V_MFMA_F32_16X16X4_F32 (16 channels: 4 lane quarters x 4).
 // Split-bf16 operands (pr > 0, MF = 32 only): a float is held as pr + 1 bf16 parts and a product is several
 // V_MFMA_F32_32X32X16_BF16; a lane holds 8 channels and a K step covers 16.
-constexpr int kc_of(int mf, int pr = 0) { return pr ? 16 : (mf == 32 ? 8 : 16); }      // channels per K step
+// MF = 16 on three parts: V_MFMA_F32_16X16X32_BF16, a K step covers 32.
+constexpr int kc_of(int mf, int pr = 0) { return pr ? 512 / mf : (mf == 32 ? 8 : 16); }      // channels per K step
 constexpr int gps_of(int mf, int pr = 0) { return kc_of(mf, pr) / 4; }                 // 4-channel groups per K step
 constexpr int parts_of(int pr) { return pr ? pr + 1 : 1; }      // bf16 parts of an operand (fp32: the value itself)
 constexpr int products_of(int pr) { return pr == 2 ? 6 : 3; }   // matrix operations per product of split operands
@@ -94,7 +95,7 @@ struct BlockParams {
     int nblocks;            // logical workgroups = N * csplit * tiles_y * tiles_x
     int chunk_kg;           // stage 1: K steps staged per chunk
     int chunk_kg2[2];       // stage 2: K steps of filter staged per chunk, per convolution
-    int waves_r1;           // stage-1 waves along the row-tile (Cout) direction
+    int waves_r1;           // stage-1 waves along the row-tile (Cout) direction (direct_conv.h: along K)
     int waves_r2;           // stage-2 waves along the row-tile direction
     int pw1, pw2;           // KIND_KSPLIT: waves along the pixel tiles of either stage (the rest divide the K steps)
     int vw2;                // stage 2 lays output pixels out in virtual rows of vw2 >= tw columns
@@ -130,6 +131,7 @@ struct Variant {
     int pr;                     // 0: fp32 matrix operations; 1, 2: operands as two or three bf16 parts (3 or 6 bf16
                                 // operations per product), in stage 2 or, for a kernel of one convolution, in stage 1
     int pr1;                    // the same for stage 1
+    bool direct() const { return pr1 == 2 && mf1 == 16; }       // stage 1 reads memory (direct_conv.h)
 };
 
 // id, kind, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1
@@ -328,6 +330,24 @@ struct Variant {
     X(161, KIND_KSPLIT, 32, 3, 1, 2, 32, 1, 2, 0, 0, 0, 0, 1)         \
     X(162, KIND_KSPLIT, 32, 3, 2, 2, 32, 2, 2, 0, 0, 0, 0, 1)
 
+// Layer 1 from memory on three parts (direct_conv.h): columns 5 and 6 are the row and pixel tiles of a wave in layer 1.
+#define XL_SPLIT_LIST_F(X)                                            \
+    X(170, KIND_FUSED2, 16, 1, 4, 2, 32, 2, 1, 3, 1, 0, 0, 2)         \
+    X(171, KIND_FUSED2, 16, 1, 1, 2, 32, 1, 2, 3, 1, 0, 0, 2)         \
+    X(172, KIND_FUSED2, 16, 1, 2, 2, 32, 1, 2, 3, 1, 0, 0, 2)         \
+    X(173, KIND_FUSED2, 16, 1, 4, 2, 32, 1, 2, 3, 1, 0, 0, 2)         \
+    X(174, KIND_FUSED2, 16, 1, 1, 2, 32, 1, 1, 3, 1, 0, 0, 2)         \
+    X(175, KIND_FUSED2, 16, 1, 2, 2, 32, 1, 1, 3, 1, 0, 0, 2)         \
+    X(176, KIND_FUSED2, 16, 1, 4, 2, 32, 1, 1, 3, 1, 0, 0, 2)         \
+    X(177, KIND_FUSED2P, 16, 1, 1, 2, 32, 2, 1, 3, 1, 0, 0, 2)        \
+    X(178, KIND_FUSED2P, 16, 1, 2, 2, 32, 2, 1, 3, 1, 0, 0, 2)        \
+    X(179, KIND_FUSED2P, 16, 1, 4, 2, 32, 2, 1, 3, 1, 0, 0, 2)        \
+    X(180, KIND_FUSED2P, 16, 1, 1, 2, 32, 1, 2, 3, 1, 0, 0, 2)        \
+    X(181, KIND_FUSED2P, 16, 1, 2, 2, 32, 1, 2, 3, 1, 0, 0, 2)        \
+    X(182, KIND_FUSED2P, 16, 1, 4, 2, 32, 1, 2, 3, 1, 0, 0, 2)        \
+    X(183, KIND_FUSED2, 16, 1, 1, 2, 32, 1, 1, 5, 0, 0, 0, 2)         \
+    X(184, KIND_FUSED2, 16, 1, 2, 2, 32, 1, 1, 5, 0, 0, 0, 2)
+
 #define XL_SPLIT_LIST_A(X)                                            \
     X(0, KIND_SINGLE, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
     X(1, KIND_SINGLE, 32, 1, 2, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
@@ -404,6 +424,7 @@ const std::vector<Variant> &variants();
 #define XL_STAGE_UNITS 1
 #endif
 constexpr int STAGE_UNITS = XL_STAGE_UNITS;      // input units (4 channels x 4 pixels) each thread stages per chunk
+constexpr int DIRECT_AHEAD = 1;         // direct_conv.h: K steps that pixels are requested ahead
 constexpr int SPLIT_STAGE_UNITS = 2;    // split-bf16 kernels: units (64 pixels x 8 channels) each wave stages per chunk
 constexpr int MAX_W_CHUNK_BYTES = 52 * 1024;  // filter bytes staged per chunk (LDS-direct loads, no registers)
 constexpr int PLANAR_SLOTS = 8;     // LDS-direct loads per wave and chunk of a planar input chunk
@@ -414,6 +435,7 @@ constexpr int thin_row_floats(int taps) { return (taps + 15) / 16 * 16; }
 constexpr int THIN_PCB = 4;         // thin_conv_pool_kernel: output channels per LDS tile (per barrier)
 constexpr int MAX_ALTERNATIVES = 64;  // candidates per block kept for on-device tuning
 constexpr int KSPLIT_PLACES = 14;     // ... of which kernels that divide the reductions take at most these
+constexpr int DIRECT_PLACES = 12;     // ... and those whose first layer reads memory (direct_conv.h)
 #ifndef XL_MIN_WAVES
 #define XL_MIN_WAVES 2
 #endif

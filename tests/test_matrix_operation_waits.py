@@ -14,8 +14,8 @@ import pytest
 from paper_2007_06000_amd import binding as B
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
-# wait states before any other instruction may touch the result: 4-cycle passes (8, 16, 8) plus 4 for bf16, plus 2 for fp32
-NEED = {"v_mfma_f32_32x32x16_bf16": 12, "v_mfma_f32_32x32x2_f32": 18, "v_mfma_f32_16x16x4_f32": 10}
+# wait states before any other instruction may touch the result: 4-cycle passes (8, 4, 16, 8) plus 4 for bf16, plus 2 for fp32
+NEED = {"v_mfma_f32_32x32x16_bf16": 12, "v_mfma_f32_16x16x32_bf16": 8, "v_mfma_f32_32x32x2_f32": 18, "v_mfma_f32_16x16x4_f32": 10}
 REG = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
 
 
