@@ -19,11 +19,11 @@ LIB = os.path.join(HERE, "libxl.so")
 # split-bf16 ones
 SOURCES = [("kernels.hip", "kernels", []),
            *[("kernels.hip", f"kernels_split_{part}{pr}", [f"-DXL_TU_SPLIT={part}", f"-DXL_TU_PR={pr}"] + extra)
-             for part, extra in (("A", []), ("B", []), ("C", []), ("D", ["-DXL_TU_CHAIN"]), ("E", ["-DXL_TU_KSPLIT"]), ("F", [])) for pr in (1, 2)],
+             for part, extra in (("A", []), ("B", []), ("C", []), ("D", ["-DXL_TU_CHAIN"]), ("E", ["-DXL_TU_KSPLIT"]), ("F", []), ("G", ["-DXL_TU_HEAD"])) for pr in (1, 2)],
            ("plan.cpp", "plan", []), ("api.cpp", "api", []), ("static_run.hip", "static_run", [])]
 HEADERS = [os.path.join(CSRC, "xl_internal.h"), os.path.join(CSRC, "plan.h"), os.path.join(CSRC, "thin_conv.h"),
            os.path.join(CSRC, "split_conv.h"), os.path.join(CSRC, "dw_conv.h"), os.path.join(CSRC, "chain_conv.h"),
-           os.path.join(CSRC, "ksplit_conv.h"), os.path.join(CSRC, "direct_conv.h"), os.path.join(CSRC, "stem_conv.h"),
+           os.path.join(CSRC, "ksplit_conv.h"), os.path.join(CSRC, "direct_conv.h"), os.path.join(CSRC, "head_conv.h"), os.path.join(CSRC, "stem_conv.h"),
            os.path.join(ROOT, "include", "xl.h")]
 
 # packed-fp32 instructions are switched off for all device code

@@ -1375,6 +1375,9 @@ __global__ void __launch_bounds__(MAX_THREADS, 4) pool_stream_kernel(const Block
 #ifdef XL_TU_KSPLIT
 #include "ksplit_conv.h"
 #endif
+#ifdef XL_TU_HEAD
+#include "head_conv.h"
+#endif
 namespace xl {
 
 // ----------------------------------------------------------------------------
@@ -1395,8 +1398,8 @@ static hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, size_
 // This file is compiled several times, in parallel: once for the fp32 variants and everything else, and once for each
 // part of the split-bf16 variants (XL_TU_SPLIT = the list, XL_TU_PR = parts - 1).
 typedef void (*BlockKernel)(const BlockParams);
-BlockKernel split_kernel_A1(int), split_kernel_B1(int), split_kernel_C1(int), split_kernel_D1(int), split_kernel_E1(int), split_kernel_F1(int);
-BlockKernel split_kernel_A2(int), split_kernel_B2(int), split_kernel_C2(int), split_kernel_D2(int), split_kernel_E2(int), split_kernel_F2(int);
+BlockKernel split_kernel_A1(int), split_kernel_B1(int), split_kernel_C1(int), split_kernel_D1(int), split_kernel_E1(int), split_kernel_F1(int), split_kernel_G1(int);
+BlockKernel split_kernel_A2(int), split_kernel_B2(int), split_kernel_C2(int), split_kernel_D2(int), split_kernel_E2(int), split_kernel_F2(int), split_kernel_G2(int);
 
 #ifdef XL_TU_SPLIT
 #define XL_CAT_(a, b, c) a##b##c
@@ -1408,6 +1411,9 @@ static BlockKernel select_split_kernel()
     return chain_kernel<PR, NPT1, NRT1, NRT2>;        // producers, K steps of layer 1, row tiles of layer 2
 #elif defined(XL_TU_KSPLIT)
     return ksplit_kernel<K1, NRT1, NPT1, NRT2, NPT2, (PX1 != 0), PR, PR1>;
+#elif defined(XL_TU_HEAD)
+    if constexpr (PX1 != 0) return head_divided_kernel<NRT1, PR>;
+    else return head_kernel<NRT1, NPT1, PR>;
 #else
     return block_kernel<KIND, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1, PR, PR1>;
 #endif
@@ -1455,8 +1461,8 @@ static BlockKernel kernel_of(int variant)
 #undef X
     }
     if (variant >= SPLIT_ID0[1]) {
-        for (auto part : {split_kernel_A1, split_kernel_B1, split_kernel_C1, split_kernel_D1, split_kernel_E1, split_kernel_F1, split_kernel_A2,
-                          split_kernel_B2, split_kernel_C2, split_kernel_D2, split_kernel_E2, split_kernel_F2})
+        for (auto part : {split_kernel_A1, split_kernel_B1, split_kernel_C1, split_kernel_D1, split_kernel_E1, split_kernel_F1, split_kernel_G1, split_kernel_A2,
+                          split_kernel_B2, split_kernel_C2, split_kernel_D2, split_kernel_E2, split_kernel_F2, split_kernel_G2})
             if (BlockKernel k = part(variant)) return k;
     }
     return nullptr;

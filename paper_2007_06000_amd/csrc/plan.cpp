@@ -31,6 +31,7 @@ const std::vector<Variant> &variants()
         XL_SPLIT_LIST_D(X)
         XL_SPLIT_LIST_E(X)
         XL_SPLIT_LIST_F(X)
+        XL_SPLIT_LIST_G(X)
 #undef X
     };
     return v;
@@ -418,7 +419,7 @@ static std::vector<Choice> search_ksplit(const BlockSpec &b, const xl_plan &pl, 
 static bool thin_table(const Variant &v) { return v.kind == KIND_THIN || v.kind == KIND_STEM; }
 
 // A variant with a handful of candidates per block.
-static bool few_candidates(const Variant &v) { return v.kind == KIND_CHAIN || v.kind == KIND_STEM; }
+static bool few_candidates(const Variant &v) { return v.kind == KIND_CHAIN || v.kind == KIND_STEM || v.kind == KIND_HEAD; }
 
 static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &lds_rejected, int pr)
 {
@@ -548,6 +549,56 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             std::sort(few.begin(), few.end(), [](const Choice &x, const Choice &y) { return x.cost < y.cost; });
             for (size_t i = 0; i < few.size() && i < 5; ++i) per_key[std::make_tuple(v.id, few[i].threads, few[i].th, few[i].tw)] = few[i];
             any_ok = any_ok || !few.empty();
+            continue;
+        }
+        if (v.kind == KIND_HEAD) {
+            if (b.kind != KIND_SINGLE || !b.gap || v.pr != pr || b.c1.k != 1 || b.c1.stride != 1 || b.c1.pad != 0) continue;
+            const int npx = b.Ho * b.Wo, npt = ceil_div(npx, 16), nrt = ceil_div(b.c1.cout, 16), nkg = ceil_div(b.c1.cin, 32), np = parts_of(pr);
+            if ((b.c1.cin + 32 * 32LL) * npx >= (1LL << 29) || (long long)(nkg + 16) * nrt * np * 1024 >= (1LL << 31)) continue;      // (32-bit offsets past the end of an image or filter)
+            // cycles: of a workgroup alone, and what every further one of its compute unit adds
+            auto offer = [&](int nw, int wr, int csplit, int lds_bytes, int occ, double life, double more) {
+                if ((pl.opts.force_threads > 0 && pl.opts.force_threads != nw * 64) || (pl.opts.force_cout_split > 0 && pl.opts.force_cout_split != csplit)) return;
+                if (lds_bytes > pl.lds_budget) {
+                    any_lds_reject = true;
+                    return;
+                }
+                Choice c;
+                c.v = v;
+                c.threads = nw * 64;
+                c.waves_r1 = wr;
+                c.th = c.mh = c.ih = b.Ho;
+                c.tw = c.vw2 = c.mw = c.iw = b.Wo;
+                c.tiles_y = c.tiles_x = c.chunk_kg = 1;
+                c.csplit = csplit;
+                c.lds_bytes = lds_bytes;
+                c.occ = std::max(1, std::min(pl.lds_per_cu / lds_bytes, occ));
+                const double wgs = (double)b.N * csplit;
+                c.cost = std::max((life + (std::ceil(wgs / pl.num_cus) - 1) * more) / 2.4e9, (double)b.alg_bytes / 5.4e12);
+                c.flops_exec = (long long)(wgs * 2.0 * ceil_div(nrt, csplit) * 16 * npt * 16 * nkg * 32);
+                c.ok = true;
+                any_ok = true;
+                Choice &kept = per_key[std::make_tuple(v.id, c.threads, c.th, c.tw)];
+                if (!kept.ok || c.cost < kept.cost) kept = c;
+            };
+            if (v.px1 != 0) {
+                const int groups = ceil_div(npx, 64);
+                for (int kw = 2; kw <= 8 && groups * kw * 64 <= head_threads(v.nrt1, pr); kw *= 2) {
+                    if ((kw > 2 && kw / 2 >= nkg) || groups * kw % v.nrt1 != 0) continue;
+                    // matrix operations and what takes the pixels apart (60 or 36 vector instructions per tile and K step) add up
+                    const double busy = nkg * groups * (v.nrt1 * products_of(pr) * 22.0 + (pr == 2 ? 255.0 : 155.0));
+                    offer(groups * kw, kw, ceil_div(nrt, v.nrt1), groups * kw * (v.nrt1 * 4096 + 64), head_threads(v.nrt1, pr) / (groups * kw * 64), 6000.0 + busy + ceil_div(nkg, kw) * 500.0, 0.95 * busy);
+                }
+                continue;
+            }
+            for (int nw : {4, 8}) {
+                if (npt > HEAD_UNITS * nw) continue;
+                for (int wr = 1; wr <= nw; wr *= 2) {
+                    const int pw = nw / wr;
+                    if (pw * v.npt1 < npt || (pw > 1 && pw / 2 * v.npt1 >= npt) || (wr > 1 && wr / 2 * v.nrt1 >= nrt)) continue;
+                    const double life = 9000.0 + nkg * (2200.0 + v.nrt1 * npt * wr / 4.0 * products_of(pr) * 17.4);
+                    offer(nw, wr, ceil_div(nrt, wr * v.nrt1), (nw * v.nrt1 * (np + 1) + 2 * npt * np) * 1024, 8 / nw, life, nw == 8 ? life : 0.6 * life);
+                }
+            }
             continue;
         }
         const bool stream = v.kind == KIND_POOLS;          // conv -> pool as a stream of tiles: same block kind

@@ -37,7 +37,7 @@ struct ConvW {
     int nrt;                // row tiles = ceil(cout / MF)
 };
 
-enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7, KIND_CHAIN = 8, KIND_KSPLIT = 9, KIND_STEM = 10 };
+enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_POOLS = 4, KIND_FUSED2P = 5, KIND_THIN = 6, KIND_DWP = 7, KIND_CHAIN = 8, KIND_KSPLIT = 9, KIND_STEM = 10, KIND_HEAD = 11 };
 
 // Kernel argument of every convolution-stage kernel.
 //   KIND_SINGLE: stage 1 writes its result to global memory (one layer, the
@@ -61,6 +61,7 @@ enum Kind { KIND_SINGLE = 0, KIND_FUSED2 = 1, KIND_POOL = 2, KIND_DW = 3, KIND_P
 //   KIND_DWP:    KIND_DW with a pointwise stage 2, both of stride 1, wave by wave without LDS (dw_conv.h).
 //   KIND_CHAIN:  KIND_FUSED2 of pointwise layers on split operands, the intermediate in registers (chain_conv.h).
 //   KIND_STEM:   KIND_POOL for 3 input channels, 3x3 with stride 2 -> pooling 3x3 with stride 2, on the bf16 matrix cores (stem_conv.h).
+//   KIND_HEAD:   KIND_SINGLE with gap, pointwise on bf16 parts: a workgroup takes whole images' pixels apart once for many channels (head_conv.h).
 //   KIND_KSPLIT: KIND_FUSED2 and KIND_FUSED2P on split operands, the waves of a workgroup dividing the reductions (ksplit_conv.h).
 struct BlockParams {
     const float *x;         // block input  [N, Cin, H, W]
@@ -131,7 +132,7 @@ struct Variant {
     int pr;                     // 0: fp32 matrix operations; 1, 2: operands as two or three bf16 parts (3 or 6 bf16
                                 // operations per product), in stage 2 or, for a kernel of one convolution, in stage 1
     int pr1;                    // the same for stage 1
-    bool direct() const { return pr1 == 2 && mf1 == 16; }       // stage 1 reads memory (direct_conv.h)
+    bool direct() const { return pr1 == 2 && mf1 == 16 && kind != KIND_HEAD; }       // stage 1 reads memory (direct_conv.h)
 };
 
 // id, kind, MF1, K1, NRT1, NPT1, MF2, NRT2, NPT2, K2A, K2B, SC, PX1
@@ -348,6 +349,15 @@ struct Variant {
     X(183, KIND_FUSED2, 16, 1, 1, 2, 32, 1, 1, 5, 0, 0, 0, 2)         \
     X(184, KIND_FUSED2, 16, 1, 2, 2, 32, 1, 1, 5, 0, 0, 0, 2)
 
+// Pointwise -> global average pooling (head_conv.h): columns 5 and 6 are the row and pixel tiles of a wave, column 13 = 1: the
+// waves divide the reduction.
+#define XL_SPLIT_LIST_G(X)                                            \
+    X(190, KIND_HEAD, 16, 1, 2, 11, 0, 0, 0, 0, 0, 0, 0, 1)           \
+    X(191, KIND_HEAD, 16, 1, 2, 7, 0, 0, 0, 0, 0, 0, 0, 1)            \
+    X(192, KIND_HEAD, 16, 1, 1, 4, 0, 0, 0, 0, 0, 0, 1, 1)            \
+    X(193, KIND_HEAD, 16, 1, 2, 4, 0, 0, 0, 0, 0, 0, 1, 1)            \
+    X(194, KIND_HEAD, 16, 1, 4, 4, 0, 0, 0, 0, 0, 0, 1, 1)
+
 #define XL_SPLIT_LIST_A(X)                                            \
     X(0, KIND_SINGLE, 32, 1, 1, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
     X(1, KIND_SINGLE, 32, 1, 2, 1, 0, 0, 0, 0, 0, 0, 0, 1)            \
@@ -424,6 +434,9 @@ const std::vector<Variant> &variants();
 #define XL_STAGE_UNITS 1
 #endif
 constexpr int STAGE_UNITS = XL_STAGE_UNITS;      // input units (4 channels x 4 pixels) each thread stages per chunk
+// ... of the kernels of head_conv.h whose waves divide the reduction: three waves per SIMD where 168 registers are enough
+constexpr int head_threads(int nrt, int pr) { return nrt == 4 && pr == 2 ? 512 : 768; }
+constexpr int HEAD_UNITS = 2;           // head_conv.h: pixel tiles of a K step that a wave takes apart, at most
 constexpr int DIRECT_AHEAD = 1;         // direct_conv.h: K steps that pixels are requested ahead
 constexpr int SPLIT_STAGE_UNITS = 2;    // split-bf16 kernels: units (64 pixels x 8 channels) each wave stages per chunk
 constexpr int MAX_W_CHUNK_BYTES = 52 * 1024;  // filter bytes staged per chunk (LDS-direct loads, no registers)

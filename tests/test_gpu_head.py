@@ -1,0 +1,75 @@
+"""Kernels for a pointwise convolution whose mean over the image is all that is kept (variants 390 to 394 and 590 to 594): channels that fill
+neither K steps of 32 nor row tiles of 16, images of one to thirteen pixel tiles, waves along pixels and along channels."""
+import numpy as np
+import pytest
+
+import xl_workloads as W
+from oracle import xlo
+
+CASES = [W.conv_gap_generic(n, cin, h, w, c1, 1, 0, 1) for n, cin, h, w, c1 in
+         [(1, 512, 13, 13, 1000), (3, 70, 7, 7, 129), (2, 33, 14, 14, 37), (5, 8, 5, 5, 10), (1, 64, 1, 1, 16), (2, 96, 12, 15, 300), (4, 31, 9, 12, 250),
+          (70, 40, 13, 13, 65), (1, 200, 4, 4, 515), (2, 32, 16, 16, 64)]]
+CASES = [pytest.param(wl, id=f"{wl.name}_n{wl.shapes[0][0]}") for wl in CASES]
+
+
+def candidates(p, base):
+    out = {}
+    for c in range(p.num_candidates(True, 0)):
+        v = p.candidate_info(True, 0, c)["variant"] - base
+        if 0 <= v < 5:
+            out.setdefault(v, []).append(c)
+    return out
+
+
+def test_every_kernel_is_planned():
+    from paper_2007_06000_amd import binding as B
+    for precision, base in ((0, 590), (1, 390)):
+        assert set().union(*(candidates(B.Plan(c.values[0], precision=precision), base) for c in CASES)) == set(range(5))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("wl", CASES)
+def test_against_the_oracle(wl, precision):
+    from paper_2007_06000_amd.session import Session
+    x, params = W.make_tensors(wl)
+    ref = xlo.forward(wl, x, params)
+    s = Session(wl, x, params, precision=precision)
+    for v, cs in candidates(s.plan, 390 if precision else 590).items():
+        for c in cs:
+            print(f"[case] {wl.name} kernel {v} candidate {s.plan.candidate_info(True, 0, c)}", flush=True)
+            s.plan.select_candidate(True, 0, c)
+            y = s.output(True)
+            # three parts: sums of up to 512 terms in two pieces, then of up to 256 values, 2^-20 is 16 roundings; two parts leave
+            # out 3 * 2^-16 of the absolute sums at most, here within four times that of the result's norm
+            assert np.linalg.norm(y - ref) <= (2.0 ** -12 if precision else 2.0 ** -20) * np.linalg.norm(ref), (v, c)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("special", [np.inf, np.nan, 3.4e38, 2.0 ** -134])
+@pytest.mark.parametrize("wl", CASES)
+def test_values_without_bf16_parts(wl, special):
+    """One such value, in the input and in the filter: what the fp32 kernels make of it, and nothing else changes."""
+    from paper_2007_06000_amd.session import Session
+    for where in ("x", "w"):
+        x, params = W.make_tensors(wl)
+        value = np.float32(special) * np.float32(1 + 2.0 ** -10 if special < 1 else 1)
+        if special < 1:         # (all of one output's terms small, so that what the parts lack would show)
+            x *= np.float32(2.0 ** -126 if where == "x" else 1)
+            params[0]["w"] *= np.float32(2.0 ** -126 if where == "w" else 1)
+            params[0]["shift"][:] = 0
+        if where == "x":
+            x[0, 1, x.shape[2] // 2, x.shape[3] // 2] = value
+        else:
+            params[0]["w"][3, 5, 0, 0] = value
+        s = Session(wl, x, params)
+        fp32 = [c for c in range(s.plan.num_candidates(True, 0)) if s.plan.candidate_info(True, 0, c)["variant"] < 200][0]
+        s.plan.select_candidate(True, 0, fp32)
+        ref = s.output(True)
+        fin = np.isfinite(ref) & (np.abs(ref) < 1e20)
+        for v, cs in candidates(s.plan, 590).items():
+            print(f"[case] {wl.name} {special} in {where} kernel {v} candidate {s.plan.candidate_info(True, 0, cs[0])}", flush=True)
+            s.plan.select_candidate(True, 0, cs[0])
+            y = s.output(True)
+            assert (np.isnan(y) == np.isnan(ref)).all() and (np.isfinite(y) == np.isfinite(ref)).all(), (where, v)
+            assert (np.abs(y[fin] - ref[fin]) <= 1e-4 + 1e-4 * np.abs(ref[fin])).all(), (where, v)
