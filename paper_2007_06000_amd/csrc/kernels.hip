@@ -999,6 +999,7 @@ block_kernel(const BlockParams args)
             const int wr2 = wave & (P.waves_r2 - 1), wp2 = wave >> lg_r2;
             const int wg_pt2 = (nwaves >> lg_r2) * NPT2;
             float *tile2 = PR ? lds + P.tile2_off : buf;        // KIND_FUSED2P: what is pooled
+            int turn = 0;
             auto run_conv = [&](auto ks_tag, const ConvW &c, int coff, int chunk_kg2) {
                 constexpr int KS2 = decltype(ks_tag)::value;
                 const int per = udiv(c.nrt + P.csplit - 1, P.csplit, P.rcp_csplit);     // row tiles of this workgroup
@@ -1012,11 +1013,35 @@ block_kernel(const BlockParams args)
                 g2.w_off = 0;
                 g2.buf_stride = P.buf_stride;
                 const int d = P.P2 - c.pad;
-                for (int rp = rtb; rp < rte; rp += g2.wg_rt) {
-                    for (int pp = 0; pp < npt2; pp += wg_pt2) {
+                // Without a barrier behind a pass (row, pixel) tiles go to the waves in turn, those of the second sibling from where the first one's
+                // ended, so that no SIMD is left without a wave where rows or pixels do not divide by the waves along them (batch 64 at 13 x 13:
+                // 256 -> 48 -> {192, 192} 27.6 -> 25.0 us, 384 -> 48 31.3 -> 27.2; the network at batch 1 112.9 -> 109.7).  One
+                // layer alone loses more by it than it gains (40 channels of 27 x 27, batch 5: 12.3 -> 12.6).
+                constexpr bool TURNS = PR != 0 && K2B != 0 && KIND != KIND_FUSED2P;
+                const int nr = TURNS ? max(0, rte - rtb + NRT2 - 1) / NRT2 : 0, items = nr * ((npt2 + NPT2 - 1) / NPT2);
+                int item = 0, p_item = 0, r_item = 0, rows_on = 0;
+                if constexpr (TURNS) {
+                    item = __builtin_amdgcn_readfirstlane(wave - turn) & (nwaves - 1);
+                    if ((nr & (nr - 1)) == 0) {
+                        const int lg = __builtin_ctz(nr | 32);
+                        p_item = item >> lg;
+                        rows_on = nwaves >> lg;
+                    } else {
+                        p_item = div_upto8(item, nr);
+                        rows_on = div_upto8(nwaves, nr);
+                    }
+                    r_item = item - p_item * nr;
+                }
+                // The older of two waves of a SIMD takes the matrix pipe whenever it can, and the younger one finishes alone, where it waits for its
+                // operands (512 -> 64 -> {256, 256} at 13 x 13: 12.7 and 20.2 us of a workgroup's 40, the pipe busy for 15.8).  Where both have as
+                // many tiles, the younger one goes first for half of a tile: 16.3 and 18.5.
+                const bool first = PR == 2 && KS2 > 1 && NRT2 * NPT2 == 2 && nwaves == 8 && c.nkg >= 4 && (!TURNS || items % 8 == 0) && __builtin_amdgcn_readfirstlane(wave) >= 4;
+                turn += items;
+                for (int rp = TURNS ? 0 : rtb; TURNS ? item < items : rp < rte; rp += TURNS ? 0 : g2.wg_rt) {
+                    for (int pp = 0; pp < (TURNS ? 1 : npt2); pp += wg_pt2) {
                         g2.rt_base = rp;
-                        const int r0 = rp + wr2 * NRT2, p0 = pp + wp2 * NPT2;
-                        g2.active = r0 < rte && p0 < npt2;
+                        const int r0 = TURNS ? rtb + r_item * NRT2 : rp + wr2 * NRT2, p0 = TURNS ? p_item * NPT2 : pp + wp2 * NPT2;
+                        g2.active = TURNS || (r0 < rte && p0 < npt2);
                         typename MM<MF2>::Acc acc2[NRT2][NPT2];
                         int off2[NPT2];
                         init_acc<MF2, NRT2, NPT2>(acc2, c, r0);
@@ -1037,8 +1062,11 @@ block_kernel(const BlockParams args)
                                 for (int r = 0; r < NRT2; ++r)
 #pragma unroll
                                     for (int p = 0; p < NPT2; ++p) zero_acc(small[r][p]);
+                                if constexpr (PR == 2 && KS2 > 1 && NRT2 * NPT2 == 2) {
+                                    if (first) __builtin_amdgcn_s_setprio(1);
+                                }
                                 conv_direct<KS2, NRT2, NPT2, PR>(acc2, small, mid, off2, P.mw, P.mid_gstride, c, r0, 0,
-                                                                 c.nkg, __builtin_amdgcn_readfirstlane(npt2 - p0), [] {});
+                                                                 c.nkg, __builtin_amdgcn_readfirstlane(npt2 - p0), [] {}, first ? c.nkg >> 1 : -1);
                                 if constexpr (PR == 2) {
                                     add_small<NRT2, NPT2>(acc2, small);
                                     if (any_not_finite<NRT2, NPT2>(acc2)) {
@@ -1101,6 +1129,13 @@ block_kernel(const BlockParams args)
                         } else if (g2.active)
                             store_global<MF2, NRT2, NPT2, SC>(acc2, P, c, coff, n, oy0, ox0, P.th, P.tw, P.vw2, r0, rte,
                                                               p0, P.relu_out, P.rcp_vw2);
+                    }
+                    item += nwaves;
+                    p_item += rows_on;
+                    r_item += nwaves - rows_on * nr;
+                    if (r_item >= nr) {
+                        r_item -= nr;
+                        ++p_item;
                     }
                 }
             };

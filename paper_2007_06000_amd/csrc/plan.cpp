@@ -152,6 +152,9 @@ static bool stem_shape(const BlockSpec &b)
 }
 
 // Model of one candidate.  Times in seconds on a nominal MI355X (2.4 GHz, 8 TB/s).
+// Stage 2 deals its tiles to the waves in turn (block_kernel).
+static bool turns(const BlockSpec &b, const Variant &v) { return v.pr != 0 && v.k2b != 0 && b.kind != KIND_FUSED2P; }
+
 static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
 {
     const Variant &v = c.v;
@@ -200,11 +203,21 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
         const int mf2 = v.mf2, NRT2 = v.nrt2, NPT2 = v.npt2;
         const int npt2 = ceil_div(c.th * c.vw2, mf2);
         const int wg_rt2 = c.waves_r2 * NRT2, wg_pt2 = (nw / c.waves_r2) * NPT2;
+        double simd2[4] = {0, 0, 0, 0};
+        int dealt = 0;
         for (int ci = 0; ci < b.n2; ++ci) {
             const ConvSpec &s = b.c2[ci];
             const int nrt = ceil_div(s.cout, mf2), nkg = ceil_div(s.cin, kc_of(mf2, v.pr));
             const int per = std::min(nrt, ceil_div(nrt, c.csplit));
             const double wave2 = (double)NRT2 * NPT2 * nkg * s.k * s.k * kstep_clk(mf2, v.pr);
+            flops2 += 2LL * per * mf2 * npt2 * mf2 * nkg * kc_of(mf2, v.pr) * s.k * s.k;
+            if (turns(b, v)) {
+                const int items = ceil_div(per, NRT2) * ceil_div(npt2, NPT2), mine = ceil_div(items, nw);
+                for (int w = 0; w < nw && w < items; ++w) simd2[(dealt + w) % 4] += (double)((items - w + nw - 1) / nw) * wave2;
+                dealt += items;
+                passes += mine;
+                continue;
+            }
             // the passes are alike except for the last of the row tiles and the last of the pixel tiles
             const int rows_last = (per - 1) % wg_rt2 + 1, px_last = (npt2 - 1) % wg_pt2 + 1;       // tiles of those
             const int row_passes = ceil_div(per, wg_rt2), px_passes = ceil_div(npt2, wg_pt2);
@@ -223,8 +236,8 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
                 }
             passes += row_passes * px_passes;
             if (!v.pr) barriers += row_passes * px_passes * ceil_div(nkg, c.chunk_kg2[ci]);      // (split operands: no filter chunks)
-            flops2 += 2LL * per * mf2 * npt2 * mf2 * nkg * kc_of(mf2, v.pr) * s.k * s.k;
         }
+        if (turns(b, v)) t2 = *std::max_element(simd2, simd2 + 4) + 2500.0 * passes;      // + epilogue / prologue of every tile of a wave
     } else if (b.kind == KIND_POOL) {
         t2 = (double)ceil_div(b.c1.cout, 4) * c.th * c.tw * b.pool_k * b.pool_k * 8.0 / c.threads * 4;
     }
@@ -726,7 +739,7 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                             for (int i = 0; i < b.n2; ++i) min_nrt = std::min(min_nrt, ceil_div(b.c2[i].cout, v.mf2));
                             for (int s = 1; s <= 8 && s <= min_nrt; s *= 2) splits.add(s);
                         }
-                        for (int w2 = 1; w2 <= nw; w2 *= 2) wr2s.add(w2);
+                        for (int w2 = 1; w2 <= (turns(b, v) ? 1 : nw); w2 *= 2) wr2s.add(w2);
                         const int tw2 = c.tw;
                         vws.add(tw2);
                         if (!pool2) {       // (the pooled form writes its tile to LDS pixel by pixel: no padded rows)

@@ -151,12 +151,12 @@ __device__ __forceinline__ void lds_barrier()
 // pixel plus the planes of its lane half; `bsrc` starts at K step kg0.  Filter in memory:
 // [K step][tap][row tile][part][lane] 16 bytes.  The operands of the next (K step, tap) steps are requested before the
 // matrix operations of the current one: filter rows PD steps ahead, pixels one.  `hook` runs once the first filter
-// rows have been requested: what it requests (the next input chunk) comes after them in the queue.
+// rows have been requested: what it requests (the next input chunk) comes after them in the queue.  From K step `lower_at` on the wave has priority 0.
 // ----------------------------------------------------------------------------
 template <int KS, int NRT, int NPT, int PR, int LIVE, typename Hook>
 __device__ __forceinline__ void conv_tiles(f32x16 (&acc)[NRT][NPT], f32x16 (&accl)[NRT][NPT], const float *bsrc,
                                            const int (&off)[NPT], int src_w, int gstride, const ConvW &c, int rt0,
-                                           int kg0, int nkg, Hook hook)
+                                           int kg0, int nkg, Hook hook, int lower_at)
 {
     constexpr int T = KS * KS, NP = PR + 1, GROUPS = 2 * NP;     // planes per K step
     constexpr int PD = NRT >= 2 ? 1 : 2;                        // steps the filter rows are requested ahead
@@ -249,6 +249,7 @@ __device__ __forceinline__ void conv_tiles(f32x16 (&acc)[NRT][NPT], f32x16 (&acc
 #pragma unroll 1
         for (int kg = 0; kg < nkg; ++kg) {
             const bool last = kg + 1 >= nkg;
+            if (kg == lower_at) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 if (t == T - 1) next_px(!last);
@@ -280,10 +281,10 @@ __device__ __forceinline__ void conv_tiles(f32x16 (&acc)[NRT][NPT], f32x16 (&acc
 template <int KS, int NRT, int NPT, int PR, typename Hook>
 __device__ __forceinline__ void conv_direct(f32x16 (&acc)[NRT][NPT], f32x16 (&accl)[NRT][NPT], const float *bsrc,
                                             const int (&off)[NPT], int src_w, int gstride, const ConvW &c, int rt0,
-                                            int kg0, int nkg, int live, Hook hook)
+                                            int kg0, int nkg, int live, Hook hook, int lower_at = -1)
 {
-    if (NPT == 1 || live > 1) conv_tiles<KS, NRT, NPT, PR, NPT>(acc, accl, bsrc, off, src_w, gstride, c, rt0, kg0, nkg, hook);
-    else conv_tiles<KS, NRT, NPT, PR, 1>(acc, accl, bsrc, off, src_w, gstride, c, rt0, kg0, nkg, hook);
+    if (NPT == 1 || live > 1) conv_tiles<KS, NRT, NPT, PR, NPT>(acc, accl, bsrc, off, src_w, gstride, c, rt0, kg0, nkg, hook, lower_at);
+    else conv_tiles<KS, NRT, NPT, PR, 1>(acc, accl, bsrc, off, src_w, gstride, c, rt0, kg0, nkg, hook, lower_at);
 }
 
 // The same sums by fp32 matrix operations on whole operands, for a wave whose sums are not all finite: rare, so it is
