@@ -16,10 +16,11 @@
 // K slots of step k and lane half h, filter row R = 4 h + 2 k:  R.0 R.1 (R+1).0 (R+1).1 R.2 (R+1).2 s s', where s s' are, for
 // k = 0, row 8's taps 0 and 1 (h = 0) and 2 and nothing (h = 1), for k = 1 the shift and nothing (h = 0).  Where a slot has no filter
 // value it is 0 and meets whatever lies there.
-// What bounds it: vector instructions, some 800 per pooled row and wave against 48 matrix operations, half of them for taking the
-// pixels apart.  Time per pass, before -> here: to 64 channels at 224 x 224, batch 64: 67 -> 40 us, batch 8: 16 -> 10.8; to 96 at
-// 150 x 200, batch 16: 29.5 -> 15.5; to 32 at 224 x 224, batch 50: 32 -> 21.  64 channels per wave, which takes a pixel apart once,
-// was slower (46 us at batch 64: 248 registers, two waves per SIMD), as was holding a third of the filter in LDS (equal).
+// Every value of a piece is taken apart once: the third column of a block is the first of its right tile too, and the fifth comes from the next lane in parts.
+// What bounds it: some 600 vector instructions and 48 matrix operations per pooled row and wave, and the waits between them (5600 cycles a row and
+// SIMD with two waves as with three).  Time per pass, on the vector ALU -> here with every K slot taken apart by itself -> here: to 64 channels at 224 x 224, batch 64: 67 -> 35.2 ->
+// 33.6 us, batch 8: 16 -> 10.9 -> 10.1.  Before, to 96 at 150 x 200, batch 16: 29.5 -> 15.5; to 32 at 224 x 224, batch 50: 32 -> 21.
+// 64 channels per wave were slower (46 us at batch 64, of 40 then: 248 registers, two waves per SIMD), a third of the filter in LDS equal.
 // Where the chip is not filled the stream kernel stays ahead (to 64 channels at 224 x 224, xl_profile with its 2 to 3 us of events, batch 1:
 // 8.6 us there, 9.5 here; batch 2: 9.5 and 9.6; batch 4: 12.3 and 10.0).
 // A wave in which a value has no bf16 parts, or one is so large that a sum might overflow, takes fp32 matrix operations instead.
@@ -34,6 +35,11 @@ namespace xl {
 __device__ __forceinline__ float next_lane(float v)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));     // wave_shl:1
+}
+
+__device__ __forceinline__ unsigned next_lane(unsigned v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true);
 }
 
 __global__ void __launch_bounds__(256, 3) stem_pool_kernel(const BlockParams P)
@@ -64,9 +70,8 @@ __global__ void __launch_bounds__(256, 3) stem_pool_kernel(const BlockParams P)
             x[i] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xr, (unsigned)(at + (tx * 31 + (ln & 31)) * 16), row * W * 4, 0));
         }
     };
-    f32x4 xa[5], xb[5];
-    load(xa, 4 * py0);
-    load(xb, 4 * py0 + 2);
+    f32x4 x[5];
+    load(x, 4 * py0);
 
     // ---- the filter in parts
     const int rows16 = (P.c1.cout + 15) / 16 * 16;
@@ -104,49 +109,60 @@ __global__ void __launch_bounds__(256, 3) stem_pool_kernel(const BlockParams P)
     int lo = relu_bound(P.c1.relu);
     asm volatile("" : "+s"(lo));
 
-    // One convolution row of the blocks: the two tiles dx = 0, 1 from the pieces x; use(dx, sums) takes the 16 sums of one.
-    auto conv_row = [&](const f32x4 (&x)[5], auto use) {
-        float largest = 0.f;
+    // One convolution row of the blocks, `row` its first image row: the two tiles dx = 0, 1 from the pieces x, for which those of the image row
+    // `next` are asked as soon as they are taken apart; use(dx, sums) takes the 16 sums of one.
+    auto conv_row = [&](int row, bool more, int next, auto use) {
+        float sum = 0.f;                // (NaN stays, and is not below LARGE)
+#pragma unroll
+        for (int i = 0; i < 5; ++i) sum += (fabsf(x[i][0]) + fabsf(x[i][1])) + (fabsf(x[i][2]) + fabsf(x[i][3]));
+        // every value is taken apart once: the third column of a block is also the first of its right tile, and what a lane needs of the next
+        // one's pieces comes in parts
+        unsigned left = 0;
+        unsigned front[5][3], back[5][3];       // columns 0, 1 and 2, 3 of the pieces
 #pragma unroll
         for (int i = 0; i < 5; ++i) {
-            largest = fmaxf(fmaxf(largest, fabsf(x[i][0])), fabsf(x[i][1]));
-            largest = fmaxf(fmaxf(largest, fabsf(x[i][2])), fabsf(x[i][3]));
+            split_exact(x[i][0], x[i][1], front[i], left);
+            split_exact(x[i][2], x[i][3], back[i], left);
         }
-        unsigned odd = 0;
-        // slot e of K step k for tile dx
-        auto slot = [&](int dx, int k, int e) {
-            const f32x4 &p = x[2 * k], &q = x[2 * k + 1];
-            if (e < 2) return p[2 * dx + e];
-            if (e < 4) return q[2 * dx + e - 2];
-            if (e == 4) return dx ? next_lane(p[0]) : p[2];
-            if (e == 5) return dx ? next_lane(q[0]) : q[2];
-            return x[4][2 * dx + e - 6];
-        };
+        const bool whole = whole_filter || __builtin_amdgcn_ballot_w64((left & 0xffffu) != 0u || !(sum < LARGE)) != 0;
+        if (more) load(x, next);
 #pragma unroll
         for (int dx = 0; dx < 2; ++dx) {
             u32x4 b[2][3];
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    unsigned w[3] = {0x3f80u, 0u, 0u};          // 1 for the shift
-                    if (!(k == 1 && j == 3)) split_pair<2>(slot(dx, k, 2 * j), slot(dx, k, 2 * j + 1), w, odd);
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) b[k][i][j] = w[i];
+                for (int i = 0; i < 3; ++i) {
+                    const int p = 2 * k, q = p + 1;
+                    b[k][i][0] = dx ? back[p][i] : front[p][i];
+                    b[k][i][1] = dx ? back[q][i] : front[q][i];
+                    const unsigned third = dx ? __builtin_amdgcn_perm(front[q][i], front[p][i], 0x05040100u) : __builtin_amdgcn_perm(back[q][i], back[p][i], 0x05040100u);
+                    b[k][i][2] = dx ? next_lane(third) : third;
+                    b[k][i][3] = k == 0 ? (dx ? back[4][i] : front[4][i]) : i == 0 ? 0x3f80u : 0u;          // (1 for the shift)
                 }
-            const bool whole = whole_filter || __builtin_amdgcn_ballot_w64(odd != 0u || largest >= LARGE) != 0;
             __builtin_amdgcn_sched_barrier(0);
             f32x16 acc;
             zero_acc(acc);
             if (__builtin_expect(whole, 0)) {
                 int ln = lane;          // (addresses are worked out here: no registers for them elsewhere)
                 asm volatile("" : "+v"(ln));
+                f32x4 z[5];
+                load(z, row);
+                // slot e of K step k
+                auto slot = [&](int k, int e) {
+                    const f32x4 &p = z[2 * k], &q = z[2 * k + 1];
+                    if (e < 2) return p[2 * dx + e];
+                    if (e < 4) return q[2 * dx + e - 2];
+                    if (e == 4) return dx ? next_lane(p[0]) : p[2];
+                    if (e == 5) return dx ? next_lane(q[0]) : q[2];
+                    return z[4][2 * dx + e - 6];
+                };
 #pragma unroll
                 for (int k = 0; k < 2; ++k)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         float v = 1.f;
-                        if (!(k == 1 && e >= 6)) v = k == 0 && e == 7 && half == 1 ? 0.f : slot(dx, k, e);
+                        if (!(k == 1 && e >= 6)) v = k == 0 && e == 7 && half == 1 ? 0.f : slot(k, e);
                         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(filter(ln, k, e), v, acc, 0, 0, 0);
                     }
                 asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc));
@@ -173,7 +189,7 @@ __global__ void __launch_bounds__(256, 3) stem_pool_kernel(const BlockParams P)
     f32x16 block, most;
 #pragma unroll 1
     for (int py = py0; py <= py1; ++py) {
-        conv_row(xa, [&](int dx, const f32x16 &v) {
+        conv_row(4 * py, py < py1, 4 * py + 2, [&](int dx, const f32x16 &v) {
             if (dx == 0) {
                 block = v;
                 return;
@@ -193,8 +209,7 @@ __global__ void __launch_bounds__(256, 3) stem_pool_kernel(const BlockParams P)
             for (int e = 0; e < 16; ++e) most[e] = fmaxf(block[e], v[e]);
         });
         if (py == py1) break;
-        load(xa, 4 * py + 4);
-        conv_row(xb, [&](int dx, const f32x16 &v) {
+        conv_row(4 * py + 2, true, 4 * py + 4, [&](int dx, const f32x16 &v) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 if (dx == 0) block[e] = fmaxf(block[e], v[e]);
@@ -202,7 +217,6 @@ __global__ void __launch_bounds__(256, 3) stem_pool_kernel(const BlockParams P)
                 if (dx == 1) most[e] = fmaxf(most[e], next_lane(block[e]));
             }
         });
-        if (py + 1 < py1) load(xb, 4 * py + 6);
     }
 }
 
