@@ -369,9 +369,12 @@ __device__ __forceinline__ void head_divided_block()
     lds_barrier();
     const int row = threadIdx.x, co = rt0 * 16 + row;
     if (row < NRT * 16 && co < c.cout) {
-        float t = 0.f;
-        for (int w = row >> 4; w < nw; w += NRT) t += red[w * 16 + (row & 15)];
-        P.y[(size_t)n * P.Cy + P.coff1 + co] = t * (1.f / (float)npx);
+        // (in four sums: one after the other the waves' sums lost more bits than all that went before)
+        float t[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int w = row >> 4; w < nw; w += 4 * NRT)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) t[k] += w + k * NRT < nw ? red[(w + k * NRT) * 16 + (row & 15)] : 0.f;
+        P.y[(size_t)n * P.Cy + P.coff1 + co] = ((t[0] + t[1]) + (t[2] + t[3])) * (1.f / (float)npx);
     }
 }
 

@@ -1144,6 +1144,7 @@ struct Builder {
     // Layers whose blocks get no kernels on split operands, or, in a plan on two parts, none that take the layer on three
     // (build_plan).
     std::set<int> fp32_layers;
+    bool compact = false;       // no kernels that take filters in parts for 16-wide tiles: a form of its own (build_plan)
     bool has_fp32_layer(const BlockSpec &b) const
     {
         bool found = fp32_layers.count(b.c1.layer) || (b.n1 == 2 && fp32_layers.count(b.c1b.layer));
@@ -1198,6 +1199,10 @@ struct Builder {
             auto on_three = [](const Choice &c) { return c.v.pr1 == 2; };
             split.erase(std::remove_if(split.begin(), split.end(), on_three), split.end());
             ksplit.erase(std::remove_if(ksplit.begin(), ksplit.end(), on_three), ksplit.end());
+            direct.clear();
+        }
+        if (compact) {
+            split.erase(std::remove_if(split.begin(), split.end(), [](const Choice &c) { return c.v.kind == KIND_HEAD; }), split.end());
             direct.clear();
         }
         if (!split.empty()) {
@@ -1755,11 +1760,14 @@ xl_status build_plan(xl_plan &pl, const xl_group *groups, int ngroups)
     // 32-row tile badly; where that is too much (2500 -> 700 channels, 3x3: 60.8 MB, 151.9 MB with three parts) the blocks
     // of the layers with the largest filters stay on fp32 kernels.  In a plan on two parts (XL_PRECISION_BF16X3) the kernels that
     // take a pointwise first layer on three are left out in the same way, as long as that makes it fit (15000 -> 512 -> {32, 32}
-    // channels: 94.4 MB, 140.5 with them).
+    // channels: 94.4 MB, 140.5 with them).  Before all that the forms for 16-wide tiles go, whose kernels always have others next to them (4400 ->
+    // 1600 channels -> mean: 98.8 MB, 141.0 with them).
     std::set<int> fp32_layers;
+    bool compact = false;
     for (;;) {
         Builder b(pl);
         b.fp32_layers = fp32_layers;
+        b.compact = compact;
         const xl_status s = b.build(groups, ngroups);
         if (s != XL_OK) return s;
         const size_t room = XL_STATIC_SCRATCH_BYTES + STATIC_SPLIT_BYTES;
@@ -1768,12 +1776,16 @@ xl_status build_plan(xl_plan &pl, const xl_group *groups, int ngroups)
         size_t all = 0;
         for (const PackedFilter &p : pl.packed)
             if (p.pr == 2) split.push_back({p.bytes, p.layer}), all += p.bytes;
-        if (pl.opts.precision != XL_PRECISION_FP32 && (split.empty() || pl.workspace_bytes - all > room)) break;
-        std::sort(split.rbegin(), split.rend());
-        size_t saved = 0;
-        for (size_t i = 0; i < split.size() && pl.workspace_bytes - saved > room; ++i) {
-            fp32_layers.insert(split[i].second);
-            saved += split[i].first;
+        if (!compact && std::any_of(pl.packed.begin(), pl.packed.end(), [](const PackedFilter &p) { return p.pr != 0 && p.mf == 16; })) {
+            compact = true;
+        } else {
+            if (pl.opts.precision != XL_PRECISION_FP32 && (split.empty() || pl.workspace_bytes - all > room)) break;
+            std::sort(split.rbegin(), split.rend());
+            size_t saved = 0;
+            for (size_t i = 0; i < split.size() && pl.workspace_bytes - saved > room; ++i) {
+                fp32_layers.insert(split[i].second);
+                saved += split[i].first;
+            }
         }
         pl.packed.clear();
         pl.unfused_steps.clear();

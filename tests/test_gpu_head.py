@@ -27,6 +27,15 @@ def test_every_kernel_is_planned():
         assert set().union(*(candidates(B.Plan(c.values[0], precision=precision), base) for c in CASES)) == set(range(5))
 
 
+@pytest.mark.parametrize("cin,head", [(2000, True), (4400, False)])
+def test_where_the_static_array_is_short_the_other_kernels_on_parts_stay(cin, head):
+    """Filters of 2000 x 1600 have room in all their forms; of 4400 x 1600 they take 141 MB of the 128 in all, 99 without those of these kernels."""
+    from paper_2007_06000_amd import binding as B
+    p = B.Plan(W.conv_gap_generic(1, cin, 7, 7, 1600, 1, 0, 1))
+    used = {p.candidate_info(True, 0, c)["variant"] for c in range(p.num_candidates(True, 0))}
+    assert p.workspace_bytes() <= 128 << 20 and any(400 <= v < 590 for v in used) and any(v >= 590 for v in used) == head
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("wl", CASES)
