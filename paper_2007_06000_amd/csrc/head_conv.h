@@ -11,8 +11,8 @@
 // come to its place in LDS a K step ahead without passing registers, which the accumulators fill (2 x 11 tiles of two accumulators: 176 of 256).
 // head_divided_kernel: where few workgroups are to be had (below).
 //
-// What bounds it: one K step of the 2 x 11 kernel takes 7000 cycles where its matrix operations take 4200, with four workgroups on the chip as with 256: LDS reads
-// (264 KB a step) that a wave waits for.  512 -> 1000 channels at 13 x 13, layer by layer -> here, three parts / two: batch 64 86.8 -> 50.4 / 54.5 -> 32.3 us, batch 8 20.6 ->
+// What bounds it: one K step of the 2 x 11 kernel takes 7000 cycles where its matrix operations take 4200, with four workgroups on the chip as with 256 (inferred: LDS reads,
+// 264 KB a step, that a wave waits for; the third part of a pixel is asked for 96 cycles of its own matrix work before it is due).  512 -> 1000 channels at 13 x 13, layer by layer -> here, three parts / two: batch 64 86.8 -> 50.4 / 54.5 -> 32.3 us, batch 8 20.6 ->
 // 12.9 / 18.0 -> 9.8, batch 1 10.8 -> 9.7; at 7 x 7, batch 64: 25.2 -> 23.0; 300 -> 500 at 10 x 9, batch 16: 11.0 -> 8.0; 128 -> 100 at 14 x 14, batch 32: 8.0 -> 6.0.
 #pragma once
 
