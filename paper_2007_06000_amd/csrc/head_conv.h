@@ -83,7 +83,7 @@ __device__ __forceinline__ void head_block()
             w_at[r] += nrt * (NP * 1024);
         }
     };
-    // units of a K step: 32 channels of one pixel tile, 8 per lane, wave after wave
+    // units of a K step: 32 channels of one pixel tile, 8 per lane, wave after wave (the channel in the lane's offset: direct_conv.h)
     unsigned off[MAX_UNITS];
     float x[MAX_UNITS][8];
 #pragma unroll
@@ -96,7 +96,7 @@ __device__ __forceinline__ void head_block()
         for (int i = 0; i < MAX_UNITS; ++i) {
             if (wave + i * nw < npt) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) x[i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off[i], j * step, 0));
+                for (int j = 0; j < 8; ++j) x[i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off[i] + j * step, 0, 0));
             }
             off[i] += 32 * step;
         }
@@ -223,7 +223,7 @@ __device__ __forceinline__ void head_block()
                         const unsigned at = px < npx ? (unsigned)(px * 4 + sub * 8 * step) : 0x80000000u;
                         const f32x4 v = direct_whole(c, min(rt0 + r, nrt - 1), [&](int kg, float (&xv)[8]) {
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) xv[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, at + kg * 32 * step, j * step, 0));
+                            for (int j = 0; j < 8; ++j) xv[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, at + kg * 32 * step + j * step, 0, 0));
                         });
 #pragma unroll
                         for (int e = 0; e < 4; ++e) s[r][e] += px < npx ? relu_from(v[e], lo) : 0.f;
@@ -282,20 +282,20 @@ __device__ __forceinline__ void head_divided_block()
     f32x4 x[8], a[NRT][NP];
     auto request_x = [&]() {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xr, off, j * step, 0));
+        for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xr, off + j * step, 0, 0));
         off += (32 * step) << lk;
     };
-    int w_at = wk * nrt * (NP * 1024);
-    auto request_a = [&]() {
+    int w_at = min(wk, nkg - 1) * nrt * (NP * 1024);
+    auto request_a = [&](int next) {            // (past the wave's last K step its rows once more: a scalar offset stays inside its buffer)
 #pragma unroll
         for (int r = 0; r < NRT; ++r)
 #pragma unroll
             for (int i = 0; i < NP; ++i)
                 a[r][i] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(wsrc, lane * 16, w_at + min(rt0 + r, nrt - 1) * (NP * 1024) + i * 1024, 0));
-        w_at += (nrt * (NP * 1024)) << lk;
+        w_at += next < mine ? (nrt * (NP * 1024)) << lk : 0;
     };
     request_x();
-    request_a();
+    request_a(1);
     const int r_sum = wave & (NRT - 1);         // the row tile whose sums the wave adds up
     const f32x4 shift = c.aff[min(rt0 + r_sum, nrt - 1) * 64 + lane];
     f32x4 acc[NRT][4], low[NRT][4];
@@ -313,7 +313,7 @@ __device__ __forceinline__ void head_divided_block()
             u32x4 b[NP];
             const float px[8] = {x[0][t], x[1][t], x[2][t], x[3][t], x[4][t], x[5][t], x[6][t], x[7][t]};
             head_parts<PR>(px, b);
-            if (t == 3) request_x();            // (past the last K step: zeros or filter rows that nothing reads)
+            if (t == 3) request_x();            // (past the last K step: zeros that nothing reads)
 #pragma unroll
             for (int i = NP - 1; i >= 0; --i)
 #pragma unroll
@@ -324,7 +324,7 @@ __device__ __forceinline__ void head_divided_block()
                         d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[r][j]), __builtin_bit_cast(bf16x8, b[i]), d, 0, 0, 0);
                     }
         }
-        request_a();
+        request_a(k + 2);
     }
     asm volatile("s_nop 15");
     float *part = lds, *red = lds + ((NRT * tiles) << lk) * 256;
@@ -354,7 +354,7 @@ __device__ __forceinline__ void head_divided_block()
                 const unsigned at = px < npx ? (unsigned)(px * 4 + sub * 8 * step) : NOWHERE;
                 v = direct_whole(c, min(rt0 + r_sum, nrt - 1), [&](int kg, float (&xv)[8]) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) xv[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, at + kg * 32 * step, j * step, 0));
+                    for (int j = 0; j < 8; ++j) xv[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, at + kg * 32 * step + j * step, 0, 0));
                 });
             }
         }

@@ -96,3 +96,28 @@ def test_values_without_bf16_parts(wl, options, special):
             y = s.output(True)
             assert (np.isnan(y) == np.isnan(ref)).all() and (np.isfinite(y) == np.isfinite(ref)).all(), (where, v)
             assert (np.abs(y[fin] - ref[fin]) <= 1e-4 + 1e-4 * np.abs(ref[fin])).all(), (where, v)
+
+
+FEW = [named(W.config(3, n=2, hw=9, cin=c, s=16, e=64), f"fire_{c}") for c in (1, 3, 7, 33)]
+FEW += [named(W.split_fire_pool(n=2, cin=c, hw=11, s=24, e=64), f"firepool_{c}") for c in (1, 7, 39)] + [named(W.straight_generic(2, 3, 9, 9, 16, 1, 0, 1, 32, 5, 2, 1), "conv5_3")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("special", [np.inf, np.nan])
+@pytest.mark.parametrize("wl", [pytest.param(wl, id=wl.name) for wl in FEW])
+def test_channels_past_the_last_one_are_not_those_of_the_next_image(wl, special, precision):
+    """Filters hold zeros for them, which only a finite value meets without harm: the second image has none."""
+    from paper_2007_06000_amd.session import Session
+    x, params = W.make_tensors(wl)
+    ref = xlo.forward(wl, x, params)
+    x[1] = special
+    s = Session(wl, x, params, precision=precision)
+    found = candidates(s.plan, 370 if precision else 570)
+    assert found
+    for v, cs in found.items():
+        for c in cs:
+            print(f"[case] {wl.name} kernel {v} candidate {s.plan.candidate_info(True, 0, c)}", flush=True)
+            s.plan.select_candidate(True, 0, c)
+            y = s.output(True)
+            assert np.linalg.norm(y[0] - ref[0]) <= (2.0 ** -12 if precision else 2.0 ** -20) * np.linalg.norm(ref[0]), (v, c)

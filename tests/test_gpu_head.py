@@ -82,3 +82,25 @@ def test_values_without_bf16_parts(wl, special):
             y = s.output(True)
             assert (np.isnan(y) == np.isnan(ref)).all() and (np.isfinite(y) == np.isfinite(ref)).all(), (where, v)
             assert (np.abs(y[fin] - ref[fin]) <= 1e-4 + 1e-4 * np.abs(ref[fin])).all(), (where, v)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("special", [np.inf, np.nan])
+@pytest.mark.parametrize("cin,hw", [(1, 4), (3, 7), (7, 13), (33, 7), (39, 5)])
+def test_channels_past_the_last_one_are_not_those_of_the_next_image(cin, hw, special, precision):
+    """Filters hold zeros for them, which only a finite value meets without harm: the second image has none."""
+    from paper_2007_06000_amd.session import Session
+    wl = W.conv_gap_generic(2, cin, hw, hw, 130, 1, 0, 1)
+    x, params = W.make_tensors(wl)
+    ref = xlo.forward(wl, x, params)
+    x[1] = special
+    s = Session(wl, x, params, precision=precision)
+    found = candidates(s.plan, 390 if precision else 590)
+    assert found
+    for v, cs in found.items():
+        for c in cs:
+            print(f"[case] {wl.name} kernel {v} candidate {s.plan.candidate_info(True, 0, c)}", flush=True)
+            s.plan.select_candidate(True, 0, c)
+            y = s.output(True)
+            assert np.linalg.norm(y[0] - ref[0]) <= (2.0 ** -12 if precision else 2.0 ** -20) * np.linalg.norm(ref[0]), (v, c)
