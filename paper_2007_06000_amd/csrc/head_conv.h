@@ -58,8 +58,9 @@ __device__ __forceinline__ void head_block()
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     const int lr = __builtin_ctz(P.waves_r1), wr = wave & (P.waves_r1 - 1), wp = wave >> lr, pw = nw >> lr;
     const int npx = P.mh * P.mw, npt = (npx + 15) >> 4, nrt = c.nrt, nkg = c.nkg;
-    const int rt0 = (cs * P.waves_r1 + wr) * NRT, pt0 = wp * NPT;
-    const int live = rt0 < nrt ? min(NPT, npt - pt0) : 0;           // pixel tiles of the wave
+    const int per = (npt + pw - 1) >> __builtin_ctz(pw);            // pixel tiles of a wave: as many to each (11 and 2 of 13 lost more bits in the last sum than 7 and 6)
+    const int rt0 = (cs * P.waves_r1 + wr) * NRT, pt0 = wp * per;
+    const int live = rt0 < nrt ? min(per, npt - pt0) : 0;
     const int step = npx * 4;                                       // bytes from channel to channel
 
     float *a_lds = lds + wave * (NRT * NP * 256);                   // filter rows of a K step: every wave its own
@@ -114,13 +115,6 @@ __device__ __forceinline__ void head_block()
     };
 
     f32x4 acc[NRT][NPT], low[PR == 2 ? NRT : 1][PR == 2 ? NPT : 1];
-#pragma unroll
-    for (int r = 0; r < NRT; ++r)
-#pragma unroll
-        for (int p = 0; p < NPT; ++p) {
-            zero_acc(acc[r][p]);
-            if constexpr (PR == 2) zero_acc(low[r][p]);
-        }
     request_a();
 #pragma unroll
     for (int r = 0; r < NRT; ++r)
@@ -129,6 +123,16 @@ __device__ __forceinline__ void head_block()
     __builtin_amdgcn_s_waitcnt(0);
     put_x(b_lds);
     request_x();
+    // (sums begin with the shift: added behind them it is one rounding more)
+#pragma unroll
+    for (int r = 0; r < NRT; ++r) {
+        const f32x4 shift = *(const f32x4 *)(shift_lds + r * 256 + lane * 4);
+#pragma unroll
+        for (int p = 0; p < NPT; ++p) {
+            acc[r][p] = shift;
+            if constexpr (PR == 2) zero_acc(low[r][p]);
+        }
+    }
     lds_barrier();
 
     const bool early = wave < nw / 2;
@@ -192,8 +196,6 @@ __device__ __forceinline__ void head_block()
         f32x4 s[NRT];
 #pragma unroll
         for (int r = 0; r < NRT; ++r) {
-            const f32x4 shift = *(const f32x4 *)(shift_lds + r * 256 + lane * 4);
-            zero_acc(s[r]);
 #pragma unroll
             for (int p = 0; p < NPT; ++p) {
                 asm volatile("" : "+v"(acc[r][p]));
@@ -201,16 +203,21 @@ __device__ __forceinline__ void head_block()
                     asm volatile("" : "+v"(low[r][p]));
                     acc[r][p] += low[r][p];
                 }
-                acc[r][p] += shift;
-                const bool valid = (pt0 + p) * 16 + col < npx;
+                const bool valid = (p < live) & ((pt0 + p) * 16 + col < npx);
                 float t = 0.f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     if (PR == 2) t = fmaf(acc[r][p][e], 0.f, t);
-                    s[r][e] += valid ? relu_from(acc[r][p][e], lo) : 0.f;
+                    acc[r][p][e] = valid ? relu_from(acc[r][p][e], lo) : 0.f;
                 }
                 again |= t != 0.f;
             }
+            // (the tiles' sums meet in pairs: one after the other they lose more bits than a kernel that has four values to a lane)
+#pragma unroll
+            for (int m = 1; m < NPT; m <<= 1)
+#pragma unroll
+                for (int p = 0; p + m < NPT; p += 2 * m) acc[r][p] += acc[r][p + m];
+            s[r] = acc[r][0];
         }
         if constexpr (PR == 2) {
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(again) != 0, 0)) {
@@ -241,14 +248,13 @@ __device__ __forceinline__ void head_block()
         }
     }
     __syncthreads();
-    const float inv = 1.f / (float)npx;
-    const int npw = min(pw, (npt + NPT - 1) / NPT);         // pixel waves with pixels
+    const int npw = (npt + per - 1) / per;          // pixel waves with pixels
     for (int row = threadIdx.x; row < rows_wg; row += blockDim.x) {
         const int co = cs * rows_wg + row;
         if (co < c.cout) {
             float t = red[row];
             for (int w = 1; w < npw; ++w) t += red[w * rows_wg + row];
-            P.y[(size_t)n * P.Cy + P.coff1 + co] = t * inv;
+            P.y[(size_t)n * P.Cy + P.coff1 + co] = t / (float)npx;
         }
     }
 }
@@ -297,15 +303,18 @@ __device__ __forceinline__ void head_divided_block()
     request_x();
     request_a(1);
     const int r_sum = wave & (NRT - 1);         // the row tile whose sums the wave adds up
-    const f32x4 shift = c.aff[min(rt0 + r_sum, nrt - 1) * 64 + lane];
     f32x4 acc[NRT][4], low[NRT][4];
 #pragma unroll
-    for (int r = 0; r < NRT; ++r)
+    for (int r = 0; r < NRT; ++r) {
+        f32x4 shift;            // (the sums of the first part begin with it)
+        zero_acc(shift);
+        if (wk == 0) shift = c.aff[min(rt0 + r, nrt - 1) * 64 + lane];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            zero_acc(acc[r][t]);
+            acc[r][t] = shift;
             zero_acc(low[r][t]);
         }
+    }
 #pragma unroll 1
     for (int k = 0; k < mine; ++k) {
 #pragma unroll
@@ -347,7 +356,6 @@ __device__ __forceinline__ void head_divided_block()
         f32x4 v = pair(0);
         if (lk > 1) v += pair(2);
         if (lk > 2) v += pair(4) + pair(6);
-        v += shift;
         if constexpr (PR == 2) {
             const float t = fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, v[3] * 0.f)));
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(t != 0.f) != 0, 0)) {
@@ -374,7 +382,7 @@ __device__ __forceinline__ void head_divided_block()
         for (int w = row >> 4; w < nw; w += 4 * NRT)
 #pragma unroll
             for (int k = 0; k < 4; ++k) t[k] += w + k * NRT < nw ? red[(w + k * NRT) * 16 + (row & 15)] : 0.f;
-        P.y[(size_t)n * P.Cy + P.coff1 + co] = ((t[0] + t[1]) + (t[2] + t[3])) * (1.f / (float)npx);
+        P.y[(size_t)n * P.Cy + P.coff1 + co] = ((t[0] + t[1]) + (t[2] + t[3])) / (float)npx;
     }
 }
 
