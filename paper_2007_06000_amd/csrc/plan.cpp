@@ -187,7 +187,9 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
     // taking the input apart: about 110 vector instructions per 64 pixels x 8 channels
     if (v.pr1 && !v.direct()) t1 += b.n1 * ceil_div(b.c1.cin, 8) * ceil_div(c.ih * c.iw, 64) / 4.0 * 500.0;
     int barriers = ceil_div(nkg1, c.chunk_kg) * b.n1;
-    if (v.direct()) t1 += c.waves_r1 > 1 ? 1000.0 + 700.0 * ceil_div(nrt1 * ceil_div(npx1, 16), nw) : 0.0;
+    // (what the waves of a divided reduction wait for each other grows with their number: 256 -> 32 -> {128, 128} at 27 x 27 with pooling, batch 1, two parts:
+    // 12.7 us in eight parts, 11.6 of the kernel that is chosen with this)
+    if (v.direct()) t1 += c.waves_r1 > 1 ? 250.0 * c.waves_r1 + 700.0 * ceil_div(nrt1 * ceil_div(npx1, 16), nw) : 0.0;
     if (b.kind == KIND_DW) {
         // vector ALU: staging one float4 per (channel group, input pixel), then per (channel group,
         // intermediate pixel) one LDS read and 4 multiply-adds per tap; ~8 issue cycles per wave instruction
@@ -267,6 +269,10 @@ static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
                                                  : out_ch * c.th * lines(c.tw) * (b.shortcut ? 2.0 : 1.0);
     const double t_mem = (double)b.alg_bytes / 8.0e12 + (in_wg + out_wg) * c.tiles_x * c.tiles_y * b.N / 24.0e12;
     c.cost = std::max(t_mfma, t_mem) + 0.15 * std::min(t_mfma, t_mem);
+    // Direct kernels of one tile per wave in either layer are slower than the model has them: 64 -> 16 -> {64, 64} at 54 x 54, batch 64, two parts: estimate and
+    // time 31.9 and 38.3 us, of the kernel of two pixel tiles 32.4 and 33.1; 96 channels at 55 x 55: 38.6 and 49.9, 40.0 and 40.1; batch 16, three
+    // parts: 11.24 and 19.2, of the staged one that is chosen again 11.32 and 19.2.
+    if (v.direct() && b.n2 == 2 && v.nrt1 * v.nrt2 * v.npt2 == 1) c.cost *= 1.05;
     // Taking the depthwise results apart is not in t1: without this the choice was a split kernel of 11.1 and 8.2 us (30 -> 63
     // channels of 104 x 46, batch 4; 30 -> 35 of 109 x 38, batch 3) where the fp32 kernels take 8.7 to 10.1 and 6.7 to 7.6.
     if (v.pr && b.kind == KIND_DW) c.cost *= 1.2;

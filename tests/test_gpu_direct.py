@@ -121,3 +121,14 @@ def test_channels_past_the_last_one_are_not_those_of_the_next_image(wl, special,
             s.plan.select_candidate(True, 0, c)
             y = s.output(True)
             assert np.linalg.norm(y[0] - ref[0]) <= (2.0 ** -12 if precision else 2.0 ** -20) * np.linalg.norm(ref[0]), (v, c)
+
+
+@pytest.mark.parametrize("wl,precision,slower", [
+    (W.config(3, n=16, cin=96, hw=55, s=16, e=64), 0, 574),          # 19.2 us either way when warm, 20.8 and 20.4 in a program's first passes
+    (W.config(3, n=64, cin=64, hw=54, s=16, e=64), 1, 374),          # 38.3 us, 33.1 of the kernel of two tiles
+    (W.config(3, n=64, cin=96, hw=55, s=16, e=64), 1, 374),          # 49.9 us, 40.1
+    (W.split_fire_pool(n=1, cin=256, hw=27, s=32, e=128), 1, 378),   # 12.7 us, 11.6 of the kernel that divides both layers
+])
+def test_the_first_choice_is_not_one_that_measured_slower(wl, precision, slower):
+    from paper_2007_06000_amd import binding as B
+    assert B.Plan(wl, precision=precision).candidate_info(True, 0, 0)["variant"] != slower
