@@ -574,7 +574,8 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
             if (b.kind != KIND_SINGLE || !b.gap || v.pr != pr || b.c1.k != 1 || b.c1.stride != 1 || b.c1.pad != 0) continue;
             const int npx = b.Ho * b.Wo, npt = ceil_div(npx, 16), nrt = ceil_div(b.c1.cout, 16), nkg = ceil_div(b.c1.cin, 32), np = parts_of(pr);
             if ((b.c1.cin + 32 * 32LL) * npx >= (1LL << 29) || (long long)(nkg + 16) * nrt * np * 1024 >= (1LL << 31)) continue;      // (32-bit offsets past the end of an image or filter)
-            // cycles: of a workgroup alone, and what every further one of its compute unit adds
+            // cycles: of a workgroup alone, and what every further one beside it on a compute unit adds; those that find no room there come after them
+            // (512 -> 1000 at 7 x 7, batch 64, two parts: 24.0 us in eight parts of 131 KB, 17.0 in four of 66)
             auto offer = [&](int nw, int wr, int csplit, int lds_bytes, int occ, double life, double more) {
                 if ((pl.opts.force_threads > 0 && pl.opts.force_threads != nw * 64) || (pl.opts.force_cout_split > 0 && pl.opts.force_cout_split != csplit)) return;
                 if (lds_bytes > pl.lds_budget) {
@@ -592,7 +593,9 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                 c.lds_bytes = lds_bytes;
                 c.occ = std::max(1, std::min(pl.lds_per_cu / lds_bytes, occ));
                 const double wgs = (double)b.N * csplit;
-                c.cost = std::max((life + (std::ceil(wgs / pl.num_cus) - 1) * more) / 2.4e9, (double)b.alg_bytes / 5.4e12);
+                const int per_cu = (int)std::ceil(wgs / pl.num_cus), full = per_cu / c.occ, rest = per_cu % c.occ;
+                auto beside = [&](int n) { return n ? life + (n - 1) * more : 0.0; };
+                c.cost = std::max((full * beside(c.occ) + beside(rest)) / 2.4e9, (double)b.alg_bytes / 5.4e12);
                 c.flops_exec = (long long)(wgs * 2.0 * ceil_div(nrt, csplit) * 16 * npt * 16 * nkg * 32);
                 c.ok = true;
                 any_ok = true;
@@ -605,7 +608,9 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     if ((kw > 2 && kw / 2 >= nkg) || groups * kw % v.nrt1 != 0) continue;
                     // matrix operations and what takes the pixels apart (60 or 36 vector instructions per tile and K step) add up
                     const double busy = nkg * groups * (v.nrt1 * products_of(pr) * 22.0 + (pr == 2 ? 255.0 : 155.0));
-                    offer(groups * kw, kw, ceil_div(nrt, v.nrt1), groups * kw * (v.nrt1 * 4096 + 64), head_threads(v.nrt1, pr) / (groups * kw * 64), 6000.0 + busy + ceil_div(nkg, kw) * 500.0, 0.95 * busy);
+                    // (six waves leave two SIMDs with one each: 512 -> 1000 at 13 x 13, three parts, 16.1 us for one such workgroup and 29.1 for two)
+                    const double uneven = groups * kw > 4 ? ceil_div(groups * kw, 4) * 4.0 / (groups * kw) : 1.0;
+                    offer(groups * kw, kw, ceil_div(nrt, v.nrt1), groups * kw * (v.nrt1 * 4096 + 64), head_threads(v.nrt1, pr) / (groups * kw * 64), 6000.0 + busy + ceil_div(nkg, kw) * 500.0, 0.95 * busy * uneven);
                 }
                 continue;
             }

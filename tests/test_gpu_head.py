@@ -126,3 +126,10 @@ def test_error_is_no_larger_than_layer_by_layer(n, cin, hw, c1):
         for c in cs:
             s.plan.select_candidate(True, 0, c)
             assert error(True) <= limit, (v, c, error(True), limit)
+
+
+@pytest.mark.parametrize("n,hw,precision,slower", [(64, 7, 1, (394, 512)), (32, 13, 1, (393, 768))])       # 24.0 us of 17.0 and 37.8 of 22.1
+def test_the_first_choice_is_not_one_of_workgroups_that_come_after_each_other(n, hw, precision, slower):
+    from paper_2007_06000_amd import binding as B
+    i = B.Plan(W.conv_gap_generic(n, 512, hw, hw, 1000, 1, 0, 1), precision=precision).candidate_info(True, 0, 0)
+    assert (i["variant"], i["threads"]) != slower
