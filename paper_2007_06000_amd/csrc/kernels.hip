@@ -405,12 +405,14 @@ __device__ __forceinline__ void conv_pass(typename MM<MF>::Acc (&acc)[NRT][NPT],
             const unsigned long long skip = (unsigned long long)c0 * HW * 4ull;
             const unsigned long long left = x_bytes > skip ? x_bytes - skip : 0ull;
             xrsrc = make_rsrc((const char *)ximg + skip, left);
+            // (a scalar offset that passes the end of its buffer is not covered by the bounds check: one or two channels of the last image)
+            const int room = __builtin_amdgcn_readfirstlane((int)(left >> 31)) ? 0x7fffffff : __builtin_amdgcn_readfirstlane((int)left);
 #pragma unroll
             for (int i = 0; i < NU; ++i) {
                 if (i * nthreads < x_units) {      // uniform: skips unit slots no thread uses
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        xst[i][j] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[i], j * HW * 4, 0));
+                        xst[i][j] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[i], min(j * HW * 4, room), 0));
                 }
             }
         }
