@@ -19,7 +19,7 @@
 // best of the other kernels -> here: 64 -> 16 -> {64, 64} at 55 x 55: 53.7 -> 46.0 us; 128 -> 32 -> {128, 128} at 27 x 27: 42.5 -> 36.7; 256 -> 32 ->
 // {128, 128} at 27 x 27 with its pooling: 60.6 -> 52.7; at 13 x 13 256 -> 48 -> {192, 192}: 32.0 -> 28.5, 512 -> 64 -> {256, 256}: 49.7 -> 46.1; the network at batch
 // 64: 494 -> 457.  Where a workgroup has few K steps and the launch one round, staging through LDS stays ahead (96 -> 16 -> {64, 64} at 55 x 55, batch 16:
-// 20.3 us there, 21.3 here; 192 -> 16 -> 32, 1x1 -> 5x5 at 28 x 28, batch 32: 15.3 and 15.9), and with few workgroups the kernels that divide both
+// 20.3 us there, 21.3 here; 192 -> 16 -> 32, 1x1 -> 5x5 at 28 x 28, batch 32: 15.3 and 15.9, but 24.3 and 20.2 at batch 64), and with few workgroups the kernels that divide both
 // layers (512 -> 64 -> {256, 256} at 13 x 13, batch 1: 16.4 and 18.5): the planner's estimate decides, and xl_tune times them all.
 // (Over 138 blocks of 1 to 64 images the planner's first choice takes 0.945 times the time of its first one without these kernels, 0.967 on two parts in
 // layer 2, and is behind it by 1 % at most, on two parts in three blocks by 1.5 to 4 %.)

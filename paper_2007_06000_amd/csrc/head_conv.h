@@ -1,19 +1,24 @@
 // Pointwise convolution -> global average pooling on bf16 parts (included by kernels.hip).
 //
-// The last layer of a classifier: every value of the input meets as many filter values as there are classes, and one number per image
-// and class is kept.  Layer by layer it wrote the product and read it again, and the workgroups of eight slices of output channels each took the whole input apart.
-// Here a workgroup has the image's pixels in front of it as fragments of the 16x16x32 bf16 operation (split_conv.h: three products of two parts or six
-// of three), and the mean is taken from the accumulators.
+// The last layer of a classifier: every value of the input meets as many filter values as there are classes, and one number per image and class is kept.
+// Layer by layer it wrote the product and read it again, and the workgroups of eight slices of output channels each took the whole input apart.  Here a
+// workgroup has the image's pixels in front of it as fragments of the 16x16x32 bf16 operation (split_conv.h: three products of two parts or six of
+// three), and the mean is taken from the accumulators.
 //
-// head_kernel: the waves of a workgroup take 16 * NRT channels each and all pixels (up to 16 * NPT; of larger images pw waves share the pixels).  The pixels of a K step
-// of 32 channels are taken apart once per workgroup, tile by tile, by whichever wave's turn it is, and lie in LDS for all, in two buffers; one barrier per K step.  Half of the
-// waves do this before their matrix operations and half in the middle of them, so that a SIMD always has a wave with matrix operations.  Filter rows of a wave are its own: they
-// come to its place in LDS a K step ahead without passing registers, which the accumulators fill (2 x 11 tiles of two accumulators: 176 of 256).
+// head_kernel: the waves of a workgroup take 16 * NRT channels each and all pixels (up to 16 * NPT; of larger images pw waves share the pixels).  The
+// pixels of a K step of 32 channels are taken apart once per workgroup, tile by tile, by whichever wave's turn it is, and lie in LDS for all, in two
+// buffers; one barrier per K step.  Half of the waves do this before their matrix operations and half in the middle of them, so that a SIMD always has a
+// wave with matrix operations.  Filter rows of a wave are its own: they come to its place in LDS a K step ahead without passing registers, which the
+// accumulators fill (2 x 11 tiles of two accumulators: 176 of 256).
 // head_divided_kernel: where few workgroups are to be had (below).
 //
-// What bounds it: one K step of the 2 x 11 kernel takes 7000 cycles where its matrix operations take 4200, with four workgroups on the chip as with 256 (inferred: LDS reads,
-// 264 KB a step, that a wave waits for; the third part of a pixel is asked for 96 cycles of its own matrix work before it is due).  512 -> 1000 channels at 13 x 13, layer by layer -> here, three parts / two: batch 64 86.8 -> 50.4 / 54.5 -> 32.3 us, batch 8 20.6 ->
-// 12.9 / 18.0 -> 9.8, batch 1 10.8 -> 9.7; at 7 x 7, batch 64: 25.2 -> 23.0; 300 -> 500 at 10 x 9, batch 16: 11.0 -> 8.0; 128 -> 100 at 14 x 14, batch 32: 8.0 -> 6.0.
+// What bounds it: one K step of the 2 x 11 kernel takes 7000 cycles where its matrix operations take 4200, with four workgroups on the chip as with 256;
+// by the counters a SIMD's matrix pipe works for 59 % of a launch and LDS reads (264 KB a step) meet no bank conflicts.  Two waits that stand in the
+// source, neither of them timed by itself: the waves that stage first wait in stage() for the filter rows they have just asked for, though their pixels
+// are there from the top of the step on; and the third part of a pixel is asked for 96 cycles of its own matrix work before it is due.
+// 512 -> 1000 channels at 13 x 13, layer by layer -> here, three parts / two: batch 64 86.8 -> 50.4 / 54.5 -> 32.3 us, batch 8 20.6 -> 12.9 /
+// 18.0 -> 9.8, batch 1 10.8 -> 9.7; at 7 x 7, batch 64: 25.2 -> 23.0; 300 -> 500 at 10 x 9, batch 16: 11.0 -> 8.0; 128 -> 100 at 14 x 14, batch 32:
+// 8.0 -> 6.0.
 #pragma once
 
 namespace xl {
@@ -260,9 +265,9 @@ __device__ __forceinline__ void head_block()
 }
 
 // The same for launches with few workgroups: the waves of a workgroup divide the pixels, 64 to a wave, and the reduction, and all take the same NRT row
-// tiles, so that the pixels are taken apart where they are multiplied (10000 of the 25000 cycles of a workgroup with 512 channels, 169 pixels and NRT = 2, which add up with the matrix
-// operations').  A lane loads 8 channels of four neighbouring pixels, which are its columns of four pixel tiles (the mean asks for no order).  Partial sums meet in LDS:
-// [row tile][pixel tile][K part][lane] float4.
+// tiles, so that the pixels are taken apart where they are multiplied (10000 of the 25000 cycles of a workgroup with 512 channels, 169 pixels and
+// NRT = 2, which add up with the matrix operations').  A lane loads 8 channels of four neighbouring pixels, which are its columns of four pixel tiles
+// (the mean asks for no order).  Partial sums meet in LDS: [row tile][pixel tile][K part][lane] float4.
 template <int NRT, int PR>
 __device__ __forceinline__ void head_divided_block()
 {

@@ -1017,7 +1017,8 @@ block_kernel(const BlockParams args)
                 const int d = P.P2 - c.pad;
                 // Without a barrier behind a pass (row, pixel) tiles go to the waves in turn, those of the second sibling from where the first one's
                 // ended, so that no SIMD is left without a wave where rows or pixels do not divide by the waves along them (batch 64 at 13 x 13:
-                // 256 -> 48 -> {192, 192} 27.6 -> 25.0 us, 384 -> 48 31.3 -> 27.2; the network at batch 1 112.9 -> 109.7).  One
+                // 256 -> 48 -> {192, 192} 27.6 -> 25.0 us, 384 -> 48 31.3 -> 27.2; the network at batch 1 112.9 -> 109.7; 88 fire modules
+                // in the kernel that the planner picks 5 % faster, from 13 % to one that is 5 % slower: 96 -> 24 -> {72, 72} at 35 x 35, batch 4, 12.5 -> 13.1).  One
                 // layer alone loses more by it than it gains (40 channels of 27 x 27, batch 5: 12.3 -> 12.6).
                 constexpr bool TURNS = PR != 0 && K2B != 0 && KIND != KIND_FUSED2P;
                 const int nr = TURNS ? max(0, rte - rtb + NRT2 - 1) / NRT2 : 0, items = nr * ((npt2 + NPT2 - 1) / NPT2);
@@ -1035,8 +1036,9 @@ block_kernel(const BlockParams args)
                     r_item = item - p_item * nr;
                 }
                 // The older of two waves of a SIMD takes the matrix pipe whenever it can, and the younger one finishes alone, where it waits for its
-                // operands (512 -> 64 -> {256, 256} at 13 x 13: 12.7 and 20.2 us of a workgroup's 40, the pipe busy for 15.8).  Where both have as
-                // many tiles, the younger one goes first for half of a tile: 16.3 and 18.5.
+                // operands (512 -> 64 -> {256, 256} at 13 x 13: 12.7 and 20.2 us of a workgroup's 40, the pipe busy for 15.8).  The younger one goes
+                // first for half of a tile: 16.3 and 18.5.  Tiles dealt in turn ask for as many to each wave; where they are not, the rule with that
+                // condition was 0.3 % slower over 15 blocks (64 channels of 56 x 56, merge, batch 32: 95.3 and 96.7 us).
                 const bool first = PR == 2 && KS2 > 1 && NRT2 * NPT2 == 2 && nwaves == 8 && c.nkg >= 4 && (!TURNS || items % 8 == 0) && __builtin_amdgcn_readfirstlane(wave) >= 4;
                 turn += items;
                 for (int rp = TURNS ? 0 : rtb; TURNS ? item < items : rp < rte; rp += TURNS ? 0 : g2.wg_rt) {

@@ -151,10 +151,10 @@ static bool stem_shape(const BlockSpec &b)
     return b.kind == KIND_POOL && b.c1.cin == 3 && b.c1.k == 3 && b.c1.stride == 2 && b.c1.pad == 0 && b.pool_k == 3 && b.pool_s == 2 && b.pool_p == 0;
 }
 
-// Model of one candidate.  Times in seconds on a nominal MI355X (2.4 GHz, 8 TB/s).
 // Stage 2 deals its tiles to the waves in turn (block_kernel).
 static bool turns(const BlockSpec &b, const Variant &v) { return v.pr != 0 && v.k2b != 0 && b.kind != KIND_FUSED2P; }
 
+// Model of one candidate.  Times in seconds on a nominal MI355X (2.4 GHz, 8 TB/s).
 static void evaluate(const BlockSpec &b, const xl_plan &pl, Choice &c)
 {
     const Variant &v = c.v;
@@ -573,7 +573,8 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
         if (v.kind == KIND_HEAD) {
             if (b.kind != KIND_SINGLE || !b.gap || v.pr != pr || b.c1.k != 1 || b.c1.stride != 1 || b.c1.pad != 0) continue;
             const int npx = b.Ho * b.Wo, npt = ceil_div(npx, 16), nrt = ceil_div(b.c1.cout, 16), nkg = ceil_div(b.c1.cin, 32), np = parts_of(pr);
-            if ((b.c1.cin + 32 * 32LL) * npx >= (1LL << 29) || (long long)(nkg + 16) * nrt * np * 1024 >= (1LL << 31)) continue;      // (32-bit offsets past the end of an image or filter)
+            // (32-bit offsets past the end of an image or filter)
+            if ((b.c1.cin + 32 * 32LL) * npx >= (1LL << 29) || (long long)(nkg + 16) * nrt * np * 1024 >= (1LL << 31)) continue;
             // cycles: of a workgroup alone, and what every further one beside it on a compute unit adds; those that find no room there come after them
             // (512 -> 1000 at 7 x 7, batch 64, two parts: 24.0 us in eight parts of 131 KB, 17.0 in four of 66)
             auto offer = [&](int nw, int wr, int csplit, int lds_bytes, int occ, double life, double more) {
@@ -610,7 +611,8 @@ static std::vector<Choice> search(const BlockSpec &b, const xl_plan &pl, bool &l
                     const double busy = nkg * groups * (v.nrt1 * products_of(pr) * 22.0 + (pr == 2 ? 255.0 : 155.0));
                     // (six waves leave two SIMDs with one each: 512 -> 1000 at 13 x 13, three parts, 16.1 us for one such workgroup and 29.1 for two)
                     const double uneven = groups * kw > 4 ? ceil_div(groups * kw, 4) * 4.0 / (groups * kw) : 1.0;
-                    offer(groups * kw, kw, ceil_div(nrt, v.nrt1), groups * kw * (v.nrt1 * 4096 + 64), head_threads(v.nrt1, pr) / (groups * kw * 64), 6000.0 + busy + ceil_div(nkg, kw) * 500.0, 0.95 * busy * uneven);
+                    offer(groups * kw, kw, ceil_div(nrt, v.nrt1), groups * kw * (v.nrt1 * 4096 + 64), head_threads(v.nrt1, pr) / (groups * kw * 64),
+                          6000.0 + busy + ceil_div(nkg, kw) * 500.0, 0.95 * busy * uneven);
                 }
                 continue;
             }

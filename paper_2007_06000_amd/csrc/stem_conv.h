@@ -16,10 +16,12 @@
 // K slots of step k and lane half h, filter row R = 4 h + 2 k:  R.0 R.1 (R+1).0 (R+1).1 R.2 (R+1).2 s s', where s s' are, for
 // k = 0, row 8's taps 0 and 1 (h = 0) and 2 and nothing (h = 1), for k = 1 the shift and nothing (h = 0).  Where a slot has no filter
 // value it is 0 and meets whatever lies there.
-// Every value of a piece is taken apart once: the third column of a block is the first of its right tile too, and the fifth comes from the next lane in parts.
+// Every value of a piece is taken apart once: the third column of a block is the first of its right tile too, and the fifth comes from the next lane
+// in parts.
 // What bounds it: some 600 vector instructions and 48 matrix operations per pooled row and wave, and the waits between them (5600 cycles a row and
-// SIMD with two waves as with three).  Time per pass, on the vector ALU -> here with every K slot taken apart by itself -> here: to 64 channels at 224 x 224, batch 64: 67 -> 35.2 ->
-// 33.6 us, batch 8: 16 -> 10.9 -> 10.1.  Before, to 96 at 150 x 200, batch 16: 29.5 -> 15.5; to 32 at 224 x 224, batch 50: 32 -> 21.
+// SIMD with two waves as with three).  Time per pass, on the vector ALU -> here with every K slot taken apart by itself -> here: to 64 channels at
+// 224 x 224, batch 64: 67 -> 35.2 -> 33.6 us, batch 8: 16 -> 10.9 -> 10.1.  Before, to 96 at 150 x 200, batch 16: 29.5 -> 15.5; to 32 at 224 x 224,
+// batch 50: 32 -> 21.
 // 64 channels per wave were slower (46 us at batch 64, of 40 then: 248 registers, two waves per SIMD), a third of the filter in LDS equal.
 // Where the chip is not filled the stream kernel stays ahead (to 64 channels at 224 x 224, xl_profile with its 2 to 3 us of events, batch 1:
 // 8.6 us there, 9.5 here; batch 2: 9.5 and 9.6; batch 4: 12.3 and 10.0).

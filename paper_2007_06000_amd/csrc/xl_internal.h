@@ -17,9 +17,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // Matrix-core tile geometry.  MF = 32 uses V_MFMA_F32_32X32X2_F32 (one K step of
 // the packed filter covers 8 input channels: 2 lane halves x 4 components),
 // MF = 16 uses V_MFMA_F32_16X16X4_F32 (16 channels: 4 lane quarters x 4).
-// Split-bf16 operands (pr > 0, MF = 32 only): a float is held as pr + 1 bf16 parts and a product is several
-// V_MFMA_F32_32X32X16_BF16; a lane holds 8 channels and a K step covers 16.
-// MF = 16 on three parts: V_MFMA_F32_16X16X32_BF16, a K step covers 32.
+// Split-bf16 operands (pr > 0): a float is held as pr + 1 bf16 parts and a product is several bf16 operations; a lane holds
+// 8 channels.  MF = 32: V_MFMA_F32_32X32X16_BF16, a K step covers 16; MF = 16 (direct_conv.h on three parts, head_conv.h on two or
+// three): V_MFMA_F32_16X16X32_BF16, a K step covers 32.
 constexpr int kc_of(int mf, int pr = 0) { return pr ? 512 / mf : (mf == 32 ? 8 : 16); }      // channels per K step
 constexpr int gps_of(int mf, int pr = 0) { return kc_of(mf, pr) / 4; }                 // 4-channel groups per K step
 constexpr int parts_of(int pr) { return pr ? pr + 1 : 1; }      // bf16 parts of an operand (fp32: the value itself)
@@ -332,6 +332,15 @@ struct Variant {
     X(162, KIND_KSPLIT, 32, 3, 2, 2, 32, 2, 2, 0, 0, 0, 0, 1)
 
 // Layer 1 from memory on three parts (direct_conv.h): columns 5 and 6 are the row and pixel tiles of a wave in layer 1.
+// Where each measured fastest of all kernels (three parts in layer 2; us, in brackets the best of the others):
+//   170  384 -> 64 -> {256, 256} at 13 x 13, batch 32: 25.0 (25.6)      171  128 -> 16 -> {64, 64} at 55 x 55, batch 64: 50.6 (52.3)
+//   172  128 -> 32 -> {128, 128} at 27 x 27, batch 64: 33.6 (36.4)      173  300 -> 48 -> {144, 144} at 20 x 20, batch 64: 40.3 (42.7)
+//   174  64 -> 16 -> {64, 64} at 55 x 55, batch 32: 25.6 (26.6)         175  192 -> 32 -> {64, 64} at 28 x 28, batch 16: 12.3 (14.2)
+//   176  300 -> 48 -> {144, 144} at 20 x 20, batch 16: 18.7 (19.5)
+//   with pooling: 177  128 -> 16 -> {64, 64} at 55 x 55, batch 8: 15.9 (16.3), 180 there at batch 32: 35.3 (42.9)
+//   178  256 -> 32 -> {128, 128} at 27 x 27, batch 8: 17.7 (17.9)       181  96 -> 24 -> {96, 96} at 40 x 40, batch 64: 58.3 (76.2)
+//   179  256 -> 48 -> {192, 192} at 27 x 27, batch 4: 20.1 (21.0), 182 there at batch 32: 54.8 (62.0)
+//   5x5: 183  192 -> 16 -> 32 at 28 x 28, batch 64: 20.2 (24.3)         184  64 -> 24 -> 48 at 40 x 40, batch 64: 56.1 (66.8)
 #define XL_SPLIT_LIST_F(X)                                            \
     X(170, KIND_FUSED2, 16, 1, 4, 2, 32, 2, 1, 3, 1, 0, 0, 2)         \
     X(171, KIND_FUSED2, 16, 1, 1, 2, 32, 1, 2, 3, 1, 0, 0, 2)         \
@@ -350,7 +359,8 @@ struct Variant {
     X(184, KIND_FUSED2, 16, 1, 2, 2, 32, 1, 1, 5, 0, 0, 0, 2)
 
 // Pointwise -> global average pooling (head_conv.h): columns 5 and 6 are the row and pixel tiles of a wave, column 13 = 1: the
-// waves divide the reduction.
+// waves divide the reduction.  Where each measured fastest (three parts; us): 512 -> 1000 at 13 x 13, batch 64: 190 52.8 (69.3), batch 32: 191 35.1
+// (46.9), batch 1: 192 10.2 (11.7), batch 8: 193 14.4 (20.9); 300 -> 500 at 10 x 10, batch 64: 194 16.5 (18.5).
 #define XL_SPLIT_LIST_G(X)                                            \
     X(190, KIND_HEAD, 16, 1, 2, 11, 0, 0, 0, 0, 0, 0, 0, 1)           \
     X(191, KIND_HEAD, 16, 1, 2, 7, 0, 0, 0, 0, 0, 0, 0, 1)            \
